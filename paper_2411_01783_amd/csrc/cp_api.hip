@@ -31,11 +31,36 @@ inline float resolve_scale(float scale, int head_dim) {
   return scale > 0.f ? scale : 1.0f / sqrtf((float)head_dim);
 }
 
-inline bool mfma_prefill_applies(const cp_shape& s) {
-  return s.dtype == CP_BF16 && s.head_dim == 128 && (s.n_q_heads / s.n_kv_heads) <= 64;
+// Calls of the MFMA kernel: one sequence of either head_dim, packed batches of head_dim 128.
+inline bool mfma_applies(const cp_shape& s) {
+  return attn_mfma_applies(s.dtype, s.head_dim, s.n_q_heads, s.n_kv_heads) &&
+         (s.batch == 1 || s.head_dim == 128);
+}
+
+inline int32_t kv_tiles(int64_t n_kv) { return (int32_t)((n_kv + kAttnTile - 1) / kAttnTile); }
+
+// One rank's queries against one shard, as an attention launch sees it.
+AttnShape single_shape(const cp_shape& s) {
+  AttnShape a = {};
+  a.dtype = s.dtype; a.head_dim = s.head_dim;
+  a.n_q_heads = s.n_q_heads; a.n_kv_heads = s.n_kv_heads;
+  a.total_q = s.total_q; a.n_tiles = kv_tiles(s.total_kv); a.n_shards = 1;
+  return a;
 }
 
 inline size_t elem_size(int32_t dtype) { return dtype == CP_FP32 ? 4 : 2; }
+
+AttnTable single_table(const cp_shape& s, const void* q, const void* k, const void* v,
+                       const int32_t* q_pos, const int32_t* kv_pos, void* out, float* lse) {
+  AttnTable t = {};
+  t.n_ranks = t.n_shards = 1;
+  t.q[0] = q; t.q_pos[0] = q_pos; t.out[0] = out; t.lse[0] = lse;
+  t.k[0] = k; t.v[0] = v; t.kv_pos[0] = kv_pos;
+  t.n_kv[0] = (int32_t)s.total_kv;
+  t.tok_begin[1] = (int32_t)s.total_q;
+  t.tile_begin[1] = kv_tiles(s.total_kv);
+  return t;
+}
 
 }  // namespace
 
@@ -109,10 +134,10 @@ size_t cp_workspace_bytes(const cp_shape* shape, int32_t kind) {
   if (check_shape(shape) != CP_OK) return 0;
   switch (kind) {
     case CP_WS_PARTIAL:
-      if (!mfma_prefill_applies(*shape)) return 0;
-      return prefill_mfma_workspace_bytes(*shape) +
+      if (!mfma_applies(*shape)) return 0;
+      return attn_mfma_workspace_bytes(single_shape(*shape)) +
              (shape->batch > 1
-                  ? varseq_layout(shape->batch, shape->total_q, shape->total_kv).total
+                  ? varseq_workspace_bytes(shape->batch, shape->total_q, shape->total_kv)
                   : 0);
     case CP_WS_DECODE:
       return decode_workspace_bytes(*shape);
@@ -139,29 +164,27 @@ int cp_attn_partial(const cp_shape* shape, const void* q, const void* k, const v
   if (s.total_q == 0) return CP_OK;
   const float scale = resolve_scale(s.softmax_scale, s.head_dim);
   hipStream_t st = (hipStream_t)stream;
-  if (mfma_prefill_applies(s) && (cu_seqlens_q == nullptr || s.batch == 1)) {
-    const size_t need = prefill_mfma_workspace_bytes(s);
+  AttnShape as = single_shape(s);
+  as.scale = scale;
+  AttnTable t = single_table(s, q, k, v, q_pos, kv_pos, out, lse);
+  const AttnOut ao = {out_dtype, 0, 0};
+  // (one sequence: the cu_seqlens of a batch of one say nothing new to the MFMA kernel)
+  const bool packed = cu_seqlens_q != nullptr && s.batch > 1;
+  if (mfma_applies(s) && (cu_seqlens_q == nullptr || s.head_dim == 128)) {
+    const size_t enc = packed ? varseq_workspace_bytes(s.batch, s.total_q, s.total_kv) : 0;
+    const size_t need = enc + attn_mfma_workspace_bytes(as);
     if (need > 0 && (workspace == nullptr || !aligned256(workspace) || workspace_bytes < need))
       return CP_ERR_WORKSPACE;
-    return launch_prefill_mfma(s, scale, q, k, v, q_pos, kv_pos, out, lse, out_dtype, workspace,
-                               workspace_bytes, nullptr, nullptr, st);
+    const int32_t* q_lo = nullptr;
+    if (packed) {  // shift every sequence into its own position range, then one launch
+      rc = launch_varseq_encode(s.batch, s.total_kv, t, &cu_seqlens_q, &cu_seqlens_kv, workspace,
+                                &q_lo, st);
+      if (rc != CP_OK) return rc;
+    }
+    return launch_attn_mfma(as, t, ao, q_lo, nullptr, (char*)workspace + enc,
+                            workspace_bytes - enc, st);
   }
-  if (mfma_prefill_applies(s)) {
-    // packed batch: shift every sequence into its own position range, then one launch
-    if (s.total_q > 0x7fffffffLL || s.total_kv > 0x7fffffffLL) return CP_ERR_SHAPE;
-    const VarseqLayout vl = varseq_layout(s.batch, s.total_q, s.total_kv);
-    const size_t need = vl.total + prefill_mfma_workspace_bytes(s);
-    if (workspace == nullptr || !aligned256(workspace) || workspace_bytes < need)
-      return CP_ERR_WORKSPACE;
-    char* ws = (char*)workspace;
-    if (launch_varseq_encode(s.batch, s.total_q, s.total_kv, q_pos, kv_pos, cu_seqlens_q,
-                             cu_seqlens_kv, ws, st) != CP_OK)
-      return CP_ERR_LAUNCH;
-    return launch_prefill_mfma(s, scale, q, k, v, (const int32_t*)(ws + vl.q_hi_off),
-                               (const int32_t*)(ws + vl.kv_off), out, lse, out_dtype,
-                               ws + vl.total, workspace_bytes - vl.total, nullptr,
-                               (const int32_t*)(ws + vl.q_lo_off), st);
-  }
+  if (s.dtype == CP_FP32 && cu_seqlens_q == nullptr) return launch_attn_fp32(as, t, ao, st);
   return launch_partial_generic(s, scale, q, k, v, q_pos, kv_pos, cu_seqlens_q, cu_seqlens_kv,
                                 out, lse, out_dtype, st);
 }
@@ -176,7 +199,7 @@ int cp_attn_partial_accumulate(const cp_shape* shape, const void* q, const void*
   const cp_shape& s = *shape;
   if (final_out != nullptr && final_dtype != CP_BF16 && final_dtype != CP_FP32)
     return CP_ERR_UNSUPPORTED;
-  if (s.batch != 1 || !mfma_prefill_applies(s) || prefill_mfma_splits_kv(s, true))
+  if (s.batch != 1 || !mfma_applies(s) || !attn_mfma_merging_applies(single_shape(s)))
     return CP_ERR_UNSUPPORTED;
   if (s.total_q > 0 && (q == nullptr || q_pos == nullptr || acc_out == nullptr || acc_lse == nullptr))
     return CP_ERR_NULL;
@@ -185,13 +208,15 @@ int cp_attn_partial_accumulate(const cp_shape* shape, const void* q, const void*
   if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(acc_out) || !aligned16(final_out))
     return CP_ERR_ALIGN;
   if (s.total_q == 0) return CP_OK;
-  const size_t need = prefill_mfma_workspace_bytes(s);
+  AttnShape as = single_shape(s);
+  as.scale = resolve_scale(s.softmax_scale, s.head_dim);
+  const size_t need = attn_mfma_workspace_bytes(as);
   if (need > 0 && (workspace == nullptr || !aligned256(workspace) || workspace_bytes < need))
     return CP_ERR_WORKSPACE;
+  const AttnTable t = single_table(s, q, k, v, q_pos, kv_pos, nullptr, acc_lse);
   const PrefillAccumulate acc = {acc_out, acc_lse, final_out, final_lse, final_dtype};
-  return launch_prefill_mfma(s, resolve_scale(s.softmax_scale, s.head_dim), q, k, v, q_pos, kv_pos,
-                             nullptr, nullptr, CP_FP32, workspace, workspace_bytes, nullptr,
-                             nullptr, (hipStream_t)stream, &acc);
+  return launch_attn_mfma_accumulate(as, t, acc, workspace, workspace_bytes,
+                                     (hipStream_t)stream);
 }
 
 // Argument checks shared by cp_attn_decode and cp_attn_decode_static. Returns CP_OK with
@@ -348,19 +373,52 @@ static cp_shape ring_shape(const cp_ring_desc* d, int q_rank, int kv_rank, bool 
   return s;
 }
 
-// Ring workspace layout: the per-tile kv_pos bounds of every rank's KV shard (computed once
-// per driver call, reused by the N calls that read the shard), then the per-call workspace.
-static bool ring_uses_tile_bounds(const cp_ring_desc* d, bool decode) {
-  cp_shape s = ring_shape(d, 0, 0, decode);
-  // (a packed batch shifts its positions per call, so bounds of the raw positions are no use)
-  return !decode && !ring_is_packed(d, decode) && mfma_prefill_applies(s);
+// Prefill drivers: a ring is one attention launch over all its ranks and shards (AttnTable)
+// wherever the kernels take it: up to kMaxTable ranks, bf16 in one sequence or packed with
+// head_dim 128, fp32 in one sequence. Otherwise (and in this build only then) it is N x N
+// partial-attention calls into the slots and a merge per rank.
+static bool ring_is_one_launch(const cp_ring_desc* d) {
+  if (d->n_ranks > kMaxTable) return false;
+  const bool packed = ring_is_packed(d, false);
+  if (d->dtype == CP_FP32) {
+    if (packed) return false;
+  } else if (!attn_mfma_applies(d->dtype, d->head_dim, d->n_q_heads, d->n_kv_heads) ||
+             (packed && d->head_dim != 128)) {
+    return false;
+  }
+  // tokens, rows and tiles of all ranks together are kept in 31 bits
+  int64_t tokens = 0, keys = 0;
+  for (int r = 0; r < d->n_ranks; ++r) {
+    if (d->n_q[r] > INT32_MAX || d->n_kv[r] > INT32_MAX - kAttnTile) return false;
+    tokens += d->n_q[r];
+    keys += d->n_kv[r];
+  }
+  return tokens * (d->n_q_heads / d->n_kv_heads) <= INT32_MAX && tokens <= INT32_MAX &&
+         keys <= (int64_t)INT32_MAX * 8;
 }
 
-static size_t ring_bounds_bytes(const cp_ring_desc* d, bool decode) {
-  if (!ring_uses_tile_bounds(d, decode)) return 0;
-  size_t total = 0;
-  for (int b = 0; b < d->n_ranks; ++b) total += kv_tile_bounds_bytes(d->n_kv[b]);
-  return total;
+static AttnShape ring_attn_shape(const cp_ring_desc* d) {
+  AttnShape s = {};
+  s.dtype = d->dtype; s.head_dim = d->head_dim;
+  s.n_q_heads = d->n_q_heads; s.n_kv_heads = d->n_kv_heads;
+  s.n_shards = d->n_ranks;
+  for (int r = 0; r < d->n_ranks; ++r) {
+    s.total_q += d->n_q[r];
+    s.n_tiles += kv_tiles(d->n_kv[r]);
+  }
+  s.per_shard = d->keep_partials != 0;
+  s.scale = resolve_scale(d->softmax_scale, d->head_dim);
+  return s;
+}
+
+static size_t ring_varseq_bytes(const cp_ring_desc* d) {
+  if (!ring_is_packed(d, false)) return 0;
+  int64_t tokens = 0, keys = 0;
+  for (int r = 0; r < d->n_ranks; ++r) {
+    tokens += d->n_q[r];
+    keys += d->n_kv[r];
+  }
+  return varseq_workspace_bytes(d->batch, tokens, keys);
 }
 
 // Shape of the one decode call KV holder b answers with when the queries are gathered.
@@ -373,31 +431,27 @@ static cp_shape gathered_decode_shape(const cp_ring_desc* d, int b) {
 
 extern "C" size_t cp_ring_workspace_bytes(const cp_ring_desc* d, int32_t decode) {
   if (check_ring(d, decode != 0) != CP_OK) return 0;
+  if (!decode && ring_is_one_launch(d))
+    return d->dtype == CP_FP32 ? 0
+                               : attn_mfma_workspace_bytes(ring_attn_shape(d)) + ring_varseq_bytes(d);
   size_t need = 0;
   for (int a = 0; a < d->n_ranks; ++a)
     for (int b = 0; b < d->n_ranks; ++b) {
       cp_shape s = ring_shape(d, a, b, decode != 0);
       need = std::max(need, cp_workspace_bytes(&s, decode ? CP_WS_DECODE : CP_WS_PARTIAL));
     }
-  if (d->gathered_q) {
+  if (d->gathered_q && decode) {
+    size_t regions = 0;
+    bool flat = true;
     for (int b = 0; b < d->n_ranks; ++b) {
-      cp_shape s = ring_shape(d, 0, b, decode != 0);
-      s.total_q = 0;
-      for (int a = 0; a < d->n_ranks; ++a) s.total_q += d->n_q[a];
-      need = std::max(need, cp_workspace_bytes(&s, decode ? CP_WS_DECODE : CP_WS_PARTIAL));
+      const cp_shape s = gathered_decode_shape(d, b);
+      need = std::max(need, cp_workspace_bytes(&s, CP_WS_DECODE));
+      flat = flat && decode_flat_applies(s);
+      regions += decode_flat_region_bytes(s);
     }
-    if (decode) {
-      size_t regions = 0;
-      bool flat = true;
-      for (int b = 0; b < d->n_ranks; ++b) {
-        const cp_shape s = gathered_decode_shape(d, b);
-        flat = flat && decode_flat_applies(s);
-        regions += decode_flat_region_bytes(s);
-      }
-      if (flat) need = std::max(need, regions);
-    }
+    if (flat) need = std::max(need, regions);
   }
-  return need + ring_bounds_bytes(d, decode != 0);
+  return need;
 }
 
 namespace {
@@ -437,178 +491,168 @@ RingSlots make_slots(const cp_ring_desc* d) {
   return r;
 }
 
-struct RingWork {
-  bool use_bounds = false;
-  bool dual = false;          // alternate the calls of a rank between two streams
-  hipStream_t aux = nullptr;
-  hipEvent_t fork = nullptr, join = nullptr;
-  size_t bounds_off[CP_MAX_PARTS] = {};
-  char* call_ws = nullptr;
-  size_t call_ws_bytes = 0;
-};
+// Slot of the partial of rank a's queries against rank b's KV: a holder's N slots in destination
+// order with gathered queries, a source's N slots otherwise; without keep_partials the slots
+// are reused for every rank.
+int64_t slot_of(const cp_ring_desc* d, int a, int b) {
+  if (!d->keep_partials) return b;
+  return d->gathered_q ? (int64_t)b * d->n_ranks + a : (int64_t)a * d->n_ranks + b;
+}
 
-// Checks the workspace and, for the MFMA path, records the tile bounds of every KV shard.
-int ring_prepare(const cp_ring_desc* d, bool decode, hipStream_t st, RingWork& w) {
+int check_ring_workspace(const cp_ring_desc* d, bool decode) {
   const size_t need = cp_ring_workspace_bytes(d, decode ? 1 : 0);
   if (need > 0 && (d->workspace == nullptr || !aligned256(d->workspace) ||
                    d->workspace_bytes < need))
     return CP_ERR_WORKSPACE;
-  w.use_bounds = ring_uses_tile_bounds(d, decode);
-  size_t off = 0;
-  if (w.use_bounds) {
-    void* bounds[CP_MAX_PARTS];
-    for (int b = 0; b < d->n_ranks; ++b) {
-      w.bounds_off[b] = off;
-      bounds[b] = (char*)d->workspace + off;
-      off += kv_tile_bounds_bytes(d->n_kv[b]);
-    }
-    const int rc = launch_kv_tile_bounds_ring(d->n_ranks, d->kv_pos, d->n_kv, bounds, st);
-    if (rc != CP_OK) return rc;
-  }
-  w.call_ws = (char*)d->workspace + off;
-  w.call_ws_bytes = d->workspace_bytes >= off ? d->workspace_bytes - off : 0;
-  // Two streams, and the merge fused into the epilogues, only when no call splits its KV axis
-  // through the shared per-call scratch.
-  bool scratch = !w.use_bounds;
-  if (!decode && w.use_bounds && (d->aux_stream != nullptr || d->fused_merge)) {
-    for (int a = 0; a < d->n_ranks && !scratch; ++a)
-      for (int b = 0; b < d->n_ranks && !scratch; ++b)
-        scratch = d->n_q[a] > 0 &&
-                  prefill_mfma_splits_kv(ring_shape(d, a, b, false), d->fused_merge != 0);
-  }
-  if (d->fused_merge && d->n_ranks > 1 && scratch) return CP_ERR_UNSUPPORTED;
-  if (d->aux_stream != nullptr && !decode && w.use_bounds && !d->fused_merge) {
-    if (!scratch) {
-      if (hipEventCreateWithFlags(&w.fork, hipEventDisableTiming) != hipSuccess) return CP_ERR_LAUNCH;
-      if (hipEventCreateWithFlags(&w.join, hipEventDisableTiming) != hipSuccess) {
-        (void)hipEventDestroy(w.fork);
-        return CP_ERR_LAUNCH;
-      }
-      w.dual = true;
-      w.aux = (hipStream_t)d->aux_stream;
-    }
-  }
   return CP_OK;
 }
 
-// Fused merge: the N steps of one rank keep a running (O, LSE) in partial slot 0. Step 0
-// writes it, steps 1 .. N-2 merge into it in their epilogues, the last step writes the merged
-// O to the rank's output. `kv_of_step(j)` names the KV rank of step j.
-template <typename KvOf>
-int ring_rank_fused(const cp_ring_desc* d, const RingWork& w, const RingSlots& slots, int a,
-                    int n, hipStream_t st, KvOf kv_of_step) {
-  float* const acc_o = (float*)slots.out(0);
-  float* const acc_l = slots.lse(0);
-  float* const lse_out = d->lse != nullptr ? d->lse[a] : nullptr;
-  if (d->n_q[a] == 0) return CP_OK;
-  int rc = ring_partial(d, w, false, a, kv_of_step(0), acc_o, acc_l, st);
-  for (int j = 1; j < n && rc == CP_OK; ++j) {
-    const bool last = j == n - 1;
-    const PrefillAccumulate acc = {acc_o, acc_l, last ? d->out[a] : nullptr,
-                                   last ? lse_out : nullptr, d->out_dtype};
-    rc = ring_partial(d, w, false, a, kv_of_step(j), nullptr, nullptr, st, &acc);
-  }
-  return rc;
-}
-
-// fused_merge == 2: all ring steps of rank a in one launch (see launch_prefill_mfma_ring).
-// `kv_of_step(j)` names the KV rank of step j.
-template <typename KvOf>
-int ring_rank_walk(const cp_ring_desc* d, const RingWork& w, const RingSlots& slots, int a,
-                   int n, hipStream_t st, KvOf kv_of_step) {
-  if (d->n_q[a] == 0) return CP_OK;
-  if (!w.use_bounds) return CP_ERR_UNSUPPORTED;
-  const void* k[CP_MAX_PARTS];
-  const void* v[CP_MAX_PARTS];
-  const int32_t* pos[CP_MAX_PARTS];
-  const void* bounds[CP_MAX_PARTS];
-  int64_t n_kv[CP_MAX_PARTS];
+// What the options that ask for the merge inside the attention launch require: the MFMA kernel
+// with head_dim 128 on one sequence per rank, and calls long enough not to split their KV axis.
+int check_fused(const cp_ring_desc* d) {
+  const int n = d->n_ranks;
+  const bool mfma = attn_mfma_applies(d->dtype, d->head_dim, d->n_q_heads, d->n_kv_heads) &&
+                    d->head_dim == 128;
+  const bool walk = d->fused_merge == 2;
+  if (n == 1 && !walk) return CP_OK;
+  if (walk && n > kMaxTable) return CP_ERR_UNSUPPORTED;
   int64_t largest = 0;
-  for (int j = 0; j < n; ++j) {
-    const int s = kv_of_step(j);
-    if (!aligned16(d->k[s]) || !aligned16(d->v[s])) return CP_ERR_ALIGN;
-    k[j] = d->k[s]; v[j] = d->v[s]; pos[j] = d->kv_pos[s]; n_kv[j] = d->n_kv[s];
-    bounds[j] = (const char*)d->workspace + w.bounds_off[s];
-    largest = std::max(largest, d->n_kv[s]);
-  }
-  if (!aligned16(d->q[a])) return CP_ERR_ALIGN;
-  cp_shape s = ring_shape(d, a, 0, false);
-  s.total_kv = largest;
-  if (!prefill_ring_walk_applies(s, n)) return CP_ERR_UNSUPPORTED;
-  const int32_t* arrived = d->arrived != nullptr ? d->arrived[a] : nullptr;
-  float* const lse_out = d->lse != nullptr ? d->lse[a] : nullptr;
-  return launch_prefill_mfma_ring(s, resolve_scale(s.softmax_scale, s.head_dim), d->q[a],
-                                  d->q_pos[a], n, k, v, pos, bounds, n_kv, arrived,
-                                  d->ring_error != nullptr ? d->ring_error + a : nullptr,
-                                  d->spin_limit, d->out[a],
-                                  lse_out != nullptr ? lse_out : slots.lse(0),  // LSE not wanted
-                                  d->out_dtype, st);
-}
-
-void ring_finish(RingWork& w) {
-  if (w.dual) {
-    (void)hipEventDestroy(w.fork);
-    (void)hipEventDestroy(w.join);
-    w.dual = false;
-  }
-}
-
-// The N partial calls of one rank: `call(j, stream)` issues step j. With two streams the
-// aux stream first waits for everything enqueued on `st` so far (the previous rank's merge
-// still reads the slots), and `st` waits for the aux stream before the caller merges.
-template <typename Call>
-int ring_rank_steps(const RingWork& w, int n, hipStream_t st, Call call) {
-  if (w.dual) {
-    if (hipEventRecord(w.fork, st) != hipSuccess ||
-        hipStreamWaitEvent(w.aux, w.fork, 0) != hipSuccess)
-      return CP_ERR_LAUNCH;
-  }
-  for (int j = 0; j < n; ++j) {
-    const int rc = call(j, (w.dual && (j & 1)) ? w.aux : st);
-    if (rc != CP_OK) return rc;
-  }
-  if (w.dual) {
-    if (hipEventRecord(w.join, w.aux) != hipSuccess ||
-        hipStreamWaitEvent(st, w.join, 0) != hipSuccess)
-      return CP_ERR_LAUNCH;
+  for (int b = 0; b < n; ++b) largest = std::max(largest, d->n_kv[b]);
+  for (int a = 0; a < n; ++a) {
+    if (!mfma) return CP_ERR_UNSUPPORTED;
+    if (d->n_q[a] == 0) continue;
+    cp_shape s = ring_shape(d, a, 0, false);
+    for (int b = 0; b < n; ++b) {
+      s.total_kv = d->n_kv[b];
+      if (!attn_mfma_merging_applies(single_shape(s))) return CP_ERR_UNSUPPORTED;
+    }
+    s.total_kv = largest;
+    if (walk && !attn_mfma_merging_applies(single_shape(s))) return CP_ERR_UNSUPPORTED;
   }
   return CP_OK;
 }
 
-// One partial-attention call of the ring: queries of rank `a` against KV of rank `b`.
-int ring_partial(const cp_ring_desc* d, const RingWork& w, bool decode, int a, int b, void* o,
-                 float* l, hipStream_t st, const PrefillAccumulate* acc = nullptr) {
-  cp_shape s = ring_shape(d, a, b, decode);
-  if (acc != nullptr && (decode || !w.use_bounds)) return CP_ERR_UNSUPPORTED;
-  if (decode)
-    return cp_attn_decode(&s, d->q[a], d->k[b], d->v[b], d->q_pos[a], d->kv_pos[b],
-                          d->cu_seqlens_kv[b], d->bid[a], o, l, d->part_dtype, w.call_ws,
-                          w.call_ws_bytes, st);
-  if (w.use_bounds && s.total_q > 0) {
-    if (!aligned16(d->q[a]) || !aligned16(d->k[b]) || !aligned16(d->v[b])) return CP_ERR_ALIGN;
-    return launch_prefill_mfma(s, resolve_scale(s.softmax_scale, s.head_dim), d->q[a], d->k[b],
-                               d->v[b], d->q_pos[a], d->kv_pos[b], o, l, d->part_dtype, w.call_ws,
-                               w.call_ws_bytes, (char*)d->workspace + w.bounds_off[b], nullptr, st,
-                               acc);
-  }
-  const bool packed = ring_is_packed(d, decode);
-  return cp_attn_partial(&s, d->q[a], d->k[b], d->v[b], d->q_pos[a], d->kv_pos[b],
-                         packed ? d->cu_seqlens_q[a] : nullptr,
-                         packed ? d->cu_seqlens_kv[b] : nullptr, o, l, d->part_dtype, w.call_ws,
-                         w.call_ws_bytes, st);
-}
-
-int ring_merge(const cp_ring_desc* d, const RingSlots& slots, int a, int64_t first_slot,
-               hipStream_t st) {
+int ring_merge(const cp_ring_desc* d, const RingSlots& slots, int a, hipStream_t st) {
   const void* outs[CP_MAX_PARTS];
   const float* lses[CP_MAX_PARTS];
-  for (int s = 0; s < d->n_ranks; ++s) {
-    outs[s] = slots.out(first_slot + s);
-    lses[s] = slots.lse(first_slot + s);
+  for (int b = 0; b < d->n_ranks; ++b) {
+    outs[b] = slots.out(slot_of(d, a, b));
+    lses[b] = slots.lse(slot_of(d, a, b));
   }
   float* lse_out = d->lse != nullptr ? d->lse[a] : nullptr;
   return cp_attn_merge(d->n_q[a] * d->n_q_heads, d->head_dim, d->n_ranks, outs, lses,
                        d->part_dtype, d->out[a], d->out_dtype, lse_out, st);
+}
+
+// The whole ring as one attention launch (plus the tile-bound pre-pass and, where the KV axis is
+// split or the partials are kept, a merge launch over all ranks).
+int ring_one_launch(const cp_ring_desc* d, hipStream_t st) {
+  const int n = d->n_ranks;
+  AttnTable t = {};
+  t.n_ranks = t.n_shards = n;
+  const RingSlots slots = make_slots(d);
+  for (int r = 0; r < n; ++r) {
+    t.q[r] = d->q[r]; t.q_pos[r] = d->q_pos[r];
+    t.out[r] = d->keep_partials ? slots.out(slot_of(d, r, 0)) : d->out[r];
+    t.lse[r] = d->keep_partials ? slots.lse(slot_of(d, r, 0))
+                                : d->lse != nullptr ? d->lse[r] : nullptr;
+    t.k[r] = d->k[r]; t.v[r] = d->v[r]; t.kv_pos[r] = d->kv_pos[r];
+    t.n_kv[r] = (int32_t)d->n_kv[r];
+    t.tok_begin[r + 1] = t.tok_begin[r] + (int32_t)d->n_q[r];
+    t.tile_begin[r + 1] = t.tile_begin[r] + kv_tiles(d->n_kv[r]);
+    if (!aligned16(d->q[r]) || !aligned16(d->k[r]) || !aligned16(d->v[r]) || !aligned16(d->out[r]))
+      return CP_ERR_ALIGN;
+  }
+  const AttnShape s = ring_attn_shape(d);
+  if (s.total_q == 0) return CP_OK;
+  // (slots of the partials lie slot_step apart along the KV shards)
+  const int64_t slot_step = d->gathered_q ? n : 1;
+  const int64_t slot_lse = slots.messages ? (int64_t)(slots.out_stride / sizeof(float))
+                                          : (int64_t)slots.lse_slot_elems;
+  const AttnOut o = {d->keep_partials ? d->part_dtype : d->out_dtype,
+                     slot_step * (int64_t)slots.out_stride, slot_step * slot_lse};
+  int rc;
+  if (d->dtype == CP_FP32) {
+    rc = launch_attn_fp32(s, t, o, st);
+  } else {
+    char* ws = (char*)d->workspace;
+    size_t left = d->workspace_bytes;
+    const int32_t* q_lo = nullptr;
+    if (ring_is_packed(d, false)) {
+      int64_t keys = 0;
+      for (int r = 0; r < n; ++r) keys += d->n_kv[r];
+      rc = launch_varseq_encode(d->batch, keys, t, d->cu_seqlens_q, d->cu_seqlens_kv, ws, &q_lo,
+                                st);
+      if (rc != CP_OK) return rc;
+      ws += ring_varseq_bytes(d);
+      left -= ring_varseq_bytes(d);
+    }
+    if (d->fused_merge == 2 && d->arrived != nullptr) {
+      // every shard behind its arrival flag: a launch per rank walks the shards in ring order
+      rc = launch_kv_tile_bounds(t, s.n_tiles, ws, st);
+      for (int k = 0; k < n && rc == CP_OK; ++k) {
+        if (d->n_q[k] == 0) continue;
+        AttnTable tk = t;
+        tk.n_ranks = 1;
+        tk.q[0] = t.q[k]; tk.q_pos[0] = t.q_pos[k]; tk.out[0] = t.out[k]; tk.lse[0] = t.lse[k];
+        tk.tok_begin[1] = (int32_t)d->n_q[k];
+        AttnShape sk = s;
+        sk.total_q = d->n_q[k];
+        rc = launch_attn_mfma_ring(sk, tk, k, d->arrived[k], d->ring_error + k, d->spin_limit,
+                                   d->out_dtype, ws, st);
+      }
+      return rc;
+    }
+    rc = launch_attn_mfma(s, t, o, q_lo, nullptr, ws, left, st);
+  }
+  if (rc != CP_OK || !d->keep_partials) return rc;
+  MergeTable m = {};
+  m.n_ranks = n; m.n_parts = n; m.n_groups = 1;
+  m.part_bytes = o.shard_out_bytes;
+  m.part_lse_elems = o.shard_lse_elems;
+  for (int a = 0; a < n; ++a) {
+    m.part[a] = t.out[a]; m.part_lse[a] = t.lse[a];
+    m.out[a] = d->out[a]; m.lse[a] = d->lse != nullptr ? d->lse[a] : nullptr;
+    m.row_begin[a + 1] = m.row_begin[a] + d->n_q[a] * d->n_q_heads;
+  }
+  return launch_merge_table(m, d->head_dim, d->part_dtype, d->out_dtype, st);
+}
+
+// N x N partial-attention calls and a merge per rank, for the rings that are not one launch.
+// `kv_of_step(k, j)`: the KV rank of step j of rank k's queries.
+template <typename KvOf>
+int ring_steps(const cp_ring_desc* d, hipStream_t st, KvOf kv_of_step) {
+  const RingSlots slots = make_slots(d);
+  const int n = d->n_ranks;
+  const bool packed = ring_is_packed(d, false);
+  for (int a = 0; a < n; ++a) {
+    for (int j = 0; j < n; ++j) {
+      const int b = kv_of_step(a, j);
+      const cp_shape s = ring_shape(d, a, b, false);
+      const int64_t slot = slot_of(d, a, b);
+      const int rc = cp_attn_partial(&s, d->q[a], d->k[b], d->v[b], d->q_pos[a], d->kv_pos[b],
+                                     packed ? d->cu_seqlens_q[a] : nullptr,
+                                     packed ? d->cu_seqlens_kv[b] : nullptr, slots.out(slot),
+                                     slots.lse(slot), d->part_dtype, d->workspace,
+                                     d->workspace_bytes, st);
+      if (rc != CP_OK) return rc;
+    }
+    const int rc = ring_merge(d, slots, a, st);
+    if (rc != CP_OK) return rc;
+  }
+  return CP_OK;
+}
+
+// Prefill in either ring order: the same N x N partials and the same merge.
+template <typename KvOf>
+int ring_prefill(const cp_ring_desc* d, hipStream_t st, KvOf kv_of_step) {
+  int rc = check_ring_workspace(d, false);
+  if (rc != CP_OK) return rc;
+  if (d->fused_merge) {
+    rc = check_fused(d);
+    if (rc != CP_OK) return rc;
+  }
+  return ring_is_one_launch(d) ? ring_one_launch(d, st) : ring_steps(d, st, kv_of_step);
 }
 
 }  // namespace
@@ -626,34 +670,12 @@ size_t cp_ring_message_bytes(const cp_ring_desc* d) {
 }
 
 int cp_ring_passkv(const cp_ring_desc* d, void* stream) {
-  int rc = check_ring(d, false);
+  const int rc = check_ring(d, false);
   if (rc != CP_OK) return rc;
   if (d->gathered_q) return CP_ERR_UNSUPPORTED;  // pass-Q only
-  hipStream_t st = (hipStream_t)stream;
-  const RingSlots slots = make_slots(d);
   const int n = d->n_ranks;
-  RingWork w;
-  rc = ring_prepare(d, false, st, w);
-  if (rc != CP_OK) return rc;
-  // Algorithm 2 as seen from each rank k in turn: N ring steps, then a local merge.
-  for (int k = 0; k < n && rc == CP_OK; ++k) {
-    if (d->fused_merge == 2) {
-      rc = ring_rank_walk(d, w, slots, k, n, st, [&](int j) { return ((k - j) % n + n) % n; });
-      continue;
-    }
-    if (d->fused_merge && n > 1) {
-      rc = ring_rank_fused(d, w, slots, k, n, st, [&](int j) { return ((k - j) % n + n) % n; });
-      continue;
-    }
-    const int64_t base = d->keep_partials ? (int64_t)k * n : 0;
-    rc = ring_rank_steps(w, n, st, [&](int j, hipStream_t sj) {
-      const int s = ((k - j) % n + n) % n;  // origin rank of the KV held at step j
-      return ring_partial(d, w, false, k, s, slots.out(base + s), slots.lse(base + s), sj);
-    });
-    if (rc == CP_OK) rc = ring_merge(d, slots, k, base, st);
-  }
-  ring_finish(w);
-  return rc;
+  // Algorithm 2: at step j rank k holds the KV of rank (k - j) mod N.
+  return ring_prefill(d, (hipStream_t)stream, [n](int k, int j) { return ((k - j) % n + n) % n; });
 }
 
 // gathered_q: the query shards of all source ranks lie back to back in one buffer (an
@@ -672,161 +694,113 @@ static bool queries_are_gathered(const cp_ring_desc* d, bool decode) {
   return true;
 }
 
-static int ring_passq_gathered(const cp_ring_desc* d, bool decode, hipStream_t st) {
-  if (!queries_are_gathered(d, decode)) return CP_ERR_UNSUPPORTED;
+// Algorithm 4 with gathered queries: one decode call per KV holder.
+static int ring_decode_gathered(const cp_ring_desc* d, hipStream_t st) {
   const RingSlots slots = make_slots(d);
   const int n = d->n_ranks;
-  RingWork w;
-  int rc = ring_prepare(d, decode, st, w);
-  if (rc != CP_OK) return rc;
-  if (decode) {
-    // Every holder's split-KV partials into its own region, one merge over splits x holders.
-    cp_shape shapes[CP_MAX_PARTS];
-    void* regions[CP_MAX_PARTS];
-    bool flat = true;
-    size_t off = 0;
-    for (int k = 0; k < n; ++k) {
-      shapes[k] = gathered_decode_shape(d, k);
-      flat = flat && decode_flat_applies(shapes[k]);
-      regions[k] = w.call_ws + off;
-      off += decode_flat_region_bytes(shapes[k]);
-    }
-    if (flat) {
-      if (off > w.call_ws_bytes) return CP_ERR_WORKSPACE;
-      for (int k = 0; k < n && rc == CP_OK; ++k) {
-        if (!aligned16(d->q[0]) || !aligned16(d->k[k]) || !aligned16(d->v[k])) rc = CP_ERR_ALIGN;
-        else
-          rc = launch_decode_flat_partials(
-              shapes[k], resolve_scale(d->softmax_scale, d->head_dim), d->q[0], d->k[k], d->v[k],
-              d->q_pos[0], d->kv_pos[k], d->cu_seqlens_kv[k], d->bid[0], regions[k],
-              decode_flat_region_bytes(shapes[k]), st);
-      }
-      if (rc != CP_OK) return rc;
-      const size_t out_row = (size_t)d->n_q_heads * d->head_dim * elem_size(d->out_dtype);
-      bool one = true;
-      for (int a = 1; a < n && one; ++a) {
-        one = (char*)d->out[a] == (char*)d->out[a - 1] + d->n_q[a - 1] * out_row;
-        if (d->lse != nullptr)
-          one = one && d->lse[a] != nullptr && d->lse[0] != nullptr &&
-                d->lse[a] == d->lse[a - 1] + d->n_q[a - 1] * d->n_q_heads;
-      }
-      if (one)
-        return launch_decode_flat_merge(n, shapes, regions, d->cu_seqlens_kv, d->bid[0],
-                                        (int64_t)n * d->n_q[0], d->out[0], d->out_dtype,
-                                        d->lse != nullptr ? d->lse[0] : nullptr, st);
-      for (int a = 0; a < n && rc == CP_OK; ++a)
-        rc = launch_decode_flat_merge(n, shapes, regions, d->cu_seqlens_kv, d->bid[a], d->n_q[a],
-                                      d->out[a], d->out_dtype,
-                                      d->lse != nullptr ? d->lse[a] : nullptr, st);
-      return rc;
-    }
+  int rc = CP_OK;
+  // Every holder's split-KV partials into its own region, one merge over splits x holders.
+  cp_shape shapes[CP_MAX_PARTS];
+  void* regions[CP_MAX_PARTS];
+  bool flat = true;
+  size_t off = 0;
+  for (int k = 0; k < n; ++k) {
+    shapes[k] = gathered_decode_shape(d, k);
+    flat = flat && decode_flat_applies(shapes[k]);
+    regions[k] = (char*)d->workspace + off;
+    off += decode_flat_region_bytes(shapes[k]);
   }
-  for (int k = 0; k < n && rc == CP_OK; ++k) {
-    cp_shape s = ring_shape(d, 0, k, decode);
-    s.total_q = (int64_t)n * d->n_q[0];
-    void* const o = slots.out((int64_t)k * n);
-    float* const l = slots.lse((int64_t)k * n);
-    if (decode) {
-      rc = cp_attn_decode(&s, d->q[0], d->k[k], d->v[k], d->q_pos[0], d->kv_pos[k],
-                          d->cu_seqlens_kv[k], d->bid[0], o, l, d->part_dtype, w.call_ws,
-                          w.call_ws_bytes, st);
-    } else if (w.use_bounds) {
+  const size_t out_row = (size_t)d->n_q_heads * d->head_dim * elem_size(d->out_dtype);
+  bool one = true;   // the ranks' outputs lie back to back as the queries do
+  for (int a = 1; a < n && one; ++a) {
+    one = (char*)d->out[a] == (char*)d->out[a - 1] + d->n_q[a - 1] * out_row;
+    if (d->lse != nullptr)
+      one = one && d->lse[a] != nullptr && d->lse[0] != nullptr &&
+            d->lse[a] == d->lse[a - 1] + d->n_q[a - 1] * d->n_q_heads;
+  }
+  float* const lse0 = d->lse != nullptr ? d->lse[0] : nullptr;
+  if (flat) {
+    if (off > d->workspace_bytes) return CP_ERR_WORKSPACE;
+    for (int k = 0; k < n && rc == CP_OK; ++k) {
       if (!aligned16(d->q[0]) || !aligned16(d->k[k]) || !aligned16(d->v[k])) rc = CP_ERR_ALIGN;
       else
-        rc = launch_prefill_mfma(s, resolve_scale(s.softmax_scale, s.head_dim), d->q[0], d->k[k],
-                                 d->v[k], d->q_pos[0], d->kv_pos[k], o, l, d->part_dtype,
-                                 w.call_ws, w.call_ws_bytes,
-                                 (char*)d->workspace + w.bounds_off[k], nullptr, st, nullptr);
-    } else {
-      rc = cp_attn_partial(&s, d->q[0], d->k[k], d->v[k], d->q_pos[0], d->kv_pos[k], nullptr,
-                           nullptr, o, l, d->part_dtype, w.call_ws, w.call_ws_bytes, st);
+        rc = launch_decode_flat_partials(
+            shapes[k], resolve_scale(d->softmax_scale, d->head_dim), d->q[0], d->k[k], d->v[k],
+            d->q_pos[0], d->kv_pos[k], d->cu_seqlens_kv[k], d->bid[0], regions[k],
+            decode_flat_region_bytes(shapes[k]), st);
     }
-  }
-  // The All2All: source rank a merges slot k * n + a of every holder k. When the outputs of
-  // the ranks lie back to back as the queries do, the N merges are one launch over the
-  // holders' whole blocks.
-  const size_t out_row = (size_t)d->n_q_heads * d->head_dim * elem_size(d->out_dtype);
-  bool one_merge = slots.max_q == d->n_q[0];
-  for (int a = 1; a < n && one_merge; ++a) {
-    one_merge = (char*)d->out[a] == (char*)d->out[a - 1] + d->n_q[a - 1] * out_row;
-    if (d->lse != nullptr)
-      one_merge = one_merge && d->lse[a] != nullptr &&
-                  d->lse[a] == d->lse[a - 1] + d->n_q[a - 1] * d->n_q_heads;
-  }
-  if (one_merge && (d->lse == nullptr || d->lse[0] != nullptr) && rc == CP_OK) {
-    const void* outs[CP_MAX_PARTS];
-    const float* lses[CP_MAX_PARTS];
-    for (int k = 0; k < n; ++k) {
-      outs[k] = slots.out((int64_t)k * n);
-      lses[k] = slots.lse((int64_t)k * n);
-    }
-    rc = cp_attn_merge((int64_t)n * d->n_q[0] * d->n_q_heads, d->head_dim, n, outs, lses,
-                       d->part_dtype, d->out[0], d->out_dtype,
-                       d->lse != nullptr ? d->lse[0] : nullptr, st);
-    ring_finish(w);
+    if (rc != CP_OK) return rc;
+    if (one)
+      return launch_decode_flat_merge(n, shapes, regions, d->cu_seqlens_kv, d->bid[0],
+                                      (int64_t)n * d->n_q[0], d->out[0], d->out_dtype, lse0, st);
+    for (int a = 0; a < n && rc == CP_OK; ++a)
+      rc = launch_decode_flat_merge(n, shapes, regions, d->cu_seqlens_kv, d->bid[a], d->n_q[a],
+                                    d->out[a], d->out_dtype,
+                                    d->lse != nullptr ? d->lse[a] : nullptr, st);
     return rc;
   }
-  for (int a = 0; a < n && rc == CP_OK; ++a) {
+  for (int k = 0; k < n; ++k) {
+    const int64_t slot = slot_of(d, 0, k);
+    rc = cp_attn_decode(&shapes[k], d->q[0], d->k[k], d->v[k], d->q_pos[0], d->kv_pos[k],
+                        d->cu_seqlens_kv[k], d->bid[0], slots.out(slot), slots.lse(slot),
+                        d->part_dtype, d->workspace, d->workspace_bytes, st);
+    if (rc != CP_OK) return rc;
+  }
+  // The All2All: source rank a merges slot k * n + a of every holder k. With the outputs back to
+  // back the N merges are one launch over the holders' whole blocks.
+  if (one) {
     const void* outs[CP_MAX_PARTS];
     const float* lses[CP_MAX_PARTS];
     for (int k = 0; k < n; ++k) {
-      outs[k] = slots.out((int64_t)k * n + a);
-      lses[k] = slots.lse((int64_t)k * n + a);
+      outs[k] = slots.out(slot_of(d, 0, k));
+      lses[k] = slots.lse(slot_of(d, 0, k));
     }
-    float* lse_out = d->lse != nullptr ? d->lse[a] : nullptr;
-    rc = cp_attn_merge(d->n_q[a] * d->n_q_heads, d->head_dim, n, outs, lses, d->part_dtype,
-                       d->out[a], d->out_dtype, lse_out, st);
+    return cp_attn_merge((int64_t)n * d->n_q[0] * d->n_q_heads, d->head_dim, n, outs, lses,
+                         d->part_dtype, d->out[0], d->out_dtype, lse0, st);
   }
-  ring_finish(w);
+  for (int a = 0; a < n && rc == CP_OK; ++a) rc = ring_merge(d, slots, a, st);
   return rc;
 }
 
-static int ring_passq_common(const cp_ring_desc* d, bool decode, void* stream) {
-  int rc = check_ring(d, decode);
+// Algorithm 4: N x N decode calls, grouped by source rank, and a merge per source.
+static int ring_decode(const cp_ring_desc* d, hipStream_t st) {
+  int rc = check_ring_workspace(d, true);
   if (rc != CP_OK) return rc;
-  if (d->fused_merge == 2) return CP_ERR_UNSUPPORTED;  // pass-KV only: the queries stay put
-  if (d->gathered_q) return ring_passq_gathered(d, decode, (hipStream_t)stream);
-  hipStream_t st = (hipStream_t)stream;
+  if (d->gathered_q) return ring_decode_gathered(d, st);
   const RingSlots slots = make_slots(d);
   const int n = d->n_ranks;
-  RingWork w;
-  rc = ring_prepare(d, decode, st, w);
-  if (rc != CP_OK) return rc;
-  if (d->keep_partials) {
-    // Algorithms 3 / 4 in ring order: at step j rank k holds the queries of rank
-    // s = (k - j) mod N. Writing the result to slot [s][k] is the permute + All2All.
-    for (int j = 0; j < n && rc == CP_OK; ++j)
-      for (int k = 0; k < n && rc == CP_OK; ++k) {
-        const int s = ((k - j) % n + n) % n;
-        rc = ring_partial(d, w, decode, s, k, slots.out((int64_t)s * n + k),
-                          slots.lse((int64_t)s * n + k), st);
-      }
-    for (int s = 0; s < n && rc == CP_OK; ++s) rc = ring_merge(d, slots, s, (int64_t)s * n, st);
-    ring_finish(w);
-    return rc;
-  }
-  // With N reusable slots the same N*N calls are issued grouped by source rank s
-  // (for each s the holders k = s, s+1, ... in ring order), so that the N partials of
-  // one source are complete, and can be merged, before the slots are reused.
   for (int s = 0; s < n && rc == CP_OK; ++s) {
-    if (d->fused_merge && n > 1) {
-      rc = ring_rank_fused(d, w, slots, s, n, st, [&](int j) { return (s + j) % n; });
-      continue;
-    }
-    rc = ring_rank_steps(w, n, st, [&](int j, hipStream_t sj) {
+    for (int j = 0; j < n && rc == CP_OK; ++j) {
       const int k = (s + j) % n;
-      return ring_partial(d, w, decode, s, k, slots.out(k), slots.lse(k), sj);
-    });
-    if (rc == CP_OK) rc = ring_merge(d, slots, s, 0, st);
+      const cp_shape sh = ring_shape(d, s, k, true);
+      const int64_t slot = slot_of(d, s, k);
+      rc = cp_attn_decode(&sh, d->q[s], d->k[k], d->v[k], d->q_pos[s], d->kv_pos[k],
+                          d->cu_seqlens_kv[k], d->bid[s], slots.out(slot), slots.lse(slot),
+                          d->part_dtype, d->workspace, d->workspace_bytes, st);
+    }
+    if (rc == CP_OK) rc = ring_merge(d, slots, s, st);
   }
-  ring_finish(w);
   return rc;
 }
 
-int cp_ring_passq(const cp_ring_desc* d, void* stream) { return ring_passq_common(d, false, stream); }
+int cp_ring_passq(const cp_ring_desc* d, void* stream) {
+  const int rc = check_ring(d, false);
+  if (rc != CP_OK) return rc;
+  if (d->fused_merge == 2) return CP_ERR_UNSUPPORTED;  // pass-KV only: the queries stay put
+  if (d->gathered_q && !queries_are_gathered(d, false)) return CP_ERR_UNSUPPORTED;
+  const int n = d->n_ranks;
+  // Algorithm 3: at step j rank k answers the queries of rank (k - j) mod N, so rank s's
+  // queries meet the KV of rank (s + j) mod N; writing the result to the slot of (s, k) is the
+  // permute + All2All.
+  return ring_prefill(d, (hipStream_t)stream, [n](int s, int j) { return (s + j) % n; });
+}
 
 int cp_ring_passq_decode(const cp_ring_desc* d, void* stream) {
-  return ring_passq_common(d, true, stream);
+  const int rc = check_ring(d, true);
+  if (rc != CP_OK) return rc;
+  if (d->fused_merge == 2) return CP_ERR_UNSUPPORTED;
+  if (d->gathered_q && !queries_are_gathered(d, true)) return CP_ERR_UNSUPPORTED;
+  return ring_decode(d, (hipStream_t)stream);
 }
 
 int cp_ring_prefill(const cp_ring_desc* d, const cp_select_params* params, int64_t p_cached,

@@ -1,0 +1,324 @@
+// fp32 attention on the matrix pipe, head_dim 64 and 128: the queries of one or more ranks
+// against one or more KV shards in one launch (AttnTable), fp32 throughout.
+//
+// v_mfma_f32_16x16x4_f32 for both products, operands straight from global memory to registers:
+// S^T = K Q^T leaves a lane with four keys of one query, so the softmax statistics are per-lane
+// scalars (two lane exchanges) and exp(S^T) is the B operand of O^T += V^T P^T as it stands. The
+// contraction order of the first product is free, so a lane takes four consecutive channels
+// per 16-byte load of K; the channel order of the second is free as well, so a lane's 16-byte
+// load of V serves four channel blocks.
+//
+// A workgroup of 4 wavefronts owns 16 * NR rows (token, head-in-group) of one KV head; the
+// 16-key blocks that any of its queries can see are listed in LDS and dealt out over the
+// wavefronts, whose results are combined in LDS at the end. Splitting the keys and not the rows
+// over the wavefronts keeps small problems (the 512-token configuration has 2048 rows) on many
+// CUs with a short serial chain each. NR = 2 (head_dim 64, many rows) halves the K/V traffic
+// from L2.
+//
+// Bound: the matrix pipe's fp32 rate (157 TFLOP/s) for long shards, launch and the chain
+// positions -> list -> K -> V for short ones.
+#include "cp_common.h"
+#include "cp_table.h"
+
+namespace cp {
+namespace {
+
+constexpr int NWAVE = 4;
+constexpr int NTHREADS = NWAVE * 64;
+constexpr int BLK = 16;                     // keys per block
+constexpr int BLKS_PER_TILE = kAttnTile / BLK;
+constexpr int MAX_LIST = NTHREADS;          // blocks looked at per chunk
+
+struct Params {
+  AttnTable t;
+  int64_t rows;              // total_q * group
+  int64_t out_shard_bytes;   // per_shard: distance between the results of two shards
+  int64_t lse_shard_elems;
+  int32_t group;
+  int32_t n_kv_heads;
+  int32_t n_tiles;
+  int32_t per_shard;
+  float scale_log2;
+};
+
+__device__ __forceinline__ floatx4_t mfma4(float a, float b, floatx4_t c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+template <int D>
+struct BlockRegs {
+  floatx4_t k[D / 16];      // key lane % 16, channels 16 j + (lane / 16) * 4 .. +3
+  floatx4_t v[4][D / 64];   // key (lane / 16) * 4 + i, channels 64 h + (lane % 16) * 4 .. +3
+  int32_t pos[4];           // of the keys (lane / 16) * 4 + i
+};
+
+template <int D, int NR, typename TO>
+__global__ __launch_bounds__(NTHREADS) void attn_fp32_kernel(const Params p) {
+  constexpr int ROWS = 16 * NR;
+  constexpr int STRIDE = D + 4;
+  __shared__ int2 list[MAX_LIST];                       // (shard, first key)
+  __shared__ int wg_scratch[8];
+  __shared__ __align__(16) float comb[NWAVE][ROWS][STRIDE];
+  __shared__ float comb_m[NWAVE][ROWS], comb_l[NWAVE][ROWS];
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int n = lane & 15, kg = lane >> 4;
+  const int row_block = ordered_row_block(blockIdx.x, gridDim.x, p.t.n_ranks, lane);
+  const int kvh = blockIdx.y;
+  const int z_shard = p.per_shard ? blockIdx.z : 0;
+
+  // ---- queries: row r of column group c is this lane's column n ----
+  floatx4_t qf[NR][D / 16];
+  int32_t qp[NR];
+  int qmax = INT32_MIN;
+#pragma unroll
+  for (int c = 0; c < NR; ++c) {
+    const int64_t r = (int64_t)row_block * ROWS + c * 16 + n;
+    const bool ok = r < p.rows;
+    const int token = ok ? (int)((uint32_t)r / (uint32_t)p.group) : 0;
+    const int hg = ok ? (int)(r - (int64_t)token * p.group) : 0;
+    const int a = rank_of_token(p.t, token);
+    const int local = token - p.t.tok_begin[a];
+    const float* q = (const float*)p.t.q[a] +
+                     (((int64_t)local * p.n_kv_heads + kvh) * p.group + hg) * D + kg * 4;
+    qp[c] = ok ? p.t.q_pos[a][local] : CP_POS_PAD_Q;
+#pragma unroll
+    for (int j = 0; j < D / 16; ++j)
+      qf[c][j] = ok ? *(const floatx4_t*)(q + j * 16) : floatx4_t{0.f, 0.f, 0.f, 0.f};
+    qmax = max(qmax, qp[c]);
+  }
+#pragma unroll
+  for (int o = 8; o > 0; o >>= 1) qmax = max(qmax, __shfl_xor(qmax, o, 64));
+  qmax = __builtin_amdgcn_readfirstlane(qmax);  // (the four wavefronts hold the same rows)
+
+  float m_run[NR], l_run[NR];
+  floatx4_t acc[NR][D / 16];
+#pragma unroll
+  for (int c = 0; c < NR; ++c) {
+    m_run[c] = -INFINITY;
+    l_run[c] = 0.f;
+#pragma unroll
+    for (int i = 0; i < D / 16; ++i) acc[c][i] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+  }
+
+  const uint32_t stride = (uint32_t)p.n_kv_heads * D;
+  auto load_block = [&](int e, BlockRegs<D>& x) {
+    const int2 le = list[e];
+    const int sh = __builtin_amdgcn_readfirstlane(le.x), key0 = __builtin_amdgcn_readfirstlane(le.y);
+    const int last = p.t.n_kv[sh] - 1 - key0;   // >= 0
+    const float* kt = (const float*)p.t.k[sh] + (int64_t)key0 * stride + kvh * D;
+    const float* vt = (const float*)p.t.v[sh] + (int64_t)key0 * stride + kvh * D;
+    const int32_t* pt = p.t.kv_pos[sh] + key0;
+    const uint32_t krow = (uint32_t)min(n, last) * stride + kg * 4;
+#pragma unroll
+    for (int j = 0; j < D / 16; ++j) x.k[j] = *(const floatx4_t*)(kt + krow + j * 16);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int key = kg * 4 + i, kc = min(key, last);
+      const int32_t pos = pt[kc];
+      x.pos[i] = key <= last ? pos : CP_POS_PAD_KV;
+#pragma unroll
+      for (int h = 0; h < D / 64; ++h)
+        x.v[i][h] = *(const floatx4_t*)(vt + (uint32_t)kc * stride + h * 64 + n * 4);
+    }
+  };
+  auto compute = [&](const BlockRegs<D>& x) {
+#pragma unroll
+    for (int c = 0; c < NR; ++c) {
+      floatx4_t s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int j = 0; j < D / 16; ++j)
+#pragma unroll
+        for (int i = 0; i < 4; i += 2) {
+          s0 = mfma4(x.k[j][i], qf[c][j][i], s0);
+          s1 = mfma4(x.k[j][i + 1], qf[c][j][i + 1], s1);
+        }
+      float s[4], mx = -INFINITY;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        s[i] = x.pos[i] <= qp[c] ? (s0[i] + s1[i]) * p.scale_log2 : -INFINITY;
+        mx = fmaxf(mx, s[i]);
+      }
+      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+      const float m_new = fmaxf(m_run[c], mx);
+      const float m_use = m_new == -INFINITY ? 0.f : m_new;
+      const float alpha = __builtin_amdgcn_exp2f(m_run[c] - m_use);
+      m_run[c] = m_new;
+      float ls = 0.f;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        s[i] = __builtin_amdgcn_exp2f(s[i] - m_use);
+        ls += s[i];
+      }
+      l_run[c] = fmaf(l_run[c], alpha, ls);
+      if (__builtin_amdgcn_ballot_w64(alpha != 1.f) != 0) {
+#pragma unroll
+        for (int i = 0; i < D / 16; ++i)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[c][i][e] *= alpha;
+      }
+      // block h * 4 + e of O^T holds the channels 64 h + 4 m + e, m its row
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int h = 0; h < D / 64; ++h)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            acc[c][h * 4 + e] = mfma4(x.v[i][h][e], s[i], acc[c][h * 4 + e]);
+    }
+  };
+
+  const int b_begin = (p.per_shard ? p.t.tile_begin[z_shard] : 0) * BLKS_PER_TILE;
+  const int b_end = (p.per_shard ? p.t.tile_begin[z_shard + 1] : p.n_tiles) * BLKS_PER_TILE;
+  for (int b0 = b_begin; b0 < b_end; b0 += MAX_LIST) {
+    // list of the blocks some query of the workgroup can see
+    const int b = b0 + tid;
+    bool live = false;
+    int sh = z_shard, key0 = 0;
+    if (b < b_end) {
+      const int tile = b / BLKS_PER_TILE;
+      if (!p.per_shard) {
+#pragma unroll 8
+        for (int i = 1; i < p.t.n_shards; ++i) sh += tile >= p.t.tile_begin[i];
+      }
+      key0 = (tile - p.t.tile_begin[sh]) * kAttnTile + (b % BLKS_PER_TILE) * BLK;
+      const int last = p.t.n_kv[sh] - 1 - key0;
+      if (last >= 0) {
+        const int32_t* pt = p.t.kv_pos[sh] + key0;
+        int lo = INT32_MAX;
+#pragma unroll
+        for (int i = 0; i < BLK; ++i) lo = min(lo, pt[min(i, last)]);
+        live = lo <= qmax;
+      }
+    }
+    const uint64_t mask = __builtin_amdgcn_ballot_w64(live);
+    __syncthreads();  // the previous list is no longer read
+    if (lane == 0) wg_scratch[wave] = __builtin_popcountll(mask);
+    __syncthreads();
+    int base = 0, n_live = 0;
+#pragma unroll
+    for (int w = 0; w < NWAVE; ++w) {
+      const int c = wg_scratch[w];
+      if (w < wave) base += c;
+      n_live += c;
+    }
+    n_live = __builtin_amdgcn_readfirstlane(n_live);
+    if (live)
+      list[base + __builtin_popcountll(mask & ((1ull << lane) - 1ull))] = make_int2(sh, key0);
+    __syncthreads();
+
+    // the next block's operands travel while the current one is used
+    BlockRegs<D> cur, nxt;
+    int e = wave;
+    if (e < n_live) load_block(e, cur);
+    while (e < n_live) {
+      const int en = e + NWAVE;
+      if (en < n_live) load_block(en, nxt);
+      compute(cur);
+      cur = nxt;
+      e = en;
+    }
+  }
+
+  // ---- combine the wavefronts (disjoint keys) ----
+#pragma unroll
+  for (int c = 0; c < NR; ++c) {
+    float l = l_run[c];
+    l += __shfl_xor(l, 16, 64);
+    l += __shfl_xor(l, 32, 64);
+    float* const o = comb[wave][c * 16 + n];
+#pragma unroll
+    for (int h = 0; h < D / 64; ++h)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const floatx4_t w = {acc[c][h * 4][i], acc[c][h * 4 + 1][i], acc[c][h * 4 + 2][i],
+                             acc[c][h * 4 + 3][i]};
+        *(floatx4_t*)(o + h * 64 + (kg * 4 + i) * 4) = w;
+      }
+    if (kg == 0) {
+      comb_m[wave][c * 16 + n] = m_run[c];
+      comb_l[wave][c * 16 + n] = l;
+    }
+  }
+  __syncthreads();
+  constexpr int TPR = 16, CPT = D / TPR;   // threads per row, channels per thread
+#pragma unroll
+  for (int c = 0; c < NR; ++c) {
+    const int row = c * 16 + tid / TPR, ch = (tid % TPR) * CPT;
+    const int64_t r = (int64_t)row_block * ROWS + row;
+    if (r >= p.rows) continue;
+    float mw[NWAVE], mmax = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < NWAVE; ++w) {
+      mw[w] = comb_m[w][row];
+      mmax = fmaxf(mmax, mw[w]);
+    }
+    float x[CPT], den = 0.f;
+#pragma unroll
+    for (int i = 0; i < CPT; ++i) x[i] = 0.f;
+    if (mmax != -INFINITY) {
+#pragma unroll
+      for (int w = 0; w < NWAVE; ++w) {
+        const float f = __builtin_amdgcn_exp2f(mw[w] - mmax);
+        den = fmaf(comb_l[w][row], f, den);
+#pragma unroll
+        for (int i = 0; i < CPT; ++i) x[i] = fmaf(comb[w][row][ch + i], f, x[i]);
+      }
+    }
+    const float inv = den > 0.f ? 1.f / den : 0.f;
+    const int token = (int)((uint32_t)r / (uint32_t)p.group);
+    const int hg = (int)(r - (int64_t)token * p.group);
+    const int a = rank_of_token(p.t, token);
+    const int64_t lin =
+        ((int64_t)(token - p.t.tok_begin[a]) * p.n_kv_heads + kvh) * p.group + hg;
+    TO* const o = (TO*)((char*)p.t.out[a] + z_shard * p.out_shard_bytes) + lin * D + ch;
+#pragma unroll
+    for (int i = 0; i < CPT; ++i) o[i] = from_float<TO>(x[i] * inv);
+    if (tid % TPR == 0 && p.t.lse[a] != nullptr)
+      p.t.lse[a][z_shard * p.lse_shard_elems + lin] =
+          den > 0.f ? (mmax + __builtin_amdgcn_logf(den)) * kLn2 : -INFINITY;
+  }
+}
+
+template <int D, int NR, typename TO>
+int launch_t(const AttnShape& s, Params& p, hipStream_t stream) {
+  const int64_t blocks = (p.rows + 16 * NR - 1) / (16 * NR);
+  if (blocks > 0x7fffffffLL) return CP_ERR_SHAPE;
+  hipLaunchKernelGGL((attn_fp32_kernel<D, NR, TO>),
+                     dim3((unsigned)blocks, s.n_kv_heads, s.per_shard ? s.n_shards : 1),
+                     dim3(NTHREADS), 0, stream, p);
+  return check_launch();
+}
+
+template <typename TO>
+int launch_o(const AttnShape& s, Params& p, hipStream_t stream) {
+  if (s.head_dim == 128) return launch_t<128, 1, TO>(s, p, stream);
+  // 32 rows per workgroup once 16 would give every CU more than four workgroups
+  if (p.rows * s.n_kv_heads > 16 * 4 * 256) return launch_t<64, 2, TO>(s, p, stream);
+  return launch_t<64, 1, TO>(s, p, stream);
+}
+
+}  // namespace
+
+int launch_attn_fp32(const AttnShape& s, const AttnTable& t, const AttnOut& o,
+                     hipStream_t stream) {
+  if (s.head_dim != 64 && s.head_dim != 128) return CP_ERR_UNSUPPORTED;
+  if (s.n_kv_heads > 65535) return CP_ERR_SHAPE;
+  // block indices are kept in 31 bits; so are row indices
+  if (s.n_tiles > 0x7fffffff / BLKS_PER_TILE - MAX_LIST) return CP_ERR_SHAPE;
+  Params p = {};
+  p.t = t;
+  p.group = s.n_q_heads / s.n_kv_heads;
+  p.rows = s.total_q * p.group;
+  if (p.rows > 0x7fffffffLL) return CP_ERR_SHAPE;
+  if (p.rows == 0) return CP_OK;
+  p.out_shard_bytes = o.shard_out_bytes;
+  p.lse_shard_elems = o.shard_lse_elems;
+  p.n_kv_heads = s.n_kv_heads;
+  p.n_tiles = s.n_tiles;
+  p.per_shard = s.per_shard ? 1 : 0;
+  p.scale_log2 = s.scale * kLog2e;
+  return o.dtype == CP_BF16 ? launch_o<bf16_t>(s, p, stream) : launch_o<float>(s, p, stream);
+}
+
+}  // namespace cp

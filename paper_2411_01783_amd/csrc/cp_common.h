@@ -41,60 +41,91 @@ int launch_partial_generic(const cp_shape& s, float scale, const void* q, const 
                            const int32_t* cu_q, const int32_t* cu_kv, void* out, float* lse,
                            int32_t out_dtype, hipStream_t stream);
 
-// bf16 MFMA kernel, head_dim 128, batch 1.
+// What one attention launch works on: the queries (and outputs) of n_ranks ranks back to back,
+// against n_shards KV shards, any query against any key that its position lets it see. A single
+// call is one rank and one shard; a ring whose ranks all live on this GPU is one launch. Passed
+// by value (kernel argument segment).
+constexpr int kMaxTable = 32;
+constexpr int kAttnTile = 128;  // keys per tile of the MFMA kernel
+struct AttnTable {
+  const void* q[kMaxTable];
+  const int32_t* q_pos[kMaxTable];
+  void* out[kMaxTable];
+  float* lse[kMaxTable];  // entries may be NULL
+  const void* k[kMaxTable];
+  const void* v[kMaxTable];
+  const int32_t* kv_pos[kMaxTable];
+  int32_t n_kv[kMaxTable];
+  int32_t tok_begin[kMaxTable + 1];   // first token of every rank, and the total
+  int32_t tile_begin[kMaxTable + 1];  // first tile (kAttnTile keys) of every shard, and the total
+  int32_t n_ranks, n_shards;
+};
+// Its sizes, from which a launch is planned (no pointers: also the workspace query's argument).
+struct AttnShape {
+  int32_t dtype, head_dim, n_q_heads, n_kv_heads;
+  int64_t total_q;      // tokens of all ranks
+  int32_t n_tiles;      // tiles of all shards
+  int32_t n_shards;
+  bool per_shard;       // keep the shards' results apart: one (O, LSE) per rank and shard
+  float scale;
+};
+// Where the results go: t.out / t.lse in `dtype`; with per_shard the result against shard b is
+// b * shard_out_bytes (and b * shard_lse_elems) further on.
+struct AttnOut {
+  int32_t dtype;
+  int64_t shard_out_bytes;
+  int64_t shard_lse_elems;
+};
+
+// bf16 MFMA kernel, head_dim 128 and 64, groups of at most 64 heads.
 // `tile_bounds`, when not NULL, holds the per-tile (min, max) of kv_pos already computed by
-// launch_kv_tile_bounds for this kv_pos array; otherwise the launcher computes it into the
-// workspace first.
-size_t prefill_mfma_workspace_bytes(const cp_shape& s);
-size_t kv_tile_bounds_bytes(int64_t total_kv);
-int launch_kv_tile_bounds(const int32_t* kv_pos, int64_t total_kv, void* bounds_out,
-                          hipStream_t stream);
-// Tile bounds of all shards of a ring in one launch; bounds_out[j] as for launch_kv_tile_bounds.
-int launch_kv_tile_bounds_ring(int n_shards, const int32_t* const* kv_pos, const int64_t* n_kv,
-                               void* const* bounds_out, hipStream_t stream);
-// `acc`, when not NULL, turns the launch into "merge into a running result": out / lse /
-// out_dtype are ignored, (acc->out, acc->lse) are read and updated (Equation 4), and if
-// acc->final_out is not NULL the merged O goes there in acc->final_dtype instead of back to
-// acc->out. Only for launches that do not split the KV axis and are not packed batches.
+// launch_kv_tile_bounds for these shards; otherwise the launcher computes it into the
+// workspace first. `q_lo`: packed batches (head_dim 128), smallest visible key position per
+// token, all ranks back to back.
+bool attn_mfma_applies(int dtype, int head_dim, int n_q_heads, int n_kv_heads);
+size_t attn_mfma_workspace_bytes(const AttnShape& s);
+int launch_kv_tile_bounds(const AttnTable& t, int n_tiles, void* bounds_out, hipStream_t stream);
+int launch_attn_mfma(const AttnShape& s, const AttnTable& t, const AttnOut& o,
+                     const int32_t* q_lo, const void* tile_bounds, void* workspace,
+                     size_t workspace_bytes, hipStream_t stream);
+
+// "Merge into a running result": (out, lse) are read and updated (Equation 4), and if final_out
+// is not NULL the merged O goes there in final_dtype instead of back to out. One rank, one
+// shard, no split of the KV axis (attn_mfma_merging_applies), head_dim 128.
 struct PrefillAccumulate {
   float* out;        // fp32 [total_q, n_q_heads, head_dim]
-  float* lse;        // fp32 [total_q, n_q_heads]
+  float* lse;        // fp32 [total_q, n_q_heads]; also t.lse[0]
   void* final_out;   // or NULL
   float* final_lse;  // or NULL
   int32_t final_dtype;
 };
-// `merging`: for a call that merges into a running result in its epilogue (see make_plan).
-bool prefill_mfma_splits_kv(const cp_shape& s, bool merging);
-int launch_prefill_mfma(const cp_shape& s, float scale, const void* q, const void* k,
-                        const void* v, const int32_t* q_pos, const int32_t* kv_pos, void* out,
-                        float* lse, int32_t out_dtype, void* workspace, size_t workspace_bytes,
-                        const void* tile_bounds, const int32_t* q_lo, hipStream_t stream,
-                        const PrefillAccumulate* acc = nullptr);
+bool attn_mfma_merging_applies(const AttnShape& s);
+int launch_attn_mfma_accumulate(const AttnShape& s, const AttnTable& t,
+                                const PrefillAccumulate& acc, void* workspace,
+                                size_t workspace_bytes, hipStream_t stream);
 
-// One launch for all ring steps of a rank (pass-KV): the shards k[j], v[j], kv_pos[j] (n_kv[j]
-// tokens each; any sizes, empty ones included) with their tile bounds, in ring order
-// j = 0..n_shards-1, walked by every workgroup with one running softmax state; writes the
-// rank's merged O / LSE. s.total_kv is the largest shard (it decides, with total_q, whether
-// the launch would split its KV axis, which the walk does not support).
+// One launch for all ring steps of one rank (pass-KV): the shards of the table walked in the
+// order ring_start, ring_start - 1, ... (mod n_shards), by every workgroup with one running
+// softmax state.
 // `arrived` (device, or NULL): int32 per step, the kernel waits (at most spin_limit polls) for
 // a nonzero value before it reads step j's shard; a wait that gives up sets bit j of *error
 // and leaves the shard out.
-bool prefill_ring_walk_applies(const cp_shape& s, int n_shards);
-int launch_prefill_mfma_ring(const cp_shape& s, float scale, const void* q, const int32_t* q_pos,
-                             int n_shards, const void* const* k, const void* const* v,
-                             const int32_t* const* kv_pos, const void* const* bounds,
-                             const int64_t* n_kv, const int32_t* arrived, int32_t* error,
-                             int32_t spin_limit, void* out, float* lse, int32_t out_dtype,
-                             hipStream_t stream);
+int launch_attn_mfma_ring(const AttnShape& s, const AttnTable& t, int ring_start,
+                          const int32_t* arrived, int32_t* error, int32_t spin_limit,
+                          int32_t out_dtype, const void* tile_bounds, hipStream_t stream);
 
-// Packed batches on the MFMA path: per-sequence position ranges (see cp_varseq.hip).
-struct VarseqLayout {
-  size_t span_off, base_off, q_hi_off, q_lo_off, kv_off, total;
-};
-VarseqLayout varseq_layout(int32_t batch, int64_t total_q, int64_t total_kv);
-int launch_varseq_encode(int32_t batch, int64_t total_q, int64_t total_kv, const int32_t* q_pos,
-                         const int32_t* kv_pos, const int32_t* cu_q, const int32_t* cu_kv,
-                         void* workspace, hipStream_t stream);
+// fp32 MFMA kernel, head_dim 64 and 128: the same table, no workspace.
+int launch_attn_fp32(const AttnShape& s, const AttnTable& t, const AttnOut& o,
+                     hipStream_t stream);
+
+// Packed batches on the MFMA path: per-sequence position ranges for the queries and keys of all
+// ranks of the table (see cp_varseq.hip). cu_q[a], cu_kv[b]: boundaries of rank a's queries and
+// of shard b's keys. Replaces t.q_pos and t.kv_pos by the shifted positions in the workspace;
+// *q_lo receives the lower bounds of the queries.
+size_t varseq_workspace_bytes(int32_t batch, int64_t total_q, int64_t total_kv);
+int launch_varseq_encode(int32_t batch, int64_t total_kv, AttnTable& t, const int32_t* const* cu_q,
+                         const int32_t* const* cu_kv, void* workspace, const int32_t** q_lo,
+                         hipStream_t stream);
 
 // split-KV decode, bf16, head_dim 128.
 size_t decode_workspace_bytes(const cp_shape& s);
@@ -122,10 +153,22 @@ int launch_merge(int64_t rows, int32_t head_dim, int32_t n_parts, const void* co
                  const float* const* lses, int32_t part_dtype, void* out, int32_t out_dtype,
                  float* lse_out, hipStream_t stream);
 
-// Equation 4 over n_parts partials laid out with a constant stride (split-KV scratch).
-int launch_merge_strided(int64_t rows, int32_t head_dim, int32_t n_parts, const float* parts_out,
-                         const float* parts_lse, int64_t part_stride_rows, void* out,
-                         int32_t out_dtype, float* lse_out, hipStream_t stream);
+// Equation 4 over partials at a constant stride, for the rows of several ranks (row_begin: rows
+// are (token, head) pairs) and, in grid.y, for n_groups runs of n_parts partials each.
+struct MergeTable {
+  const void* part[kMaxTable];       // part 0 of the rank's rows
+  const float* part_lse[kMaxTable];
+  void* out[kMaxTable];
+  float* lse[kMaxTable];             // entries may be NULL
+  int64_t row_begin[kMaxTable + 1];
+  int64_t part_bytes;                // bytes from one part to the next
+  int64_t part_lse_elems;
+  int64_t group_out_bytes;           // bytes between the outputs of two groups
+  int64_t group_lse_elems;
+  int32_t n_ranks, n_parts, n_groups;
+};
+int launch_merge_table(const MergeTable& m, int32_t head_dim, int32_t part_dtype,
+                       int32_t out_dtype, hipStream_t stream);
 
 inline int check_launch() {
   return hipGetLastError() == hipSuccess ? CP_OK : CP_ERR_LAUNCH;

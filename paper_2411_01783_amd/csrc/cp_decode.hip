@@ -14,7 +14,7 @@
 //     transposed on the way in; every HBM read is a full 256-byte row per 16 lanes, the next
 //     tile is prefetched into registers while the current one is used). The four wavefront
 //     results are combined in LDS and written as one fp32 partial (O, LSE) per split;
-//     Equation 4 over the splits finishes the call (merge_split_kernel).
+//     Equation 4 over the splits finishes the call (merge_table_kernel).
 //   decode_flat_kernel  every sequence named at most once (CP_SHAPE_UNIQUE_BID): equal key
 //     ranges per workgroup regardless of the sequences, direct-to-LDS loads; see below.
 #include "cp_common.h"
@@ -1142,8 +1142,14 @@ int launch_decode(const cp_shape& s, float scale, const void* q, const void* k, 
   hipLaunchKernelGGL(decode_kernel, dim3(splits, (unsigned)s.total_q, s.n_kv_heads),
                      dim3(NTHREADS), smem, stream, p);
   if (check_launch() != CP_OK) return CP_ERR_LAUNCH;
-  return launch_merge_strided((int64_t)rows, D, splits, p.part_out, p.part_lse, (int64_t)rows,
-                              out, out_dtype, lse, stream);
+  MergeTable m = {};
+  m.n_ranks = m.n_groups = 1;
+  m.n_parts = splits;
+  m.part[0] = p.part_out; m.part_lse[0] = p.part_lse; m.out[0] = out; m.lse[0] = lse;
+  m.row_begin[1] = (int64_t)rows;
+  m.part_bytes = (int64_t)rows * D * 4;
+  m.part_lse_elems = (int64_t)rows;
+  return launch_merge_table(m, D, CP_FP32, out_dtype, stream);
 }
 
 }  // namespace cp

@@ -110,43 +110,51 @@ __global__ __launch_bounds__(256) void merge_kernel(MergePtrs ptrs, int n_parts_
   }
 }
 
-// Split-KV scratch of one call (partials s * stride apart, every row written: finite zeros
-// and LSE = -inf when a split saw nothing). Few rows, so the kernel is bound by latency, not
-// by bandwidth: a thread requests the LSE values of all parts and 16 data vectors at a time
-// back to back, and the arithmetic is branch-free (a branch on the weights would pull the
-// loads behind the wait for the LSE values).
-template <typename TO>
-__global__ __launch_bounds__(64) void merge_split_kernel(const float* __restrict__ parts_out,
-                                                         const float* __restrict__ parts_lse,
-                                                         int64_t part_stride_rows, int n_parts,
-                                                         int64_t rows, int head_dim,
-                                                         TO* __restrict__ out,
-                                                         float* __restrict__ lse_out) {
-  constexpr int VEC = 4, BATCH = 16;
+// Partials at a constant stride (split-KV scratch, ring slots), every row written: finite
+// values and LSE = -inf where a part saw nothing. Bound by latency on few rows and by bandwidth
+// on many; in both a thread wants all its requests out at once: it asks for the LSE values of
+// all parts and for up to 16 data vectors back to back, and the arithmetic is branch-free (a
+// branch on the weights would pull the loads behind the wait for the LSE values). NP is the
+// part count rounded up; parts past the end repeat the last one with weight zero.
+template <typename TP, typename TO, int VEC, int NP>
+__global__ __launch_bounds__(256) void merge_table_kernel(const MergeTable m, int head_dim) {
+  constexpr int BATCH = NP < 16 ? NP : 16;
   const int vec_per_row = head_dim / VEC;
   const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= rows * vec_per_row) return;
   const int64_t row = idx / vec_per_row;
+  if (row >= m.row_begin[m.n_ranks]) return;
   const int col = (int)(idx - row * vec_per_row) * VEC;
-  float lv[CP_MAX_PARTS];
+  int a = 0;
+#pragma unroll 8
+  for (int i = 1; i < m.n_ranks; ++i) a += row >= m.row_begin[i];
+  const int64_t r = row - m.row_begin[a];
+  const int n_parts = m.n_parts;
+  const int64_t first = (int64_t)blockIdx.y * n_parts;
+  const float* const lse = m.part_lse[a] + first * m.part_lse_elems + r;
+  const char* const src = (const char*)m.part[a] + first * m.part_bytes +
+                          (r * head_dim + col) * (int64_t)sizeof(TP);
+  float lv[NP];
 #pragma unroll
-  for (int s = 0; s < CP_MAX_PARTS; ++s)
-    lv[s] = s < n_parts ? parts_lse[s * part_stride_rows + row] : -INFINITY;
-  float acc[VEC] = {0.f, 0.f, 0.f, 0.f};
+  for (int s = 0; s < NP; ++s)
+    lv[s] = lse[(int64_t)min(s, n_parts - 1) * m.part_lse_elems];
+  float acc[VEC];
+#pragma unroll
+  for (int i = 0; i < VEC; ++i) acc[i] = 0.f;
   float den = 0.f, lmax = -INFINITY;
 #pragma unroll
-  for (int b = 0; b < CP_MAX_PARTS / BATCH; ++b) {
-    if (b * BATCH >= n_parts) break;  // uniform
+  for (int b = 0; b < NP / BATCH; ++b) {
     float xs[BATCH][VEC];
 #pragma unroll
-    for (int i = 0; i < BATCH; ++i) {
-      const int s = min(b * BATCH + i, n_parts - 1);  // parts past the end: weight 0 below
-      load_vec<float, VEC>(parts_out + (s * part_stride_rows + row) * head_dim + col, xs[i]);
-    }
+    for (int i = 0; i < BATCH; ++i)
+      load_vec<TP, VEC>((const TP*)(src + (int64_t)min(b * BATCH + i, n_parts - 1) * m.part_bytes),
+                        xs[i]);
     __builtin_amdgcn_sched_barrier(0);  // keep the requests together, ahead of the arithmetic
     if (b == 0) {
 #pragma unroll
-      for (int s = 0; s < CP_MAX_PARTS; ++s) lmax = fmaxf(lmax, lv[s]);
+      for (int s = 0; s < NP; ++s) {
+        if (s >= n_parts) lv[s] = -INFINITY;
+        lmax = fmaxf(lmax, lv[s]);
+      }
     }
     const bool any = lmax != -INFINITY;
 #pragma unroll
@@ -160,9 +168,11 @@ __global__ __launch_bounds__(64) void merge_split_kernel(const float* __restrict
   const float inv = den > 0.f ? 1.f / den : 0.f;
 #pragma unroll
   for (int c = 0; c < VEC; ++c) acc[c] *= inv;
-  store_vec<TO, VEC>(out + row * head_dim + col, acc);
-  if (lse_out != nullptr && col == 0)
-    lse_out[row] = den > 0.f ? lmax + __logf(den) : -INFINITY;
+  char* const o = (char*)m.out[a] + (int64_t)blockIdx.y * m.group_out_bytes;
+  store_vec<TO, VEC>((TO*)o + r * head_dim + col, acc);
+  if (m.lse[a] != nullptr && col == 0)
+    m.lse[a][(int64_t)blockIdx.y * m.group_lse_elems + r] =
+        den > 0.f ? lmax + __logf(den) : -INFINITY;
 }
 
 template <typename TP, typename TO, int VEC>
@@ -207,35 +217,41 @@ int launch_merge(int64_t rows, int32_t head_dim, int32_t n_parts, const void* co
   return launch_np<bf16_t, bf16_t, 8>(ptrs, n_parts, rows, head_dim, out, lse_out, stream);
 }
 
-constexpr int64_t kStridedStreamRows = 4096;
+namespace {
 
-int launch_merge_strided(int64_t rows, int32_t head_dim, int32_t n_parts, const float* parts_out,
-                         const float* parts_lse, int64_t part_stride_rows, void* out,
-                         int32_t out_dtype, float* lse_out, hipStream_t stream) {
-  const int64_t n_vec = rows * (head_dim / 4);
+template <typename TP, typename TO, int VEC>
+int launch_table_t(const MergeTable& m, int32_t head_dim, hipStream_t stream) {
+  const int64_t n_vec = m.row_begin[m.n_ranks] * (head_dim / VEC);
   if (n_vec == 0) return CP_OK;
-  if (n_parts < 1 || n_parts > CP_MAX_PARTS || n_vec > 0x7fffffffLL * 64) return CP_ERR_SHAPE;
-  // Many rows: the work is bound by bandwidth, not by latency, and the streaming kernel with
-  // its compile-time part counts moves it faster (measured at 16384 rows x 4 parts: 14 us
-  // here against 8 us there; with a run-time part count it is slower than this kernel).
-  if (rows >= kStridedStreamRows && (n_parts == 2 || n_parts == 4 || n_parts == 8 || n_parts == 16)) {
-    const void* outs[CP_MAX_PARTS];
-    const float* lses[CP_MAX_PARTS];
-    for (int s = 0; s < n_parts; ++s) {
-      outs[s] = parts_out + (int64_t)s * part_stride_rows * head_dim;
-      lses[s] = parts_lse + (int64_t)s * part_stride_rows;
-    }
-    return launch_merge(rows, head_dim, n_parts, outs, lses, CP_FP32, out, out_dtype, lse_out,
-                        stream);
-  }
-  const dim3 grid((unsigned)((n_vec + 63) / 64));
-  if (out_dtype == CP_FP32)
-    hipLaunchKernelGGL(merge_split_kernel<float>, grid, dim3(64), 0, stream, parts_out, parts_lse,
-                       part_stride_rows, n_parts, rows, head_dim, (float*)out, lse_out);
-  else
-    hipLaunchKernelGGL(merge_split_kernel<bf16_t>, grid, dim3(64), 0, stream, parts_out,
-                       parts_lse, part_stride_rows, n_parts, rows, head_dim, (bf16_t*)out, lse_out);
+  // one wavefront per workgroup while that is what spreads the rows over the 256 CUs
+  const int threads = n_vec * m.n_groups < 256 * 4 * 256 ? 64 : 256;
+  const int64_t blocks = (n_vec + threads - 1) / threads;
+  if (blocks > 0x7fffffffLL) return CP_ERR_SHAPE;
+  const dim3 grid((unsigned)blocks, m.n_groups);
+#define CP_MERGE_TABLE(NP)                                                                      \
+  hipLaunchKernelGGL((merge_table_kernel<TP, TO, VEC, NP>), grid, dim3(threads), 0, stream, m, \
+                     head_dim)
+  if (m.n_parts <= 2) CP_MERGE_TABLE(2);
+  else if (m.n_parts <= 4) CP_MERGE_TABLE(4);
+  else if (m.n_parts <= 8) CP_MERGE_TABLE(8);
+  else if (m.n_parts <= 16) CP_MERGE_TABLE(16);
+  else if (m.n_parts <= 32) CP_MERGE_TABLE(32);
+  else CP_MERGE_TABLE(64);
+#undef CP_MERGE_TABLE
   return check_launch();
+}
+
+}  // namespace
+
+int launch_merge_table(const MergeTable& m, int32_t head_dim, int32_t part_dtype,
+                       int32_t out_dtype, hipStream_t stream) {
+  if (m.n_parts < 1 || m.n_parts > CP_MAX_PARTS || m.n_groups < 1 || m.n_groups > 65535)
+    return CP_ERR_SHAPE;
+  if (part_dtype == CP_FP32)
+    return out_dtype == CP_FP32 ? launch_table_t<float, float, 4>(m, head_dim, stream)
+                                : launch_table_t<float, bf16_t, 4>(m, head_dim, stream);
+  return out_dtype == CP_FP32 ? launch_table_t<bf16_t, float, 8>(m, head_dim, stream)
+                              : launch_table_t<bf16_t, bf16_t, 8>(m, head_dim, stream);
 }
 
 }  // namespace cp
