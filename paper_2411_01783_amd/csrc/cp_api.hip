@@ -37,14 +37,14 @@ inline bool mfma_applies(const cp_shape& s) {
          (s.batch == 1 || s.head_dim == 128);
 }
 
-inline int32_t kv_tiles(int64_t n_kv) { return (int32_t)((n_kv + kAttnTile - 1) / kAttnTile); }
+inline int32_t kv_blocks(int64_t n_kv) { return (int32_t)((n_kv + kAttnBlock - 1) / kAttnBlock); }
 
 // One rank's queries against one shard, as an attention launch sees it.
 AttnShape single_shape(const cp_shape& s) {
   AttnShape a = {};
   a.dtype = s.dtype; a.head_dim = s.head_dim;
   a.n_q_heads = s.n_q_heads; a.n_kv_heads = s.n_kv_heads;
-  a.total_q = s.total_q; a.n_tiles = kv_tiles(s.total_kv); a.n_shards = 1;
+  a.total_q = s.total_q; a.n_blocks = kv_blocks(s.total_kv); a.n_shards = 1;
   return a;
 }
 
@@ -58,7 +58,7 @@ AttnTable single_table(const cp_shape& s, const void* q, const void* k, const vo
   t.k[0] = k; t.v[0] = v; t.kv_pos[0] = kv_pos;
   t.n_kv[0] = (int32_t)s.total_kv;
   t.tok_begin[1] = (int32_t)s.total_q;
-  t.tile_begin[1] = kv_tiles(s.total_kv);
+  t.blk_begin[1] = kv_blocks(s.total_kv);
   return t;
 }
 
@@ -181,7 +181,7 @@ int cp_attn_partial(const cp_shape* shape, const void* q, const void* k, const v
                                 &q_lo, st);
       if (rc != CP_OK) return rc;
     }
-    return launch_attn_mfma(as, t, ao, q_lo, nullptr, (char*)workspace + enc,
+    return launch_attn_mfma(as, t, ao, q_lo, (char*)workspace + enc,
                             workspace_bytes - enc, st);
   }
   if (s.dtype == CP_FP32 && cu_seqlens_q == nullptr) return launch_attn_fp32(as, t, ao, st);
@@ -389,7 +389,7 @@ static bool ring_is_one_launch(const cp_ring_desc* d) {
   // tokens, rows and tiles of all ranks together are kept in 31 bits
   int64_t tokens = 0, keys = 0;
   for (int r = 0; r < d->n_ranks; ++r) {
-    if (d->n_q[r] > INT32_MAX || d->n_kv[r] > INT32_MAX - kAttnTile) return false;
+    if (d->n_q[r] > INT32_MAX || d->n_kv[r] > INT32_MAX - kAttnBlock) return false;
     tokens += d->n_q[r];
     keys += d->n_kv[r];
   }
@@ -404,7 +404,7 @@ static AttnShape ring_attn_shape(const cp_ring_desc* d) {
   s.n_shards = d->n_ranks;
   for (int r = 0; r < d->n_ranks; ++r) {
     s.total_q += d->n_q[r];
-    s.n_tiles += kv_tiles(d->n_kv[r]);
+    s.n_blocks += kv_blocks(d->n_kv[r]);
   }
   s.per_shard = d->keep_partials != 0;
   s.scale = resolve_scale(d->softmax_scale, d->head_dim);
@@ -433,7 +433,9 @@ extern "C" size_t cp_ring_workspace_bytes(const cp_ring_desc* d, int32_t decode)
   if (check_ring(d, decode != 0) != CP_OK) return 0;
   if (!decode && ring_is_one_launch(d))
     return d->dtype == CP_FP32 ? 0
-                               : attn_mfma_workspace_bytes(ring_attn_shape(d)) + ring_varseq_bytes(d);
+           : d->fused_merge == 2 && d->arrived != nullptr
+               ? attn_mfma_ring_workspace_bytes(ring_attn_shape(d))
+               : attn_mfma_workspace_bytes(ring_attn_shape(d)) + ring_varseq_bytes(d);
   size_t need = 0;
   for (int a = 0; a < d->n_ranks; ++a)
     for (int b = 0; b < d->n_ranks; ++b) {
@@ -559,7 +561,7 @@ int ring_one_launch(const cp_ring_desc* d, hipStream_t st) {
     t.k[r] = d->k[r]; t.v[r] = d->v[r]; t.kv_pos[r] = d->kv_pos[r];
     t.n_kv[r] = (int32_t)d->n_kv[r];
     t.tok_begin[r + 1] = t.tok_begin[r] + (int32_t)d->n_q[r];
-    t.tile_begin[r + 1] = t.tile_begin[r] + kv_tiles(d->n_kv[r]);
+    t.blk_begin[r + 1] = t.blk_begin[r] + kv_blocks(d->n_kv[r]);
     if (!aligned16(d->q[r]) || !aligned16(d->k[r]) || !aligned16(d->v[r]) || !aligned16(d->out[r]))
       return CP_ERR_ALIGN;
   }
@@ -588,22 +590,11 @@ int ring_one_launch(const cp_ring_desc* d, hipStream_t st) {
       left -= ring_varseq_bytes(d);
     }
     if (d->fused_merge == 2 && d->arrived != nullptr) {
-      // every shard behind its arrival flag: a launch per rank walks the shards in ring order
-      rc = launch_kv_tile_bounds(t, s.n_tiles, ws, st);
-      for (int k = 0; k < n && rc == CP_OK; ++k) {
-        if (d->n_q[k] == 0) continue;
-        AttnTable tk = t;
-        tk.n_ranks = 1;
-        tk.q[0] = t.q[k]; tk.q_pos[0] = t.q_pos[k]; tk.out[0] = t.out[k]; tk.lse[0] = t.lse[k];
-        tk.tok_begin[1] = (int32_t)d->n_q[k];
-        AttnShape sk = s;
-        sk.total_q = d->n_q[k];
-        rc = launch_attn_mfma_ring(sk, tk, k, d->arrived[k], d->ring_error + k, d->spin_limit,
-                                   d->out_dtype, ws, st);
-      }
-      return rc;
+      // every shard behind its arrival flag, walked in ring order
+      return launch_attn_mfma_ring(s, t, d->arrived, d->ring_error, d->spin_limit, d->out_dtype,
+                                   ws, left, st);
     }
-    rc = launch_attn_mfma(s, t, o, q_lo, nullptr, ws, left, st);
+    rc = launch_attn_mfma(s, t, o, q_lo, ws, left, st);
   }
   if (rc != CP_OK || !d->keep_partials) return rc;
   MergeTable m = {};

@@ -26,7 +26,7 @@ namespace {
 constexpr int NWAVE = 4;
 constexpr int NTHREADS = NWAVE * 64;
 constexpr int BLK = 16;                     // keys per block
-constexpr int BLKS_PER_TILE = kAttnTile / BLK;
+constexpr int PER = kAttnBlock / BLK;       // blocks here per block of the table
 constexpr int MAX_LIST = NTHREADS;          // blocks looked at per chunk
 
 struct Params {
@@ -36,7 +36,7 @@ struct Params {
   int64_t lse_shard_elems;
   int32_t group;
   int32_t n_kv_heads;
-  int32_t n_tiles;
+  int32_t n_blocks;          // of the table
   int32_t per_shard;
   float scale_log2;
 };
@@ -168,20 +168,20 @@ __global__ __launch_bounds__(NTHREADS) void attn_fp32_kernel(const Params p) {
     }
   };
 
-  const int b_begin = (p.per_shard ? p.t.tile_begin[z_shard] : 0) * BLKS_PER_TILE;
-  const int b_end = (p.per_shard ? p.t.tile_begin[z_shard + 1] : p.n_tiles) * BLKS_PER_TILE;
+  const int b_begin = (p.per_shard ? p.t.blk_begin[z_shard] : 0) * PER;
+  const int b_end = (p.per_shard ? p.t.blk_begin[z_shard + 1] : p.n_blocks) * PER;
   for (int b0 = b_begin; b0 < b_end; b0 += MAX_LIST) {
     // list of the blocks some query of the workgroup can see
     const int b = b0 + tid;
     bool live = false;
     int sh = z_shard, key0 = 0;
     if (b < b_end) {
-      const int tile = b / BLKS_PER_TILE;
+      const int blk = b / PER;
       if (!p.per_shard) {
 #pragma unroll 8
-        for (int i = 1; i < p.t.n_shards; ++i) sh += tile >= p.t.tile_begin[i];
+        for (int i = 1; i < p.t.n_shards; ++i) sh += blk >= p.t.blk_begin[i];
       }
-      key0 = (tile - p.t.tile_begin[sh]) * kAttnTile + (b % BLKS_PER_TILE) * BLK;
+      key0 = (blk - p.t.blk_begin[sh]) * kAttnBlock + (b % PER) * BLK;
       const int last = p.t.n_kv[sh] - 1 - key0;
       if (last >= 0) {
         const int32_t* pt = p.t.kv_pos[sh] + key0;
@@ -305,7 +305,7 @@ int launch_attn_fp32(const AttnShape& s, const AttnTable& t, const AttnOut& o,
   if (s.head_dim != 64 && s.head_dim != 128) return CP_ERR_UNSUPPORTED;
   if (s.n_kv_heads > 65535) return CP_ERR_SHAPE;
   // block indices are kept in 31 bits; so are row indices
-  if (s.n_tiles > 0x7fffffff / BLKS_PER_TILE - MAX_LIST) return CP_ERR_SHAPE;
+  if (s.n_blocks > 0x7fffffff / PER - MAX_LIST) return CP_ERR_SHAPE;
   Params p = {};
   p.t = t;
   p.group = s.n_q_heads / s.n_kv_heads;
@@ -315,7 +315,7 @@ int launch_attn_fp32(const AttnShape& s, const AttnTable& t, const AttnOut& o,
   p.out_shard_bytes = o.shard_out_bytes;
   p.lse_shard_elems = o.shard_lse_elems;
   p.n_kv_heads = s.n_kv_heads;
-  p.n_tiles = s.n_tiles;
+  p.n_blocks = s.n_blocks;
   p.per_shard = s.per_shard ? 1 : 0;
   p.scale_log2 = s.scale * kLog2e;
   return o.dtype == CP_BF16 ? launch_o<bf16_t>(s, p, stream) : launch_o<float>(s, p, stream);

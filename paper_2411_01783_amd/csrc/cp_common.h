@@ -46,7 +46,7 @@ int launch_partial_generic(const cp_shape& s, float scale, const void* q, const 
 // call is one rank and one shard; a ring whose ranks all live on this GPU is one launch. Passed
 // by value (kernel argument segment).
 constexpr int kMaxTable = 32;
-constexpr int kAttnTile = 128;  // keys per tile of the MFMA kernel
+constexpr int kAttnBlock = 32;  // keys per block of the MFMA kernel
 struct AttnTable {
   const void* q[kMaxTable];
   const int32_t* q_pos[kMaxTable];
@@ -57,14 +57,14 @@ struct AttnTable {
   const int32_t* kv_pos[kMaxTable];
   int32_t n_kv[kMaxTable];
   int32_t tok_begin[kMaxTable + 1];   // first token of every rank, and the total
-  int32_t tile_begin[kMaxTable + 1];  // first tile (kAttnTile keys) of every shard, and the total
+  int32_t blk_begin[kMaxTable + 1];   // first block (kAttnBlock keys) of every shard, and the total
   int32_t n_ranks, n_shards;
 };
 // Its sizes, from which a launch is planned (no pointers: also the workspace query's argument).
 struct AttnShape {
   int32_t dtype, head_dim, n_q_heads, n_kv_heads;
   int64_t total_q;      // tokens of all ranks
-  int32_t n_tiles;      // tiles of all shards
+  int32_t n_blocks;     // blocks of all shards
   int32_t n_shards;
   bool per_shard;       // keep the shards' results apart: one (O, LSE) per rank and shard
   float scale;
@@ -78,16 +78,13 @@ struct AttnOut {
 };
 
 // bf16 MFMA kernel, head_dim 128 and 64, groups of at most 64 heads.
-// `tile_bounds`, when not NULL, holds the per-tile (min, max) of kv_pos already computed by
-// launch_kv_tile_bounds for these shards; otherwise the launcher computes it into the
-// workspace first. `q_lo`: packed batches (head_dim 128), smallest visible key position per
-// token, all ranks back to back.
+// `q_lo`: packed batches (head_dim 128), smallest visible key position per token, all ranks back
+// to back.
 bool attn_mfma_applies(int dtype, int head_dim, int n_q_heads, int n_kv_heads);
 size_t attn_mfma_workspace_bytes(const AttnShape& s);
-int launch_kv_tile_bounds(const AttnTable& t, int n_tiles, void* bounds_out, hipStream_t stream);
 int launch_attn_mfma(const AttnShape& s, const AttnTable& t, const AttnOut& o,
-                     const int32_t* q_lo, const void* tile_bounds, void* workspace,
-                     size_t workspace_bytes, hipStream_t stream);
+                     const int32_t* q_lo, void* workspace, size_t workspace_bytes,
+                     hipStream_t stream);
 
 // "Merge into a running result": (out, lse) are read and updated (Equation 4), and if final_out
 // is not NULL the merged O goes there in final_dtype instead of back to out. One rank, one
@@ -104,15 +101,15 @@ int launch_attn_mfma_accumulate(const AttnShape& s, const AttnTable& t,
                                 const PrefillAccumulate& acc, void* workspace,
                                 size_t workspace_bytes, hipStream_t stream);
 
-// One launch for all ring steps of one rank (pass-KV): the shards of the table walked in the
-// order ring_start, ring_start - 1, ... (mod n_shards), by every workgroup with one running
-// softmax state.
-// `arrived` (device, or NULL): int32 per step, the kernel waits (at most spin_limit polls) for
-// a nonzero value before it reads step j's shard; a wait that gives up sets bit j of *error
-// and leaves the shard out.
-int launch_attn_mfma_ring(const AttnShape& s, const AttnTable& t, int ring_start,
-                          const int32_t* arrived, int32_t* error, int32_t spin_limit,
-                          int32_t out_dtype, const void* tile_bounds, hipStream_t stream);
+// One launch for all ring steps of all ranks (pass-KV), rank k walking the shards in the order
+// k, k - 1, ... (mod n_ranks) with one running softmax state per row, each shard behind its
+// arrival flag. arrived[k] (device): int32 per step of rank k; the kernel waits (at most
+// spin_limit polls) for a nonzero value before it reads step j's shard; a wait that gives up
+// sets bit j of error[k] and leaves the shard out.
+size_t attn_mfma_ring_workspace_bytes(const AttnShape& s);
+int launch_attn_mfma_ring(const AttnShape& s, const AttnTable& t, const int32_t* const* arrived,
+                          int32_t* error, int32_t spin_limit, int32_t out_dtype, void* workspace,
+                          size_t workspace_bytes, hipStream_t stream);
 
 // fp32 MFMA kernel, head_dim 64 and 128: the same table, no workspace.
 int launch_attn_fp32(const AttnShape& s, const AttnTable& t, const AttnOut& o,

@@ -10,31 +10,32 @@
 //     ranks' tokens back to back. The causal mask depends on the token only, so all G heads of
 //     a token share mask and K/V tile: GQA turns into a taller M dimension.
 //   - A workgroup of 8 wavefronts owns 256 consecutive rows, 32 per wavefront, and walks the
-//     128-key tiles of the KV shards, brought straight into LDS (double buffered) and consumed
-//     in blocks of 32 keys by a three-stage software pipeline per wavefront (see
-//     cp_prefill_pipe.h).
+//     keys of the KV shards in tiles of four 32-key blocks, brought straight into LDS (double
+//     buffered) and consumed block by block by a three-stage software pipeline per wavefront
+//     (see cp_prefill_pipe.h).
 //   - Scores are produced transposed, S^T = K Q^T with v_mfma_f32_32x32x16_bf16:
 //     a lane then holds 16 keys of ONE query per 32-key block, so the softmax
 //     row statistics are per-lane scalars (one cross-lane exchange with lane^32)
 //     and the exponentiated block is already in the B-operand layout of the
 //     second product O^T += V^T P^T. No register shuffle between the products.
-//   - Tile skipping (load-balanced sharding leaves half of every off-diagonal
-//     step fully masked): a pre-pass records min/max kv_pos of every KV tile;
-//     each workgroup compacts the tiles any of its queries can see into a list
-//     in LDS and walks only those; only tiles that straddle a query position
-//     pay for the mask.
+//   - Block skipping (load-balanced sharding leaves half of every off-diagonal step fully
+//     masked): from the min/max kv_pos of every block a workgroup compacts the blocks that any of
+//     its queries can see into a list in LDS and walks only those, four to a tile wherever they
+//     lie; only blocks that straddle a query position pay for the mask.
 //   - A ring whose ranks all live here is one launch: every rank's rows against the tiles of all
 //     shards, so that Equation 4 over the ring steps happens inside the online softmax. (A
 //     launch per ring step costs 12 to 17 us at small query shards whatever its work: 256
 //     launches and 256 split merges for 16 ranks, 6.06 ms at 1024 new tokens on 131072 cached
 //     ones, where the arithmetic is 0.85 ms at the rate of a large matrix product.)
-//   - Where the row blocks alone leave compute units idle the KV axis is split over grid.z,
-//     every part taking an equal share of the tiles its rows can see; the parts' fp32 results
-//     go to the workspace and are combined with Eq. 4.
+//   - Small and middling calls, whose row blocks would leave compute units idle or with very
+//     different walks, are cut into equal shares by the workgroups themselves (PLAN). Where
+//     their positions do not fit LDS and the row blocks leave CUs idle, the KV axis is split over
+//     grid.z (SPLIT). Both write fp32 partials of what they cut to the workspace, which a second
+//     launch merges with Eq. 4.
 //   - The epilogue transposes the accumulators through LDS so that every output
 //     row leaves as one contiguous 4 D byte (fp32) or 2 D byte (bf16) run.
 //   - The same body also merges into a running (O, LSE) in its epilogue (ACC), and walks the
-//     shards of one rank's ring steps in ring order, each behind an arrival flag (RING,
+//     shards of every rank's ring steps in ring order, each behind an arrival flag (RING,
 //     prefill_ring_walk_kernel).
 #include "cp_common.h"
 #include "cp_table.h"
@@ -43,68 +44,85 @@ namespace cp {
 namespace {
 
 constexpr int BM = 256;         // rows per workgroup
-constexpr int TILE = kAttnTile; // keys per LDS tile
-constexpr int NWAVE = 8;        // wavefronts per workgroup
+constexpr int BLOCK = kAttnBlock;  // keys per block: what is listed, masked and pipelined
+constexpr int TILE = 4 * BLOCK;    // keys per LDS tile
+constexpr int NWAVE = 8;           // wavefronts per workgroup
 constexpr int NTHREADS = NWAVE * 64;
 constexpr int POS_BYTES = TILE * 4;
-constexpr int MAX_LIVE = 512;   // visible-tile list entries per chunk (8 wavefronts x 64 tiles)
+constexpr int MAX_LIVE = NTHREADS;        // blocks looked at (and listed) per chunk
+constexpr int PLAN_MAX_BLOCKS = 960;      // PLAN: block bounds kept in LDS (30K keys; what fits)
+constexpr int PLAN_MAX_UNITS = 1024;      // PLAN: units per KV head
+constexpr int kPlanWorkgroups = 256;      // one per CU
+constexpr int kUnitCost = 3;              // start-up and epilogue of a unit, in tile steps
 constexpr float kRescaleSlack = 8.f;               // log2 units
 constexpr float kOverflowSum = 1099511627776.f;    // 2^40: a block sum beyond it is redone
 constexpr float kDeadRowRef = 1e30f;               // reference of a row that sees no key
 
 struct Params {
   AttnTable t;            // queries and outputs per rank, KV per shard
-  const int2* bounds;     // [n_tiles] (min, max) of kv_pos per tile, shard after shard
+  const int32_t* arrived[kMaxTable];  // RING: per rank [n_shards], nonzero once step j's shard
+                                      // may be read
+  int32_t rb_begin[kMaxTable + 1];    // RING: first row block of every rank
+  const int2* bounds;     // (min, max) of kv_pos per block, shard after shard (not PLAN)
   const int32_t* q_lo;    // BAND only: smallest visible key position per query token
-  float* part_out;        // SPLIT: [grid.z][rows_all_heads][D] fp32
-  float* part_lse;        // SPLIT: [grid.z][rows_all_heads]
+  float* part_out;        // SPLIT: [grid.z][rows_all_heads][D] fp32; PLAN: [2 slots per wg][BM][D]
+  float* part_lse;        // likewise, without D
+  int2* plan_rec;         // PLAN: (unit, begin in it) of every share, for plan_merge_kernel
   float* acc;             // ACC: running O, fp32 [rows_all_heads][D] (running LSE: t.lse[0])
   void* final_out;        // ACC: where the merged O goes on the last step (else NULL)
   float* final_lse;       // ACC: optional copy of the merged LSE
-  const int32_t* arrived; // RING: or NULL: [n_shards], nonzero once step j's shard may be read
-  int32_t* ring_error;    // RING: bit j is set when the wait of step j gave up
+  int32_t* ring_error;    // RING: per rank; bit j is set when the wait of step j gave up
   int64_t rows;           // R = total_q * G
   int64_t rows_all_heads; // total_q * n_q_heads
-  int64_t out_shard_stride;  // per_shard, not SPLIT: bytes between the outputs of two shards
+  int64_t out_shard_stride;  // per_shard: bytes between the outputs of two shards
   int64_t lse_shard_stride;  // and elements between their LSE
   int32_t group;          // G
   int32_t n_kv_heads;
-  int32_t n_tiles;        // of all shards
-  int32_t n_sub;          // parts of the KV axis (of every shard's, if per_shard)
+  int32_t n_row_blocks;
+  int32_t n_z;            // shards whose results are kept apart (1 if not per_shard)
+  int32_t n_blocks;       // of all shards
+  int32_t bounds_shift;   // blocks per entry of `bounds`: 1 << bounds_shift
+  int32_t n_sub;          // SPLIT: parts of the KV axis (of every shard's, if per_shard)
   int32_t per_shard;      // the shards' results are kept apart
-  int32_t ring_start;     // RING: shard of step 0
+  int32_t cut_units;      // PLAN: equal shares (else a workgroup per unit)
   int32_t spin_limit;     // RING: polls per shard before giving up
   float scale_log2;       // softmax scale * log2(e)
 };
 
-// (min, max) of kv_pos per tile, for the shards of a whole call in one launch (a launch per
-// shard costs more than the work: a shard of 8K keys is 64 tiles). One wavefront per tile.
-__global__ __launch_bounds__(256) void kv_tile_bounds_kernel(const AttnTable t, int32_t n_tiles,
-                                                              int2* __restrict__ bounds) {
-  const int gt = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (gt >= n_tiles) return;
-  int j = 0;
-  for (int i = 1; i < t.n_shards; ++i) j += gt >= t.tile_begin[i];  // (wave-uniform)
-  const int tile = gt - t.tile_begin[j];
-  const int32_t* __restrict__ kv_pos = t.kv_pos[j];
-  const int32_t total_kv = t.n_kv[j];
+// (min, max) of kv_pos per 32-key block (or, coarse, per four), for the shards of a whole call
+// in one launch (a launch per shard costs more than the work: a shard of 8K keys is 256
+// blocks). A wavefront takes four blocks.
+template <bool COARSE>
+__global__ __launch_bounds__(256) void kv_bounds_kernel(const AttnTable t, int32_t n_blocks,
+                                                         int2* __restrict__ bounds) {
   const int lane = threadIdx.x & 63;
+  const int b = (blockIdx.x * 4 + (threadIdx.x >> 6)) * 4 + (lane >> 4);
   int lo = INT32_MAX, hi = INT32_MIN;
+  if (b < n_blocks) {
+    int j = 0;
+    for (int i = 1; i < t.n_shards; ++i) j += b >= t.blk_begin[i];
+    const int32_t* __restrict__ kv_pos = t.kv_pos[j];
+    const int total_kv = t.n_kv[j];
 #pragma unroll
-  for (int h = 0; h < TILE / 64; ++h) {
-    const int idx = tile * TILE + h * 64 + lane;
-    if (idx < total_kv) {
-      const int32_t x = kv_pos[idx];
-      lo = min(lo, x);
-      hi = max(hi, x);
+    for (int h = 0; h < BLOCK; h += 16) {
+      const int idx = (b - t.blk_begin[j]) * BLOCK + h + (lane & 15);
+      if (idx < total_kv) {
+        const int32_t x = kv_pos[idx];
+        lo = min(lo, x);
+        hi = max(hi, x);
+      }
     }
   }
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
+  for (int o = COARSE ? 32 : 8; o > 0; o >>= 1) {
     lo = min(lo, __shfl_xor(lo, o, 64));
     hi = max(hi, __shfl_xor(hi, o, 64));
   }
-  if (lane == 0) bounds[gt] = make_int2(lo, hi);
+  if (COARSE) {
+    if (lane == 0 && b < n_blocks) bounds[b >> 2] = make_int2(lo, hi);
+  } else {
+    if ((lane & 15) == 0 && b < n_blocks) bounds[b] = make_int2(lo, hi);
+  }
 }
 
 __device__ __forceinline__ floatx16_t mfma32(bf16x8_t a, bf16x8_t b, floatx16_t c) {
@@ -153,55 +171,73 @@ int choose_splits(int64_t wgs, int tiles, double rows, int head_dim, int max_spl
 }
 
 struct Plan {
-  int n_row_blocks, n_sub, n_z;   // n_z = grid.z
-  bool split;                     // fp32 partials in the workspace
-  size_t bounds_bytes, part_out_bytes, part_lse_bytes;
-  size_t total() const { return bounds_bytes + part_out_bytes + part_lse_bytes; }
+  Mode mode;
+  int n_row_blocks, n_blocks, n_sub, n_z;  // n_z: shards kept apart
+  bool cut, coarse;
+  size_t bounds_bytes, part_out_bytes, part_lse_bytes, rec_bytes;
+  size_t total() const { return bounds_bytes + part_out_bytes + part_lse_bytes + rec_bytes; }
 };
 
 Plan make_plan(const AttnShape& s) {
-  Plan pl;
+  Plan pl = {};
   const int group = s.n_q_heads / s.n_kv_heads;
   pl.n_row_blocks = (int)((s.total_q * group + BM - 1) / BM);
-  const int64_t wgs = (int64_t)pl.n_row_blocks * s.n_kv_heads;
-  const double rows = (double)s.total_q * s.n_q_heads;
-  if (s.per_shard) {
-    // one part per shard at least: the parts of a shard are chosen for the average shard
-    const int avg = (s.n_tiles + s.n_shards - 1) / s.n_shards;
-    pl.n_sub = choose_splits(wgs * s.n_shards, avg, rows * s.n_shards, s.head_dim,
-                             16);
-    pl.n_z = s.n_shards * pl.n_sub;
-    pl.split = pl.n_sub > 1;
-  } else {
-    pl.n_sub = choose_splits(wgs, s.n_tiles, rows, s.head_dim, CP_MAX_PARTS);
-    pl.n_z = pl.n_sub;
-    pl.split = pl.n_sub > 1;
-  }
-  pl.bounds_bytes = round256((size_t)std::max(s.n_tiles, 1) * sizeof(int2));
+  pl.n_blocks = s.n_blocks;
+  pl.n_z = s.per_shard ? s.n_shards : 1;
+  pl.n_sub = 1;
+  const int64_t units = (int64_t)pl.n_row_blocks * pl.n_z;   // per KV head
+  const int64_t wgs = units * s.n_kv_heads;
+  // A single call of 256 row blocks and more has no workspace but its position bounds, one
+  // entry per 128 keys.
+  const bool single_large = s.n_shards == 1 && !s.per_shard && wgs >= 256;
   const size_t rows_all = (size_t)s.total_q * s.n_q_heads;
-  pl.part_out_bytes = pl.split ? round256((size_t)pl.n_z * rows_all * s.head_dim * 4) : 0;
-  pl.part_lse_bytes = pl.split ? round256((size_t)pl.n_z * rows_all * 4) : 0;
+  pl.coarse = s.n_shards == 1;
+  const size_t entries = pl.coarse ? (s.n_blocks + 3) / 4 : s.n_blocks;
+  // (the planned launch has its bounds in LDS, but cp_attn_partial_accumulate, which shares the
+  // workspace query, does not)
+  pl.bounds_bytes = round256(std::max<size_t>(entries, 1) * sizeof(int2));
+  if (!single_large && s.n_blocks <= PLAN_MAX_BLOCKS && units <= PLAN_MAX_UNITS &&
+      wgs <= 8 * PLAN_MAX_UNITS &&
+      // (the line of all units times 256, and token rows, within 32 bits)
+      wgs * (24 + s.n_blocks / 4) < (1ll << 23)) {
+    pl.mode = PLAN;
+    // Up to six tiles a unit there is nothing worth cutting (the plan and the merge launch take
+    // as long as three tile steps).
+    const int64_t tiles = (s.n_blocks / pl.n_z + 3) / 4;
+    pl.cut = tiles > 6;
+    if (pl.cut) {
+      pl.part_out_bytes = (size_t)2 * kPlanWorkgroups * BM * s.head_dim * 4;
+      pl.part_lse_bytes = (size_t)2 * kPlanWorkgroups * BM * 4;
+      pl.rec_bytes = (kPlanWorkgroups + 2) * sizeof(int2);
+    }
+    return pl;
+  }
+  // Otherwise the KV axis is split where the workgroups alone leave CUs idle: for every shard
+  // kept apart by the size of the average shard.
+  const int tiles = (int)((s.n_blocks / pl.n_z + 3) / 4);
+  pl.n_sub = choose_splits(wgs, tiles, (double)rows_all * pl.n_z, s.head_dim,
+                           s.per_shard ? 16 : CP_MAX_PARTS);
+  pl.mode = pl.n_sub > 1 ? SPLIT : WHOLE;
+  if (pl.mode == SPLIT) {
+    pl.part_out_bytes = round256((size_t)pl.n_z * pl.n_sub * rows_all * s.head_dim * 4);
+    pl.part_lse_bytes = round256((size_t)pl.n_z * pl.n_sub * rows_all * 4);
+  }
   return pl;
 }
 
-template <int D>
 using Kern = void (*)(Params);
 
-template <int D>
-Kern<D> pick_kernel(bool split, bool band, bool bf16_out) {
-  if constexpr (D == 128) {
-    if (band)
-      return split ? prefill_mfma_kernel<128, float, true, true>
-             : bf16_out ? prefill_mfma_kernel<128, bf16_t, true, false>
-                        : prefill_mfma_kernel<128, float, true, false>;
-  }
-  return split ? prefill_mfma_kernel<D, float, false, true>
-         : bf16_out ? prefill_mfma_kernel<D, bf16_t, false, false>
-                    : prefill_mfma_kernel<D, float, false, false>;
+template <int D, bool BAND>
+Kern pick_kernel(Mode mode, bool bf16_out) {
+  if (mode == SPLIT) return prefill_mfma_kernel<D, float, BAND, SPLIT>;
+  if (mode == PLAN)
+    return bf16_out ? prefill_mfma_kernel<D, bf16_t, BAND, PLAN>
+                    : prefill_mfma_kernel<D, float, BAND, PLAN>;
+  return bf16_out ? prefill_mfma_kernel<D, bf16_t, BAND, WHOLE>
+                  : prefill_mfma_kernel<D, float, BAND, WHOLE>;
 }
 
-int launch_body(void (*kern)(Params), int smem, const dim3& grid, const Params& p,
-                hipStream_t stream) {
+int launch_body(Kern kern, int smem, const dim3& grid, const Params& p, hipStream_t stream) {
   if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem) !=
       hipSuccess)
     return CP_ERR_LAUNCH;
@@ -209,21 +245,30 @@ int launch_body(void (*kern)(Params), int smem, const dim3& grid, const Params& 
   return check_launch();
 }
 
+int launch_kv_bounds(const AttnTable& t, int n_blocks, bool coarse, void* out, hipStream_t stream) {
+  if (n_blocks == 0) return CP_OK;
+  hipLaunchKernelGGL(coarse ? kv_bounds_kernel<true> : kv_bounds_kernel<false>,
+                     dim3((n_blocks + 15) / 16), dim3(256), 0, stream, t, n_blocks, (int2*)out);
+  return check_launch();
+}
+
 int check_rows(const AttnShape& s) {
   if (s.n_kv_heads > 65535) return CP_ERR_SHAPE;
-  if (s.total_q * (s.n_q_heads / s.n_kv_heads) > 0x7fffffffLL) return CP_ERR_SHAPE;  // 31-bit rows
+  const int64_t rows = s.total_q * (s.n_q_heads / s.n_kv_heads);
+  if (rows > 0x7fffffffLL) return CP_ERR_SHAPE;  // 31-bit rows
+  if ((rows + BM) / BM * s.n_kv_heads > 0x7fffffffLL) return CP_ERR_SHAPE;
   return CP_OK;
 }
 
-void fill_params(const AttnShape& s, const AttnTable& t, const void* bounds, Params& p) {
+void fill_params(const AttnShape& s, const AttnTable& t, Params& p) {
   p.t = t;
-  p.bounds = (const int2*)bounds;
   p.group = s.n_q_heads / s.n_kv_heads;
   p.rows = s.total_q * p.group;
   p.rows_all_heads = s.total_q * s.n_q_heads;
+  p.n_row_blocks = (int32_t)((p.rows + BM - 1) / BM);
   p.n_kv_heads = s.n_kv_heads;
-  p.n_tiles = s.n_tiles;
-  p.n_sub = 1;
+  p.n_blocks = s.n_blocks;
+  p.n_sub = p.n_z = 1;
   p.scale_log2 = s.scale * kLog2e;
 }
 
@@ -236,59 +281,74 @@ bool attn_mfma_applies(int dtype, int head_dim, int n_q_heads, int n_kv_heads) {
 
 size_t attn_mfma_workspace_bytes(const AttnShape& s) { return make_plan(s).total(); }
 
+size_t attn_mfma_ring_workspace_bytes(const AttnShape& s) {
+  return round256((size_t)std::max(s.n_blocks, 1) * sizeof(int2));
+}
+
 bool attn_mfma_merging_applies(const AttnShape& s) {
   const int64_t rows = s.total_q * (s.n_q_heads / s.n_kv_heads);
   const int64_t wgs = (rows + BM - 1) / BM * s.n_kv_heads;
   if (s.head_dim != 128) return false;
   if (wgs >= 128 || wgs == 0) return true;
-  return choose_splits(wgs, s.n_tiles, (double)s.total_q * s.n_q_heads, s.head_dim,
+  return choose_splits(wgs, (s.n_blocks + 3) / 4, (double)s.total_q * s.n_q_heads, s.head_dim,
                        CP_MAX_PARTS) == 1;
 }
 
-int launch_kv_tile_bounds(const AttnTable& t, int n_tiles, void* bounds_out, hipStream_t stream) {
-  if (n_tiles == 0) return CP_OK;
-  hipLaunchKernelGGL(kv_tile_bounds_kernel, dim3((n_tiles + 3) / 4), dim3(256), 0, stream, t,
-                     n_tiles, (int2*)bounds_out);
-  return check_launch();
-}
-
 int launch_attn_mfma(const AttnShape& s, const AttnTable& t, const AttnOut& o,
-                     const int32_t* q_lo, const void* tile_bounds, void* workspace,
-                     size_t workspace_bytes, hipStream_t stream) {
+                     const int32_t* q_lo, void* workspace, size_t workspace_bytes,
+                     hipStream_t stream) {
   const Plan pl = make_plan(s);
   if (workspace_bytes < pl.total()) return CP_ERR_WORKSPACE;
   if (pl.n_row_blocks == 0) return CP_OK;
-  const int rc = check_rows(s);
+  int rc = check_rows(s);
   if (rc != CP_OK) return rc;
-  char* ws = (char*)workspace;
-  if (tile_bounds == nullptr && launch_kv_tile_bounds(t, s.n_tiles, ws, stream) != CP_OK)
-    return CP_ERR_LAUNCH;
-  Params p = {};
-  fill_params(s, t, tile_bounds != nullptr ? tile_bounds : ws, p);
-  p.q_lo = q_lo;
-  p.n_sub = pl.n_sub;
-  p.per_shard = s.per_shard ? 1 : 0;
-  p.part_out = (float*)(ws + pl.bounds_bytes);
-  p.part_lse = (float*)(ws + pl.bounds_bytes + pl.part_out_bytes);
-  p.out_shard_stride = o.shard_out_bytes;
-  p.lse_shard_stride = o.shard_lse_elems;
   const bool bf16_out = o.dtype == CP_BF16, band = q_lo != nullptr;
   if (band && s.head_dim != 128) return CP_ERR_UNSUPPORTED;
-  const dim3 grid(pl.n_row_blocks, s.n_kv_heads, pl.n_z);
-  const int rl = s.head_dim == 128
-                     ? launch_body(pick_kernel<128>(pl.split, band, bf16_out), Geo<128>::SMEM, grid,
-                                   p, stream)
-                     : launch_body(pick_kernel<64>(pl.split, band, bf16_out), Geo<64>::SMEM, grid,
-                                   p, stream);
-  if (rl != CP_OK || !pl.split) return rl;
+  char* ws = (char*)workspace;
+  Params p = {};
+  fill_params(s, t, p);
+  p.bounds = (const int2*)ws;
+  p.bounds_shift = pl.coarse ? 2 : 0;
+  p.part_out = (float*)(ws + pl.bounds_bytes);
+  p.part_lse = (float*)(ws + pl.bounds_bytes + pl.part_out_bytes);
+  p.plan_rec = (int2*)(ws + pl.bounds_bytes + pl.part_out_bytes + pl.part_lse_bytes);
+  p.q_lo = q_lo;
+  p.n_sub = pl.n_sub;
+  p.n_z = pl.n_z;
+  p.per_shard = s.per_shard ? 1 : 0;
+  p.cut_units = pl.cut ? 1 : 0;
+  p.out_shard_stride = o.shard_out_bytes;
+  p.lse_shard_stride = o.shard_lse_elems;
+  if (pl.mode != PLAN) {
+    rc = launch_kv_bounds(t, s.n_blocks, pl.coarse, ws, stream);
+    if (rc != CP_OK) return rc;
+  }
+  const Kern kern = s.head_dim == 64 ? pick_kernel<64, false>(pl.mode, bf16_out)
+                    : band           ? pick_kernel<128, true>(pl.mode, bf16_out)
+                                     : pick_kernel<128, false>(pl.mode, bf16_out);
+  const int smem = s.head_dim == 64 ? (pl.mode == PLAN ? Geo<64>::SMEM_PLAN : Geo<64>::SMEM)
+                                    : (pl.mode == PLAN ? Geo<128>::SMEM_PLAN : Geo<128>::SMEM);
+  const unsigned wgs = (unsigned)(pl.n_row_blocks * s.n_kv_heads);
+  const dim3 grid = pl.mode == PLAN ? dim3(pl.cut ? kPlanWorkgroups : wgs * pl.n_z)
+                                    : dim3(wgs, 1, pl.n_z * pl.n_sub);
+  rc = launch_body(kern, smem, grid, p, stream);
+  if (rc != CP_OK) return rc;
 
+  if (pl.cut) {
+    const dim3 mgrid(kPlanWorkgroups - 1, kMergeParts);
+    auto mk = s.head_dim == 64 ? (bf16_out ? plan_merge_kernel<64, bf16_t> : plan_merge_kernel<64, float>)
+                               : (bf16_out ? plan_merge_kernel<128, bf16_t> : plan_merge_kernel<128, float>);
+    hipLaunchKernelGGL(mk, mgrid, dim3(256), 0, stream, p);
+    return check_launch();
+  }
+  if (pl.mode != SPLIT) return CP_OK;
   // Equation 4 over the parts: of the whole KV axis, or of every shard into the shard's output
   MergeTable m = {};
   m.n_ranks = t.n_ranks;
   m.n_parts = pl.n_sub;
   m.part_bytes = p.rows_all_heads * s.head_dim * 4;
   m.part_lse_elems = p.rows_all_heads;
-  m.n_groups = s.per_shard ? s.n_shards : 1;
+  m.n_groups = pl.n_z;
   m.group_out_bytes = o.shard_out_bytes;
   m.group_lse_elems = o.shard_lse_elems;
   for (int a = 0; a < t.n_ranks; ++a) {
@@ -307,41 +367,53 @@ int launch_attn_mfma_accumulate(const AttnShape& s, const AttnTable& t,
                                 const PrefillAccumulate& acc, void* workspace,
                                 size_t workspace_bytes, hipStream_t stream) {
   if (!attn_mfma_merging_applies(s)) return CP_ERR_UNSUPPORTED;
-  const size_t bounds_bytes = round256((size_t)std::max(s.n_tiles, 1) * sizeof(int2));
-  if (workspace_bytes < bounds_bytes) return CP_ERR_WORKSPACE;
-  const int rc = check_rows(s);
+  const size_t bounds = round256((size_t)std::max((s.n_blocks + 3) / 4, 1) * sizeof(int2));
+  if (workspace_bytes < bounds) return CP_ERR_WORKSPACE;
+  int rc = check_rows(s);
   if (rc != CP_OK) return rc;
-  if (launch_kv_tile_bounds(t, s.n_tiles, workspace, stream) != CP_OK) return CP_ERR_LAUNCH;
+  rc = launch_kv_bounds(t, s.n_blocks, true, workspace, stream);
+  if (rc != CP_OK) return rc;
   Params p = {};
-  fill_params(s, t, workspace, p);
+  fill_params(s, t, p);
+  p.bounds = (const int2*)workspace;
+  p.bounds_shift = 2;
   p.acc = acc.out;
   p.final_out = acc.final_out;
   p.final_lse = acc.final_lse;
-  const int64_t blocks = (p.rows + BM - 1) / BM;
-  const dim3 grid((unsigned)blocks, s.n_kv_heads, 1);
   return launch_body(acc.final_out != nullptr && acc.final_dtype == CP_BF16
-                         ? prefill_mfma_kernel<128, bf16_t, false, false, true>
-                         : prefill_mfma_kernel<128, float, false, false, true>,
-                     Geo<128>::SMEM, grid, p, stream);
+                         ? prefill_mfma_kernel<128, bf16_t, false, ACC>
+                         : prefill_mfma_kernel<128, float, false, ACC>,
+                     Geo<128>::SMEM, dim3((unsigned)(p.n_row_blocks * p.n_kv_heads)), p, stream);
 }
 
-int launch_attn_mfma_ring(const AttnShape& s, const AttnTable& t, int ring_start,
-                          const int32_t* arrived, int32_t* error, int32_t spin_limit,
-                          int32_t out_dtype, const void* tile_bounds, hipStream_t stream) {
-  if (t.n_ranks != 1 || ring_start < 0 || ring_start >= t.n_shards) return CP_ERR_SHAPE;
-  if (arrived != nullptr && (error == nullptr || spin_limit < 1)) return CP_ERR_SHAPE;
-  const int rc = check_rows(s);
+int launch_attn_mfma_ring(const AttnShape& s, const AttnTable& t, const int32_t* const* arrived,
+                          int32_t* error, int32_t spin_limit, int32_t out_dtype, void* workspace,
+                          size_t workspace_bytes, hipStream_t stream) {
+  if (arrived == nullptr || error == nullptr || spin_limit < 1) return CP_ERR_SHAPE;
+  if (t.n_ranks != t.n_shards) return CP_ERR_SHAPE;
+  if (workspace_bytes < attn_mfma_ring_workspace_bytes(s)) return CP_ERR_WORKSPACE;
+  int rc = check_rows(s);
+  if (rc != CP_OK) return rc;
+  rc = launch_kv_bounds(t, s.n_blocks, false, workspace, stream);
   if (rc != CP_OK) return rc;
   Params p = {};
-  fill_params(s, t, tile_bounds, p);
-  p.arrived = arrived; p.ring_error = error; p.spin_limit = spin_limit;
-  p.ring_start = ring_start;
-  const int64_t blocks = (p.rows + BM - 1) / BM;
+  fill_params(s, t, p);
+  p.bounds = (const int2*)workspace;
+  p.ring_error = error;
+  p.spin_limit = spin_limit;
+  int64_t blocks = 0;
+  for (int a = 0; a < t.n_ranks; ++a) {
+    p.arrived[a] = arrived[a];
+    p.rb_begin[a] = (int32_t)blocks;
+    blocks += ((int64_t)(t.tok_begin[a + 1] - t.tok_begin[a]) * p.group + BM - 1) / BM;
+  }
+  p.rb_begin[t.n_ranks] = (int32_t)blocks;
   if (blocks == 0) return CP_OK;
-  const dim3 grid((unsigned)blocks, s.n_kv_heads, 1);
+  if (blocks * p.n_kv_heads > 0x7fffffffLL) return CP_ERR_SHAPE;
+  p.n_row_blocks = (int32_t)blocks;
   return launch_body(out_dtype == CP_BF16 ? prefill_ring_walk_kernel<bf16_t>
                                           : prefill_ring_walk_kernel<float>,
-                     Geo<128>::SMEM, grid, p, stream);
+                     Geo<128>::SMEM, dim3((unsigned)(blocks * p.n_kv_heads)), p, stream);
 }
 
 }  // namespace cp

@@ -31,9 +31,10 @@
 typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
 
-// Sizes and LDS layout for head_dim D. The list of visible tiles holds, per tile, the
-// addresses of its K and V rows (this KV head) and of its positions, so that a workgroup walks
-// tiles of any number of KV shards with one loop.
+// Sizes and LDS layout for head_dim D. The list of visible 32-key blocks holds, per block, the
+// addresses of its K and V rows (this KV head) and of its positions; four consecutive entries
+// make a tile, wherever their keys lie, so that a workgroup walks any number of KV shards with
+// one loop and spends nothing on blocks it cannot see.
 template <int D>
 struct Geo {
   static constexpr int ROW = D * 2;              // one K or V row in bytes
@@ -48,12 +49,18 @@ struct Geo {
   static constexpr int OFF_V = 2 * KD;
   static constexpr int OFF_POS = OFF_V + 2 * KD;
   static constexpr int OFF_SCRATCH = OFF_POS + 2 * POS_BYTES;
-  static constexpr int OFF_LIVE = OFF_SCRATCH + 128;
-  static constexpr int OFF_LIVE_LO = OFF_LIVE + MAX_LIVE * 32;
-  static constexpr int SMEM = OFF_LIVE_LO + MAX_LIVE * 4;
+  static constexpr int OFF_LIVE = OFF_SCRATCH + 256;
+  static constexpr int OFF_LIVE_POS = OFF_LIVE + MAX_LIVE * 16;
+  static constexpr int OFF_LIVE_RANGE = OFF_LIVE_POS + MAX_LIVE * 16;
+  static constexpr int OFF_BOUNDS = OFF_LIVE_RANGE + MAX_LIVE * 8;
+  static constexpr int SMEM = OFF_BOUNDS;                        // bounds from global memory
+  static constexpr int OFF_WEIGHT = OFF_BOUNDS + PLAN_MAX_BLOCKS * 8;  // PLAN: bounds kept in LDS
+  static constexpr int OFF_SHARDS = OFF_WEIGHT + PLAN_MAX_UNITS * 2;   // units' weights
+  static constexpr int SMEM_PLAN = OFF_SHARDS + kMaxTable * 32;        // and the shards
   static constexpr int OUT_STRIDE = D * 4 + 16;  // epilogue staging: one fp32 output row + pad
   static_assert(NWAVE * 32 * OUT_STRIDE <= SMEM, "epilogue staging fits in the allocation");
-  static_assert(SMEM <= 160 * 1024, "LDS budget of one CU");
+  static_assert(SMEM_PLAN <= 160 * 1024, "LDS budget of one CU");
+  
   static_assert(2 * KD <= 65536, "K fragment offsets fit the 16-bit LDS offset field");
   static_assert(NKS == NVF, "the two halves of a pipeline step have the same length");
   // Chunk c of K row r lands at position c ^ k_perm(r): 16 lanes that read the same chunk of
@@ -156,7 +163,7 @@ __device__ __forceinline__ void pipe_body(PipeRegs<D>& R, const bf16x8_t (&qf)[D
                                           const uint32_t (&kaddr)[D / 16],
                                           const uint32_t (&vaddr)[D / 32],
                                           uint32_t paddr, int32_t qp, int32_t ql,
-                                          float scale_log2, bool need_mask, bool& have_ref,
+                                          float scale_log2, bool need_mask, bool dead, bool& have_ref,
                                           Hook hook) {
   using G = Geo<D>;
   constexpr int CUR = BLK & 1, NXT = CUR ^ 1;
@@ -176,16 +183,18 @@ __device__ __forceinline__ void pipe_body(PipeRegs<D>& R, const bf16x8_t (&qf)[D
   bool raise = false;
 
   // Online softmax in the log2 domain, reference maximum m_run per row.
-  // Full form (masked tiles, and until every row of the wavefront has a reference): block
-  // maximum, and the reference is raised when the maximum exceeds it by more than
-  // kRescaleSlack. Fast form (everything else): no maximum at all. The exponentials are taken
-  // against the standing reference, whatever the block holds; the reference is never above a
-  // score the row has seen, so nothing underflows that should not, and a block whose
-  // exponentials sum to more than kOverflowSum (a score 40 log2 units above the reference) is
-  // detected from its sum and redone in the full form. O and l are rescaled at the end of
-  // the step, after the MFMAs that still belong to the old reference. The denominator sums
-  // the unrounded exponentials: LSE must be good to 1e-3 even on rows with a handful of
-  // keys, which bf16 rounding of P would not give.
+  // Fast form (nearly every block): no maximum at all. The exponentials are taken against the
+  // standing reference, whatever the block holds; the reference is never above a score the row
+  // has seen, so nothing underflows that should not, and a block whose exponentials sum to more
+  // than kOverflowSum (a score 40 log2 units above the reference) is detected from its sum and
+  // redone in the full form. A block that straddles a query position is masked first
+  // (need_mask); one that no row of this wavefront can see (dead: the workgroup's other
+  // wavefronts can) is taken against an infinite reference, i.e. as zeros.
+  // Full form (until every row of the wavefront has a reference): block maximum, and the
+  // reference is raised when the maximum exceeds it by more than kRescaleSlack. O and l are
+  // rescaled at the end of the step, after the MFMAs that still belong to the old reference. The
+  // denominator sums the unrounded exponentials: LSE must be good to 1e-3 even on rows with a
+  // handful of keys, which bf16 rounding of P would not give.
   auto block_max = [&]() __attribute__((always_inline)) -> float {
     float a = fmaxf(fmaxf(s[0], s[1]), s[2]);
     float b = fmaxf(fmaxf(s[3], s[4]), s[5]);
@@ -212,34 +221,38 @@ __device__ __forceinline__ void pipe_body(PipeRegs<D>& R, const bf16x8_t (&qf)[D
   auto valu = [&](auto jc) __attribute__((always_inline)) {
     constexpr int J = decltype(jc)::value;
     if constexpr (J == 0) {
-      const bool full = need_mask | !have_ref;  // scalar flags: one branch on the hot path
-      if (__builtin_expect(full, 0)) {  // wave-uniform, rare: laid out off the hot path
-        if (need_mask) {
-          // Masked tiles are the few on the diagonal: their kv_pos reads are simply waited
-          // for (which also completes every older LDS read, so the counted waits hold).
-          u32x4_t kp0 = lds_read_b128<POFF + 0>(paddr), kp1 = lds_read_b128<POFF + 32>(paddr);
-          u32x4_t kp2 = lds_read_b128<POFF + 64>(paddr), kp3 = lds_read_b128<POFF + 96>(paddr);
-          lgkm_wait<0>(kp0, kp1, kp2, kp3);
+      m_use = R.m_run;
+      if (__builtin_expect(need_mask | !have_ref, 0)) {  // wave-uniform, rare: off the hot path
+        if (dead) {
+          m_use = INFINITY;
+        } else {
+          if (need_mask) {
+            // The kv_pos reads are simply waited for (which also completes every older LDS read,
+            // so the counted waits hold).
+            u32x4_t kp0 = lds_read_b128<POFF + 0>(paddr), kp1 = lds_read_b128<POFF + 32>(paddr);
+            u32x4_t kp2 = lds_read_b128<POFF + 64>(paddr), kp3 = lds_read_b128<POFF + 96>(paddr);
+            lgkm_wait<0>(kp0, kp1, kp2, kp3);
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int32_t k0 = (int32_t)kp0[r], k1 = (int32_t)kp1[r];
-            const int32_t k2 = (int32_t)kp2[r], k3 = (int32_t)kp3[r];
-            if (k0 > qp || (BAND && k0 < ql)) s[0 + r] = -INFINITY;
-            if (k1 > qp || (BAND && k1 < ql)) s[4 + r] = -INFINITY;
-            if (k2 > qp || (BAND && k2 < ql)) s[8 + r] = -INFINITY;
-            if (k3 > qp || (BAND && k3 < ql)) s[12 + r] = -INFINITY;
+            for (int r = 0; r < 4; ++r) {
+              const int32_t k0 = (int32_t)kp0[r], k1 = (int32_t)kp1[r];
+              const int32_t k2 = (int32_t)kp2[r], k3 = (int32_t)kp3[r];
+              if (k0 > qp || (BAND && k0 < ql)) s[0 + r] = -INFINITY;
+              if (k1 > qp || (BAND && k1 < ql)) s[4 + r] = -INFINITY;
+              if (k2 > qp || (BAND && k2 < ql)) s[8 + r] = -INFINITY;
+              if (k3 > qp || (BAND && k3 < ql)) s[12 + r] = -INFINITY;
+            }
+          }
+          if (!have_ref) {
+            const float m_step = block_max() * scale_log2;
+            raise = m_step > R.m_run + kRescaleSlack;  // true on the first visible block
+            const float m_new = raise ? m_step : R.m_run;
+            alpha = __builtin_amdgcn_exp2f(R.m_run - (m_new == -INFINITY ? 0.f : m_new));
+            R.l_run *= alpha;
+            R.m_run = m_new;
+            m_use = m_new == -INFINITY ? 0.f : m_new;
+            have_ref = __builtin_amdgcn_ballot_w64(m_new == -INFINITY) == 0;
           }
         }
-        const float m_step = block_max() * scale_log2;
-        raise = m_step > R.m_run + kRescaleSlack;  // true on the first visible block
-        const float m_new = raise ? m_step : R.m_run;
-        alpha = __builtin_amdgcn_exp2f(R.m_run - (m_new == -INFINITY ? 0.f : m_new));
-        R.l_run *= alpha;
-        R.m_run = m_new;
-        m_use = m_new == -INFINITY ? 0.f : m_new;
-        have_ref = __builtin_amdgcn_ballot_w64(m_new == -INFINITY) == 0;
-      } else {
-        m_use = R.m_run;
       }
       pin(m_use);
     } else {
@@ -337,24 +350,22 @@ __device__ __forceinline__ void pipe_body(PipeRegs<D>& R, const bf16x8_t (&qf)[D
 }
 
 // ---- arrival flags of the ring walk (RING): the bounded wait for a shard ----
-__device__ __forceinline__ int ring_flag(const Params& p, int step) {
-  return __hip_atomic_load(p.arrived + step, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+__device__ __forceinline__ int ring_flag(const Params& p, int rank, int step) {
+  return __hip_atomic_load(p.arrived[rank] + step, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
-// Makes sure that the shard of ring step `step` may be read. With arrival flags, thread 0 looks
-// at the step's flag first: `peek` is what it read of that flag while the previous shard
-// was being walked (so a shard that arrived in time costs no round trip here); if that was
+// Makes sure that the shard of ring step `step` of rank `rank` may be read: thread 0 looks at the
+// step's flag first: `peek` is what it read of that flag while the previous shard was being walked (so a shard that arrived in time costs no round trip here); if that was
 // zero it polls (uncached loads, a short sleep between them, at most p.spin_limit of them).
 // The whole workgroup learns the outcome through LDS; false = the flag never came up:
-// bit `step` of *p.ring_error is set and the caller leaves the shard out. Every wait ends.
-__device__ __forceinline__ bool ring_enter(const Params& p, int step, int tid, int* wg_scratch,
-                                           int& peek) {
-  if (p.arrived == nullptr) return true;
+// bit `step` of the rank's error word is set and the caller leaves the shard out. Every wait ends.
+__device__ __forceinline__ bool ring_enter(const Params& p, int rank, int step, int tid,
+                                           int* wg_scratch, int& peek) {
   int* const slot = wg_scratch + 20 + (step & 1);  // two slots: a wavefront may lag one step
   if (tid == 0) {
     int ok = 1;
     if (peek == 0) {
       int budget = p.spin_limit;
-      while (ring_flag(p, step) == 0) {
+      while (ring_flag(p, rank, step) == 0) {
         if (--budget <= 0) {
           ok = 0;
           break;
@@ -362,10 +373,10 @@ __device__ __forceinline__ bool ring_enter(const Params& p, int step, int tid, i
         __builtin_amdgcn_s_sleep(32);
       }
     }
-    if (!ok) atomicOr(p.ring_error, 1 << step);  // which step gave up (n_shards <= 32)
+    if (!ok) atomicOr(p.ring_error + rank, 1 << step);  // which step gave up (n_shards <= 32)
     *slot = ok;
     // a look at the next step's flag, used when the walk gets there
-    peek = step + 1 < p.t.n_shards ? ring_flag(p, step + 1) : 0;
+    peek = step + 1 < p.t.n_shards ? ring_flag(p, rank, step + 1) : 0;
   }
   lds_barrier();
   const int ok = __builtin_amdgcn_readfirstlane(*slot);
@@ -378,524 +389,984 @@ __device__ __forceinline__ bool ring_enter(const Params& p, int step, int tid, i
   return ok != 0;
 }
 
-// The walk of one workgroup: 256 consecutive (token, head-in-group) rows of one KV head, over
-// the queries of all ranks of the table back to back, against the visible tiles of the KV
-// shards.
+// ---------------------------------------------------------------------------
+// PLAN: equal shares for the workgroups.
+//
+// A causal prefill gives its row blocks walks of very different lengths (one tile to all of
+// them), a packed batch even more so; with a workgroup per row block, or an equal number of
+// splits for each, the longest walk sets the time (6229 tokens, 8 heads, 195 row blocks of up
+// to 49 tiles: 204 us where the work is 70 us of all compute units). So the launch is 256
+// workgroups (one per CU) that take equal shares of the whole work, cutting row blocks where a
+// share ends. A unit is a row block of one KV head (against one shard, where shards are kept
+// apart); its weight is an estimate of its visible tiles plus kUnitCost for start-up and
+// epilogue. Every workgroup works the plan out for itself, from kv_pos and q_pos, in LDS: that
+// costs it 3 to 6 us, less than the launches that would hand it over, and replaces the
+// position-bound pre-pass. (Counting a unit's visible blocks exactly took up to 45 us at 700
+// units and 350 blocks, so the weight comes from its first and last query and from at most 32
+// blocks, 128 in a packed batch; a cut is made at the same fraction of the unit's true list of tiles.) What a share cuts goes to the workspace as fp32 partials (at most two per
+// workgroup) and is merged by plan_merge_kernel. Only for calls whose positions and unit list
+// fit LDS; larger ones have row blocks enough to keep every CU busy.
+// ---------------------------------------------------------------------------
+
+// Shares: workgroup i of W takes [share_begin(i), share_begin(i + 1)) of the line of all units
+// (the host keeps total * 256 within 32 bits).
+__device__ inline int plan_workgroups(uint32_t total, int max_wgs) {
+  const uint32_t w = total / (kUnitCost + 2);   // a share is worth its own start-up
+  return (int)(w < 1 ? 1 : w > (uint32_t)max_wgs ? (uint32_t)max_wgs : w);
+}
+__device__ inline int share_begin(int i, uint32_t total, int n_wgs) {
+  return (int)((uint32_t)i * total / (uint32_t)n_wgs);
+}
+
+struct Share {
+  int unit;     // first unit
+  int begin;    // begin of the share, counted from the begin of that unit
+  int length;
+};
+
+// Copies of the table that are looked up per lane while planning (over the tile buffers, which
+// are not in use yet).
+struct PlanLds {
+  const int32_t* q_pos[kMaxTable];
+  const int32_t* kv_pos[kMaxTable];
+  int n_kv[kMaxTable];
+  int tok_begin[kMaxTable + 1];
+  int blk_begin[kMaxTable + 1];
+};
+
+// x rotated by N within each row of 16 lanes.
+template <int N>
+__device__ __forceinline__ int row_ror(int x) {
+  return __builtin_amdgcn_update_dpp(x, x, 0x120 + N, 0xf, 0xf, false);
+}
+__device__ __forceinline__ int row_max(int x) {  // over 16 lanes
+  x = max(x, row_ror<8>(x));
+  x = max(x, row_ror<4>(x));
+  x = max(x, row_ror<2>(x));
+  return max(x, row_ror<1>(x));
+}
+__device__ __forceinline__ int row_min(int x) {
+  x = min(x, row_ror<8>(x));
+  x = min(x, row_ror<4>(x));
+  x = min(x, row_ror<2>(x));
+  return min(x, row_ror<1>(x));
+}
+__device__ __forceinline__ int row_sum(int x) {
+  x += row_ror<8>(x);
+  x += row_ror<4>(x);
+  x += row_ror<2>(x);
+  return x + row_ror<1>(x);
+}
+// Over the wavefront; the results are wave-uniform (scalar).
+__device__ __forceinline__ int wave_max(int x) {
+  x = row_max(x);
+  return max(max(__builtin_amdgcn_readlane(x, 0), __builtin_amdgcn_readlane(x, 16)),
+             max(__builtin_amdgcn_readlane(x, 32), __builtin_amdgcn_readlane(x, 48)));
+}
+__device__ __forceinline__ int wave_min(int x) {
+  x = row_min(x);
+  return min(min(__builtin_amdgcn_readlane(x, 0), __builtin_amdgcn_readlane(x, 16)),
+             min(__builtin_amdgcn_readlane(x, 32), __builtin_amdgcn_readlane(x, 48)));
+}
+__device__ __forceinline__ int wave_sum(int x) {
+  x = row_sum(x);
+  return __builtin_amdgcn_readlane(x, 0) + __builtin_amdgcn_readlane(x, 16) +
+         __builtin_amdgcn_readlane(x, 32) + __builtin_amdgcn_readlane(x, 48);
+}
+
+// (min, max) of the positions of every 32-key block into LDS. Loads are issued many at a time:
+// this is a chain of memory latencies, nothing else.
+__device__ __forceinline__ void plan_bounds(const Params& p, int2* lds_bounds, const PlanLds& L,
+                                            int tid) {
+  // 8 threads per block, 4 positions per thread, up to 8 blocks per thread at a time
+  constexpr int PER = 8, STEP = NTHREADS / 8;
+  int sh = 0;
+  for (int b0 = 0; b0 < p.n_blocks; b0 += PER * STEP) {
+    int32_t x[PER][4];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      if (b0 + u * STEP < p.n_blocks) {   // uniform
+        const int b = min(b0 + u * STEP + (tid >> 3), p.n_blocks - 1);
+        int first = 0, n_kv = p.t.n_kv[0];
+        const int32_t* pos = p.t.kv_pos[0];
+        if (p.t.n_shards > 1) {
+          while (b >= L.blk_begin[sh + 1]) ++sh;
+          first = L.blk_begin[sh];
+          n_kv = L.n_kv[sh];
+          pos = L.kv_pos[sh];
+        }
+        const int key0 = (b - first) * BLOCK + (tid & 7);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)   // (past the end: the last key again, same bounds)
+          x[u][i] = pos[min(key0 + i * 8, n_kv - 1)];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      if (b0 + u * STEP < p.n_blocks) {
+        const int b = b0 + u * STEP + (tid >> 3);
+        int lo = min(min(x[u][0], x[u][1]), min(x[u][2], x[u][3]));
+        int hi = max(max(x[u][0], x[u][1]), max(x[u][2], x[u][3]));
+#pragma unroll
+        for (int o = 4; o > 0; o >>= 1) {
+          lo = min(lo, __shfl_xor(lo, o, 64));
+          hi = max(hi, __shfl_xor(hi, o, 64));
+        }
+        if ((tid & 7) == 0 && b < p.n_blocks) lds_bounds[b] = make_int2(lo, hi);
+      }
+    }
+  }
+}
+
+// A shard as the list of visible blocks looks it up per lane (PLAN: in LDS).
+struct LdsShard {
+  const void* k;
+  const void* v;
+  const int32_t* kv_pos;
+  int32_t n_kv, blk_begin;
+};
+
+// Bounds of all blocks, and this workgroup's share. `weight`: the units' planned tiles (LDS).
+template <bool BAND>
+__device__ __forceinline__ Share plan_share(const Params& p, int2* lds_bounds, uint16_t* weight,
+                                            PlanLds& L, LdsShard* shards, int* wg_scratch,
+                                            int tid) {
+  const int lane = tid & 63, wave = tid >> 6;
+  Share sh = {0, 0, 0};
+  if (tid >= 64 && tid < 64 + p.t.n_shards) {
+    const int i = tid - 64;
+    shards[i] = {p.t.k[i], p.t.v[i], p.t.kv_pos[i], p.t.n_kv[i], p.t.blk_begin[i]};
+  }
+  if (p.t.n_ranks > 1 || p.t.n_shards > 1) {
+    if (tid <= kMaxTable) {
+      L.tok_begin[tid] = p.t.tok_begin[tid];
+      L.blk_begin[tid] = p.t.blk_begin[tid];
+      if (tid < kMaxTable) {
+        L.q_pos[tid] = p.t.q_pos[tid];
+        L.kv_pos[tid] = p.t.kv_pos[tid];
+        L.n_kv[tid] = p.t.n_kv[tid];
+      }
+    }
+    __syncthreads();
+  }
+  if (!p.cut_units) {  // a workgroup per unit
+    plan_bounds(p, lds_bounds, L, tid);
+    __syncthreads();
+    const int i = blockIdx.x / p.n_kv_heads, kvh = blockIdx.x - i * p.n_kv_heads;
+    const int z = p.n_z > 1 ? i / p.n_row_blocks : 0;
+    const int rb = ordered_row_block(i - z * p.n_row_blocks, p.n_row_blocks, p.t.n_ranks, lane);
+    sh.unit = (kvh * p.n_z + z) * p.n_row_blocks + rb;
+    return sh;
+  }
+  const int n_rb = p.n_row_blocks, n_units = n_rb * p.n_z;
+  // Position range of every row block as its first and its last query have it; PER blocks per
+  // thread, requested before the key positions.
+  constexpr int PER = PLAN_MAX_UNITS / NTHREADS;
+  int mx[PER], lo[PER];
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    mx[k] = INT32_MIN;
+    lo[k] = INT32_MAX;
+    if (k * NTHREADS < n_units) {  // uniform
+      const int u = min(k * NTHREADS + tid, n_units - 1);
+      const int z = p.n_z > 1 ? u / n_rb : 0, rb = u - z * n_rb;
+      int a = 0;
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const int64_t row = e == 0 ? (int64_t)rb * BM : min<int64_t>((int64_t)rb * BM + BM, p.rows) - 1;
+        const int t = (int)((uint32_t)row / (uint32_t)p.group);
+        int32_t x;
+        if (p.t.n_ranks > 1) {
+          while (t >= L.tok_begin[a + 1]) ++a;
+          x = L.q_pos[a][t - L.tok_begin[a]];
+        } else {
+          x = p.t.q_pos[0][t];
+        }
+        mx[k] = max(mx[k], x);
+        if (BAND) lo[k] = min(lo[k], x >= 0 ? p.q_lo[t] : INT32_MAX);
+      }
+    }
+  }
+  plan_bounds(p, lds_bounds, L, tid);
+  __syncthreads();
+  // Planned tiles: every stride-th block of the range looked at (more of them in a packed batch,
+  // where a row block sees few).
+  constexpr int SAMPLES = BAND ? 128 : 32;
+  const int avg = (p.n_blocks + p.n_z - 1) / p.n_z, stride = (avg + SAMPLES - 1) / SAMPLES;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    if (k * NTHREADS < n_units) {
+      const int u = min(k * NTHREADS + tid, n_units - 1);
+      const int z = p.n_z > 1 ? u / n_rb : 0;
+      const int b0 = p.per_shard ? L.blk_begin[z] : 0;
+      const int b1 = p.per_shard ? L.blk_begin[z + 1] : p.n_blocks;
+      int cnt = 0;
+      for (int b = b0; b < b1; b += 8 * stride) {
+        int2 x[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[i] = lds_bounds[min(b + i * stride, b1 - 1)];
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          cnt += b + i * stride < b1 && x[i].x <= mx[k] && (!BAND || x[i].y >= lo[k]) ? 1 : 0;
+      }
+      weight[u] = (uint16_t)max(1, (cnt * stride + 3) >> 2);
+    }
+  }
+  __syncthreads();
+  // prefix sums
+  int x[PER], sum = 0;
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int u = tid * PER + i;
+    sum += u < n_units ? kUnitCost + (int)weight[u] : 0;
+    x[i] = sum;
+  }
+  int scan = sum;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(scan, o, 64);
+    if (lane >= o) scan += y;
+  }
+  if (lane == 63) wg_scratch[wave] = scan;
+  __syncthreads();
+  int before = scan - sum, total1 = 0;
+#pragma unroll
+  for (int w = 0; w < NWAVE; ++w) {
+    const int c = wg_scratch[w];
+    if (w < wave) before += c;
+    total1 += c;
+  }
+#pragma unroll
+  for (int i = 0; i < PER; ++i) x[i] += before;
+  total1 = __builtin_amdgcn_readfirstlane(total1);
+  // the line of units, KV head after KV head
+  const uint32_t total = (uint32_t)total1 * (uint32_t)p.n_kv_heads;
+  const int n_wgs = plan_workgroups(total, gridDim.x);
+  const int i = blockIdx.x;
+  if (i >= n_wgs) {
+    if (tid == 0) p.plan_rec[i + 1] = make_int2(-1, 0);
+    return sh;
+  }
+  // A boundary in the start-up of a unit moves to its begin: nothing is cut there. (Moving those
+  // near an end as well, to save the cut, made the calls of short units up to 30 % slower: the
+  // shares are short, too.)
+  const int s_end[2] = {share_begin(i, total, n_wgs), share_begin(i + 1, total, n_wgs)};
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    const int kvh = min((int)((uint32_t)s_end[e] / (uint32_t)total1), p.n_kv_heads - 1);
+    const int in_head = s_end[e] - kvh * total1;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const int u = tid * PER + k;
+      const int first = k == 0 ? before : x[k - 1];
+      // (the end of the line belongs to the last unit)
+      if (u < n_units && first <= in_head &&
+          (in_head < x[k] || (u == n_units - 1 && in_head == x[k]))) {
+        int unit = kvh * n_units + u, off = in_head - first;
+        if (off <= kUnitCost) off = 0;
+        else if (in_head == x[k]) { unit += 1; off = 0; }
+        wg_scratch[16 + 4 * e] = unit;
+        wg_scratch[17 + 4 * e] = off;
+        wg_scratch[18 + 4 * e] = kvh * total1 + (unit == kvh * n_units + u ? first + off : x[k]);
+        // for the merge: unit, begin of the share in it
+        if (e == 0) p.plan_rec[i] = make_int2(unit, off);
+        else if (i == n_wgs - 1) p.plan_rec[n_wgs] = make_int2(-1, 0);
+      }
+    }
+  }
+  __syncthreads();
+  sh.unit = __builtin_amdgcn_readfirstlane(wg_scratch[16]);
+  sh.begin = __builtin_amdgcn_readfirstlane(wg_scratch[17]);
+  sh.length = __builtin_amdgcn_readfirstlane(wg_scratch[22] - wg_scratch[18]);
+  return sh;
+}
+
+// How a launch deals out its work.
+enum Mode {
+  WHOLE,  // a workgroup per row block (and shard, where shards are kept apart)
+  SPLIT,  // grid.z parts of the KV axis per row block, fp32 partials in the workspace
+  PLAN,   // equal shares of everything (above)
+  ACC,    // WHOLE, merged into a running (O, LSE) in the epilogue (Equation 4 step by step)
+  RING    // WHOLE, the shards walked one by one in ring order, each behind its arrival flag
+          // (bounded wait), with one running (O, l, m) in registers: the merge of Equation 4
+          // happens inside the online softmax
+};
+
+// A workgroup's walk: 256 consecutive (token, head-in-group) rows of one KV head, over the
+// queries of all ranks of the table back to back, against the visible blocks of the KV shards.
 // BAND: packed batch. Positions are shifted per sequence and a query also has a lower bound
 // q_lo (the shift of its sequence): visible iff q_lo <= kv_pos <= q_pos.
-// SPLIT: the launch splits the KV axis over grid.z and writes fp32 partials to the workspace.
-// ACC: the result is merged into a running (O, LSE) in the epilogue instead of being written
-// as a partial (Equation 4 applied step by step); see the epilogue.
-// RING: the shards are walked one by one in ring order (from p.ring_start downwards), each
-// behind its arrival flag (bounded wait), with one running (O, l, m) in registers: the merge of
-// Equation 4 happens inside the online softmax.
-template <int D, typename TO, bool BAND, bool SPLIT, bool ACC, bool RING>
+template <int D, typename TO, bool BAND, Mode MODE>
 __device__ __forceinline__ void prefill_body(const Params& p) {
-  static_assert(!RING || (!BAND && !SPLIT && !ACC), "the ring walk is its own variant");
   using G = Geo<D>;
+  static_assert(4 * G::KD >= (int)sizeof(PlanLds), "the planning arrays lie over the tile buffers");
   constexpr int ROW = G::ROW;
   extern __shared__ __align__(16) char smem[];
   char* const kbuf0 = smem;
   char* const vbuf0 = smem + G::OFF_V;
   int32_t* const posbuf0 = (int32_t*)(smem + G::OFF_POS);
   int* const wg_scratch = (int*)(smem + G::OFF_SCRATCH);
-  int4* const live = (int4*)(smem + G::OFF_LIVE);
-  int32_t* const live_lo_pos = (int32_t*)(smem + G::OFF_LIVE_LO);
+  int4* const live = (int4*)(smem + G::OFF_LIVE);            // addresses of K and V (below)
+  int4* const live_pos = (int4*)(smem + G::OFF_LIVE_POS);    // address of kv_pos, keys
+  int2* const live_range = (int2*)(smem + G::OFF_LIVE_RANGE);  // (min, max) of kv_pos
+  int2* const lds_bounds = (int2*)(smem + G::OFF_BOUNDS);
+  uint16_t* const weight = (uint16_t*)(smem + G::OFF_WEIGHT);
+  LdsShard* const shards = (LdsShard*)(smem + G::OFF_SHARDS);
   const uint32_t smem_lds = (uint32_t)(size_t)(CP_LDS_AS char*)smem;
 
-  const int tid = threadIdx.x;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-  const int n = lane & 31, g = lane >> 5;
-  const int row_block = ordered_row_block(blockIdx.x, gridDim.x, p.t.n_ranks, lane);
-  const int kvh = blockIdx.y;
-  // grid.z: the n_sub parts of the KV axis, of every shard in turn when shards are kept apart
-  const int z_shard = p.per_shard ? blockIdx.z / p.n_sub : 0;
-  const int z_sub = blockIdx.z - z_shard * p.n_sub;
-
-  // ---- tiles of this workgroup (the ring walk moves on from shard to shard) ----
-  int cur_shard = RING ? p.ring_start : z_shard;
-  int t_begin = RING || p.per_shard ? p.t.tile_begin[cur_shard] : 0;
-  int t_end = RING || p.per_shard ? p.t.tile_begin[cur_shard + 1] : p.n_tiles;
-
-  // ---- this lane's query row ----
-  // (rows fit 31 bits: checked by the launcher)
-  const int64_t r = (int64_t)row_block * BM + wave * 32 + n;
-  const bool row_ok = r < p.rows;
-  // The start-up chain is q_pos -> visible tiles -> first tile; the bounds of the first 512
-  // tiles are requested now so that they arrive together with q_pos, and the Q fragments
-  // (needed last) are requested after both and waited for only before the first product.
-  int2 first_bounds = make_int2(0, 0);
-  if (t_begin + wave * 64 + lane < t_end) first_bounds = p.bounds[t_begin + wave * 64 + lane];
-  int32_t qp = CP_POS_PAD_Q, ql = INT32_MIN;
-  bf16x8_t qf[G::NKS];
-  {
-    const int token = row_ok ? (int)((uint32_t)r / (uint32_t)p.group) : 0;
-    const int hg = row_ok ? (int)(r - (int64_t)token * p.group) : 0;
-    const bf16_t* q = (const bf16_t*)p.t.q[0];
-    const int32_t* q_pos = p.t.q_pos[0];
-    int first = 0;
-    if (p.t.n_ranks > 1) {
-      const int a = rank_of_token(p.t, token);
-      q = (const bf16_t*)p.t.q[a];
-      q_pos = p.t.q_pos[a];
-      first = p.t.tok_begin[a];
-    }
-    if (row_ok) qp = q_pos[token - first];
-    if (BAND && row_ok) ql = p.q_lo[token];
-    const int64_t row = ((int64_t)(token - first) * p.n_kv_heads + kvh) * p.group + hg;
-#pragma unroll
-    for (int ks = 0; ks < G::NKS; ++ks) {
-      uint4 x = make_uint4(0, 0, 0, 0);
-      if (row_ok) x = *(const uint4*)(q + row * D + ks * 16 + g * 8);
-      qf[ks] = __builtin_bit_cast(bf16x8_t, x);
+  // ---- what this workgroup does first ----
+  int row_block = 0, kvh = 0, z_shard = 0, z_sub = 0, rank = 0;
+  Share share = {0, 0, 0};
+  if constexpr (MODE == PLAN) {
+    share = plan_share<BAND>(p, lds_bounds, weight, *(PlanLds*)smem, shards, wg_scratch,
+                                threadIdx.x);
+    if (p.cut_units && share.length == 0) return;
+    __syncthreads();   // the planning arrays are dead
+  } else {
+    // The KV heads of a row block are neighbours in dispatch order: the rows of one head are
+    // n_kv_heads * 2 D bytes apart, so workgroups that all read the same head use only some of
+    // the memory channels.
+    const int i = blockIdx.x / p.n_kv_heads;
+    kvh = blockIdx.x - i * p.n_kv_heads;
+    row_block = ordered_row_block(i, p.n_row_blocks, p.t.n_ranks, threadIdx.x & 63);
+    // grid.z: the n_sub parts of the KV axis, of every shard in turn when shards are kept apart
+    z_shard = p.per_shard ? blockIdx.z / p.n_sub : 0;
+    z_sub = blockIdx.z - z_shard * p.n_sub;
+    if constexpr (MODE == RING) {   // row blocks do not straddle ranks here
+      while (p.rb_begin[rank + 1] <= row_block) ++rank;
+      row_block -= p.rb_begin[rank];
     }
   }
-  const float scale_log2 = p.scale_log2;
 
-  // ---- query position range of the wavefront and of the workgroup ----
-  // rows that can see anything: a padded query (CP_POS_PAD_Q) and the rows past the end of
-  // the shard cannot, and stay out of the ranges below
-  const bool sees = row_ok && qp >= 0;
-  int w_qmin = sees ? qp : INT32_MAX, w_qmax = qp;
-  int w_lomin = BAND && sees ? ql : INT32_MAX, w_lomax = BAND && sees ? ql : INT32_MIN;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    w_qmin = min(w_qmin, __shfl_xor(w_qmin, o, 64));
-    w_qmax = max(w_qmax, __shfl_xor(w_qmax, o, 64));
-    if (BAND) {
-      w_lomin = min(w_lomin, __shfl_xor(w_lomin, o, 64));
-      w_lomax = max(w_lomax, __shfl_xor(w_lomax, o, 64));
+  for (;;) {  // (PLAN: the units of the share, else once)
+    // (The thread index is made opaque here: what is computed from it would otherwise be kept in
+    // registers across the units, of which there are none to spare.)
+    int tid = threadIdx.x;
+    if constexpr (MODE == PLAN) asm volatile("" : "+v"(tid));
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int n = lane & 31, g = lane >> 5;
+    if constexpr (MODE == PLAN) {
+      const int units = p.n_row_blocks * p.n_z;
+      kvh = share.unit / units;
+      const int u = share.unit - kvh * units;
+      z_shard = p.n_z > 1 ? u / p.n_row_blocks : 0;
+      row_block = u - z_shard * p.n_row_blocks;
     }
-  }
-  if (lane == 0) {
-    wg_scratch[wave] = w_qmax;
-    if (BAND) wg_scratch[NWAVE + 1 + wave] = w_lomin;
-  }
-  lds_barrier();
-  int wg_qmax = INT32_MIN, wg_lomin = INT32_MAX;
-#pragma unroll
-  for (int w = 0; w < NWAVE; ++w) {
-    wg_qmax = max(wg_qmax, wg_scratch[w]);
-    if (BAND) wg_lomin = min(wg_lomin, wg_scratch[NWAVE + 1 + w]);
-  }
-  // wave-uniform by construction; say so, so that control flow stays on the scalar unit
-  wg_qmax = __builtin_amdgcn_readfirstlane(wg_qmax);
-  w_qmin = __builtin_amdgcn_readfirstlane(w_qmin);
-  if (BAND) {
-    wg_lomin = __builtin_amdgcn_readfirstlane(wg_lomin);
-    w_lomax = __builtin_amdgcn_readfirstlane(w_lomax);
-  }
+    // ---- blocks of this workgroup (the ring walk moves on from shard to shard) ----
+    int cur_shard = MODE == RING ? rank : z_shard;
+    const bool one_shard = MODE == RING || p.per_shard;
+    int b_begin = one_shard ? p.t.blk_begin[cur_shard] : 0;
+    int b_end = one_shard ? p.t.blk_begin[cur_shard + 1] : p.n_blocks;
+    auto block_bounds = [&](int b) -> int2 {
+      return MODE == PLAN ? lds_bounds[b] : p.bounds[b >> p.bounds_shift];
+    };
 
-  bool have_ref = false;  // every row of the wavefront has a finite reference maximum
-  PipeRegs<D> R;
-  // Reference max of scaled scores (log2 domain). A row that can see nothing gets a finite
-  // reference no score reaches: its exponentials are all zero whichever softmax form its
-  // wavefront takes (so one padded row does not keep the other 31 on the masked form), its
-  // denominator stays zero, and the epilogue writes O = 0, LSE = -inf for it.
-  R.m_run = sees ? -INFINITY : kDeadRowRef;
-  R.l_run = 0.f;        // running denominator over this lane's half of the keys
-#pragma unroll
-  for (int db = 0; db < G::NDB; ++db)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) R.o[db][i] = 0.f;
-
-  // ---- tile loader: this wavefront brings rows wave*16 .. wave*16+15 of K and of V, 1 KiB
-  // (LOAD_ROWS rows) per instruction; lane l covers row l / CHUNKS of them, chunk position
-  // l % CHUNKS. Part I of a tile is one such instruction for K and one for V. Rows past the end
-  // of the shard are clamped to its last row (they are masked by their position).
-  const uint32_t stride_b = (uint32_t)p.n_kv_heads * ROW;  // bytes between tokens
-  const int l_row = lane / G::CHUNKS, l_pos = lane % G::CHUNKS;
-  struct Tile {          // (wave-uniform)
-    const char* k;
-    const char* v;
-    const int32_t* pos;
-    int n_valid;
-    bool mask;  // one of its keys can be hidden from one of this wavefront's rows (this
-                // includes the tiles that only other wavefronts of the workgroup can see)
-  };
-  auto issue_part = [&](auto ic, const Tile& t, int b) __attribute__((always_inline)) {
-    constexpr int I = decltype(ic)::value;
-    if constexpr (I < G::PARTS) {
-      const int row = wave * 16 + I * G::LOAD_ROWS + l_row;
-      const uint32_t roff = __umul24((uint32_t)min(row, t.n_valid - 1), stride_b);
-      const int pr = I * G::LOAD_ROWS + l_row;  // row % 16 selects the permutation
-      load_lds16(t.k + (roff + ((l_pos ^ G::k_perm(pr)) * 16)),
-                 kbuf0 + b * G::KD + (wave * 16 + I * G::LOAD_ROWS) * ROW);
-      load_lds16(t.v + (roff + ((l_pos ^ G::v_perm(pr)) * 16)),
-                 vbuf0 + b * G::KD + (wave * 16 + I * G::LOAD_ROWS) * ROW);
-    }
-  };
-  // kv_pos of the tile goes through a register (the tail needs the pad value)
-  auto load_pos = [&](const Tile& t) -> int32_t {
-    return tid < t.n_valid ? t.pos[tid] : CP_POS_PAD_KV;   // (used by tid < TILE)
-  };
-
-  // ---- fragment addressing (LDS byte addresses, buffer 0) ----
-  // K: lane (n, g) reads chunk 2*ks + g of key row n of a block
-  uint32_t kaddr[G::NKS];
-#pragma unroll
-  for (int ks = 0; ks < G::NKS; ++ks)
-    kaddr[ks] = smem_lds + n * ROW + ((2 * ks + g) ^ G::k_perm(n)) * 16;
-  // V: in its 16-lane group this lane addresses key vj of four and 8 bytes (4 channels) vq
-  const int grp = lane >> 4, vj = (lane & 15) >> 2, vq = lane & 3;
-  uint32_t vaddr[G::NDB];
-#pragma unroll
-  for (int db = 0; db < G::NDB; ++db)
-    vaddr[db] = smem_lds + G::OFF_V + ((grp >> 1) * 4 + vj) * ROW +
-                (((db * 4 + (grp & 1) * 2 + (vq >> 1)) ^ G::v_perm(vj)) * 16) + (vq & 1) * 8;
-  uint32_t paddr = smem_lds + G::OFF_POS + g * 16;
-
-  auto visible = [&](const int2& b) -> bool {
-    return b.x <= wg_qmax && (!BAND || b.y >= wg_lomin);
-  };
-  // Where the KV axis is split, every part takes an equal share of the tiles that this
-  // workgroup can see: entries [part_lo, part_hi) of the list of visible tiles. A range of more
-  // than one list has to be counted first.
-  int part_lo = 0, part_hi = INT32_MAX;
-  if (!RING && p.n_sub > 1 && t_end - t_begin > MAX_LIVE) {
-    int cnt = 0;
-    for (int t = t_begin + tid; t < t_end; t += NTHREADS) cnt += visible(p.bounds[t]) ? 1 : 0;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o, 64);
-    lds_barrier();
-    if (lane == 0) wg_scratch[wave] = cnt;
-    lds_barrier();
-    int total = 0;
-#pragma unroll
-    for (int w = 0; w < NWAVE; ++w) total += wg_scratch[w];
-    total = __builtin_amdgcn_readfirstlane(total);
-    part_lo = (int)((int64_t)total * z_sub / p.n_sub);
-    part_hi = (int)((int64_t)total * (z_sub + 1) / p.n_sub);
-  }
-
-  int flag_peek = 0;
-  const int n_steps = RING ? p.t.n_shards : 1;
-  for (int step = 0; step < n_steps; ++step) {
-    if constexpr (RING) {
-      if (step > 0) {
-        cur_shard = cur_shard > 0 ? cur_shard - 1 : p.t.n_shards - 1;
-        t_begin = p.t.tile_begin[cur_shard];
-        t_end = p.t.tile_begin[cur_shard + 1];
-      }
-      if (!ring_enter(p, step, tid, wg_scratch, flag_peek))
-        continue;  // the shard never arrived: reported through ring_error, walk goes on
-    }
-    int seen = 0;  // visible tiles before this chunk of the range
-    for (int c0 = t_begin; c0 < t_end; c0 += MAX_LIVE) {
-      // Compact the tiles some query of the workgroup can see (smallest key position not
-      // beyond the largest query position) into an ascending list in LDS.
-      lds_barrier();  // previous chunk (list, tile buffers) fully consumed
-      int n_live;
-      {
-        const int t = c0 + wave * 64 + lane;
-        int2 b = make_int2(0, 0);
-        bool lv = false;
-        if (t < t_end) {
-          b = (c0 == t_begin && step == 0) ? first_bounds : p.bounds[t];
-          lv = visible(b);
+    // ---- this lane's query row ----
+    // (rows fit 31 bits: checked by the launcher)
+    const int64_t r = (int64_t)row_block * BM + wave * 32 + n;
+    const bool row_ok = r < (MODE == RING ? p.t.tok_begin[rank + 1] - p.t.tok_begin[rank]
+                                          : p.t.tok_begin[p.t.n_ranks]) * (int64_t)p.group;
+    // The start-up chain is q_pos -> visible blocks -> first tile; the bounds of the first 512
+    // blocks are requested now so that they arrive together with q_pos, and the Q fragments
+    // (needed last) are requested after both and waited for only before the first product.
+    int2 first_bounds = make_int2(0, 0);
+    if (b_begin + tid < b_end) first_bounds = block_bounds(b_begin + tid);
+    int32_t qp = CP_POS_PAD_Q, ql = INT32_MIN;
+    bf16x8_t qf[G::NKS];
+    {
+      int token = row_ok ? (int)((uint32_t)r / (uint32_t)p.group) : 0;
+      const int hg = row_ok ? (int)(r - (int64_t)token * p.group) : 0;
+      const bf16_t* q = (const bf16_t*)p.t.q[MODE == RING ? rank : 0];
+      const int32_t* q_pos = p.t.q_pos[MODE == RING ? rank : 0];
+      if (BAND && row_ok) ql = p.q_lo[token];
+      if (MODE != RING && p.t.n_ranks > 1) {
+        // (scalar loads where the row block lies within one rank, which it mostly does)
+        const int t0 = (int)((uint32_t)(row_block * BM) / (uint32_t)p.group);
+        const int a0 = rank_of_token(p.t, t0);
+        q = (const bf16_t*)p.t.q[a0];
+        q_pos = p.t.q_pos[a0];
+        int first = p.t.tok_begin[a0];
+        if ((int64_t)row_block * BM + BM > (int64_t)p.t.tok_begin[a0 + 1] * p.group) {
+          const int a = rank_of_token(p.t, token);
+          q = (const bf16_t*)p.t.q[a];
+          q_pos = p.t.q_pos[a];
+          first = p.t.tok_begin[a];
         }
-        const uint64_t mask = __builtin_amdgcn_ballot_w64(lv);
-        if (lane == 0) wg_scratch[wave] = __builtin_popcountll(mask);
+        token -= row_ok ? first : token;
+      }
+      if (row_ok) qp = q_pos[token];
+      const int64_t row = ((int64_t)token * p.n_kv_heads + kvh) * p.group + hg;
+#pragma unroll
+      for (int ks = 0; ks < G::NKS; ++ks) {
+        uint4 x = make_uint4(0, 0, 0, 0);
+        if (row_ok) x = *(const uint4*)(q + row * D + ks * 16 + g * 8);
+        qf[ks] = __builtin_bit_cast(bf16x8_t, x);
+      }
+    }
+    const float scale_log2 = p.scale_log2;
+
+    // ---- query position range of the wavefront and of the workgroup ----
+    // rows that can see anything: a padded query (CP_POS_PAD_Q) and the rows past the end of
+    // the shard cannot, and stay out of the ranges below
+    const bool sees = row_ok && qp >= 0;
+    const int w_qmin = wave_min(sees ? qp : INT32_MAX), w_qmax = wave_max(qp);
+    const int w_lomin = BAND ? wave_min(sees ? ql : INT32_MAX) : 0;
+    const int w_lomax = BAND ? wave_max(sees ? ql : INT32_MIN) : 0;
+    if (lane == 0) {
+      wg_scratch[wave] = w_qmax;
+      if (BAND) wg_scratch[NWAVE + 1 + wave] = w_lomin;
+    }
+    lds_barrier();
+    int wg_qmax = INT32_MIN, wg_lomin = INT32_MAX;
+#pragma unroll
+    for (int w = 0; w < NWAVE; ++w) {
+      wg_qmax = max(wg_qmax, wg_scratch[w]);
+      if (BAND) wg_lomin = min(wg_lomin, wg_scratch[NWAVE + 1 + w]);
+    }
+    // wave-uniform by construction; say so, so that control flow stays on the scalar unit
+    wg_qmax = __builtin_amdgcn_readfirstlane(wg_qmax);
+    if (BAND) wg_lomin = __builtin_amdgcn_readfirstlane(wg_lomin);
+
+    bool have_ref = false;  // every row of the wavefront has a finite reference maximum
+    PipeRegs<D> R;
+    // Reference max of scaled scores (log2 domain). A row that can see nothing gets a finite
+    // reference no score reaches: its exponentials are all zero whichever softmax form its
+    // wavefront takes (so one padded row does not keep the other 31 on the masked form), its
+    // denominator stays zero, and the epilogue writes O = 0, LSE = -inf for it.
+    R.m_run = sees ? -INFINITY : kDeadRowRef;
+    R.l_run = 0.f;        // running denominator over this lane's half of the keys
+#pragma unroll
+    for (int db = 0; db < G::NDB; ++db)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) R.o[db][i] = 0.f;
+
+    // ---- tile loader: this wavefront brings rows (wave & 1) * 16 .. + 15 of the tile's block
+    // wave / 2, of K and of V, 1 KiB (LOAD_ROWS rows) per instruction; lane l covers row
+    // l / CHUNKS of them, chunk position l % CHUNKS. Part I of a tile is one such instruction
+    // for K and one for V. Rows past the end of the shard are clamped to its last row (they are
+    // masked by their position).
+    const uint32_t stride_b = (uint32_t)p.n_kv_heads * ROW;  // bytes between tokens
+    const int l_row = lane / G::CHUNKS, l_pos = lane % G::CHUNKS;
+    struct Tile {          // (wave-uniform)
+      const char* k;       // this wavefront's block
+      const char* v;
+      int last;            // its last valid row
+      int mask;            // bit b: block b has a key that is hidden from one of this
+                           // wavefront's rows; bit 4 + b: from all of them
+    };
+    auto issue_part = [&](auto ic, const Tile& t, int b) __attribute__((always_inline)) {
+      constexpr int I = decltype(ic)::value;
+      if constexpr (I < G::PARTS) {
+        const int pr = I * G::LOAD_ROWS + l_row;  // row % 16 selects the permutation
+        const int row = (wave & 1) * 16 + pr;
+        const uint32_t roff = __umul24((uint32_t)min(row, t.last), stride_b);
+        load_lds16(t.k + (roff + ((l_pos ^ G::k_perm(pr)) * 16)),
+                   kbuf0 + b * G::KD + (wave * 16 + I * G::LOAD_ROWS) * ROW);
+        load_lds16(t.v + (roff + ((l_pos ^ G::v_perm(pr)) * 16)),
+                   vbuf0 + b * G::KD + (wave * 16 + I * G::LOAD_ROWS) * ROW);
+      }
+    };
+
+    // ---- fragment addressing (LDS byte addresses, buffer 0) ----
+    // K: lane (n, g) reads chunk 2*ks + g of key row n of a block
+    uint32_t kaddr[G::NKS];
+#pragma unroll
+    for (int ks = 0; ks < G::NKS; ++ks)
+      kaddr[ks] = smem_lds + n * ROW + ((2 * ks + g) ^ G::k_perm(n)) * 16;
+    // V: in its 16-lane group this lane addresses key vj of four and 8 bytes (4 channels) vq
+    const int grp = lane >> 4, vj = (lane & 15) >> 2, vq = lane & 3;
+    uint32_t vaddr[G::NDB];
+#pragma unroll
+    for (int db = 0; db < G::NDB; ++db)
+      vaddr[db] = smem_lds + G::OFF_V + ((grp >> 1) * 4 + vj) * ROW +
+                  (((db * 4 + (grp & 1) * 2 + (vq >> 1)) ^ G::v_perm(vj)) * 16) + (vq & 1) * 8;
+    uint32_t paddr = smem_lds + G::OFF_POS + g * 16;
+
+    auto visible = [&](const int2& b) -> bool {
+      return b.x <= wg_qmax && (!BAND || b.y >= wg_lomin);
+    };
+    // The part of the list of visible blocks that is walked here: [part_lo, part_hi). Parts are
+    // whole tiles of the list.
+    int part_lo = 0, part_hi = INT32_MAX;
+    bool whole = true, first_piece = true;  // PLAN: the unit is not cut; its first piece
+    if constexpr (MODE == SPLIT || MODE == PLAN) {
+      int total = 0;
+      if (MODE == SPLIT || p.cut_units) {
+        int cnt = 0;
+        for (int b = b_begin + tid; b < b_end; b += NTHREADS) cnt += visible(block_bounds(b)) ? 1 : 0;
+        cnt = wave_sum(cnt);
         lds_barrier();
-        int base = 0, total = 0;
+        if (lane == 0) wg_scratch[wave] = cnt;
+        lds_barrier();
 #pragma unroll
-        for (int w = 0; w < NWAVE; ++w) {
-          const int c = wg_scratch[w];
-          if (w < wave) base += c;
-          total += c;
-        }
+        for (int w = 0; w < NWAVE; ++w) total += wg_scratch[w];
         total = __builtin_amdgcn_readfirstlane(total);
-        if (!RING && p.n_sub > 1 && t_end - t_begin <= MAX_LIVE) {
-          part_lo = (int)((uint32_t)(total * z_sub) / (uint32_t)p.n_sub);
-          part_hi = (int)((uint32_t)(total * (z_sub + 1)) / (uint32_t)p.n_sub);
+      }
+      if constexpr (MODE == SPLIT) {
+        const int tiles = (total + 3) >> 2;
+        part_lo = 4 * (int)((int64_t)tiles * z_sub / p.n_sub);
+        part_hi = 4 * (int)((int64_t)tiles * (z_sub + 1) / p.n_sub);
+      } else if (p.cut_units) {
+        const int units = p.n_row_blocks * p.n_z;
+        const int planned = __builtin_amdgcn_readfirstlane((int)weight[share.unit % units]);
+        const int end = min(kUnitCost + planned, share.begin + share.length);
+        const int lo = max(0, share.begin - kUnitCost), hi = end - kUnitCost;
+        share.length -= end - share.begin;
+        if (hi <= lo) return;  // the share ends within the unit's start-up
+        whole = lo == 0 && hi == planned;
+        first_piece = lo == 0;
+        const int tiles = (total + 3) >> 2;   // (pieces can come out empty: they are written as such)
+        part_lo = 4 * (int)((uint32_t)(tiles * lo) / (uint32_t)planned);
+        part_hi = 4 * (int)((uint32_t)(tiles * hi) / (uint32_t)planned);
+      }
+    }
+
+    int flag_peek = 0;
+    const int n_steps = MODE == RING ? p.t.n_shards : 1;
+    for (int step = 0; step < n_steps; ++step) {
+      if constexpr (MODE == RING) {
+        if (step > 0) {
+          cur_shard = cur_shard > 0 ? cur_shard - 1 : p.t.n_shards - 1;
+          b_begin = p.t.blk_begin[cur_shard];
+          b_end = p.t.blk_begin[cur_shard + 1];
         }
-        const int lo = max(part_lo, seen), hi = min(part_hi, seen + total);
-        const int idx = seen + base + __builtin_popcountll(mask & ((1ull << lane) - 1ull));
-        if (lv && idx >= lo && idx < hi) {
-          int sh = cur_shard;
-          if (!RING && !p.per_shard) {
-#pragma unroll 8
-            for (int i = 1; i < p.t.n_shards; ++i) sh += t >= p.t.tile_begin[i];
+        if (!ring_enter(p, rank, step, tid, wg_scratch, flag_peek))
+          continue;  // the shard never arrived: reported through ring_error, walk goes on
+      }
+      int seen = 0;  // visible blocks before this chunk of the range
+      for (int c0 = b_begin; c0 < b_end; c0 += MAX_LIVE) {
+        // Compact the blocks some query of the workgroup can see (smallest key position not
+        // beyond the largest query position) into an ascending list in LDS.
+        lds_barrier();  // previous chunk (list, tile buffers) fully consumed
+        int n_live;     // tiles
+        {
+          const int b = c0 + tid;
+          int2 bb = make_int2(0, 0);
+          bool lv = false;
+          if (b < b_end) {
+            bb = (c0 == b_begin && step == 0) ? first_bounds : block_bounds(b);
+            lv = visible(bb);
           }
-          const int key0 = (t - p.t.tile_begin[sh]) * TILE;
-          const int valid = min(TILE, p.t.n_kv[sh] - key0);
-          const uint64_t off = (uint64_t)key0 * stride_b + (uint32_t)kvh * ROW;
-          const uint64_t ka = (uint64_t)p.t.k[sh] + off, va = (uint64_t)p.t.v[sh] + off;
-          const uint64_t pa = (uint64_t)(p.t.kv_pos[sh] + key0);
-          // (a ragged tile always pays for the mask: its largest position is the pad's)
-          live[2 * (idx - lo)] = make_int4((int)ka, (int)(ka >> 32), (int)va, (int)(va >> 32));
-          live[2 * (idx - lo) + 1] =
-              make_int4((int)pa, (int)(pa >> 32), valid, valid < TILE ? INT32_MAX : b.y);
-          if (BAND) live_lo_pos[idx - lo] = b.x;
+          const uint64_t mask = __builtin_amdgcn_ballot_w64(lv);
+          if (lane == 0) wg_scratch[wave] = __builtin_popcountll(mask);
+          lds_barrier();
+          int base = 0, total = 0;
+#pragma unroll
+          for (int w = 0; w < NWAVE; ++w) {
+            const int c = wg_scratch[w];
+            if (w < wave) base += c;
+            total += c;
+          }
+          total = __builtin_amdgcn_readfirstlane(total);
+          const int lo = max(part_lo, seen), hi = min(part_hi, seen + total);
+          const int idx = seen + base + __builtin_popcountll(mask & ((1ull << lane) - 1ull));
+          if (lv && idx >= lo && idx < hi) {
+            int sh = cur_shard;
+            if (!one_shard) {
+#pragma unroll 8
+              for (int i = 1; i < p.t.n_shards; ++i) sh += b >= p.t.blk_begin[i];
+            }
+            LdsShard e;
+            if constexpr (MODE == PLAN) e = shards[sh];
+            else e = {p.t.k[sh], p.t.v[sh], p.t.kv_pos[sh], p.t.n_kv[sh], p.t.blk_begin[sh]};
+            const int key0 = (b - e.blk_begin) * BLOCK;
+            const int valid = min(BLOCK, e.n_kv - key0);
+            const uint64_t off = (uint64_t)key0 * stride_b + (uint32_t)kvh * ROW;
+            const uint64_t ka = (uint64_t)e.k + off, va = (uint64_t)e.v + off;
+            const uint64_t pa = (uint64_t)(e.kv_pos + key0);
+            // (the last valid row travels in the upper 16 bits of V's address, which are zero)
+            const int4 kv = make_int4((int)ka, (int)(ka >> 32), (int)va,
+                                      (int)(va >> 32) | (valid - 1) << 16);
+            live[idx - lo] = kv;
+            live_pos[idx - lo] = make_int4((int)pa, (int)(pa >> 32), valid, 0);
+            // (a ragged block always pays for the mask: its largest position is the pad's)
+            live_range[idx - lo] = make_int2(bb.x, valid < BLOCK ? INT32_MAX : bb.y);
+            if (idx == hi - 1) {  // fill the last tile with blocks of no keys
+              for (int i = idx - lo + 1; (i & 3) != 0; ++i) {
+                live[i] = kv;
+                live_pos[i] = make_int4((int)pa, (int)(pa >> 32), 0, 0);
+                live_range[i] = make_int2(INT32_MAX, INT32_MAX);
+              }
+            }
+          }
+          seen += total;
+          n_live = (max(0, hi - lo) + 3) >> 2;
         }
-        seen += total;
-        n_live = max(0, hi - lo);
-      }
-      lds_barrier();
-      if (n_live == 0) continue;
+        lds_barrier();
+        if (n_live == 0) continue;
 
-      // ---- prologue: tile 0 into buffer 0, Q stage of block 0 ----
-      int32_t next_pos = 0;
-      auto read_entry = [&](int idx, Tile& t) {
-        const int i = idx < n_live ? idx : n_live - 1;
-        const int4 a = live[2 * i], b = live[2 * i + 1];
-        auto uni = [](int x) { return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(x); };
-        t.k = (const char*)(uni(a.x) | uni(a.y) << 32);
-        t.v = (const char*)(uni(a.z) | uni(a.w) << 32);
-        t.pos = (const int32_t*)(uni(b.x) | uni(b.y) << 32);
-        t.n_valid = __builtin_amdgcn_readfirstlane(b.z);
-        t.mask = __builtin_amdgcn_readfirstlane(b.w) > w_qmin;
-        if (BAND) t.mask |= __builtin_amdgcn_readfirstlane(live_lo_pos[i]) < w_lomax;
-      };
-      Tile next;
-      bool need_mask;
-      {
-        Tile t0;
-        read_entry(0, t0);
-        read_entry(1, next);
-        need_mask = t0.mask;
-        issue_part(IntC<0>{}, t0, 0);
-        issue_part(IntC<1>{}, t0, 0);
-        issue_part(IntC<2>{}, t0, 0);
-        issue_part(IntC<3>{}, t0, 0);
-        const int32_t pos = load_pos(t0);
-        if (tid < TILE) posbuf0[tid] = pos;
-        __syncthreads();  // waits for the tile (vmcnt) and publishes it
-#pragma unroll
-        for (int ks = 0; ks < G::NKS; ++ks) R.kf[ks] = lds_read_b128<0>(kaddr[ks]);
-#pragma unroll
-        for (int ks = 0; ks < G::NKS; ks += 4)
-          lgkm_wait<0>(R.kf[ks], R.kf[ks + 1], R.kf[ks + 2], R.kf[ks + 3]);
-#pragma unroll
-        for (int i = 0; i < 16; ++i) R.s[0][i] = 0.f;
-#pragma unroll
-        for (int ks = 0; ks < G::NKS; ++ks)
-          R.s[0] = mfma32(__builtin_bit_cast(bf16x8_t, R.kf[ks]), qf[ks], R.s[0]);
-        __builtin_amdgcn_sched_barrier(0);
-        // stand-in V fragments for the empty P stage of the first step (finite data, P = 0)
-#pragma unroll
-        for (int m = 0; m < G::NVF; ++m) R.vf[m] = lds_read_vt_frag<0, ROW>(vaddr[m % G::NDB]);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) R.pb[1][0][i] = R.pb[1][1][i] = 0u;
-        __builtin_amdgcn_sched_barrier(0);
-      }
-
-      // The next tile is requested during the first two steps, one part (a K and a V
-      // instruction per wavefront) at a time: a burst fills the memory pipeline's queue and
-      // stalls every wavefront behind it.
-      auto no_hook = [](auto) {};
-      constexpr int PPS = G::PARTS / 2;  // parts per step
-      for (int it = 0; it < n_live; ++it) {
-        const bool has_next = it + 1 < n_live;
-        const int nb = (it + 1) & 1;
-        pipe_body<D, 0, BAND>(R, qf, kaddr, vaddr, paddr, qp, ql, scale_log2, need_mask, have_ref,
-                              [&](auto mc) __attribute__((always_inline)) {
-                                constexpr int M = decltype(mc)::value;
-                                if (M == 1 && __builtin_expect(has_next, 1)) issue_part(IntC<0>{}, next, nb);
-                                if (M == 9 && __builtin_expect(has_next, 1)) issue_part(IntC<1>{}, next, nb);
-                              });
-        pipe_body<D, 1, BAND>(R, qf, kaddr, vaddr, paddr, qp, ql, scale_log2, need_mask, have_ref,
-                              [&](auto mc) __attribute__((always_inline)) {
-                                constexpr int M = decltype(mc)::value;
-                                if (M == 1 && __builtin_expect(has_next, 1)) issue_part(IntC<PPS>{}, next, nb);
-                                if (M == 2 * G::NKS - 7 && __builtin_expect(has_next, 1)) {
-                                  if constexpr (PPS > 1) issue_part(IntC<3>{}, next, nb);
-                                  next_pos = load_pos(next);
-                                }
-                              });
-        pipe_body<D, 2, BAND>(R, qf, kaddr, vaddr, paddr, qp, ql, scale_log2, need_mask, have_ref, no_hook);
-        // barrier Y: the next tile has landed in every wavefront
-        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-        if (has_next && tid < TILE) posbuf0[nb * TILE + tid] = next_pos;
-        const bool cur_mask = need_mask;
-        need_mask = next.mask;
-        read_entry(it + 2, next);  // no direct-to-LDS load is in flight here
-        __syncthreads();
-#pragma unroll
-        for (int ks = 0; ks < G::NKS; ++ks) kaddr[ks] ^= G::KD;  // K of the next tile from here on
-        pipe_body<D, 3, BAND>(R, qf, kaddr, vaddr, paddr, qp, ql, scale_log2, cur_mask, have_ref, no_hook);
-        // barrier X: every LDS read of this tile has completed; its buffers may be refilled
-        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
-        __syncthreads();
-#pragma unroll
-        for (int db = 0; db < G::NDB; ++db) vaddr[db] ^= G::KD;
-        paddr ^= POS_BYTES;
-      }
-
-      // ---- drain: P stage of the last block ----
-      {
-        auto last = [&](auto mc) __attribute__((always_inline)) {
-          constexpr int M = decltype(mc)::value;
-          if constexpr (M < G::NVF) {
-            lgkm_wait<2 * (G::NVF - 1 - M)>(R.vf[M]);
-            R.o[M % G::NDB] = mfma32(__builtin_bit_cast(bf16x8_t, R.vf[M]),
-                                     __builtin_bit_cast(bf16x8_t, R.pb[1][M / G::NDB]),
-                                     R.o[M % G::NDB]);
+        // ---- prologue: tile 0 into buffer 0, Q stage of block 0 ----
+        // (kv_pos of a tile goes through a register: the tail needs the pad value)
+        int32_t next_pos = 0;
+        auto read_entry = [&](int idx, Tile& t) {
+          const int i = (idx < n_live ? idx : n_live - 1) * 4;
+          const int4 kv = live[i + (wave >> 1)];
+          const int2 range = live_range[i + (lane & 3)];
+          auto uni = [](int x) { return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(x); };
+          t.k = (const char*)(uni(kv.x) | uni(kv.y) << 32);
+          const int v_hi = __builtin_amdgcn_readfirstlane(kv.w);
+          t.v = (const char*)(uni(kv.z) | (uint64_t)(uint32_t)(v_hi & 0xffff) << 32);
+          t.last = (int)((uint32_t)v_hi >> 16);
+          bool m = range.y > w_qmin, none = range.x > w_qmax;
+          if (BAND) {
+            m |= range.x < w_lomax;
+            none |= range.y < w_lomin;
+          }
+          const int mm = (int)(__builtin_amdgcn_ballot_w64(m) & 15);
+          t.mask = mm | ((int)__builtin_amdgcn_ballot_w64(none) & mm) << 4;
+          if (wave < TILE / 64) {   // kv_pos of the key tid
+            const int4 own = live_pos[i + (tid >> 5)];
+            next_pos = CP_POS_PAD_KV;
+            if ((tid & 31) < own.z) {
+              const int32_t* const pos = (const int32_t*)((uint64_t)(uint32_t)own.x |
+                                                          (uint64_t)(uint32_t)own.y << 32);
+              next_pos = pos[tid & 31];
+            }
           }
         };
-        last(IntC<0>{}); last(IntC<1>{}); last(IntC<2>{}); last(IntC<3>{});
-        last(IntC<4>{}); last(IntC<5>{}); last(IntC<6>{}); last(IntC<7>{});
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      // back to buffer-0 addressing for the next chunk
-      if (n_live & 1) {
+        Tile next;
+        int mask;
+        {
+          Tile t0;
+          read_entry(0, t0);
+          mask = t0.mask;
+          issue_part(IntC<0>{}, t0, 0);
+          issue_part(IntC<1>{}, t0, 0);
+          issue_part(IntC<2>{}, t0, 0);
+          issue_part(IntC<3>{}, t0, 0);
+          if (tid < TILE) posbuf0[tid] = next_pos;
+          __syncthreads();  // waits for the tile (vmcnt) and publishes it
+          read_entry(1, next);
 #pragma unroll
-        for (int ks = 0; ks < G::NKS; ++ks) kaddr[ks] ^= G::KD;
+          for (int ks = 0; ks < G::NKS; ++ks) R.kf[ks] = lds_read_b128<0>(kaddr[ks]);
 #pragma unroll
-        for (int db = 0; db < G::NDB; ++db) vaddr[db] ^= G::KD;
-        paddr ^= POS_BYTES;
-      }
-    }
-  }
-
-  // ---- epilogue ----
-  static_assert(!(ACC && SPLIT), "the running result is merged by unsplit launches only");
-  const float l_tot = R.l_run + xor32(R.l_run);
-  float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-  const float lse_val =
-      l_tot > 0.f ? (R.m_run + __builtin_amdgcn_logf(l_tot)) * kLn2 : -INFINITY;
-  // Where this lane's row goes: its O (as an address) and its LSE.
-  int64_t row_lin;        // row of [tokens, N_H] in the buffer written to
-  char* o_row;
-  float* lse_row = nullptr;
-  {
-    const int token = row_ok ? (int)((uint32_t)r / (uint32_t)p.group) : 0;
-    const int hg = row_ok ? (int)(r - (int64_t)token * p.group) : 0;
-    int first = 0;
-    char* o = (char*)p.t.out[0];
-    float* l = p.t.lse[0];
-    if (!SPLIT && p.t.n_ranks > 1) {
-      const int a = rank_of_token(p.t, token);
-      first = p.t.tok_begin[a];
-      o = (char*)p.t.out[a];
-      l = p.t.lse[a];
-    }
-    row_lin = ((int64_t)(token - first) * p.n_kv_heads + kvh) * p.group + hg;
-    if (SPLIT) {
-      row_lin += (int64_t)blockIdx.z * p.rows_all_heads;
-      o = (char*)p.part_out;
-      l = p.part_lse;
-    } else {
-      o += (int64_t)z_shard * p.out_shard_stride;
-      if (l != nullptr) l += (int64_t)z_shard * p.lse_shard_stride;
-    }
-    o_row = o + row_lin * (D * (int64_t)(SPLIT ? 4 : sizeof(TO)));
-    if (l != nullptr) lse_row = l + row_lin;
-  }
-  // ACC: weights of Equation 4 for the pair (running result, this step). a_old scales the
-  // stored row, the step's row is scaled on its way into the staging buffer. A row the step
-  // saw nothing of keeps its stored value (a_old = 1, nothing staged): it is not touched at
-  // all unless this is the step that writes the final output.
-  float a_old = 0.f;
-  if (ACC) {
-    const float lse_old = row_ok ? *lse_row : -INFINITY;
-    const float m = fmaxf(lse_old, lse_val);
-    const float w_old = m == -INFINITY ? 0.f : __expf(lse_old - m);
-    const float w_cur = m == -INFINITY ? 0.f : __expf(lse_val - m);
-    const float den = w_old + w_cur;
-    const float rden = den > 0.f ? 1.f / den : 0.f;
-    a_old = l_tot > 0.f ? w_old * rden : 1.f;
-    inv *= w_cur * rden;
-    const float lse_new = den > 0.f ? m + __logf(den) : -INFINITY;
-    if (row_ok && g == 0) {
-      if (l_tot > 0.f) *lse_row = lse_new;
-      if (p.final_lse != nullptr) p.final_lse[row_lin] = lse_new;
-    }
-  } else {
-    if (row_ok && g == 0 && lse_row != nullptr) *lse_row = lse_val;
-  }
-
-  // Transpose through LDS (the tile buffers are dead once every wavefront has left the walk;
-  // each wavefront then uses a private region). Accumulator (db, i) of lane (n, g) is channel
-  // db*32 + (i/4)*8 + g*4 + i%4 of query n.
-  __syncthreads();
-  char* const stage = smem + wave * 32 * G::OUT_STRIDE;
+          for (int ks = 0; ks < G::NKS; ks += 4)
+            lgkm_wait<0>(R.kf[ks], R.kf[ks + 1], R.kf[ks + 2], R.kf[ks + 3]);
 #pragma unroll
-  for (int db = 0; db < G::NDB; ++db)
+          for (int i = 0; i < 16; ++i) R.s[0][i] = 0.f;
 #pragma unroll
-    for (int i4 = 0; i4 < 4; ++i4) {
-      const int d0 = db * 32 + i4 * 8 + g * 4;
-      floatx4_t w = {R.o[db][i4 * 4 + 0] * inv, R.o[db][i4 * 4 + 1] * inv,
-                     R.o[db][i4 * 4 + 2] * inv, R.o[db][i4 * 4 + 3] * inv};
-      *(floatx4_t*)(stage + n * G::OUT_STRIDE + d0 * 4) = w;
-    }
-  wave_lds_fence();
-  const int64_t r0 = (int64_t)row_block * BM + wave * 32;
-  auto row_address = [&](int rr) -> char* {
-    const uint64_t x = (uint64_t)o_row;
-    const uint32_t lo = (uint32_t)__shfl((int)(uint32_t)x, rr, 64);
-    const uint32_t hi = (uint32_t)__shfl((int)(uint32_t)(x >> 32), rr, 64);
-    return (char*)((uint64_t)hi << 32 | lo);
-  };
-  if constexpr (ACC) {
-    // The stored row (fp32, o_row) times its weight is added to the step's row, 4 channels per
-    // lane; the sum goes back to its place, or to the final output on the last step.
-    const bool to_final = p.final_out != nullptr;  // uniform
-    const bool seen_row = l_tot > 0.f;
-    constexpr int LPR = D / 4, RPP = 64 / LPR;     // lanes per row, rows per pass
+          for (int ks = 0; ks < G::NKS; ++ks)
+            R.s[0] = mfma32(__builtin_bit_cast(bf16x8_t, R.kf[ks]), qf[ks], R.s[0]);
+          __builtin_amdgcn_sched_barrier(0);
+          // stand-in V fragments for the empty P stage of the first step (finite data, P = 0)
 #pragma unroll
-    for (int pass = 0; pass < 32 / RPP; ++pass) {
-      const int rr = pass * RPP + lane / LPR, c = (lane % LPR) * 4;
-      float* const old_row = p.acc + (int64_t)__shfl(row_lin, rr, 64) * D + c;
-      const float ao = __shfl(a_old, rr, 64);
-      const bool touch = (to_final || __shfl((int)seen_row, rr, 64) != 0) && r0 + rr < p.rows;
-      floatx4_t a = *(const floatx4_t*)(stage + rr * G::OUT_STRIDE + c * 4);
-      if (touch) {
-        if (ao != 0.f) {
-          const floatx4_t old = *(const floatx4_t*)old_row;
+          for (int m = 0; m < G::NVF; ++m) R.vf[m] = lds_read_vt_frag<0, ROW>(vaddr[m % G::NDB]);
 #pragma unroll
-          for (int x = 0; x < 4; ++x) a[x] = fmaf(ao, old[x], a[x]);
+          for (int i = 0; i < 4; ++i) R.pb[1][0][i] = R.pb[1][1][i] = 0u;
+          __builtin_amdgcn_sched_barrier(0);
         }
-        if (!to_final) {
-          *(floatx4_t*)old_row = a;
-        } else {
-          TO* const o = (TO*)p.final_out + (int64_t)__shfl(row_lin, rr, 64) * D + c;
-          if constexpr (sizeof(TO) == 4) {
-            *(floatx4_t*)o = a;
-          } else {
-            bf16x4_t w;
+
+        // The next tile is requested during the first two steps, one part (a K and a V
+        // instruction per wavefront) at a time: a burst fills the memory pipeline's queue and
+        // stalls every wavefront behind it.
+        auto no_hook = [](auto) {};
+        constexpr int PPS = G::PARTS / 2;  // parts per step
+        for (int it = 0; it < n_live; ++it) {
+          const bool has_next = it + 1 < n_live;
+          const int nb = (it + 1) & 1;
+          pipe_body<D, 0, BAND>(R, qf, kaddr, vaddr, paddr, qp, ql, scale_log2, mask & 1,
+                                mask & 16, have_ref,
+                                [&](auto mc) __attribute__((always_inline)) {
+                                  constexpr int M = decltype(mc)::value;
+                                  if (M == 1 && __builtin_expect(has_next, 1)) issue_part(IntC<0>{}, next, nb);
+                                  if (M == 9 && __builtin_expect(has_next, 1)) issue_part(IntC<1>{}, next, nb);
+                                });
+          pipe_body<D, 1, BAND>(R, qf, kaddr, vaddr, paddr, qp, ql, scale_log2, mask & 2,
+                                mask & 32, have_ref,
+                                [&](auto mc) __attribute__((always_inline)) {
+                                  constexpr int M = decltype(mc)::value;
+                                  if (M == 1 && __builtin_expect(has_next, 1)) issue_part(IntC<PPS>{}, next, nb);
+                                  if (M == 9 && __builtin_expect(has_next, 1)) issue_part(IntC<3>{}, next, nb);
+                                });
+          pipe_body<D, 2, BAND>(R, qf, kaddr, vaddr, paddr, qp, ql, scale_log2, mask & 4,
+                                mask & 64, have_ref, no_hook);
+          // barrier Y: the next tile has landed in every wavefront
+          __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+          if (has_next && tid < TILE) posbuf0[nb * TILE + tid] = next_pos;
+          const int cur_mask = mask;
+          mask = next.mask;
+          read_entry(it + 2, next);  // no direct-to-LDS load is in flight here
+          __syncthreads();
 #pragma unroll
-            for (int x = 0; x < 4; ++x) w[x] = static_cast<bf16_t>(a[x]);
-            *(bf16x4_t*)o = w;
+          for (int ks = 0; ks < G::NKS; ++ks) kaddr[ks] ^= G::KD;  // K of the next tile from here on
+          pipe_body<D, 3, BAND>(R, qf, kaddr, vaddr, paddr, qp, ql, scale_log2, cur_mask & 8,
+                                cur_mask & 128, have_ref, no_hook);
+          // barrier X: every LDS read of this tile has completed; its buffers may be refilled
+          __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+          __syncthreads();
+#pragma unroll
+          for (int db = 0; db < G::NDB; ++db) vaddr[db] ^= G::KD;
+          paddr ^= POS_BYTES;
+        }
+
+        // ---- drain: P stage of the last block ----
+        {
+          auto last = [&](auto mc) __attribute__((always_inline)) {
+            constexpr int M = decltype(mc)::value;
+            if constexpr (M < G::NVF) {
+              lgkm_wait<2 * (G::NVF - 1 - M)>(R.vf[M]);
+              R.o[M % G::NDB] = mfma32(__builtin_bit_cast(bf16x8_t, R.vf[M]),
+                                       __builtin_bit_cast(bf16x8_t, R.pb[1][M / G::NDB]),
+                                       R.o[M % G::NDB]);
+            }
+          };
+          last(IntC<0>{}); last(IntC<1>{}); last(IntC<2>{}); last(IntC<3>{});
+          last(IntC<4>{}); last(IntC<5>{}); last(IntC<6>{}); last(IntC<7>{});
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        // back to buffer-0 addressing for the next chunk
+        if (n_live & 1) {
+#pragma unroll
+          for (int ks = 0; ks < G::NKS; ++ks) kaddr[ks] ^= G::KD;
+#pragma unroll
+          for (int db = 0; db < G::NDB; ++db) vaddr[db] ^= G::KD;
+          paddr ^= POS_BYTES;
+        }
+      }
+    }
+
+    // ---- epilogue ----
+    const float l_tot = R.l_run + xor32(R.l_run);
+    float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+    const float lse_val =
+        l_tot > 0.f ? (R.m_run + __builtin_amdgcn_logf(l_tot)) * kLn2 : -INFINITY;
+    // Where this lane's row goes: its O (as an address) and its LSE. `partial`: to the
+    // workspace, in fp32.
+    const bool partial = MODE == SPLIT || (MODE == PLAN && !whole);
+    int64_t row_lin;        // row of [tokens, N_H] in the buffer written to
+    char* o_row;
+    float* lse_row = nullptr;
+    if (MODE == PLAN && partial) {
+      const int slot = 2 * blockIdx.x + (first_piece ? 1 : 0);
+      row_lin = (int64_t)slot * BM + wave * 32 + n;
+      o_row = (char*)(p.part_out + row_lin * D);
+      lse_row = p.part_lse + row_lin;
+    } else {
+      int token = row_ok ? (int)((uint32_t)r / (uint32_t)p.group) : 0;
+      const int hg = row_ok ? (int)(r - (int64_t)token * p.group) : 0;
+      char* o = (char*)p.t.out[MODE == RING ? rank : 0];
+      float* l = p.t.lse[MODE == RING ? rank : 0];
+      if (MODE != SPLIT && MODE != RING && p.t.n_ranks > 1) {
+        const int a = rank_of_token(p.t, token);
+        token -= p.t.tok_begin[a];
+        o = (char*)p.t.out[a];
+        l = p.t.lse[a];
+      }
+      row_lin = ((int64_t)token * p.n_kv_heads + kvh) * p.group + hg;
+      if (MODE == SPLIT) {
+        row_lin += (int64_t)blockIdx.z * p.rows_all_heads;
+        o = (char*)p.part_out;
+        l = p.part_lse;
+      } else {
+        o += (int64_t)z_shard * p.out_shard_stride;
+        if (l != nullptr) l += (int64_t)z_shard * p.lse_shard_stride;
+      }
+      o_row = o + row_lin * (D * (int64_t)(MODE == SPLIT ? 4 : sizeof(TO)));
+      if (l != nullptr) lse_row = l + row_lin;
+    }
+    // ACC: weights of Equation 4 for the pair (running result, this step). a_old scales the
+    // stored row, the step's row is scaled on its way into the staging buffer. A row the step
+    // saw nothing of keeps its stored value (a_old = 1, nothing staged): it is not touched at
+    // all unless this is the step that writes the final output.
+    float a_old = 0.f;
+    if constexpr (MODE == ACC) {
+      const float lse_old = row_ok ? *lse_row : -INFINITY;
+      const float m = fmaxf(lse_old, lse_val);
+      const float w_old = m == -INFINITY ? 0.f : __expf(lse_old - m);
+      const float w_cur = m == -INFINITY ? 0.f : __expf(lse_val - m);
+      const float den = w_old + w_cur;
+      const float rden = den > 0.f ? 1.f / den : 0.f;
+      a_old = l_tot > 0.f ? w_old * rden : 1.f;
+      inv *= w_cur * rden;
+      const float lse_new = den > 0.f ? m + __logf(den) : -INFINITY;
+      if (row_ok && g == 0) {
+        if (l_tot > 0.f) *lse_row = lse_new;
+        if (p.final_lse != nullptr) p.final_lse[row_lin] = lse_new;
+      }
+    } else {
+      if (row_ok && g == 0 && lse_row != nullptr) *lse_row = lse_val;
+    }
+
+    // Transpose through LDS (the tile buffers are dead once every wavefront has left the walk;
+    // each wavefront then uses a private region). Accumulator (db, i) of lane (n, g) is channel
+    // db*32 + (i/4)*8 + g*4 + i%4 of query n.
+    __syncthreads();
+    char* const stage = smem + wave * 32 * G::OUT_STRIDE;
+#pragma unroll
+    for (int db = 0; db < G::NDB; ++db)
+#pragma unroll
+      for (int i4 = 0; i4 < 4; ++i4) {
+        const int d0 = db * 32 + i4 * 8 + g * 4;
+        floatx4_t w = {R.o[db][i4 * 4 + 0] * inv, R.o[db][i4 * 4 + 1] * inv,
+                       R.o[db][i4 * 4 + 2] * inv, R.o[db][i4 * 4 + 3] * inv};
+        *(floatx4_t*)(stage + n * G::OUT_STRIDE + d0 * 4) = w;
+      }
+    wave_lds_fence();
+    // (rows in order: row rr of the wavefront exists iff its lane's does)
+    const uint64_t rows_ok = __builtin_amdgcn_ballot_w64(row_ok);
+    auto row_address = [&](int rr) -> char* {
+      const uint64_t x = (uint64_t)o_row;
+      const uint32_t lo = (uint32_t)__shfl((int)(uint32_t)x, rr, 64);
+      const uint32_t hi = (uint32_t)__shfl((int)(uint32_t)(x >> 32), rr, 64);
+      return (char*)((uint64_t)hi << 32 | lo);
+    };
+    if constexpr (MODE == ACC) {
+      // The stored row (fp32) times its weight is added to the step's row, 4 channels per
+      // lane; the sum goes back to its place, or to the final output on the last step.
+      const bool to_final = p.final_out != nullptr;  // uniform
+      const bool seen_row = l_tot > 0.f;
+      constexpr int LPR = D / 4, RPP = 64 / LPR;     // lanes per row, rows per pass
+#pragma unroll
+      for (int pass = 0; pass < 32 / RPP; ++pass) {
+        const int rr = pass * RPP + lane / LPR, c = (lane % LPR) * 4;
+        const int64_t rl = __shfl(row_lin, rr, 64);
+        float* const old_row = p.acc + rl * D + c;
+        const float ao = __shfl(a_old, rr, 64);
+        const bool touch = (to_final || __shfl((int)seen_row, rr, 64) != 0) && (rows_ok >> rr & 1);
+        floatx4_t a = *(const floatx4_t*)(stage + rr * G::OUT_STRIDE + c * 4);
+        if (touch) {
+          if (ao != 0.f) {
+            const floatx4_t old = *(const floatx4_t*)old_row;
+#pragma unroll
+            for (int x = 0; x < 4; ++x) a[x] = fmaf(ao, old[x], a[x]);
+          }
+          if (!to_final) {
+            *(floatx4_t*)old_row = a;
+          } else {
+            TO* const o = (TO*)p.final_out + rl * D + c;
+            if constexpr (sizeof(TO) == 4) {
+              *(floatx4_t*)o = a;
+            } else {
+              bf16x4_t w;
+#pragma unroll
+              for (int x = 0; x < 4; ++x) w[x] = static_cast<bf16_t>(a[x]);
+              *(bf16x4_t*)o = w;
+            }
           }
         }
       }
-    }
-  } else if constexpr (!SPLIT && sizeof(TO) == 2) {
-    constexpr int LPR = D / 8, RPP = 64 / LPR;
+    } else if (MODE != SPLIT && sizeof(TO) == 2 && !partial) {
+      constexpr int LPR = D / 8, RPP = 64 / LPR;
 #pragma unroll
-    for (int pass = 0; pass < 32 / RPP; ++pass) {
-      const int rr = pass * RPP + lane / LPR, c = (lane % LPR) * 8;
-      char* const o = row_address(rr);
-      const floatx4_t a = *(const floatx4_t*)(stage + rr * G::OUT_STRIDE + c * 4);
-      const floatx4_t b = *(const floatx4_t*)(stage + rr * G::OUT_STRIDE + c * 4 + 16);
-      bf16x8_t w;
+      for (int pass = 0; pass < 32 / RPP; ++pass) {
+        const int rr = pass * RPP + lane / LPR, c = (lane % LPR) * 8;
+        char* const o = row_address(rr);
+        const floatx4_t a = *(const floatx4_t*)(stage + rr * G::OUT_STRIDE + c * 4);
+        const floatx4_t b = *(const floatx4_t*)(stage + rr * G::OUT_STRIDE + c * 4 + 16);
+        bf16x8_t w;
 #pragma unroll
-      for (int x = 0; x < 4; ++x) {
-        w[x] = static_cast<bf16_t>(a[x]);
-        w[4 + x] = static_cast<bf16_t>(b[x]);
+        for (int x = 0; x < 4; ++x) {
+          w[x] = static_cast<bf16_t>(a[x]);
+          w[4 + x] = static_cast<bf16_t>(b[x]);
+        }
+        if (rows_ok >> rr & 1) *(bf16x8_t*)(o + c * 2) = w;
       }
-      if (r0 + rr < p.rows) *(bf16x8_t*)(o + c * 2) = w;
-    }
-  } else {
-    constexpr int LPR = D / 4, RPP = 64 / LPR;
+    } else {
+      constexpr int LPR = D / 4, RPP = 64 / LPR;
 #pragma unroll
-    for (int pass = 0; pass < 32 / RPP; ++pass) {
-      const int rr = pass * RPP + lane / LPR, c = (lane % LPR) * 4;
-      char* const o = row_address(rr);
-      const floatx4_t a = *(const floatx4_t*)(stage + rr * G::OUT_STRIDE + c * 4);
-      if (r0 + rr < p.rows) *(floatx4_t*)(o + c * 4) = a;
+      for (int pass = 0; pass < 32 / RPP; ++pass) {
+        const int rr = pass * RPP + lane / LPR, c = (lane % LPR) * 4;
+        char* const o = row_address(rr);
+        const floatx4_t a = *(const floatx4_t*)(stage + rr * G::OUT_STRIDE + c * 4);
+        if (rows_ok >> rr & 1) *(floatx4_t*)(o + c * 4) = a;
+      }
     }
+    if constexpr (MODE != PLAN) return;
+    if (!p.cut_units || share.length <= 0) return;
+    share.unit += 1;
+    share.begin = 0;
+    lds_barrier();   // the staging buffer is read before the next unit's tiles arrive (the
+                     // stores need not have left)
   }
 }
 
-template <int D, typename TO, bool BAND, bool SPLIT, bool ACC = false>
+template <int D, typename TO, bool BAND, Mode MODE>
 __global__ __launch_bounds__(NTHREADS) void prefill_mfma_kernel(const Params p) {
-  prefill_body<D, TO, BAND, SPLIT, ACC, false>(p);
+  prefill_body<D, TO, BAND, MODE>(p);
 }
 
-// All ring steps of a rank in one launch, each behind its arrival flag (the RING variant).
+// All ring steps of every rank, each behind its arrival flag (the RING variant).
 template <typename TO>
 __global__ __launch_bounds__(NTHREADS) void prefill_ring_walk_kernel(const Params p) {
-  prefill_body<128, TO, false, false, false, true>(p);
+  prefill_body<128, TO, false, RING>(p);
+}
+
+// Equation 4 over the pieces of the units that PLAN cut: grid.x is the share boundary, grid.y a
+// part of the unit's rows. The first boundary inside a unit merges it (most boundaries cut one,
+// into two pieces). Bound by the partials, up to 67 MB each way, and by latency where there are
+// few: a thread has all its rows' loads of two pieces in flight at once.
+constexpr int kMergeParts = 8;
+template <int D, typename TO>
+__global__ __launch_bounds__(256) void plan_merge_kernel(const Params p) {
+  const int i = blockIdx.x + 1;
+  // (a share that begins behind the start-up of a unit cuts it; the records end with unit -1)
+  const int2 prev = p.plan_rec[i - 1], rec = p.plan_rec[i], next = p.plan_rec[i + 1];
+  if (rec.x < 0 || rec.y == 0) return;
+  if (prev.x == rec.x && prev.y != 0) return;
+  int last = i;                       // the last workgroup with a piece of the unit
+  if (next.x == rec.x)
+    while (p.plan_rec[last + 1].x == rec.x) ++last;
+  constexpr int TPR = D / 4, RPP = 256 / TPR;   // threads per row, rows per pass
+  constexpr int U = BM / kMergeParts / RPP;     // rows per thread
+  const int col = (threadIdx.x % TPR) * 4;
+  const int row0 = blockIdx.y * (BM / kMergeParts) + threadIdx.x / TPR;
+  float lmax[U], den[U];
+  floatx4_t acc[U];
+#pragma unroll
+  for (int k = 0; k < U; ++k) {
+    lmax[k] = -INFINITY;
+    den[k] = 0.f;
+    acc[k] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+  }
+  for (int j0 = i - 1; j0 <= last; j0 += 2) {
+    floatx4_t x[U][2];
+    float l[U][2];
+#pragma unroll
+    for (int k = 0; k < U; ++k)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        const int j = min(j0 + b, last);   // (slots hold whole row blocks)
+        const int64_t s = (int64_t)(j == i - 1 ? 2 * j + 1 : 2 * j) * BM + row0 + k * RPP;
+        l[k][b] = p.part_lse[s];
+        x[k][b] = __builtin_nontemporal_load((const floatx4_t*)(p.part_out + s * D + col));
+      }
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      const float l1 = j0 + 1 <= last ? l[k][1] : -INFINITY;
+      const float m = fmaxf(lmax[k], fmaxf(l[k][0], l1));
+      if (m != -INFINITY) {
+        const float old = __expf(lmax[k] - m), w0 = __expf(l[k][0] - m), w1 = __expf(l1 - m);
+        den[k] = fmaf(den[k], old, w0 + w1);
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          acc[k][c] = fmaf(acc[k][c], old, fmaf(w0, x[k][0][c], w1 * x[k][1][c]));
+        lmax[k] = m;
+      }
+    }
+  }
+  const int units = p.n_row_blocks * p.n_z;
+  const int kvh = rec.x / units, u = rec.x - kvh * units;
+  const int z = u / p.n_row_blocks, rb = u - z * p.n_row_blocks;
+#pragma unroll
+  for (int k = 0; k < U; ++k) {
+    const int64_t r = (int64_t)rb * BM + row0 + k * RPP;
+    if (r >= p.rows) continue;
+    const float inv = den[k] > 0.f ? 1.f / den[k] : 0.f;
+    const int token = (int)((uint32_t)r / (uint32_t)p.group);
+    const int hg = (int)(r - (int64_t)token * p.group);
+    const int a = p.t.n_ranks > 1 ? rank_of_token(p.t, token) : 0;
+    const int64_t lin = ((int64_t)(token - p.t.tok_begin[a]) * p.n_kv_heads + kvh) * p.group + hg;
+    TO* const o = (TO*)((char*)p.t.out[a] + z * p.out_shard_stride) + lin * D + col;
+    if constexpr (sizeof(TO) == 4) {
+      *(floatx4_t*)o = acc[k] * inv;
+    } else {
+      bf16x4_t w;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) w[c] = static_cast<bf16_t>(acc[k][c] * inv);
+      *(bf16x4_t*)o = w;
+    }
+    if (col == 0 && p.t.lse[a] != nullptr)
+      p.t.lse[a][z * p.lse_shard_stride + lin] =
+          den[k] > 0.f ? lmax[k] + __logf(den[k]) : -INFINITY;
+  }
 }
