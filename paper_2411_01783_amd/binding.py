@@ -1,12 +1,14 @@
-"""Thin ctypes binding of libcp_attn.so (include/cp_attn.h), same names as the C ABI.
+"""Thin binding of libcp_attn.so (include/cp_attn.h), same names as the C ABI.
 
 Argument marshalling only: torch supplies device memory and the current HIP
-stream; every step of the path runs in the library's kernels. There is no CPU
+stream; every step of the path runs in the library's kernels. The calls of a serving loop are
+marshalled in native code (csrc/py_calls.cpp), the others through ctypes. There is no CPU
 or PyTorch fallback: a missing library raises at first use.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
 from typing import List, Optional, Sequence
 
@@ -15,6 +17,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libcp_attn.so")
+CALLS_PATH = os.path.join(_HERE, "_py_calls.so")
 
 CP_BF16, CP_FP32 = 0, 1
 CP_WS_PARTIAL, CP_WS_DECODE, CP_WS_MERGE = 0, 1, 2
@@ -80,17 +83,19 @@ class CpError(RuntimeError):
 
 
 _lib = None
+_native = None      # the _py_calls module, connected to the library
 
 
 def load() -> ctypes.CDLL:
-    """Load libcp_attn.so. Raises if it has not been built (no fallback)."""
-    global _lib
+    """Load libcp_attn.so and the native calls. Raises if they have not been built (no fallback)."""
+    global _lib, _native
     if _lib is not None:
         return _lib
-    if not os.path.exists(LIB_PATH):
-        raise RuntimeError(
-            "libcp_attn.so not found at %s: build it with "
-            "`python -m paper_2411_01783_amd.build` (there is no CPU fallback)" % LIB_PATH)
+    for path in (LIB_PATH, CALLS_PATH):
+        if not os.path.exists(path):
+            raise RuntimeError(
+                "%s not found at %s: build it with `python -m paper_2411_01783_amd.build` "
+                "(there is no CPU fallback)" % (os.path.basename(path), path))
     lib = ctypes.CDLL(LIB_PATH)
     lib.cp_version.restype = ctypes.c_int
     lib.cp_strerror.restype = ctypes.c_char_p
@@ -135,8 +140,21 @@ def load() -> ctypes.CDLL:
     lib.cp_kv_append.argtypes = [ctypes.POINTER(cp_shape)] + [_vp] * 11
     lib.cp_decode_owner.restype = _i32
     lib.cp_decode_owner.argtypes = [_i32, _i32, _i32]
-    _lib = lib
+    spec = importlib.util.spec_from_file_location("_py_calls", CALLS_PATH)
+    native = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(native)
+    native.connect(*[ctypes.cast(getattr(lib, name), _vp).value for name in (
+        "cp_workspace_bytes", "cp_attn_partial", "cp_attn_decode", "cp_attn_decode_static",
+        "cp_attn_merge", "cp_kv_append", "cp_ring_passkv", "cp_ring_passq",
+        "cp_ring_passq_decode")])
+    _lib, _native = lib, native
     return lib
+
+
+def _calls():
+    if _native is None:
+        load()
+    return _native
 
 
 def strerror(status: int) -> str:
@@ -171,6 +189,11 @@ def _stream(stream) -> Optional[int]:
     if stream is None:
         stream = torch.cuda.current_stream()
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
+
+
+def _raw(stream) -> Optional[int]:
+    """A stream argument for the native calls: None is torch's current stream."""
+    return None if stream is None else _stream(stream)
 
 
 def make_shape(dtype: int, head_dim: int, n_q_heads: int, n_kv_heads: int, total_q: int,
@@ -233,24 +256,11 @@ def cp_attn_partial(q, k, v, q_pos, kv_pos, cu_seqlens_q=None, cu_seqlens_kv=Non
                     out_dtype: Optional[torch.dtype] = None, softmax_scale: float = 0.0,
                     out=None, lse=None, workspace=None, stream=None):
     """(O, LSE) of q [Tq, N_H, d] against k, v [Tkv, N_KV, d] under kv_pos <= q_pos."""
-    lib = load()
-    tq, nh, d = q.shape
-    tkv, nkv, _ = k.shape
-    batch = 1 if cu_seqlens_q is None else cu_seqlens_q.numel() - 1
-    shape = make_shape(dtype_code(q.dtype), d, nh, nkv, tq, tkv, batch, softmax_scale)
-    odt = q.dtype if out_dtype is None else out_dtype
-    if out is None:
-        out = torch.empty((tq, nh, d), dtype=odt, device=q.device)
-    if lse is None:
-        lse = torch.empty((tq, nh), dtype=torch.float32, device=q.device)
-    if workspace is None:
-        workspace = _workspace(cp_workspace_bytes(shape, CP_WS_PARTIAL), q.device)
-    wp, wn = _ws_ptr(workspace)
-    _check(lib.cp_attn_partial(ctypes.byref(shape), _ptr(q), _ptr(k), _ptr(v), _ptr(q_pos),
-                               _ptr(kv_pos), _ptr(cu_seqlens_q), _ptr(cu_seqlens_kv), _ptr(out),
-                               _ptr(lse), dtype_code(out.dtype), wp, wn, _stream(stream)),
-           "cp_attn_partial")
-    return out, lse
+    r = (_native or _calls()).partial(q, k, v, q_pos, kv_pos, cu_seqlens_q, cu_seqlens_kv,
+                                      out_dtype, softmax_scale, out, lse, workspace, _raw(stream))
+    if type(r) is int:
+        raise CpError(r, "cp_attn_partial")
+    return r
 
 
 def cp_attn_partial_accumulate(q, k, v, q_pos, kv_pos, acc_out, acc_lse, final_out=None,
@@ -278,39 +288,20 @@ def cp_attn_decode(q, k, v, q_pos, kv_pos, cu_seqlens_kv, bid,
                    out=None, lse=None, workspace=None, stream=None, unique_bid: bool = False):
     """Decode step: query i attends to KV segment bid[i] of the packed k, v. `unique_bid`:
     the caller's promise that no sequence id occurs twice (CP_SHAPE_UNIQUE_BID)."""
-    lib = load()
-    nq, nh, d = q.shape
-    tkv, nkv, _ = k.shape
-    batch = cu_seqlens_kv.numel() - 1
-    shape = make_shape(dtype_code(q.dtype), d, nh, nkv, nq, tkv, batch, softmax_scale,
-                       CP_SHAPE_UNIQUE_BID if unique_bid else 0)
-    odt = q.dtype if out_dtype is None else out_dtype
-    if out is None:
-        out = torch.empty((nq, nh, d), dtype=odt, device=q.device)
-    if lse is None:
-        lse = torch.empty((nq, nh), dtype=torch.float32, device=q.device)
-    if workspace is None:
-        workspace = _workspace(cp_workspace_bytes(shape, CP_WS_DECODE), q.device)
-    wp, wn = _ws_ptr(workspace)
-    _check(lib.cp_attn_decode(ctypes.byref(shape), _ptr(q), _ptr(k), _ptr(v), _ptr(q_pos),
-                              _ptr(kv_pos), _ptr(cu_seqlens_kv), _ptr(bid), _ptr(out), _ptr(lse),
-                              dtype_code(out.dtype), wp, wn, _stream(stream)),
-           "cp_attn_decode")
-    return out, lse
+    r = (_native or _calls()).decode(q, k, v, q_pos, kv_pos, cu_seqlens_kv, bid, out_dtype,
+                                     softmax_scale, out, lse, workspace, _raw(stream), unique_bid)
+    if type(r) is int:
+        raise CpError(r, "cp_attn_decode")
+    return r
 
 
 def cp_attn_decode_static(q, k, v, q_pos, kv_pos, cu_seqlens_kv, bid, out, lse,
                           softmax_scale: float = 0.0, stream=None, unique_bid: bool = False):
     """cp_attn_decode into caller-provided `out` / `lse`, with the library's own scratch array
     in place of a workspace: the call allocates nothing (nor does this wrapper)."""
-    nq, nh, d = q.shape
-    tkv, nkv, _ = k.shape
-    shape = make_shape(dtype_code(q.dtype), d, nh, nkv, nq, tkv, cu_seqlens_kv.numel() - 1,
-                       softmax_scale, CP_SHAPE_UNIQUE_BID if unique_bid else 0)
-    _check(load().cp_attn_decode_static(ctypes.byref(shape), _ptr(q), _ptr(k), _ptr(v),
-                                        _ptr(q_pos), _ptr(kv_pos), _ptr(cu_seqlens_kv), _ptr(bid),
-                                        _ptr(out), _ptr(lse), dtype_code(out.dtype),
-                                        _stream(stream)), "cp_attn_decode_static")
+    _check((_native or _calls()).decode_static(q, k, v, q_pos, kv_pos, cu_seqlens_kv, bid, out,
+                                               lse, softmax_scale, _raw(stream), unique_bid),
+           "cp_attn_decode_static")
     return out, lse
 
 
@@ -345,16 +336,11 @@ class KVCache:
 def cp_kv_append(cache: KVCache, k_new: torch.Tensor, v_new: torch.Tensor,
                  pos_new: torch.Tensor, cu_seqlens_new: torch.Tensor, stream=None) -> None:
     """Append rows [cu_new[b], cu_new[b+1]) of k_new / v_new to sequence b of the cache."""
-    n_new, nkv, d = k_new.shape
-    shape = make_shape(dtype_code(k_new.dtype), d, nkv, nkv, n_new, cache.slots, cache.batch)
-    if k_new.dtype != cache.k.dtype or tuple(cache.k.shape[1:]) != (nkv, d):
-        raise ValueError("new K/V rows do not match the cache's row shape or dtype")
-    if cu_seqlens_new.numel() != cache.batch + 1 or pos_new.numel() != n_new:
-        raise ValueError("cu_seqlens_new / pos_new sizes do not match")
-    _check(load().cp_kv_append(ctypes.byref(shape), _ptr(k_new), _ptr(v_new), _ptr(pos_new),
-                               _ptr(cu_seqlens_new), _ptr(cache.k), _ptr(cache.v),
-                               _ptr(cache.kv_pos), _ptr(cache.cu), _ptr(cache.used),
-                               _ptr(cache.dropped), _stream(stream)), "cp_kv_append")
+    r = (_native or _calls()).append(k_new, v_new, pos_new, cu_seqlens_new, cache.k, cache.v,
+                                     cache.kv_pos, cache.cu, cache.used, cache.dropped,
+                                     cache.slots, cache.batch, _raw(stream))
+    if r:
+        raise CpError(r, "cp_kv_append")
 
 
 def cp_decode_owner(seq: int, decode_iter: int, n_ranks: int) -> int:
@@ -367,21 +353,10 @@ def cp_attn_merge(outs: Sequence[torch.Tensor], lses: Sequence[torch.Tensor],
                   out_dtype: Optional[torch.dtype] = None, out=None, lse_out=None,
                   want_lse: bool = True, stream=None):
     """Equation 4 over partial outputs outs[s] [..., d] with lses[s] [...]."""
-    lib = load()
-    n = len(outs)
-    d = outs[0].shape[-1]
-    rows = outs[0].numel() // d
-    odt = outs[0].dtype if out_dtype is None else out_dtype
-    if out is None:
-        out = torch.empty(outs[0].shape, dtype=odt, device=outs[0].device)
-    if lse_out is None and want_lse:
-        lse_out = torch.empty(outs[0].shape[:-1], dtype=torch.float32, device=outs[0].device)
-    optr = (_vp * n)(*[_ptr(t) for t in outs])
-    lptr = (_vp * n)(*[_ptr(t) for t in lses])
-    _check(lib.cp_attn_merge(rows, d, n, optr, lptr, dtype_code(outs[0].dtype), _ptr(out),
-                             dtype_code(out.dtype), _ptr(lse_out), _stream(stream)),
-           "cp_attn_merge")
-    return out, lse_out
+    r = (_native or _calls()).merge(outs, lses, out_dtype, out, lse_out, want_lse, _raw(stream))
+    if type(r) is int:
+        raise CpError(r, "cp_attn_merge")
+    return r
 
 
 class Ring:
@@ -500,14 +475,19 @@ class Ring:
         return self.partial_out[slot, :m], self.partial_lse[slot, :m]
 
 
-def cp_ring_passkv(ring: Ring, stream=None):
-    _check(load().cp_ring_passkv(ctypes.byref(ring.desc), _stream(stream)), "cp_ring_passkv")
+def _ring_call(which: int, name: str, ring: Ring, stream):
+    rc = (_native or _calls()).ring(which, ctypes.addressof(ring.desc), _raw(stream))
+    if rc:
+        raise CpError(rc, name)
     return ring.out, ring.lse
+
+
+def cp_ring_passkv(ring: Ring, stream=None):
+    return _ring_call(0, "cp_ring_passkv", ring, stream)
 
 
 def cp_ring_passq(ring: Ring, stream=None):
-    _check(load().cp_ring_passq(ctypes.byref(ring.desc), _stream(stream)), "cp_ring_passq")
-    return ring.out, ring.lse
+    return _ring_call(1, "cp_ring_passq", ring, stream)
 
 
 def cp_ring_prefill(ring: Ring, p_cached: int, n_q_heads: int, n_kv_heads: int,
@@ -523,6 +503,4 @@ def cp_ring_prefill(ring: Ring, p_cached: int, n_q_heads: int, n_kv_heads: int,
 
 
 def cp_ring_passq_decode(ring: Ring, stream=None):
-    _check(load().cp_ring_passq_decode(ctypes.byref(ring.desc), _stream(stream)),
-           "cp_ring_passq_decode")
-    return ring.out, ring.lse
+    return _ring_call(2, "cp_ring_passq_decode", ring, stream)

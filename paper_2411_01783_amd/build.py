@@ -1,4 +1,5 @@
-"""Build libcp_attn.so (HIP, gfx950 only) in-tree with hipcc.
+"""Build libcp_attn.so (HIP, gfx950 only, with hipcc) and the CPython module _py_calls.so of
+binding.py (host C++, with g++) in-tree.
 
 Usage: python -m paper_2411_01783_amd.build [--force]
 """
@@ -16,6 +17,8 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 OBJ_DIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libcp_attn.so")
+PY_SRC = os.path.join(CSRC, "py_calls.cpp")
+PY_LIB = os.path.join(HERE, "_py_calls.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -48,8 +51,36 @@ def _compile(src: str) -> str:
     return obj
 
 
+def build_py_calls(force: bool = False) -> str:
+    """Compile _py_calls.so against this interpreter's and torch's headers. Returns its path."""
+    header = os.path.join(INCLUDE, "cp_attn.h")
+    if not force and os.path.exists(PY_LIB) and \
+            os.path.getmtime(PY_LIB) >= max(os.path.getmtime(p) for p in (PY_SRC, header)):
+        return PY_LIB
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(torch.__file__)
+    tmp = PY_LIB + ".tmp.%d" % os.getpid()
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+           "-I", INCLUDE, "-isystem", os.path.join(root, "include"),
+           "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
+           "-I", sysconfig.get_paths()["include"], PY_SRC, "-o", tmp,
+           "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("g++ failed for %s:\n%s" % (PY_SRC, res.stderr))
+    if res.stderr.strip():
+        sys.stderr.write(res.stderr)
+    os.replace(tmp, PY_LIB)
+    return PY_LIB
+
+
 def build(force: bool = False, jobs: int = 4) -> str:
-    """Compile every csrc/*.hip for gfx950 and link libcp_attn.so. Returns its path."""
+    """Compile every csrc/*.hip for gfx950 and link libcp_attn.so, and the module of the
+    binding's calls. Returns the library's path."""
+    build_py_calls(force)
     if not force and os.path.exists(LIB) and os.path.getmtime(LIB) >= _newest_dep():
         return LIB
     os.makedirs(OBJ_DIR, exist_ok=True)
