@@ -443,15 +443,14 @@ extern "C" size_t cp_ring_workspace_bytes(const cp_ring_desc* d, int32_t decode)
       need = std::max(need, cp_workspace_bytes(&s, decode ? CP_WS_DECODE : CP_WS_PARTIAL));
     }
   if (d->gathered_q && decode) {
-    size_t regions = 0;
+    cp_shape shapes[CP_MAX_PARTS];
     bool flat = true;
     for (int b = 0; b < d->n_ranks; ++b) {
-      const cp_shape s = gathered_decode_shape(d, b);
-      need = std::max(need, cp_workspace_bytes(&s, CP_WS_DECODE));
-      flat = flat && decode_flat_applies(s);
-      regions += decode_flat_region_bytes(s);
+      shapes[b] = gathered_decode_shape(d, b);
+      need = std::max(need, cp_workspace_bytes(&shapes[b], CP_WS_DECODE));
+      flat = flat && decode_flat_applies(shapes[b]);
     }
-    if (flat) need = std::max(need, regions);
+    if (flat) need = std::max(need, decode_flat_bytes(d->n_ranks, shapes));
   }
   return need;
 }
@@ -690,17 +689,14 @@ static int ring_decode_gathered(const cp_ring_desc* d, hipStream_t st) {
   const RingSlots slots = make_slots(d);
   const int n = d->n_ranks;
   int rc = CP_OK;
-  // Every holder's split-KV partials into its own region, one merge over splits x holders.
   cp_shape shapes[CP_MAX_PARTS];
-  void* regions[CP_MAX_PARTS];
   bool flat = true;
-  size_t off = 0;
   for (int k = 0; k < n; ++k) {
     shapes[k] = gathered_decode_shape(d, k);
     flat = flat && decode_flat_applies(shapes[k]);
-    regions[k] = (char*)d->workspace + off;
-    off += decode_flat_region_bytes(shapes[k]);
+    if (!aligned16(d->k[k]) || !aligned16(d->v[k])) return CP_ERR_ALIGN;
   }
+  if (!aligned16(d->q[0])) return CP_ERR_ALIGN;
   const size_t out_row = (size_t)d->n_q_heads * d->head_dim * elem_size(d->out_dtype);
   bool one = true;   // the ranks' outputs lie back to back as the queries do
   for (int a = 1; a < n && one; ++a) {
@@ -711,24 +707,12 @@ static int ring_decode_gathered(const cp_ring_desc* d, hipStream_t st) {
   }
   float* const lse0 = d->lse != nullptr ? d->lse[0] : nullptr;
   if (flat) {
-    if (off > d->workspace_bytes) return CP_ERR_WORKSPACE;
-    for (int k = 0; k < n && rc == CP_OK; ++k) {
-      if (!aligned16(d->q[0]) || !aligned16(d->k[k]) || !aligned16(d->v[k])) rc = CP_ERR_ALIGN;
-      else
-        rc = launch_decode_flat_partials(
-            shapes[k], resolve_scale(d->softmax_scale, d->head_dim), d->q[0], d->k[k], d->v[k],
-            d->q_pos[0], d->kv_pos[k], d->cu_seqlens_kv[k], d->bid[0], regions[k],
-            decode_flat_region_bytes(shapes[k]), st);
-    }
-    if (rc != CP_OK) return rc;
-    if (one)
-      return launch_decode_flat_merge(n, shapes, regions, d->cu_seqlens_kv, d->bid[0],
-                                      (int64_t)n * d->n_q[0], d->out[0], d->out_dtype, lse0, st);
-    for (int a = 0; a < n && rc == CP_OK; ++a)
-      rc = launch_decode_flat_merge(n, shapes, regions, d->cu_seqlens_kv, d->bid[a], d->n_q[a],
-                                    d->out[a], d->out_dtype,
-                                    d->lse != nullptr ? d->lse[a] : nullptr, st);
-    return rc;
+    // every holder's split-KV partials in one launch, one merge over splits x holders
+    const int64_t all = (int64_t)n * d->n_q[0];
+    return launch_decode_flat(n, shapes, resolve_scale(d->softmax_scale, d->head_dim), d->q[0],
+                              d->k, d->v, d->q_pos[0], d->kv_pos, d->cu_seqlens_kv, d->bid[0],
+                              one ? 1 : n, one ? &all : d->n_q, d->out, d->out_dtype, d->lse,
+                              d->workspace, d->workspace_bytes, st);
   }
   for (int k = 0; k < n; ++k) {
     const int64_t slot = slot_of(d, 0, k);

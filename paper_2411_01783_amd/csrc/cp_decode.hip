@@ -336,12 +336,16 @@ __global__ __launch_bounds__(NTHREADS, 2) void decode_kernel(Params p) {
 // current one is used, and what is left after the last byte has landed is one 16-key unit.
 //
 // A range may hold the end of a sequence. Every wavefront then writes what it has accumulated
-// for the ending sequence as a partial of its own (a "tail": slot n_main + seq * FW + wave,
-// with LSE = -inf and no data if it saw nothing) and starts afresh; what the wavefronts hold
+// for the ending sequence as a partial of its own (a "tail": slot n_main + (holder * batch + seq)
+// * FW + wave, with LSE = -inf and no data if it saw nothing) and starts afresh; what the wavefronts hold
 // when the range ends belongs to one sequence, is combined in LDS and becomes the workgroup's
 // main partial (slot = workgroup index). flat_parts() below lists, for a sequence, which slots
-// hold its partials; the merge kernel applies Equation 4 over them (over all KV holders of a
-// ring at once, if asked to).
+// hold its partials; the merge kernel applies Equation 4 over them.
+//
+// The KV holders of a ring are one launch: their ranges are equally long and all workgroups are
+// resident at once, so the ring is one long stream of K and V (16 launches of 90 MB each paid
+// their ramp and tail 16 times, and left 85 MB of partials of short ranges to merge). A range is
+// at least 64 keys, one unit per wavefront: shorter ones take as long and only make partials.
 // ---------------------------------------------------------------------------
 constexpr int FW = 4;                           // wavefronts per workgroup
 constexpr int F_WG_PER_CU = 2;                  // (8 wavefronts per CU: 4 x 2 was faster than 8 x 1)
@@ -355,24 +359,32 @@ constexpr int F_SMEM = FW * F_WAVE_LDS;         // 66 KiB: two workgroups per CU
 constexpr int F_UNIT_VMEM_OPS = 9;              // 4 K, 4 V and 1 position request per unit
 static_assert(F_SMEM >= FW * CB_WAVE * 4, "combine buffer aliases the unit buffers");
 
-struct FlatParams {
-  const bf16_t* q;
+// One KV holder of a flat launch: its packed KV is cut into ranges of wg_keys keys, one per
+// workgroup (the last one short).
+struct FlatHolder {
   const bf16_t* k;
   const bf16_t* v;
-  const int32_t* q_pos;
   const int32_t* kv_pos;
   const int32_t* cu_kv;
+  int32_t total_kv;
+  int32_t wg_begin;  // its first workgroup, which is also its first main slot
+};
+constexpr int kMaxHolders = CP_MAX_PARTS;
+struct FlatParams {
+  FlatHolder holder[kMaxHolders];
+  const bf16_t* q;
+  const int32_t* q_pos;
   const int32_t* bid;
-  float* part_out;   // [n_main + batch * FW][n_q_heads][D]
-  float* part_lse;   // [n_main + batch * FW][n_q_heads]
+  float* part_out;   // [n_main + n_holders * batch * FW][n_q_heads][D]
+  float* part_lse;   // [n_main + n_holders * batch * FW][n_q_heads]
+  int32_t n_holders;
   int32_t n_q;
   int32_t n_q_heads;
   int32_t n_kv_heads;
   int32_t group;
   int32_t batch;
-  int32_t total_kv;
   int32_t wg_keys;   // keys per workgroup range, a multiple of UNIT
-  int32_t n_main;    // workgroups per KV head = main slots
+  int32_t n_main;    // workgroups per KV head = main slots, of all holders
   float scale_log2;
 };
 
@@ -455,16 +467,38 @@ struct SeqCtx {
   bf16x8_t qf[4];   // Q^T fragments: lane (hd, kg) holds channels kg*32 + ks*8 .. +7 of head hd
 };
 
-__global__ __launch_bounds__(FTHREADS, F_WG_PER_CU) void decode_flat_kernel(FlatParams p) {
+__global__ __launch_bounds__(FTHREADS, F_WG_PER_CU) void decode_flat_kernel(const FlatParams fp) {
   extern __shared__ __align__(16) char smem[];
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int hd = lane & 15;   // query head within the group (N side)
   const int kg = lane >> 4;   // key / channel sub-group
   const int g = blockIdx.x, kvh = blockIdx.y;
-  const int32_t w0 = g * p.wg_keys;
-  if (w0 >= p.total_kv) return;  // (no slot of such a workgroup is ever read)
-  const int32_t w1 = min(w0 + p.wg_keys, p.total_kv);
+  int holder = 0;
+  if (fp.n_holders > 1) {  // the last one whose first workgroup is not after this one
+    const int begin = lane < fp.n_holders ? fp.holder[lane].wg_begin : INT32_MAX;
+    holder = __builtin_popcountll(__builtin_amdgcn_ballot_w64(begin <= g)) - 1;
+  }
+  // (what one holder's walk needs, in registers)
+  struct {
+    const bf16_t *q, *k, *v;
+    const int32_t *q_pos, *kv_pos, *cu_kv, *bid;
+    float *part_out, *part_lse;
+    int32_t n_q, n_q_heads, n_kv_heads, group, batch, total_kv, tail;
+    float scale_log2;
+  } p;
+  {
+    const FlatHolder& h = fp.holder[holder];
+    p.q = fp.q; p.k = h.k; p.v = h.v;
+    p.q_pos = fp.q_pos; p.kv_pos = h.kv_pos; p.cu_kv = h.cu_kv; p.bid = fp.bid;
+    p.part_out = fp.part_out; p.part_lse = fp.part_lse;
+    p.n_q = fp.n_q; p.n_q_heads = fp.n_q_heads; p.n_kv_heads = fp.n_kv_heads;
+    p.group = fp.group; p.batch = fp.batch; p.total_kv = h.total_kv;
+    p.tail = fp.n_main + holder * fp.batch * FW;
+    p.scale_log2 = fp.scale_log2;
+  }
+  const int32_t w0 = (g - fp.holder[holder].wg_begin) * fp.wg_keys;
+  const int32_t w1 = min(w0 + fp.wg_keys, p.total_kv);
   char* const buf0 = smem + wave * F_WAVE_LDS;
   char* const buf1 = buf0 + F_BUF_BYTES;
 
@@ -619,7 +653,7 @@ __global__ __launch_bounds__(FTHREADS, F_WG_PER_CU) void decode_flat_kernel(Flat
   auto flush_tail = [&]() CP_INL {
     if (cur.qi >= 0 && cur.hi > cur.lo) {
       const float l_tot = quad_sum(l_run);
-      const int64_t slot = (int64_t)p.n_main + (int64_t)cur.s * FW + wave;
+      const int64_t slot = (int64_t)p.tail + (int64_t)cur.s * FW + wave;
       const int64_t row = slot * p.n_q_heads + kvh * p.group + hd;
       if (head_ok) {
         if (l_tot > 0.f) {
@@ -847,79 +881,93 @@ __host__ __device__ inline FlatParts flat_parts(int32_t a, int32_t b, int32_t wg
 // One workgroup of MW wavefronts per row. Thread t looks up part t of the row (its slot and
 // LSE); the largest LSE and the weights are reduced across the workgroup; then the wavefronts
 // share out the parts, every lane accumulating two channels of the parts its wavefront takes
-// (four loads in flight per lane), and the MW sums are added up in LDS.
-constexpr int kMaxHolders = CP_MAX_PARTS;
+// (FM_U loads in flight per lane), and the MW sums are added up in LDS. Bound by its chain of
+// memory latencies (bid, cu_seqlens_kv, LSE, rows): one holder's slots need no table in LDS.
 struct FlatMergeParams {
-  const float* part_out[kMaxHolders];
-  const float* part_lse[kMaxHolders];
   const int32_t* cu_kv[kMaxHolders];
   int32_t total_kv[kMaxHolders];
-  int32_t wg_keys[kMaxHolders];
-  int32_t n_main[kMaxHolders];
+  int32_t wg_begin[kMaxHolders];
+  const float* part_out;
+  const float* part_lse;
   const int32_t* bid;
+  int32_t n_main;
+  int32_t wg_keys;
+  int32_t batch;
   int32_t n_holders;
   int32_t n_q_heads;
 };
 
-// MW wavefronts per workgroup: 16 for a ring of holders, 4 for the few parts of one call
-// (measured: 2 -> 4 wavefronts 6.0 -> 5.3 us; eight loads in flight per lane instead of four
-// gain nothing there and cost the ring's merge 6 %).
+// MW wavefronts per workgroup: 8 for a ring of holders, 4 for the few parts of one call.
 constexpr int FM_U = 4;     // row loads in flight per lane
-constexpr int FM_MW1 = 4;   // wavefronts per row for one holder
-template <typename TO, int MW>
-__global__ __launch_bounds__(MW * 64) void decode_flat_merge_kernel(FlatMergeParams mp,
+template <typename TO, int MW, bool ONE>
+__global__ __launch_bounds__(MW * 64) void decode_flat_merge_kernel(const FlatMergeParams mp,
                                                                      TO* __restrict__ out,
                                                                      float* __restrict__ lse_out) {
   constexpr int MTHREADS = MW * 64;
   static_assert(MTHREADS >= D, "one thread per channel writes the row");
-  __shared__ int part_begin[kMaxHolders + 1];  // first part index of every holder
-  __shared__ int holder_lo[kMaxHolders], holder_mains[kMaxHolders];
+  __shared__ int part_begin[ONE ? 1 : kMaxHolders + 1];  // first part index of every holder
+  __shared__ int holder_lo[ONE ? 1 : kMaxHolders], holder_mains[ONE ? 1 : kMaxHolders];
   __shared__ float red[MW];
   __shared__ float w_of[MTHREADS];
-  __shared__ const float* src_of[MTHREADS];
+  __shared__ int src_of[MTHREADS];
   __shared__ float sums[MW][D];
   const int row = blockIdx.x;  // query * n_q_heads + head
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int qi = row / mp.n_q_heads, h = row - qi * mp.n_q_heads;
   const int s = mp.bid[qi];
-  // thread k looks up holder k's slots of this sequence (one round trip for all holders),
-  // thread 0 then lines the holders' parts up
-  if (tid < mp.n_holders) {
-    const int k = tid;
+  int n_parts, one_lo = 0, one_mains = 0;
+  if constexpr (ONE) {
     const FlatParts fp =
-        flat_parts(mp.cu_kv[k][s], mp.cu_kv[k][s + 1], mp.wg_keys[k], mp.total_kv[k]);
-    const int mains = max(0, fp.g_hi - fp.g_lo + 1);
-    holder_lo[k] = fp.g_lo;
-    holder_mains[k] = mains;
-    part_begin[k + 1] = mains + (fp.tail ? FW : 0);
-  }
-  __syncthreads();
-  if (tid == 0) {
-    int n = 0;
-    for (int k = 0; k < mp.n_holders; ++k) {
-      const int c = part_begin[k + 1];
-      part_begin[k] = n;
-      n += c;
+        flat_parts(mp.cu_kv[0][s], mp.cu_kv[0][s + 1], mp.wg_keys, mp.total_kv[0]);
+    one_lo = fp.g_lo;
+    one_mains = max(0, fp.g_hi - fp.g_lo + 1);
+    n_parts = one_mains + (fp.tail ? FW : 0);
+  } else {
+    // lane k of the first wavefront looks up holder k's slots of this sequence (one round trip
+    // for all holders) and lines the holders' parts up
+    if (wave == 0) {
+      int c = 0;
+      if (lane < mp.n_holders) {
+        const FlatParts fp =
+            flat_parts(mp.cu_kv[lane][s], mp.cu_kv[lane][s + 1], mp.wg_keys, mp.total_kv[lane]);
+        const int mains = max(0, fp.g_hi - fp.g_lo + 1);
+        holder_lo[lane] = mp.wg_begin[lane] + fp.g_lo;
+        holder_mains[lane] = mains;
+        c = mains + (fp.tail ? FW : 0);
+      }
+      int end = c;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(end, o, 64);
+        if (lane >= o) end += y;
+      }
+      if (lane < mp.n_holders) part_begin[lane] = end - c;
+      if (lane == mp.n_holders - 1) part_begin[mp.n_holders] = end;
     }
-    part_begin[mp.n_holders] = n;
+    __syncthreads();
+    n_parts = part_begin[mp.n_holders];
   }
-  __syncthreads();
-  const int n_parts = part_begin[mp.n_holders];
   float acc0 = 0.f, acc1 = 0.f, den = 0.f, lmax = -INFINITY;
   // (more than MTHREADS parts: several passes, each merged into the running result)
   for (int base = 0; base < n_parts; base += MTHREADS) {
     const int t = base + tid;
     float my_lse = -INFINITY;
-    const float* my_src = nullptr;
+    int my_src = 0;     // row of the partials
     if (t < n_parts) {
-      int k = 0;
-      while (part_begin[k + 1] <= t) ++k;
-      const int j = t - part_begin[k];
-      const int64_t slot = j < holder_mains[k]
-                               ? (int64_t)holder_lo[k] + j
-                               : (int64_t)mp.n_main[k] + (int64_t)s * FW + (j - holder_mains[k]);
-      my_lse = mp.part_lse[k][slot * mp.n_q_heads + h];
-      my_src = mp.part_out[k] + (slot * mp.n_q_heads + h) * D;
+      int k = 0, j = t, lo = one_lo, mains = one_mains;
+      if constexpr (!ONE) {
+        int hi = mp.n_holders;   // the holder with part_begin[k] <= t < part_begin[k + 1]
+        while (hi - k > 1) {
+          const int mid = (k + hi) >> 1;
+          if (part_begin[mid] <= t) k = mid; else hi = mid;
+        }
+        j = t - part_begin[k];
+        lo = holder_lo[k];
+        mains = holder_mains[k];
+      }
+      const int slot = j < mains ? lo + j : mp.n_main + (k * mp.batch + s) * FW + (j - mains);
+      my_src = slot * mp.n_q_heads + h;
+      my_lse = mp.part_lse[my_src];
     }
     float pmax = my_lse;
 #pragma unroll
@@ -954,7 +1002,8 @@ __global__ __launch_bounds__(MW * 64) void decode_flat_merge_kernel(FlatMergePar
           const int ee = min(e + u * MW, cnt - 1);
           wj[u] = e + u * MW < cnt ? w_of[ee] : 0.f;
           // a part with zero weight may hold anything (it is read, then dropped)
-          x[u] = __builtin_nontemporal_load((const floatx2_t*)src_of[ee] + lane);
+          x[u] = __builtin_nontemporal_load(
+              (const floatx2_t*)(mp.part_out + (int64_t)src_of[ee] * D) + lane);
         }
 #pragma unroll
         for (int u = 0; u < FM_U; ++u) {
@@ -1007,47 +1056,78 @@ bool decode_flat_applies(const cp_shape& s) {
 }
 
 namespace {
+constexpr int kMinRange = FW * UNIT;  // keys of a range: a unit per wavefront at least
 struct FlatPlan {
-  int n_main, wg_keys;
+  int wg_keys, n_main;
+  int wg_begin[kMaxHolders];
   size_t slots, out_bytes, lse_bytes;
 };
-FlatPlan flat_plan(const cp_shape& s) {
-  FlatPlan pl;
-  pl.n_main = std::max(1, 256 * F_WG_PER_CU / s.n_kv_heads);  // all resident, over all KV heads
-  const int64_t per = (s.total_kv + pl.n_main - 1) / pl.n_main;
-  pl.wg_keys = (int)std::max<int64_t>(UNIT, (per + UNIT - 1) / UNIT * UNIT);
-  pl.slots = (size_t)pl.n_main + (size_t)s.batch * FW;
-  pl.out_bytes = round256(pl.slots * s.n_q_heads * D * 4);
-  pl.lse_bytes = round256(pl.slots * s.n_q_heads * 4);
+// Equal ranges over the packed KV of all holders, as many as are resident at once (two workgroups
+// per CU over all KV heads); every holder's last range may be short.
+FlatPlan flat_plan(int n_holders, const cp_shape* shapes) {
+  FlatPlan pl = {};
+  const int64_t target = std::max(1, 256 * F_WG_PER_CU / shapes[0].n_kv_heads);
+  int64_t total = 0;
+  for (int k = 0; k < n_holders; ++k) total += shapes[k].total_kv;
+  auto ranges = [&](int64_t keys) {
+    int64_t n = 0;
+    for (int k = 0; k < n_holders; ++k) n += (shapes[k].total_kv + keys - 1) / keys;
+    return n;
+  };
+  int64_t keys = std::max<int64_t>(kMinRange, ((total + target - 1) / target + UNIT - 1) / UNIT * UNIT);
+  // (a short last range per holder can push the count over the target; more holders than
+  // workgroups cannot be helped)
+  while (ranges(keys) > std::max<int64_t>(target, n_holders)) keys += std::max<int64_t>(UNIT, keys / 64 / UNIT * UNIT);
+  pl.wg_keys = (int)std::min<int64_t>(keys, 0x7fffffc0);
+  for (int k = 0; k < n_holders; ++k) {
+    pl.wg_begin[k] = pl.n_main;
+    pl.n_main += (int)((shapes[k].total_kv + pl.wg_keys - 1) / pl.wg_keys);
+  }
+  pl.slots = (size_t)pl.n_main + (size_t)n_holders * shapes[0].batch * FW;
+  pl.out_bytes = round256(pl.slots * shapes[0].n_q_heads * D * 4);
+  pl.lse_bytes = round256(pl.slots * shapes[0].n_q_heads * 4);
   return pl;
 }
 }  // namespace
 
-size_t decode_flat_region_bytes(const cp_shape& s) {
-  const FlatPlan pl = flat_plan(s);
+size_t decode_flat_bytes(int n_holders, const cp_shape* shapes) {
+  const FlatPlan pl = flat_plan(n_holders, shapes);
   return pl.out_bytes + pl.lse_bytes;
 }
 
-int launch_decode_flat_partials(const cp_shape& s, float scale, const void* q, const void* k,
-                                const void* v, const int32_t* q_pos, const int32_t* kv_pos,
-                                const int32_t* cu_kv, const int32_t* bid, void* region,
-                                size_t region_bytes, hipStream_t stream) {
-  const FlatPlan pl = flat_plan(s);
-  if (region_bytes < pl.out_bytes + pl.lse_bytes) return CP_ERR_WORKSPACE;
+int launch_decode_flat(int n_holders, const cp_shape* shapes, float scale, const void* q,
+                       const void* const* k, const void* const* v, const int32_t* q_pos,
+                       const int32_t* const* kv_pos, const int32_t* const* cu_kv,
+                       const int32_t* bid, int n_outs, const int64_t* n_q, void* const* out,
+                       int32_t out_dtype, float* const* lse, void* workspace,
+                       size_t workspace_bytes, hipStream_t stream) {
+  if (n_holders < 1 || n_holders > kMaxHolders) return CP_ERR_SHAPE;
+  const cp_shape& s = shapes[0];
+  const FlatPlan pl = flat_plan(n_holders, shapes);
+  if (workspace_bytes < pl.out_bytes + pl.lse_bytes) return CP_ERR_WORKSPACE;
   if (s.n_kv_heads > 65535) return CP_ERR_SHAPE;
-  // key indices, range starts and per-lane offsets inside a tile are kept in 32 bits
-  if (s.total_kv > 0x7fffffffLL - 2 * (int64_t)pl.wg_keys) return CP_ERR_SHAPE;
+  // key indices, range starts, partial rows and per-lane offsets inside a tile are kept in 32 bits
+  for (int h = 0; h < n_holders; ++h)
+    if (shapes[h].total_kv > 0x7fffffffLL - 2 * (int64_t)pl.wg_keys) return CP_ERR_SHAPE;
   if ((int64_t)s.n_kv_heads * D * 64 > 0x7fffffffLL) return CP_ERR_SHAPE;
-  FlatParams p;
-  p.q = (const bf16_t*)q; p.k = (const bf16_t*)k; p.v = (const bf16_t*)v;
-  p.q_pos = q_pos; p.kv_pos = kv_pos; p.cu_kv = cu_kv; p.bid = bid;
-  p.part_out = (float*)region;
-  p.part_lse = (float*)((char*)region + pl.out_bytes);
+  if ((int64_t)pl.slots * s.n_q_heads > 0x7fffffffLL) return CP_ERR_SHAPE;
+  FlatParams p = {};
+  FlatMergeParams mp = {};
+  for (int h = 0; h < n_holders; ++h) {
+    p.holder[h] = {(const bf16_t*)k[h], (const bf16_t*)v[h], kv_pos[h], cu_kv[h],
+                   (int32_t)shapes[h].total_kv, pl.wg_begin[h]};
+    mp.cu_kv[h] = cu_kv[h];
+    mp.total_kv[h] = (int32_t)shapes[h].total_kv;
+    mp.wg_begin[h] = pl.wg_begin[h];
+  }
+  p.q = (const bf16_t*)q; p.q_pos = q_pos; p.bid = bid;
+  p.part_out = (float*)workspace;
+  p.part_lse = (float*)((char*)workspace + pl.out_bytes);
+  p.n_holders = n_holders;
   p.n_q = (int32_t)s.total_q;
   p.n_q_heads = s.n_q_heads; p.n_kv_heads = s.n_kv_heads;
   p.group = s.n_q_heads / s.n_kv_heads;
   p.batch = s.batch;
-  p.total_kv = (int32_t)s.total_kv;
   p.wg_keys = pl.wg_keys;
   p.n_main = pl.n_main;
   p.scale_log2 = scale * kLog2e;
@@ -1056,50 +1136,39 @@ int launch_decode_flat_partials(const cp_shape& s, float scale, const void* q, c
     return CP_ERR_LAUNCH;
   hipLaunchKernelGGL(decode_flat_kernel, dim3(pl.n_main, s.n_kv_heads), dim3(FTHREADS), F_SMEM,
                      stream, p);
-  return check_launch();
-}
+  if (check_launch() != CP_OK) return CP_ERR_LAUNCH;
 
-int launch_decode_flat_merge(int n_holders, const cp_shape* shapes, void* const* regions,
-                             const int32_t* const* cu_kv, const int32_t* bid, int64_t n_q,
-                             void* out, int32_t out_dtype, float* lse, hipStream_t stream) {
-  if (n_holders < 1 || n_holders > kMaxHolders) return CP_ERR_SHAPE;
-  if (n_q == 0) return CP_OK;
-  FlatMergeParams mp = {};
-  for (int k = 0; k < n_holders; ++k) {
-    const FlatPlan pl = flat_plan(shapes[k]);
-    mp.part_out[k] = (const float*)regions[k];
-    mp.part_lse[k] = (const float*)((const char*)regions[k] + pl.out_bytes);
-    mp.cu_kv[k] = cu_kv[k];
-    mp.total_kv[k] = (int32_t)shapes[k].total_kv;
-    mp.wg_keys[k] = pl.wg_keys;
-    mp.n_main[k] = pl.n_main;
-  }
-  mp.bid = bid;
+  mp.part_out = p.part_out; mp.part_lse = p.part_lse;
+  mp.n_main = pl.n_main; mp.wg_keys = pl.wg_keys; mp.batch = s.batch;
   mp.n_holders = n_holders;
-  mp.n_q_heads = shapes[0].n_q_heads;
-  const int64_t rows = n_q * shapes[0].n_q_heads;
-  if (rows > 0x7fffffffLL) return CP_ERR_SHAPE;
-  const dim3 grid((unsigned)rows);
-  if (n_holders == 1) {
-    if (out_dtype == CP_FP32)
-      hipLaunchKernelGGL((decode_flat_merge_kernel<float, FM_MW1>), grid, dim3(FM_MW1 * 64), 0, stream, mp,
-                         (float*)out, lse);
-    else
-      hipLaunchKernelGGL((decode_flat_merge_kernel<bf16_t, FM_MW1>), grid, dim3(FM_MW1 * 64), 0, stream, mp,
-                         (bf16_t*)out, lse);
-  } else {
-    if (out_dtype == CP_FP32)
-      hipLaunchKernelGGL((decode_flat_merge_kernel<float, 16>), grid, dim3(1024), 0, stream, mp,
-                         (float*)out, lse);
-    else
-      hipLaunchKernelGGL((decode_flat_merge_kernel<bf16_t, 16>), grid, dim3(1024), 0, stream, mp,
-                         (bf16_t*)out, lse);
+  mp.n_q_heads = s.n_q_heads;
+  int64_t first = 0;
+  for (int a = 0; a < n_outs; ++a) {   // the queries' results, in n_outs runs
+    mp.bid = bid + first;
+    first += n_q[a];
+    const int64_t rows = n_q[a] * s.n_q_heads;
+    if (rows == 0) continue;
+    if (rows > 0x7fffffffLL) return CP_ERR_SHAPE;
+    float* const l = lse != nullptr ? lse[a] : nullptr;
+    const dim3 grid((unsigned)rows);
+#define CP_FLAT_MERGE(TO, MW, ONE)                                                            \
+  hipLaunchKernelGGL((decode_flat_merge_kernel<TO, MW, ONE>), grid, dim3(MW * 64), 0, stream, \
+                     mp, (TO*)out[a], l)
+    if (n_holders == 1) {
+      if (out_dtype == CP_FP32) CP_FLAT_MERGE(float, 4, true);
+      else CP_FLAT_MERGE(bf16_t, 4, true);
+    } else {
+      if (out_dtype == CP_FP32) CP_FLAT_MERGE(float, 8, false);
+      else CP_FLAT_MERGE(bf16_t, 8, false);
+    }
+#undef CP_FLAT_MERGE
+    if (check_launch() != CP_OK) return CP_ERR_LAUNCH;
   }
-  return check_launch();
+  return CP_OK;
 }
 
 size_t decode_workspace_bytes(const cp_shape& s) {
-  if (decode_flat_applies(s)) return decode_flat_region_bytes(s);
+  if (decode_flat_applies(s)) return decode_flat_bytes(1, &s);
   const int splits = plan_splits(s);
   const size_t rows = (size_t)s.total_q * s.n_q_heads;
   return round256(splits * rows * D * 4) + round256(splits * rows * 4);
@@ -1109,13 +1178,9 @@ int launch_decode(const cp_shape& s, float scale, const void* q, const void* k, 
                   const int32_t* q_pos, const int32_t* kv_pos, const int32_t* cu_kv,
                   const int32_t* bid, void* out, float* lse, int32_t out_dtype, void* workspace,
                   size_t workspace_bytes, hipStream_t stream) {
-  if (decode_flat_applies(s)) {
-    const int rc = launch_decode_flat_partials(s, scale, q, k, v, q_pos, kv_pos, cu_kv, bid,
-                                               workspace, workspace_bytes, stream);
-    if (rc != CP_OK) return rc;
-    return launch_decode_flat_merge(1, &s, &workspace, &cu_kv, bid, s.total_q, out, out_dtype, lse,
-                                    stream);
-  }
+  if (decode_flat_applies(s))
+    return launch_decode_flat(1, &s, scale, q, &k, &v, q_pos, &kv_pos, &cu_kv, bid, 1, &s.total_q,
+                              &out, out_dtype, &lse, workspace, workspace_bytes, stream);
   const int splits = plan_splits(s);
   const size_t rows = (size_t)s.total_q * s.n_q_heads;
   const size_t out_bytes = round256(splits * rows * D * 4);
