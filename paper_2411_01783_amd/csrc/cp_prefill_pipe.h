@@ -598,8 +598,9 @@ __device__ __forceinline__ Share plan_share(const Params& p, int2* lds_bounds, u
     if (k * NTHREADS < n_units) {
       const int u = min(k * NTHREADS + tid, n_units - 1);
       const int z = p.n_z > 1 ? u / n_rb : 0;
-      const int b0 = p.per_shard ? L.blk_begin[z] : 0;
-      const int b1 = p.per_shard ? L.blk_begin[z + 1] : p.n_blocks;
+      // (the table in LDS is only filled for several ranks or shards)
+      const int b0 = p.n_z > 1 ? L.blk_begin[z] : 0;
+      const int b1 = p.n_z > 1 ? L.blk_begin[z + 1] : p.n_blocks;
       int cnt = 0;
       for (int b = b0; b < b1; b += 8 * stride) {
         int2 x[8];

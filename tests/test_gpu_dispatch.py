@@ -1,0 +1,200 @@
+"""GPU parity at the edges of the launch rules: which kernel or work split a call gets depends on
+its sizes, and these are the sizes on either side of each rule, against the fp64 oracle.
+
+Tolerances: those of gpu_util (2e-2 max-abs on O and 1e-3 on LSE for bf16 inputs of unit scale,
+1e-4 and 1e-5 for fp32), which bound the rounding of the inputs' products and of the probabilities
+whatever the split; a key counted twice or left out of the few hundred a short row sees is a
+relative change of 1 / keys of its denominator, above the LSE bound."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import LSE_RTOL_FP32, O_ATOL_FP32, check, dev, i32, randn
+from paper_2411_01783_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+def ring_case(seed, kv_sizes, q_sizes, nh, nkv, d, dtype="bf16"):
+    """Ring whose KV shards hold the positions 0 .. in runs in random order, and whose queries stand
+    at random positions (some padded), dealt out over the ranks."""
+    rng = np.random.default_rng(seed)
+    total, t = sum(kv_sizes), sum(q_sizes)
+    k, k64 = randn(seed + 1, (total, nkv, d), dtype)
+    v, v64 = randn(seed + 2, (total, nkv, d), dtype)
+    q, q64 = randn(seed + 3, (t, nh, d), dtype)
+    # runs of 48 positions in random order: blocks that are visible, hidden and cut by the mask
+    runs = [np.arange(a, min(a + 48, total)) for a in range(0, total, 48)]
+    order = np.concatenate([runs[i] for i in rng.permutation(len(runs))])
+    kv_pos = np.split(order, np.cumsum(kv_sizes)[:-1])
+    q_all = np.sort(rng.integers(-1, total, size=t))
+    rows = np.split(rng.permutation(t), np.cumsum(q_sizes)[:-1])
+    rows = [np.sort(r) for r in rows]
+    args = ([dev(q[r]) for r in rows], [dev(k[p]) for p in kv_pos], [dev(v[p]) for p in kv_pos],
+            [i32(q_all[r]) for r in rows], [i32(p) for p in kv_pos])
+    return args, rows, kv_pos, q_all, (q64, k64, v64)
+
+
+def check_ring(oracle, ring, out, lse, case, keep, atol=2e-2, rtol=1e-3):
+    _, rows, kv_pos, q_all, (q64, k64, v64) = case
+    ref_o, ref_l = oracle.attn(q64, k64, v64, q_all, np.arange(len(k64)))
+    for a, r in enumerate(rows):
+        check(out[a], lse[a], ref_o[r], ref_l[r], atol, rtol, "merged rank %d" % a)
+        if not keep:
+            continue
+        for b, p in enumerate(kv_pos):
+            if len(r) == 0:
+                continue
+            po, pl = ring.partial(a, b)
+            if len(p) == 0:
+                assert torch.isneginf(pl).all() and (po == 0).all()
+                continue
+            o, l = oracle.attn(q64[r], k64[p], v64[p], q_all[r], p)
+            check(po, pl, o, l, atol, rtol, "partial %d, %d" % (a, b))
+
+
+# kv sizes, query sizes, heads, kv heads, d:
+#   six tiles a unit (a workgroup per unit) and seven (equal shares, cut and merged)
+#   960 blocks (bounds in LDS) and 961 (KV axis split over the grid), shards merged and kept apart
+#   an empty shard, a rank without queries, a last block of one key, groups of 1, 3 and 64 heads
+@pytest.mark.parametrize("kv_sizes,q_sizes,nh,nkv,d", [
+    ([768], [97], 16, 1, 128),
+    ([800], [97], 16, 1, 128),
+    ([769, 31], [40, 57], 16, 1, 64),
+    ([15360, 15360], [33, 16], 4, 1, 128),
+    ([15361, 15360], [33, 16], 4, 1, 128),
+    ([10239, 10273, 10209], [8, 0, 41], 8, 2, 64),
+    ([1500, 0, 33, 1], [0, 300, 1, 17], 3, 1, 128),
+    ([1000, 1057], [100, 31], 6, 2, 64),
+    ([130, 999], [257, 3], 5, 5, 128),
+    ([640, 321], [64, 5], 64, 1, 128),
+])
+@pytest.mark.parametrize("keep", [False, True])
+def test_ring_launch_rules(oracle, kv_sizes, q_sizes, nh, nkv, d, keep):
+    n = max(len(kv_sizes), len(q_sizes))
+    kv_sizes = kv_sizes + [0] * (n - len(kv_sizes))
+    case = ring_case(4100 + n, kv_sizes, q_sizes, nh, nkv, d)
+    ring = B.Ring(*case[0], out_dtype=torch.float32, keep_partials=keep)
+    for order in (B.cp_ring_passkv, B.cp_ring_passq):
+        out, lse = order(ring)
+        torch.cuda.synchronize()
+        check_ring(oracle, ring, out, lse, case, keep)
+
+
+def test_ring_of_more_ranks_than_one_launch_takes(oracle):
+    case = ring_case(4200, [9] * 33, [5] * 33, 4, 2, 128)
+    for keep in (False, True):
+        ring = B.Ring(*case[0], out_dtype=torch.float32, keep_partials=keep)
+        out, lse = B.cp_ring_passkv(ring)
+        torch.cuda.synchronize()
+        check_ring(oracle, ring, out, lse, case, keep)
+
+
+# row blocks of 4 tokens: 255 and 256 of them in one call (planned; a workgroup each without a
+# plan), 1024 and 1026 units of two shards kept apart (planned; not)
+@pytest.mark.parametrize("shards,tokens", [(1, 1020), (1, 1021), (2, 2048), (2, 2049)])
+def test_unit_limits(oracle, shards, tokens):
+    nh, tkv = 64, 70
+    rng = np.random.default_rng(tokens)
+    q, q64 = randn(4301, (tokens, nh, 128))
+    k, k64 = randn(4302, (tkv, 1, 128))
+    v, v64 = randn(4303, (tkv, 1, 128))
+    qp = rng.integers(-1, tkv, size=tokens)
+    some = np.r_[0:5, tokens // 2 - 3:tokens // 2 + 3, tokens - 5:tokens]
+    ref_o, ref_l = oracle.attn(q64[some], k64, v64, qp[some], np.arange(tkv))
+    if shards == 1:
+        o, l = B.cp_attn_partial(dev(q), dev(k), dev(v), i32(qp), i32(np.arange(tkv)))
+    else:
+        half, cut = tokens // 2, 37
+        ring = B.Ring([dev(q[:half]), dev(q[half:])], [dev(k[:cut]), dev(k[cut:])],
+                      [dev(v[:cut]), dev(v[cut:])], [i32(qp[:half]), i32(qp[half:])],
+                      [i32(np.arange(cut)), i32(np.arange(cut, tkv))], out_dtype=torch.float32,
+                      keep_partials=True)
+        out, lse = B.cp_ring_passkv(ring)
+        o, l = torch.cat(out), torch.cat(lse)
+    torch.cuda.synchronize()
+    check(o[some], l[some], ref_o, ref_l, what="sampled rows")
+
+
+# fp32: 16 and 32 rows a workgroup (head_dim 64, 16384 rows), head_dim 128, lists of more than
+# 256 blocks of 16 keys
+@pytest.mark.parametrize("kv_sizes,q_sizes,nh,nkv,d", [
+    ([17, 1], [16, 17], 4, 1, 64),
+    ([300, 0, 213], [100, 0, 90], 8, 2, 64),
+    ([1000, 1049], [1024, 1024], 8, 1, 64),
+    ([1000, 1050], [1025, 1024], 8, 1, 64),
+    ([4100, 37], [21, 12], 4, 2, 128),
+])
+@pytest.mark.parametrize("keep", [False, True])
+def test_fp32_ring(oracle, kv_sizes, q_sizes, nh, nkv, d, keep):
+    case = ring_case(4400, kv_sizes, q_sizes, nh, nkv, d, "fp32")
+    ring = B.Ring(*case[0], keep_partials=keep)
+    out, lse = B.cp_ring_passkv(ring)
+    torch.cuda.synchronize()
+    check_ring(oracle, ring, out, lse, case, keep, O_ATOL_FP32, LSE_RTOL_FP32)
+
+
+# batches on either side of the 1024 sequences whose spans the encode kernel scans by itself
+@pytest.mark.parametrize("batch", [1023, 1024, 1025])
+def test_packed_batch_of_many_sequences(oracle, batch):
+    nh = 2
+    lens = 1 + np.arange(batch) % 4
+    cu = np.concatenate([[0], np.cumsum(lens)])
+    total = int(cu[-1])
+    pos = np.concatenate([np.arange(n) for n in lens])
+    q, q64 = randn(4501, (total, nh, 128))
+    k, k64 = randn(4502, (total, 1, 128))
+    v, v64 = randn(4503, (total, 1, 128))
+    o, l = B.cp_attn_partial(dev(q), dev(k), dev(v), i32(pos), i32(pos), i32(cu), i32(cu))
+    torch.cuda.synchronize()
+    ref_o, ref_l = oracle.attn(q64, k64, v64, pos, pos, cu, cu)
+    check(o, l, ref_o, ref_l, what="batch %d" % batch)
+
+
+# flat decode over several holders: ranges of 64 keys (the smallest) with a short last one, more
+# holders than fit one round of workgroups per KV head, sequences that end at a range's end, in
+# its last key, or hold nothing on a holder
+@pytest.mark.parametrize("n,lengths,nh,nkv", [
+    (2, [[64, 128, 1, 63], [65, 0, 64, 128]], 16, 1),
+    (3, [[700, 33], [1, 0], [0, 9000]], 8, 2),
+    (33, [[5, 60]] * 33, 32, 16),
+    (2, [[30000, 9, 41], [16, 31000, 17]], 16, 1),
+])
+def test_decode_ring_ranges(oracle, n, lengths, nh, nkv):
+    batch = len(lengths[0])
+    m = (batch + n - 1) // n                  # queries per rank; equal, so the batch is filled up
+    lengths = [list(x) + [0] * (m * n - batch) for x in lengths]
+    batch = m * n
+    q, q64 = randn(4601, (batch, nh, 128))
+    keys = [sum(x[b] for x in lengths) for b in range(batch)]
+    ks, vs, kps, cus, refs = [], [], [], [], [([], [], []) for _ in range(batch)]
+    begin = [0] * batch
+    for r, ls in enumerate(lengths):
+        total = sum(ls)
+        k, k64 = randn(4610 + 2 * r, (total, nkv, 128))
+        v, v64 = randn(4611 + 2 * r, (total, nkv, 128))
+        cu = np.concatenate([[0], np.cumsum(ls)])
+        pos = []
+        for b, L in enumerate(ls):
+            p = begin[b] + np.arange(L)
+            begin[b] += L
+            pos.append(p)
+            for dst, src in zip(refs[b], (k64[cu[b]:cu[b + 1]], v64[cu[b]:cu[b + 1]], p)):
+                dst.append(src)
+        ks.append(dev(k)); vs.append(dev(v)); cus.append(i32(cu)); kps.append(i32(np.concatenate(pos)))
+    bid = np.random.default_rng(46).permutation(batch)
+    qp = np.array([max(0, keys[b] - 1 - (b % 3)) for b in bid])   # (some keys lie behind the query)
+    qd, qpd, bd = dev(q), i32(qp), i32(bid)
+    sl = [slice(r * m, (r + 1) * m) for r in range(n)]
+    ring = B.Ring([qd[x] for x in sl], ks, vs, [qpd[x] for x in sl], kps, out_dtype=torch.float32,
+                  keep_partials=True, gathered_q=True, cu_seqlens_kv=cus, bid=[bd[x] for x in sl],
+                  unique_bid=True)
+    out, lse = B.cp_ring_passq_decode(ring)
+    torch.cuda.synchronize()
+    for i, b in enumerate(bid):
+        k64, v64, p = (np.concatenate(x) for x in refs[b])
+        if len(p) == 0:
+            ref_o, ref_l = np.zeros((1, nh, 128)), np.full((1, nh), -np.inf)
+        else:
+            ref_o, ref_l = oracle.attn(q64[i:i + 1], k64, v64, qp[i:i + 1], p)
+        check(ring.out_all[i:i + 1], ring.lse_all[i:i + 1], ref_o, ref_l, what="sequence %d" % b)
