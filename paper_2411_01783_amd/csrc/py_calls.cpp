@@ -142,6 +142,18 @@ PyObject* pair(PyObject* a, PyObject* b) {
 }
 PyObject* status(int rc) { return PyLong_FromLong(rc); }
 
+// Other threads run while the library is called, as they do in a ctypes call: a launch blocks
+// once the stream's queue is full. The tensors are the caller's arguments or held on the stack.
+struct Unlocked {
+  PyThreadState* const state = PyEval_SaveThread();
+  ~Unlocked() { PyEval_RestoreThread(state); }
+};
+template <typename F, typename... A>
+int call(F f, A... args) {
+  const Unlocked u;
+  return f(args...);
+}
+
 void arguments(Py_ssize_t n, Py_ssize_t want) {
   if (n != want) raise(PyExc_TypeError, "wrong number of arguments");
   if (fn.decode == nullptr) raise(PyExc_RuntimeError, "the library is not loaded");
@@ -171,7 +183,7 @@ PyObject* partial(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const at::Tensor lse = result(a[10], {q.size(0), q.size(1)}, q, at::kFloat);
     Workspace w;
     use_workspace(w, a[11], s, CP_WS_PARTIAL, q);
-    const int rc = fn.partial(&s, pointer(q), pointer(k), pointer(a[2]), (int32_t*)pointer(a[3]),
+    const int rc = call(fn.partial, &s, pointer(q), pointer(k), pointer(a[2]), (int32_t*)pointer(a[3]),
                               (int32_t*)pointer(a[4]), (int32_t*)pointer(a[5]),
                               (int32_t*)pointer(a[6]), pointer(out), (float*)pointer(lse),
                               dtype_code(out.scalar_type()), w.ptr, w.bytes, stream_of(a[12]));
@@ -192,7 +204,7 @@ PyObject* decode(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const at::Tensor lse = result(a[10], {q.size(0), q.size(1)}, q, at::kFloat);
     Workspace w;
     use_workspace(w, a[11], s, CP_WS_DECODE, q);
-    const int rc = fn.decode(&s, pointer(q), pointer(k), pointer(a[2]), (int32_t*)pointer(a[3]),
+    const int rc = call(fn.decode, &s, pointer(q), pointer(k), pointer(a[2]), (int32_t*)pointer(a[3]),
                              (int32_t*)pointer(a[4]), (int32_t*)pointer(a[5]),
                              (int32_t*)pointer(a[6]), pointer(out), (float*)pointer(lse),
                              dtype_code(out.scalar_type()), w.ptr, w.bytes, stream_of(a[12]));
@@ -209,7 +221,7 @@ PyObject* decode_static(PyObject*, PyObject* const* a, Py_ssize_t n) {
     if (unique < 0) throw Raised{};
     const cp_shape s = rows_shape(q, k, tensor(a[5]).numel() - 1, number(a[9]),
                                   unique ? CP_SHAPE_UNIQUE_BID : 0);
-    return status(fn.decode_static(&s, pointer(q), pointer(k), pointer(a[2]),
+    return status(call(fn.decode_static, &s, pointer(q), pointer(k), pointer(a[2]),
                                    (int32_t*)pointer(a[3]), (int32_t*)pointer(a[4]),
                                    (int32_t*)pointer(a[5]), (int32_t*)pointer(a[6]), pointer(out),
                                    (float*)pointer(a[8]), dtype_code(out.scalar_type()),
@@ -246,7 +258,7 @@ PyObject* merge(PyObject*, PyObject* const* a, Py_ssize_t n) {
       op[i] = pointer(PySequence_Fast_GET_ITEM(outs, i));
       lp[i] = (const float*)pointer(PySequence_Fast_GET_ITEM(lses, i));
     }
-    const int rc = fn.merge(rows, (int32_t)d, (int32_t)parts, op, lp,
+    const int rc = call(fn.merge, rows, (int32_t)d, (int32_t)parts, op, lp,
                             dtype_code(o0.scalar_type()), pointer(out),
                             dtype_code(out.scalar_type()),
                             lse.defined() ? (float*)pointer(lse) : nullptr, stream_of(a[6]));
@@ -286,7 +298,7 @@ PyObject* append(PyObject*, PyObject* const* a, Py_ssize_t n) {
     s.batch = (int32_t)batch;
     s.total_q = k.size(0);
     s.total_kv = slots;
-    return status(fn.append(&s, pointer(k), pointer(a[1]), (int32_t*)pointer(a[2]),
+    return status(call(fn.append, &s, pointer(k), pointer(a[1]), (int32_t*)pointer(a[2]),
                             (int32_t*)pointer(a[3]), pointer(cache), pointer(a[5]),
                             (int32_t*)pointer(a[6]), (int32_t*)pointer(a[7]),
                             (int32_t*)pointer(a[8]), (int32_t*)pointer(a[9]), stream_of(a[12])));
@@ -301,7 +313,7 @@ PyObject* ring(PyObject*, PyObject* const* a, Py_ssize_t n) {
     if (which < 0 || which > 2) raise(PyExc_ValueError, "no such ring driver");
     void* const desc = PyLong_AsVoidPtr(a[1]);
     if (PyErr_Occurred()) throw Raised{};
-    return status(fn.ring[which]((const cp_ring_desc*)desc, stream_of(a[2])));
+    return status(call(fn.ring[which], (const cp_ring_desc*)desc, stream_of(a[2])));
   });
 }
 
