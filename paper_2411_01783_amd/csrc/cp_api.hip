@@ -561,7 +561,8 @@ int ring_one_launch(const cp_ring_desc* d, hipStream_t st) {
     t.n_kv[r] = (int32_t)d->n_kv[r];
     t.tok_begin[r + 1] = t.tok_begin[r] + (int32_t)d->n_q[r];
     t.blk_begin[r + 1] = t.blk_begin[r] + kv_blocks(d->n_kv[r]);
-    if (!aligned16(d->q[r]) || !aligned16(d->k[r]) || !aligned16(d->v[r]) || !aligned16(d->out[r]))
+    if (!aligned16(d->q[r]) || !aligned16(d->k[r]) || !aligned16(d->v[r]) ||
+        (d->n_q[r] > 0 && !aligned16(d->out[r])))
       return CP_ERR_ALIGN;
   }
   const AttnShape s = ring_attn_shape(d);
