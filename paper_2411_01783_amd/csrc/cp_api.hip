@@ -609,6 +609,32 @@ int ring_one_launch(const cp_ring_desc* d, hipStream_t st) {
   return launch_merge_table(m, d->head_dim, d->part_dtype, d->out_dtype, st);
 }
 
+// fused_merge of a rank of such a ring, which has one slot for its partials: step 0 writes a
+// running (O, LSE) there, the following steps merge into it in their epilogues and the last one
+// writes the rank's output.
+template <typename KvOf>
+int ring_rank_fused(const cp_ring_desc* d, const RingSlots& slots, int a, hipStream_t st,
+                    KvOf kv_of_step) {
+  float* const acc_out = (float*)slots.out(0);
+  float* const acc_lse = slots.lse(0);
+  for (int j = 0; j < d->n_ranks; ++j) {
+    const int b = kv_of_step(a, j);
+    const cp_shape s = ring_shape(d, a, b, false);
+    const bool last = j == d->n_ranks - 1;
+    const int rc =
+        j == 0 ? cp_attn_partial(&s, d->q[a], d->k[b], d->v[b], d->q_pos[a], d->kv_pos[b], nullptr,
+                                 nullptr, acc_out, acc_lse, CP_FP32, d->workspace,
+                                 d->workspace_bytes, st)
+               : cp_attn_partial_accumulate(&s, d->q[a], d->k[b], d->v[b], d->q_pos[a],
+                                            d->kv_pos[b], acc_out, acc_lse,
+                                            last ? d->out[a] : nullptr, d->out_dtype,
+                                            last && d->lse != nullptr ? d->lse[a] : nullptr,
+                                            d->workspace, d->workspace_bytes, st);
+    if (rc != CP_OK) return rc;
+  }
+  return CP_OK;
+}
+
 // N x N partial-attention calls and a merge per rank, for the rings that are not one launch.
 // `kv_of_step(k, j)`: the KV rank of step j of rank k's queries.
 template <typename KvOf>
@@ -617,6 +643,11 @@ int ring_steps(const cp_ring_desc* d, hipStream_t st, KvOf kv_of_step) {
   const int n = d->n_ranks;
   const bool packed = ring_is_packed(d, false);
   for (int a = 0; a < n; ++a) {
+    if (d->fused_merge && n > 1) {
+      const int rc = ring_rank_fused(d, slots, a, st, kv_of_step);
+      if (rc != CP_OK) return rc;
+      continue;
+    }
     for (int j = 0; j < n; ++j) {
       const int b = kv_of_step(a, j);
       const cp_shape s = ring_shape(d, a, b, false);

@@ -90,6 +90,20 @@ def test_ring_of_more_ranks_than_one_launch_takes(oracle):
         check_ring(oracle, ring, out, lse, case, keep)
 
 
+# merged step by step in one slot: nothing behind the slot is written
+def test_fused_ring_of_more_ranks_than_one_launch_takes(oracle):
+    case = ring_case(4200, [9] * 33, [5] * 32 + [0], 4, 2, 128)
+    ring = B.Ring(*case[0], out_dtype=torch.float32, fused_merge=True)
+    block = torch.full((33, *ring.partial_out.shape[1:]), 7.0, device="cuda")
+    rows = torch.full((33, *ring.partial_lse.shape[1:]), 7.0, device="cuda")
+    ring.desc.partial_out, ring.desc.partial_lse = block.data_ptr(), rows.data_ptr()
+    for order in (B.cp_ring_passkv, B.cp_ring_passq):
+        out, lse = order(ring)
+        torch.cuda.synchronize()
+        check_ring(oracle, ring, out, lse, case, False)
+        assert (block[1:] == 7.0).all() and (rows[1:] == 7.0).all()
+
+
 # row blocks of 4 tokens: 255 and 256 of them in one call (planned; a workgroup each without a
 # plan), 1024 and 1026 units of two shards kept apart (planned; not)
 @pytest.mark.parametrize("shards,tokens", [(1, 1020), (1, 1021), (2, 2048), (2, 2049)])
