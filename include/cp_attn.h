@@ -253,44 +253,39 @@ typedef struct {
    * Partial-result buffers (device). Slot i holds max_n_q * n_q_heads * head_dim
    * elements of part_dtype in partial_out and max_n_q * n_q_heads floats in
    * partial_lse, where max_n_q = max_k n_q[k]. With keep_partials == 0 there are
-   * n_ranks slots, reused for every rank (slot s = KV origin rank in pass-KV,
-   * = KV holder rank in pass-Q). With keep_partials != 0 there are
-   * n_ranks * n_ranks slots and the partial of queries of rank a against KV of
-   * rank b stays in slot a * n_ranks + b.
+   * n_ranks slots, which are scratch: a prefill ring that runs as one attention launch (up to
+   * 32 ranks; bf16 in one sequence, or packed with head_dim 128; fp32 in one sequence) applies
+   * Equation 4 inside the online softmax and leaves them alone, any other ring reuses them for
+   * every rank (slot s = KV origin rank in pass-KV, = KV holder rank in pass-Q). With
+   * keep_partials != 0 there are n_ranks * n_ranks slots and the partial of queries of rank a
+   * against KV of rank b stays in slot a * n_ranks + b.
    */
   void* partial_out;
   float* partial_lse;
   int32_t keep_partials;
   /*
-   * 1: prefill drivers merge in the epilogues instead of keeping N partials per rank
-   * (cp_attn_partial_accumulate): step 0 of a rank writes a running (O, LSE) into partial
-   * slot 0, the following steps merge into it and the last one writes the rank's output.
-   * One slot suffices; no merge pass. Requires part_dtype == CP_FP32, keep_partials == 0, no
-   * decode, and calls that do not split their KV axis (else CP_ERR_UNSUPPORTED). 0: off.
-   * 2 (cp_ring_passkv only): one launch per rank walks the KV shards of all N ring steps in
-   * ring order with one running softmax state in registers, so Equation 4 is applied inside
-   * the online softmax and only the rank's output is written: no partials, no merge pass, no
+   * 1: the merge must happen inside the attention launch: one partial slot suffices, no merge
+   * pass. Requires part_dtype == CP_FP32, keep_partials == 0, no decode, and calls that do not
+   * split their KV axis (else CP_ERR_UNSUPPORTED). 0: no such demand (a ring that is one launch
+   * merges there all the same).
+   * 2 (cp_ring_passkv only): the KV shards of all N ring steps are walked inside one launch,
+   * every rank's with one running softmax state in registers, so Equation 4 is applied inside
+   * the online softmax and only the ranks' outputs are written: no partials, no merge pass, no
    * per-step launch. Same requirements as 1 (decided on the largest KV shard), and
-   * n_ranks <= 32. See `arrived` below for how a step waits for its shard.
+   * n_ranks <= 32. With `arrived` below a rank walks the shards in ring order, each behind its
+   * flag; without it the launch walks the visible blocks of all shards in the order they lie.
    */
   int32_t fused_merge;
-  void* workspace; /* (device) max over ranks of the per-call workspace */
+  void* workspace; /* (device) cp_ring_workspace_bytes(desc, decode) */
   size_t workspace_bytes;
   /* decode (cp_ring_passq_decode) and packed prefill batches (cu_seqlens_q below) */
   int32_t batch;                       /* sequences packed in every rank's KV */
   const int32_t* const* cu_seqlens_kv; /* (host) -> (device) int32 [batch+1] per rank */
   const int32_t* const* bid;           /* (host) -> (device) int32 [n_q[k]] per rank */
   /*
-   * Optional second HIP stream (default priority), or NULL. When given, the prefill
-   * drivers issue the N partial-attention calls of one rank alternately on `stream` and
-   * on aux_stream, so that the tail of one call (its last workgroups, its output writes)
-   * overlaps the start of the next; both are joined before the rank's merge, and
-   * everything the driver enqueues is ordered after prior work on `stream` and before
-   * later work on it. The calls of one rank write different partial slots and only read
-   * their inputs, so their order does not matter. Ignored (single stream) by the decode
-   * driver and whenever a call needs per-call scratch (split KV walks of short query
-   * shards), which consecutive calls share. Two events are created and destroyed per
-   * driver call; no device memory is allocated.
+   * A second HIP stream (default priority), or NULL. Accepted and not used: a prefill ring is
+   * one launch over all ranks and shards, so there are no calls of a rank to overlap. Everything
+   * a driver enqueues goes to `stream`.
    */
   void* aux_stream;
   /*
@@ -390,7 +385,8 @@ int cp_ring_passq(const cp_ring_desc* desc, void* stream);
  */
 int cp_ring_passq_decode(const cp_ring_desc* desc, void* stream);
 
-/* Workspace the ring drivers need: the maximum over all (query rank, KV rank) calls. */
+/* Workspace the ring drivers need, for the launches this descriptor takes. Reads sizes and
+ * options only, besides the checks of the descriptor that the drivers make. */
 size_t cp_ring_workspace_bytes(const cp_ring_desc* desc, int32_t decode);
 
 /* Ring order chosen by cp_select_order. */
