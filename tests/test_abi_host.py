@@ -236,6 +236,25 @@ def test_workspace_sizes(lib):
     assert B.cp_workspace_bytes(dec, B.CP_WS_MERGE) == 0
 
 
+def test_workspace_of_the_largest_kv_serves_smaller_calls(lib):
+    rng = np.random.default_rng(7)
+    for nh, nkv in ((16, 1), (8, 2), (16, 4)):
+        for batch in (1, 5, 32):
+            sizes = sorted({1, 63, 64, 65, 163840, *(int(x) for x in 2 ** rng.uniform(0, 18, 200))})
+            need = [B.cp_workspace_bytes(_shape(n_q_heads=nh, n_kv_heads=nkv, total_q=batch,
+                                                total_kv=n, batch=batch,
+                                                flags=B.CP_SHAPE_UNIQUE_BID), B.CP_WS_DECODE)
+                    for n in sizes]
+            assert need == sorted(need)
+        for total_q in (5, 300, 1023):   # bounds in LDS up to 960 blocks of 32 keys
+            small = [B.cp_workspace_bytes(_shape(n_q_heads=nh, n_kv_heads=nkv, total_q=total_q,
+                                                 total_kv=n), B.CP_WS_PARTIAL)
+                     for n in (1, 768, 800, 20000, 30720)]
+            for n in (30721, 65536, 131072):
+                assert B.cp_workspace_bytes(_shape(n_q_heads=nh, n_kv_heads=nkv, total_q=total_q,
+                                                   total_kv=n), B.CP_WS_PARTIAL) >= max(small)
+
+
 def test_ring_descriptor_validation(lib):
     d = B.cp_ring_desc()
     assert lib.cp_ring_passkv(None, None) == -1
