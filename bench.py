@@ -4,14 +4,13 @@
 One "step" is one pass of the whole hot path over one batch of synthetic input: for the
 default workload (Llama3-405B per-GPU head shape, 128K full prefill, pass-KV) that is the
 complete ring of Algorithm 2 over all 16 virtual CP ranks: every rank's queries against the
-16 load-balanced KV shards in ring order, merged with Equation 4. The headline runs a rank's
-16 ring steps inside one launch (running softmax state in registers, every shard behind an
-arrival flag); `aux` also times a launch per ring step with the merge in the attention
-epilogues, and with 16 stored partials and a separate merge kernel per rank. Inputs are
-resident in HBM before the timed region.
+16 load-balanced KV shards in ring order, merged with Equation 4. The headline runs the ring
+steps of all ranks inside one launch (running softmax state in registers, every shard behind an
+arrival flag); `aux` also times a launch per ring step into stored partials, with their merge.
+Inputs are resident in HBM before the timed region.
 
 Prints ONE JSON line. `value` is causal-effective TFLOP/s (4 * d * N_H * visible pairs).
-`roofline` describes the dominant kernel (the bf16 MFMA attention kernel walking a rank's
+`roofline` describes the dominant kernel (the bf16 MFMA attention kernel walking the
 ring), timed with HIP events around whole driver calls in a second pass (median of the
 timed steps; mean, minimum and maximum beside it). `cpu_baseline` times the fp64 oracle on a
 bounded sample of the same workload. `aux` carries the other configurations, each with a
@@ -104,18 +103,14 @@ def build_prefill(w: W.Workload):
     vs = [v[i].contiguous() for i in idx]
     del q
     ps = [_i32(p) for p in pos]
-    # Headline: every rank's N ring steps walked inside ONE launch (running softmax state in
+    # Headline: the N ring steps of all ranks walked inside ONE launch (running softmax state in
     # registers, so Equation 4 is applied inside the online softmax; shards visited in ring
     # order, each behind its arrival flag - all set here, the shards being resident).
     flags = [torch.ones(n, dtype=torch.int32, device="cuda") for _ in range(n)]
     ring = B.Ring(qs, ks, vs, ps, ps, out_dtype=torch.bfloat16, fused_merge=2, arrived=flags)
-    # one launch per ring step, the merge in the attention epilogues (one running fp32 (O, LSE)
-    # per rank). One stream: with the drivers' optional second stream consecutive launches
-    # overlap, which gains under 1 % here and makes per-kernel durations in a trace meaningless.
-    steps = B.Ring(qs, ks, vs, ps, ps, out_dtype=torch.bfloat16, fused_merge=True)
     # scratch for the per-call measurements: 16 fp32 partials and their separate merge
     parts = B.Ring(qs, ks, vs, ps, ps, out_dtype=torch.bfloat16, part_dtype=torch.float32)
-    return dict(ring=ring, steps=steps, parts=parts, pos=pos, qs=qs, ks=ks, vs=vs, ps=ps, k_full=k, v_full=v)
+    return dict(ring=ring, parts=parts, pos=pos, qs=qs, ks=ks, vs=vs, ps=ps, k_full=k, v_full=v)
 
 
 def time_steps(fn, steps: int, warmup: int) -> float:
@@ -280,25 +275,18 @@ def bench_decode(w: W.Workload, reps: int = 20, graph: bool = True, probe_only: 
     ts = event_times(lambda: B.cp_ring_passq_decode(gring), reps, 3)
     us_rank = float(np.median(ts)) * 1e3 / n
     res = dict(workload=w.name, kv_mb_per_rank=round(kv_bytes / n / 1e6, 4),
-               launches="per KV holder one decode_flat_kernel over all 32 queries (sequence ids "
-                        "unique: CP_SHAPE_UNIQUE_BID); one decode_flat_merge_kernel over splits "
-                        "x holders for the whole ring",
+               launches="one decode_flat_kernel over all 32 queries and the KV of all holders "
+                        "(sequence ids unique: CP_SHAPE_UNIQUE_BID); one "
+                        "decode_flat_merge_kernel over splits x holders",
                ms_per_rank=round(us_rank / 1e3, 5), gbs=round(ring_bytes / n / us_rank / 1e3, 1),
                frac_hbm=round(ring_bytes / n / us_rank / 1e3 / PEAK_HBM_GBS, 4),
                per_rank=spread(ts, n))
     t_kernel = stored_traffic("decode_flat_kernel", w.name)
     t_merge = stored_traffic("decode_flat_merge_kernel", w.name)
     res["roofline"] = roofline_block(
-        "hbm", "decode_flat_kernel (+ 1/16 of the ring's decode_flat_merge_kernel)",
-        ring_bytes / n, us_rank,
-        None if t_kernel is None or t_merge is None else t_kernel + t_merge / n)
-    k_us = stored_kernel_us("cp::decode_flat_kernel", "512x1x1")
-    if k_us is not None:
-        res["kernel_alone"] = {
-            "kernel": "decode_flat_kernel", "us_per_launch": round(k_us, 2),
-            "frac_hbm": round(ring_bytes / n / k_us / 1e3 / PEAK_HBM_GBS, 4),
-            "source": "profiles/bench_default_run_kernel_stats.txt (rocprofv3 kernel trace of "
-                      "the default run, stored in the repository; not measured in this run)"}
+        "hbm", "decode_flat_kernel + decode_flat_merge_kernel (the ring of 16 holders)",
+        ring_bytes, us_rank * n,
+        None if t_kernel is None or t_merge is None else t_kernel + t_merge)
     ref = gring.out_all.clone()
     if graph:
         # the same ring replayed from one HIP graph (the paper runs decode under graphs,
@@ -439,10 +427,9 @@ def bench_partial_prefill(names, reps: int = 5, cpu: bool = False):
         for label, fn in (("passq", B.cp_ring_passq), ("passkv", B.cp_ring_passkv)):
             sec = time_steps(lambda: fn(ring), reps, 2)
             row[label + "_ms_per_ring"] = round(sec * 1e3, 3)
-            row[label + "_us_per_call"] = round(sec * 1e6 / (n * n), 2)
             row[label + "_tflops"] = round(flop / sec / 1e12, 1)
-        # pass-Q with the (small) query shards gathered: one call per KV holder answers all
-        # 16 steps, then the same 16 merges
+        # pass-Q with the (small) query shards gathered: every KV holder answers all 16 steps, the
+        # holders' results kept apart as All2All messages, one merge launch
         m = len(qpos[0])
         q_all = take(q, np.concatenate(qpos) - p_cached)
         qpos_all = _i32(np.concatenate(qpos))
@@ -454,21 +441,21 @@ def bench_partial_prefill(names, reps: int = 5, cpu: bool = False):
         row["passq_gathered_ms_per_ring"] = round(sec * 1e3, 3)
         row["passq_gathered_us_per_rank"] = round(sec * 1e6 / n, 2)
         row["passq_gathered_tflops"] = round(flop / sec / 1e12, 1)
-        # Roofline of the gathered call of one KV holder (+ 1/16 of the one merge launch).
+        # Roofline of the gathered ring per KV holder (1/16 of its launches, merge included).
         # The arithmetic intensity is (T/N) * 16 FLOP per KV byte: memory-bound at T = 128
         # (every holder reads its 4.2 MB of K and V once), matrix-bound from T = 1024 on.
         kv_bytes_rank = sum(int(t.numel()) * 2 * 2 for t in ring.tensors[1]) / n
         io_bytes_rank = t_new * w.n_q_heads * w.head_dim * 2 + \
             (t_new // n) * w.n_q_heads * (w.head_dim * 2 + 4)
-        kern = "prefill_mfma_kernel (KV axis split over grid.z) + merge_split_kernel"
+        kern = "prefill_mfma_kernel (all holders in one launch) + merge_table_kernel"
         if t_new * 16 / n < 315:
             row["roofline"] = roofline_block("hbm", kern, kv_bytes_rank + io_bytes_rank,
                                              sec * 1e6 / n)
         else:
             row["roofline"] = roofline_block("mfma", kern, flop / n, sec * 1e6 / n)
-        row["roofline_literal_step"] = roofline_block(
-            "mfma", kern + ", one launch per ring step (Algorithm 3 as printed)",
-            flop / (n * n), row["passq_us_per_call"])
+        row["roofline_passq_ring"] = roofline_block(
+            "mfma", "prefill_mfma_kernel, the ring's steps inside one launch (Algorithm 3)",
+            flop, row["passq_ms_per_ring"] * 1e3)
         row["passq_gathered_max_abs_diff"] = round(max(
             float((a.float() - b.float()).abs().max()) for a, b in zip(gring.out, ring.out)), 5)
         if cpu and t_new <= 128:
@@ -593,10 +580,10 @@ def hbm_read_probe(nbytes: int, n_buffers: int = 16, reps: int = 5):
     return out
 
 
-def pmc_probe(st):
+def pmc_probe(w, st):
     """The work the counter runs profile: a streaming kernel that reads and writes
-    PROBE_COPY_BYTES (the scale reference), one pass-KV ring pass in one launch per rank, one
-    with a launch per step and stored partials (and their merge), one decode pass."""
+    PROBE_COPY_BYTES (the scale reference), one pass-KV ring pass, the same with a launch
+    per step and stored partials (and their merge), one decode pass."""
     src = torch.ones(PROBE_COPY_BYTES // 4, dtype=torch.float32, device="cuda")
     dst = torch.empty_like(src)
     for _ in range(3):
@@ -604,23 +591,9 @@ def pmc_probe(st):
     torch.cuda.synchronize()
     B.cp_ring_passkv(st["ring"])
     torch.cuda.synchronize()
-    B.cp_ring_passkv(st["parts"])
-    torch.cuda.synchronize()
+    kernel_pass_prefill(w, st, ranks=list(range(w.n_ranks)))
     bench_decode(W.WORKLOADS["decode_b32"], probe_only=True)
     print("pmc probe done")
-
-
-def stored_kernel_us(kernel: str, grid: str):
-    """Average duration (us) of a kernel and grid in the committed kernel-trace summary of the
-    default bench run, or None."""
-    path = os.path.join(ROOT, "profiles", "bench_default_run_kernel_stats.txt")
-    if not os.path.exists(path):
-        return None
-    for line in open(path):
-        f = line.split()
-        if len(f) >= 5 and f[0] == kernel and f[1] == grid:
-            return float(f[4]) / 1e3
-    return None
 
 
 def stored_traffic(kernel: str, workload: str):
@@ -716,18 +689,17 @@ def main():
     st = build_prefill(w)
     ring = st["ring"]
     if args.pmc_probe:
-        pmc_probe(st)
+        pmc_probe(w, st)
         return
     sec = time_steps(lambda: B.cp_ring_passkv(ring), args.steps, args.warmup)
     t = w.t_new
     flop_step = 4.0 * w.head_dim * w.n_q_heads * (t * (t + 1) // 2)
     tflops = flop_step / sec / 1e12
 
-    # dominant kernel: the ring walk, one launch per rank; HIP events around a whole driver call
-    # (16 launches and one tile-bound pre-pass over all shards), once per timed step
+    # dominant kernel: the ring walk, one launch over all ranks; HIP events around a whole driver
+    # call (that launch and the position-bound pre-pass over all shards), once per timed step
     walk_ms = event_times(lambda: B.cp_ring_passkv(ring), args.steps, 0)
-    us_per_launch = float(np.median(walk_ms)) * 1e3 / w.n_ranks
-    flop_per_launch = flop_step / w.n_ranks     # every rank sees the same number of pairs
+    us_per_launch = float(np.median(walk_ms)) * 1e3
     kp = kernel_pass_prefill(w, st, ranks=list(range(w.n_ranks)))
     result = {
         "metric": "per-rank partial-attn+merge TFLOP/s (% bf16 MFMA peak); decode HBM GB/s",
@@ -737,18 +709,18 @@ def main():
         "config": {"workload": w.name, "order": "pass-KV", "virtual_ranks": w.n_ranks,
                    "tokens": t, "n_q_heads": w.n_q_heads, "n_kv_heads": w.n_kv_heads,
                    "head_dim": w.head_dim,
-                   "launches": "one per rank: its 16 ring steps are walked inside the kernel, "
-                               "each shard behind an arrival flag (all set: shards resident)",
+                   "launches": "one over all ranks: every rank's 16 ring steps are walked inside "
+                               "the kernel, each shard behind an arrival flag (all set: shards "
+                               "resident)",
                    "merge": "Equation 4 inside the online softmax (running state in registers)",
                    "flops": "causal-effective 4*d*N_H*pairs",
                    "ms_per_rank": round(sec * 1e3 / w.n_ranks, 3)},
         "frac_of_peak": round(tflops / PEAK_BF16_TFLOPS, 4),
         "roofline": roofline_block(
-            "mfma", "prefill_ring_walk_kernel", flop_per_launch, us_per_launch,
+            "mfma", "prefill_ring_walk_kernel", flop_step, us_per_launch,
             stored_traffic("prefill_ring_walk_kernel", w.name),
-            launches=w.n_ranks * args.steps, per_launch=spread(walk_ms, w.n_ranks),
-            timing="median over the timed steps of a HIP-event pair around one driver call "
-                   "(16 launches), divided by 16"),
+            launches=args.steps, per_launch=spread(walk_ms),
+            timing="median over the timed steps of a HIP-event pair around one driver call"),
         "aux": {},
     }
     aux = result["aux"]
@@ -770,32 +742,7 @@ def main():
                                    stored_traffic("merge_kernel_ring", w.name))}
     aux["per_call"] = per_call_prefill(w, st)
     if not args.no_aux and w.name == "prefill_128k":
-        # a launch per ring step with stored partials and the merge kernel: fp32 partials, and
-        # bf16 partials (the width the paper's All2All model assumes)
-        parts = st["parts"]
-        secp = time_steps(lambda: B.cp_ring_passkv(parts), args.steps, args.warmup)
-        aux["ring_separate_merge_fp32_partials"] = {
-            "tflops": round(flop_step / secp / 1e12, 2),
-            "frac_of_peak": round(flop_step / secp / 1e12 / PEAK_BF16_TFLOPS, 4),
-            "ms_per_rank": round(secp * 1e3 / w.n_ranks, 3)}
-        ring16 = B.Ring(st["qs"], st["ks"], st["vs"], st["ps"], st["ps"], out_dtype=torch.bfloat16,
-                        part_dtype=torch.bfloat16)
-        sec16 = time_steps(lambda: B.cp_ring_passkv(ring16), args.steps, args.warmup)
-        aux["ring_separate_merge_bf16_partials"] = {
-            "tflops": round(flop_step / sec16 / 1e12, 2),
-            "frac_of_peak": round(flop_step / sec16 / 1e12 / PEAK_BF16_TFLOPS, 4),
-            "ms_per_rank": round(sec16 * 1e3 / w.n_ranks, 3)}
-        del ring16
-        # one launch per ring step, Equation 4 in the attention epilogues
-        stp = st["steps"]
-        secs = time_steps(lambda: B.cp_ring_passkv(stp), args.steps, args.warmup)
-        aux["ring_launch_per_step_merge_in_epilogues"] = {
-            "tflops": round(flop_step / secs / 1e12, 2),
-            "frac_of_peak": round(flop_step / secs / 1e12 / PEAK_BF16_TFLOPS, 4),
-            "ms_per_rank": round(secs * 1e3 / w.n_ranks, 3),
-            "max_abs_diff_vs_headline": round(max(
-                float((a.float() - b.float()).abs().max()) for a, b in zip(stp.out, ring.out)), 5)}
-        # the headline's walk without arrival flags
+        # the same ring without arrival flags: the visible blocks of all shards in one list
         walk = B.Ring(st["qs"], st["ks"], st["vs"], st["ps"], st["ps"], out_dtype=torch.bfloat16,
                       fused_merge=2)
         tw = event_times(lambda: B.cp_ring_passkv(walk), args.steps, 2)

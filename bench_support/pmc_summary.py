@@ -28,7 +28,7 @@ KERNELS = [("prefill_ring_walk_kernel", "prefill_ring_walk_kernel"),
            ("prefill_mfma_kernel", "prefill_mfma_kernel"),
            ("decode_flat_merge_kernel", "decode_flat_merge_kernel"),
            ("decode_flat_kernel", "decode_flat_kernel"), ("decode_kernel", "decode_kernel"),
-           ("merge_split_kernel", "merge_kernel_split"), ("merge_kernel", "merge_kernel_ring")]
+           ("plan_merge_kernel", "plan_merge_kernel"), ("merge_kernel", "merge_kernel_ring")]
 COPY_MARK = "MulFunctor"
 
 
@@ -131,6 +131,7 @@ def short_name(name: str) -> str:
     name = name.replace("(anonymous namespace)::", "")
     if name.startswith("void "):
         name = name[5:]
+    name = name.replace("(cp::Mode)", "")
     cut = name.find("(")
     return name if cut < 0 else name[:cut]
 
@@ -171,23 +172,22 @@ def stats_main():
                     if isinstance(e, dict):
                         tag = e.get("workload", k)
                         block("aux.%s[%s].roofline" % (k, tag), e.get("roofline"))
-                        block("aux.%s[%s].roofline_literal_step" % (k, tag),
-                              e.get("roofline_literal_step"))
+                        block("aux.%s[%s].roofline_passq_ring" % (k, tag),
+                              e.get("roofline_passq_ring"))
         # The headline's timed region: bench.py's first calls of the ring walk are the warm-up
-        # steps, then the timed steps, one launch per virtual rank each.
-        n_ranks = line.get("config", {}).get("virtual_ranks", 0)
+        # steps, then the timed steps, one launch each.
         head = [(k, v) for k, v in in_order.items() if "prefill_ring_walk_kernel" in k[0]]
-        if n_ranks and head:
+        if head:
             key, seq = max(head, key=lambda kv: len(kv[1]))
             seq.sort()
-            lo, hi = line["warmup"] * n_ranks, (line["warmup"] + line["steps"]) * n_ranks
+            lo, hi = line["warmup"], line["warmup"] + line["steps"]
             timed = [d for _, d in seq[lo:hi]]
             if len(timed) == hi - lo:
                 avg = sum(timed) / len(timed)
                 f.write("\ntimed region of the headline (launches %d..%d of %s in dispatch order): "
-                        "avg %.1f us, min %.1f, max %.1f; %d x avg = %.3f ms of ms_per_step %.3f\n"
+                        "avg %.1f us, min %.1f, max %.1f; ms_per_step %.3f\n"
                         % (lo + 1, hi, key[0], avg / 1e3, min(timed) / 1e3, max(timed) / 1e3,
-                           n_ranks, n_ranks * avg / 1e6, line["ms_per_step"]))
+                           line["ms_per_step"]))
         f.write("\nper-kernel durations of the same process (rocprofv3 kernel trace), one row per "
                 "kernel and grid (workgroups x, y, z):\n")
         f.write("%-64s %-16s %7s %14s %11s %11s %7s %11s %11s\n"
@@ -213,8 +213,7 @@ def main():
     copy_bytes = 1 << 28
     rd = per_dispatch(fetch_csv, "FETCH_SIZE")
     wr = per_dispatch(write_csv, "WRITE_SIZE")
-    rd_copy = sum(rd["copy"]) / len(rd["copy"])
-    wr_copy = sum(wr["copy"]) / len(wr["copy"])
+    rd_copy, wr_copy = max(rd["copy"]), max(wr["copy"])   # (smaller products run beside it)
     f_rd = copy_bytes / rd_copy   # bytes per counter unit
     f_wr = copy_bytes / wr_copy
     for tag in sorted(set(rd) | set(wr)):
