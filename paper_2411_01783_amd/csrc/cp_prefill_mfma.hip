@@ -56,7 +56,7 @@ constexpr int kPlanWorkgroups = 256;      // one per CU
 constexpr int kUnitCost = 3;              // start-up and epilogue of a unit, in tile steps
 constexpr float kRescaleSlack = 8.f;               // log2 units
 constexpr float kOverflowSum = 1099511627776.f;    // 2^40: a block sum beyond it is redone
-constexpr float kDeadRowRef = 1e30f;               // reference of a row that sees no key
+constexpr float kDeadRowRef = INFINITY;            // reference of a row that sees no key
 
 struct Params {
   AttnTable t;            // queries and outputs per rank, KV per shard

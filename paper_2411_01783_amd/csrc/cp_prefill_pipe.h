@@ -186,9 +186,10 @@ __device__ __forceinline__ void pipe_body(PipeRegs<D>& R, const bf16x8_t (&qf)[D
   // standing reference, whatever the block holds; the reference is never above a score the row
   // has seen, so nothing underflows that should not, and a block whose exponentials sum to more
   // than kOverflowSum (a score 40 log2 units above the reference) is detected from its sum and
-  // redone in the full form. A block that straddles a query position is masked first
-  // (need_mask); one that no row of this wavefront can see (dead: the workgroup's other
-  // wavefronts can) is taken against an infinite reference, i.e. as zeros.
+  // redone in the full form, for the rows concerned. A block that straddles a query position is
+  // masked first (need_mask), and so is, without a look at its positions, one that no row of this
+  // wavefront can see (dead: the workgroup's other wavefronts can): whatever form the block takes,
+  // a score that its row must not see is -inf in it.
   // Full form (until every row of the wavefront has a reference): block maximum, and the
   // reference is raised when the maximum exceeds it by more than kRescaleSlack. O and l are
   // rescaled at the end of the step, after the MFMAs that still belong to the old reference. The
@@ -223,34 +224,35 @@ __device__ __forceinline__ void pipe_body(PipeRegs<D>& R, const bf16x8_t (&qf)[D
       m_use = R.m_run;
       if (__builtin_expect(need_mask | !have_ref, 0)) {  // wave-uniform, rare: off the hot path
         if (dead) {
-          m_use = INFINITY;
-        } else {
-          if (need_mask) {
-            // The kv_pos reads are simply waited for (which also completes every older LDS read,
-            // so the counted waits hold).
-            u32x4_t kp0 = lds_read_b128<POFF + 0>(paddr), kp1 = lds_read_b128<POFF + 32>(paddr);
-            u32x4_t kp2 = lds_read_b128<POFF + 64>(paddr), kp3 = lds_read_b128<POFF + 96>(paddr);
-            lgkm_wait<0>(kp0, kp1, kp2, kp3);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const int32_t k0 = (int32_t)kp0[r], k1 = (int32_t)kp1[r];
-              const int32_t k2 = (int32_t)kp2[r], k3 = (int32_t)kp3[r];
-              if (k0 > qp || (BAND && k0 < ql)) s[0 + r] = -INFINITY;
-              if (k1 > qp || (BAND && k1 < ql)) s[4 + r] = -INFINITY;
-              if (k2 > qp || (BAND && k2 < ql)) s[8 + r] = -INFINITY;
-              if (k3 > qp || (BAND && k3 < ql)) s[12 + r] = -INFINITY;
-            }
+          for (int i = 0; i < 16; ++i) s[i] = -INFINITY;
+        } else if (need_mask) {
+          // The kv_pos reads are simply waited for (which also completes every older LDS read,
+          // so the counted waits hold).
+          u32x4_t kp0 = lds_read_b128<POFF + 0>(paddr), kp1 = lds_read_b128<POFF + 32>(paddr);
+          u32x4_t kp2 = lds_read_b128<POFF + 64>(paddr), kp3 = lds_read_b128<POFF + 96>(paddr);
+          lgkm_wait<0>(kp0, kp1, kp2, kp3);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int32_t k0 = (int32_t)kp0[r], k1 = (int32_t)kp1[r];
+            const int32_t k2 = (int32_t)kp2[r], k3 = (int32_t)kp3[r];
+            if (k0 > qp || (BAND && k0 < ql)) s[0 + r] = -INFINITY;
+            if (k1 > qp || (BAND && k1 < ql)) s[4 + r] = -INFINITY;
+            if (k2 > qp || (BAND && k2 < ql)) s[8 + r] = -INFINITY;
+            if (k3 > qp || (BAND && k3 < ql)) s[12 + r] = -INFINITY;
           }
-          if (!have_ref) {
-            const float m_step = block_max() * scale_log2;
-            raise = m_step > R.m_run + kRescaleSlack;  // true on the first visible block
-            const float m_new = raise ? m_step : R.m_run;
-            alpha = __builtin_amdgcn_exp2f(R.m_run - (m_new == -INFINITY ? 0.f : m_new));
-            R.l_run *= alpha;
-            R.m_run = m_new;
-            m_use = m_new == -INFINITY ? 0.f : m_new;
-            have_ref = __builtin_amdgcn_ballot_w64(m_new == -INFINITY) == 0;
-          }
+        }
+        if (!have_ref) {
+          const float m_step = block_max() * scale_log2;
+          // true on the first visible block, also if its scores are NaN: such a row is lost, and
+          // must not keep the others of its wavefront on the full form
+          raise = !(m_step <= R.m_run + kRescaleSlack);
+          const float m_new = raise ? m_step : R.m_run;
+          alpha = __builtin_amdgcn_exp2f(R.m_run - (m_new == -INFINITY ? 0.f : m_new));
+          R.l_run *= alpha;
+          R.m_run = m_new;
+          m_use = m_new == -INFINITY ? 0.f : m_new;
+          have_ref = __builtin_amdgcn_ballot_w64(m_new == -INFINITY) == 0;
         }
       }
       pin(m_use);
@@ -318,11 +320,16 @@ __device__ __forceinline__ void pipe_body(PipeRegs<D>& R, const bf16x8_t (&qf)[D
   second(IntC<4>{}); second(IntC<5>{}); second(IntC<6>{}); second(IntC<7>{});
 
   // A block of the fast form whose exponentials ran away from the reference (rare): redo
-  // its softmax in the full form. No row's sum can pass the test with an infinity or a NaN.
+  // its softmax in the full form, with a new reference for the rows that did and the same result
+  // for the others. No row's sum can pass the test with an infinity or a NaN; a row whose
+  // reference has become one is lost, and is not looked at again.
   float blk = lsum0 + lsum1;
-  if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(blk <= kOverflowSum)) != 0, 0)) {
+  const bool over = !(blk <= kOverflowSum) && R.m_run < INFINITY;
+  if (__builtin_expect(__builtin_amdgcn_ballot_w64(over) != 0, 0)) {
+    const float over_f = over ? 1.f : 0.f;
+    const bool row_over = over_f + xor32(over_f) > 0.f;   // in either half of the row's keys
     const float m_step = block_max() * scale_log2;
-    const float m_new = fmaxf(R.m_run, m_step);
+    const float m_new = row_over ? fmaxf(R.m_run, m_step) : R.m_run;
     m_use = m_new == -INFINITY ? 0.f : m_new;
     const float a2 = __builtin_amdgcn_exp2f(R.m_run - m_use);
     R.l_run *= a2;
@@ -832,10 +839,11 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
 
     bool have_ref = false;  // every row of the wavefront has a finite reference maximum
     PipeRegs<D> R;
-    // Reference max of scaled scores (log2 domain). A row that can see nothing gets a finite
-    // reference no score reaches: its exponentials are all zero whichever softmax form its
-    // wavefront takes (so one padded row does not keep the other 31 on the masked form), its
-    // denominator stays zero, and the epilogue writes O = 0, LSE = -inf for it.
+    // Reference max of scaled scores (log2 domain). A row that can see nothing gets a reference
+    // no score reaches: its exponentials are all zero whichever softmax form its
+    // wavefront takes (so one padded row does not keep the other 31 on the masked form), or NaN if
+    // its query is not finite, which nothing says of a padded one. The epilogue writes O = 0,
+    // LSE = -inf for it.
     R.m_run = sees ? -INFINITY : kDeadRowRef;
     R.l_run = 0.f;        // running denominator over this lane's half of the keys
 #pragma unroll
@@ -1129,7 +1137,9 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
     }
 
     // ---- epilogue ----
-    const float l_tot = R.l_run + xor32(R.l_run);
+    const float l_sum = R.l_run + xor32(R.l_run);
+    const float l_tot = sees ? l_sum : 0.f;
+    const bool no_key = l_tot == 0.f;
     float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
     const float lse_val =
         l_tot > 0.f ? (R.m_run + __builtin_amdgcn_logf(l_tot)) * kLn2 : -INFINITY;
@@ -1202,6 +1212,7 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
         const int d0 = db * 32 + i4 * 8 + g * 4;
         floatx4_t w = {R.o[db][i4 * 4 + 0] * inv, R.o[db][i4 * 4 + 1] * inv,
                        R.o[db][i4 * 4 + 2] * inv, R.o[db][i4 * 4 + 3] * inv};
+        if (no_key) w = floatx4_t{0.f, 0.f, 0.f, 0.f};   // (O may be NaN there)
         *(floatx4_t*)(stage + n * G::OUT_STRIDE + d0 * 4) = w;
       }
     wave_lds_fence();
