@@ -9,7 +9,7 @@
 //
 // The KV axis is consumed in blocks of 32 keys and each wavefront runs three stages at
 // once, one block apart:
-//     P(i-1):  O^T += V^T P^T of the previous block        (D / 16 MFMA, matrix pipe)
+//     P(i-1):  O^T += V^T P^T of the previous block        (D / 16 MFMA, matrix pipe; 12 at D = 64)
 //     SM(i):   mask, row maximum, exponentials of block i   (vector pipe)
 //     Q(i+1):  S^T = K Q^T of the next block                (D / 16 MFMA, matrix pipe)
 // The three are independent, so the vector work is issued between the MFMAs of its
@@ -43,6 +43,9 @@ struct Geo {
   static constexpr int NKS = D / 16;             // MFMAs of S^T per block, K fragments
   static constexpr int NDB = D / 32;             // 32-channel blocks of O^T
   static constexpr int NVF = 2 * NDB;            // MFMAs of O^T per block, V^T fragments
+  // bf16 terms of a probability. head_dim 64: three, which hold all 24 bits of the fp32 value (the
+  // products with V are exact and summed in fp32: nothing is rounded to 16 bits). head_dim 128: one.
+  static constexpr int TERMS = D == 64 ? 3 : 1;
   static constexpr int CHUNKS = ROW / 16;        // 16-byte chunks of a row
   static constexpr int LOAD_ROWS = 64 / CHUNKS;  // rows one 1 KiB load instruction brings
   static constexpr int PARTS = 16 / LOAD_ROWS;   // load instructions per wavefront for K (or V)
@@ -137,7 +140,8 @@ template <int D>
 struct PipeRegs {
   floatx16_t o[D / 32];    // O^T accumulators, blocks of 32 channels
   floatx16_t s[2];         // scores of block i (index: parity of i) and of block i+1
-  u32x4_t pb[2][2];        // probabilities (bf16 pairs) of block i (parity of i) / i-1, two 16-key slices
+  // probabilities (bf16 pairs, per term) of block i (parity of i) / i-1, two 16-key slices
+  u32x4_t pb[2][Geo<D>::TERMS][2];
   u32x4_t kf[D / 16];      // K fragments of block i+1
   u32x4_t vf[D / 16];      // V^T fragments of block i-1
   float m_run, l_run;
@@ -208,10 +212,18 @@ __device__ __forceinline__ void pipe_body(PipeRegs<D>& R, const bf16x8_t (&qf)[D
   auto finish = [&](int v) __attribute__((always_inline)) {
     if (v & 1) {
       lsum1 += e[v];
-      unsigned pk = pack_bf16(e[v - 1], e[v]);
-      pin(pk);
+      float a = e[v - 1], b = e[v];
+#pragma unroll
+      for (int t = 0; t < G::TERMS; ++t) {
+        unsigned pk = pack_bf16(a, b);
+        if (t + 1 < G::TERMS) {   // what the term leaves over (exact)
+          a -= __builtin_bit_cast(float, pk << 16);
+          b -= __builtin_bit_cast(float, pk & 0xffff0000u);
+        }
+        pin(pk);
+        R.pb[CUR][t][v >> 3][(v & 7) >> 1] = pk;
+      }
       pin(lsum1);
-      R.pb[CUR][v >> 3][(v & 7) >> 1] = pk;
     } else {
       lsum0 += e[v];
       pin(lsum0);
@@ -284,9 +296,11 @@ __device__ __forceinline__ void pipe_body(PipeRegs<D>& R, const bf16x8_t (&qf)[D
       // LDS operations issued after V fragment M: H - 1 - M later V fragments (two reads each)
       // and M K fragments
       lgkm_wait<2 * (H - 1 - M) + M>(R.vf[M]);
-      R.o[M % G::NDB] = mfma32(__builtin_bit_cast(bf16x8_t, R.vf[M]),
-                               __builtin_bit_cast(bf16x8_t, R.pb[NXT][M / G::NDB]),
-                               R.o[M % G::NDB]);
+#pragma unroll
+      for (int t = 0; t < G::TERMS; ++t)
+        R.o[M % G::NDB] = mfma32(__builtin_bit_cast(bf16x8_t, R.vf[M]),
+                                 __builtin_bit_cast(bf16x8_t, R.pb[NXT][t][M / G::NDB]),
+                                 R.o[M % G::NDB]);
       R.kf[M] = lds_read_b128<KOFF>(kaddr[M]);
       hook(IntC<M>{});
       slices(IntC<M>{});
@@ -818,7 +832,8 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
     // ---- query position range of the wavefront and of the workgroup ----
     // rows that can see anything: a padded query (CP_POS_PAD_Q) and the rows past the end of
     // the shard cannot, and stay out of the ranges below
-    const bool sees = row_ok && qp >= 0;
+    // (head_dim 64: any position but the padding's, as on the vector kernel)
+    const bool sees = row_ok && (D == 64 ? qp != CP_POS_PAD_Q : qp >= 0);
     const int w_qmin = wave_min(sees ? qp : INT32_MAX), w_qmax = wave_max(qp);
     const int w_lomin = BAND ? wave_min(sees ? ql : INT32_MAX) : 0;
     const int w_lomax = BAND ? wave_max(sees ? ql : INT32_MIN) : 0;
@@ -1063,7 +1078,9 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
 #pragma unroll
           for (int m = 0; m < G::NVF; ++m) R.vf[m] = lds_read_vt_frag<0, ROW>(vaddr[m % G::NDB]);
 #pragma unroll
-          for (int i = 0; i < 4; ++i) R.pb[1][0][i] = R.pb[1][1][i] = 0u;
+          for (int t = 0; t < G::TERMS; ++t)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) R.pb[1][t][0][i] = R.pb[1][t][1][i] = 0u;
           __builtin_amdgcn_sched_barrier(0);
         }
 
@@ -1116,9 +1133,11 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
             constexpr int M = decltype(mc)::value;
             if constexpr (M < G::NVF) {
               lgkm_wait<2 * (G::NVF - 1 - M)>(R.vf[M]);
-              R.o[M % G::NDB] = mfma32(__builtin_bit_cast(bf16x8_t, R.vf[M]),
-                                       __builtin_bit_cast(bf16x8_t, R.pb[1][M / G::NDB]),
-                                       R.o[M % G::NDB]);
+#pragma unroll
+              for (int t = 0; t < G::TERMS; ++t)
+                R.o[M % G::NDB] = mfma32(__builtin_bit_cast(bf16x8_t, R.vf[M]),
+                                         __builtin_bit_cast(bf16x8_t, R.pb[1][t][M / G::NDB]),
+                                         R.o[M % G::NDB]);
             }
           };
           last(IntC<0>{}); last(IntC<1>{}); last(IntC<2>{}); last(IntC<3>{});

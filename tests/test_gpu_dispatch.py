@@ -9,7 +9,7 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_util import LSE_RTOL_FP32, O_ATOL_FP32, check, dev, i32, randn
+from gpu_util import LSE_RTOL_FP32, O_ATOL_FP32, check, dev, i32, randn, rel_l2
 from paper_2411_01783_amd import binding as B
 
 pytestmark = pytest.mark.gpu
@@ -212,3 +212,33 @@ def test_decode_ring_ranges(oracle, n, lengths, nh, nkv):
         else:
             ref_o, ref_l = oracle.attn(q64[i:i + 1], k64, v64, qp[i:i + 1], p)
         check(ring.out_all[i:i + 1], ring.lse_all[i:i + 1], ref_o, ref_l, what="sequence %d" % b)
+
+
+# bf16 inputs of head_dim 64: the probabilities keep their 24 bits, so that what separates an fp32
+# result from the exact one is fp32 sums over the keys. A sum of n terms in fp32 errs by about
+# 2^-24 sqrt(n) of its size; probabilities rounded to bf16 would err by 1e-3 whatever n.
+@pytest.mark.parametrize("kv_sizes,q_sizes,nh,nkv", [
+    ([300], [300], 8, 8),            # a workgroup per unit
+    ([769, 331], [140, 57], 16, 2),  # equal shares
+    ([420], [1040], 64, 1),          # more row blocks than CUs
+])
+def test_head_dim_64_keeps_fp32_probabilities(oracle, kv_sizes, q_sizes, nh, nkv):
+    case = ring_case(4700, kv_sizes, q_sizes, nh, nkv, 64)
+    out, _ = B.cp_ring_passkv(B.Ring(*case[0], out_dtype=torch.float32))
+    torch.cuda.synchronize()
+    _, rows, _, q_all, (q64, k64, v64) = case
+    ref_o, _ = oracle.attn(q64, k64, v64, q_all, np.arange(len(k64)))
+    err = rel_l2(torch.cat(out), np.concatenate([ref_o[r] for r in rows]))
+    assert err < 2.0 ** -24 * np.sqrt(sum(kv_sizes)), err
+
+
+# a position below zero that is not the padding's is a position like any other
+def test_head_dim_64_takes_negative_positions(oracle):
+    q, q64 = randn(4711, (40, 4, 64))
+    k, k64 = randn(4712, (90, 1, 64))
+    v, v64 = randn(4713, (90, 1, 64))
+    qp, kp = np.arange(40) - 30, np.arange(90) - 50
+    qp[qp == B.CP_POS_PAD_Q] = 5
+    o, l = B.cp_attn_partial(dev(q), dev(k), dev(v), i32(qp), i32(kp), out_dtype=torch.float32)
+    torch.cuda.synchronize()
+    check(o, l, *oracle.attn(q64, k64, v64, qp, kp))
