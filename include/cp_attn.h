@@ -32,6 +32,11 @@
  *     batches, both belong to the same sequence). Padding is expressed through
  *     positions: a padded KV slot carries CP_POS_PAD_KV, a padded query row
  *     carries CP_POS_PAD_Q.
+ *   - What a query does not see does not reach it: a NaN or infinity in another
+ *     query, in a padded one, or in a hidden K row. In cp_attn_partial,
+ *     cp_attn_partial_accumulate and the prefill rings without arrival flags that
+ *     holds for a hidden V row too; the decode calls and the walk behind arrival
+ *     flags multiply a hidden V by zero and need it finite.
  */
 #ifndef CP_ATTN_H
 #define CP_ATTN_H

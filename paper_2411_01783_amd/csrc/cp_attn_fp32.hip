@@ -247,7 +247,7 @@ __global__ __launch_bounds__(NTHREADS) void attn_fp32_kernel(const Params p) {
   for (int c = 0; c < NR; ++c) {
     const int row = c * 16 + tid / TPR, ch = (tid % TPR) * CPT;
     const int64_t r = (int64_t)row_block * ROWS + row;
-    if (r >= p.rows) continue;
+    const bool row_ok = r < p.rows;
     float mw[NWAVE], mmax = -INFINITY;
 #pragma unroll
     for (int w = 0; w < NWAVE; ++w) {
@@ -267,14 +267,48 @@ __global__ __launch_bounds__(NTHREADS) void attn_fp32_kernel(const Params p) {
       }
     }
     const float inv = den > 0.f ? 1.f / den : 0.f;
-    const int token = (int)((uint32_t)r / (uint32_t)p.group);
-    const int hg = (int)(r - (int64_t)token * p.group);
+    const int token = row_ok ? (int)((uint32_t)r / (uint32_t)p.group) : 0;
+    const int hg = row_ok ? (int)(r - (int64_t)token * p.group) : 0;
     const int a = rank_of_token(p.t, token);
     const int64_t lin =
         ((int64_t)(token - p.t.tok_begin[a]) * p.n_kv_heads + kvh) * p.group + hg;
-    TO* const o = (TO*)((char*)p.t.out[a] + z_shard * p.out_shard_bytes) + lin * D + ch;
+    char* const out0 = (char*)p.t.out[a] + z_shard * p.out_shard_bytes;
+    // Rows that a V they do not see has spoiled (see VectorRow).
+    float spoil = 0.f;   // stays zero if O is finite
 #pragma unroll
-    for (int i = 0; i < CPT; ++i) o[i] = from_float<TO>(x[i] * inv);
+    for (int i = 0; i < CPT; ++i) spoil = fmaf(x[i], 0.f, spoil);
+    uint64_t spoiled = __builtin_amdgcn_ballot_w64(row_ok && den > 0.f && den < INFINITY &&
+                                                   !(spoil == 0.f));
+    const bool mine = (spoiled >> (lane & ~(TPR - 1)) & ((1u << TPR) - 1)) != 0;
+    while (__builtin_expect(spoiled != 0, 0)) {
+      const int rl = __builtin_ctzll(spoiled) & ~(TPR - 1);   // first lane of the row
+      spoiled &= ~(((1ull << TPR) - 1) << rl);
+      const int ra = __builtin_amdgcn_readlane(a, rl);
+      const int64_t rlin = (int64_t)(
+          (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)lin, rl) |
+          (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(lin >> 32), rl) << 32);
+      VectorRow<float, D> vr;
+      vr.q = (const float*)p.t.q[ra] + rlin * D;
+      vr.scale_log2 = p.scale_log2;
+      vr.qp = p.t.q_pos[ra][__builtin_amdgcn_readlane(token, rl) - p.t.tok_begin[ra]];
+      vr.ql = INT32_MIN;
+      for (int sh = z_shard; sh < (p.per_shard ? z_shard + 1 : p.t.n_shards); ++sh)
+        for (int key0 = 0; key0 < p.t.n_kv[sh]; key0 += 64) {
+          const int64_t off = (int64_t)key0 * stride + kvh * D;
+          vr.keys((const float*)p.t.k[sh] + off, (const float*)p.t.v[sh] + off,
+                  p.t.kv_pos[sh] + key0, min(64, p.t.n_kv[sh] - key0), stride, lane);
+        }
+      TO* const o = (TO*)((char*)p.t.out[ra] + z_shard * p.out_shard_bytes) + rlin * D;
+#pragma unroll
+      for (int i = 0; i < D / 64; ++i)
+        o[lane * (D / 64) + i] = from_float<TO>(vr.acc[i] * (1.f / vr.l));
+    }
+    if (!row_ok) continue;
+    if (!mine) {
+      TO* const o = (TO*)out0 + lin * D + ch;
+#pragma unroll
+      for (int i = 0; i < CPT; ++i) o[i] = from_float<TO>(den > 0.f ? x[i] * inv : 0.f);
+    }
     if (tid % TPR == 0 && p.t.lse[a] != nullptr)
       p.t.lse[a][z_shard * p.lse_shard_elems + lin] =
           den > 0.f ? (mmax + __builtin_amdgcn_logf(den)) * kLn2 : -INFINITY;

@@ -1074,9 +1074,9 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
           for (int ks = 0; ks < G::NKS; ++ks)
             R.s[0] = mfma32(__builtin_bit_cast(bf16x8_t, R.kf[ks]), qf[ks], R.s[0]);
           __builtin_amdgcn_sched_barrier(0);
-          // stand-in V fragments for the empty P stage of the first step (finite data, P = 0)
+          // the empty P stage of the first step: V and P are zero
 #pragma unroll
-          for (int m = 0; m < G::NVF; ++m) R.vf[m] = lds_read_vt_frag<0, ROW>(vaddr[m % G::NDB]);
+          for (int m = 0; m < G::NVF; ++m) R.vf[m] = u32x4_t{0u, 0u, 0u, 0u};
 #pragma unroll
           for (int t = 0; t < G::TERMS; ++t)
 #pragma unroll
@@ -1196,6 +1196,20 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
       o_row = o + row_lin * (D * (int64_t)(MODE == SPLIT ? 4 : sizeof(TO)));
       if (l != nullptr) lse_row = l + row_lin;
     }
+    // Rows that a V they do not see has spoiled (see VectorRow). Not in the ring walk, whose main
+    // loop would pay for it with 200 spilled registers.
+    uint32_t spoiled = 0;
+    if constexpr (MODE != RING) {
+      float spoil = 0.f;   // stays zero if O is finite
+#pragma unroll
+      for (int db = 0; db < G::NDB; ++db)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) spoil = fmaf(R.o[db][i], 0.f, spoil);
+      spoil += xor32(spoil);
+      spoiled = (uint32_t)__builtin_amdgcn_ballot_w64(
+          row_ok && l_tot > 0.f && l_tot < INFINITY && !(spoil == 0.f));
+    }
+    float share_of_row = 1.f;   // ACC: weight of this step
     // ACC: weights of Equation 4 for the pair (running result, this step). a_old scales the
     // stored row, the step's row is scaled on its way into the staging buffer. A row the step
     // saw nothing of keeps its stored value (a_old = 1, nothing staged): it is not touched at
@@ -1209,7 +1223,8 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
       const float den = w_old + w_cur;
       const float rden = den > 0.f ? 1.f / den : 0.f;
       a_old = l_tot > 0.f ? w_old * rden : 1.f;
-      inv *= w_cur * rden;
+      share_of_row = w_cur * rden;
+      inv *= share_of_row;
       const float lse_new = den > 0.f ? m + __logf(den) : -INFINITY;
       if (row_ok && g == 0) {
         if (l_tot > 0.f) *lse_row = lse_new;
@@ -1235,6 +1250,42 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
         *(floatx4_t*)(stage + n * G::OUT_STRIDE + d0 * 4) = w;
       }
     wave_lds_fence();
+    if constexpr (MODE != RING) {
+      while (__builtin_expect(spoiled != 0, 0)) {
+        const int rr = __builtin_ctz(spoiled);
+        spoiled &= spoiled - 1;
+        const int row = row_block * BM + wave * 32 + rr;
+        int token = (int)((uint32_t)row / (uint32_t)p.group);
+        const int hg = row - token * p.group;
+        const int a = p.t.n_ranks > 1 ? rank_of_token(p.t, token) : 0;
+        token -= p.t.tok_begin[a];
+        VectorRow<bf16_t, D> vr;
+        vr.q = (const bf16_t*)p.t.q[a] + (((int64_t)token * p.n_kv_heads + kvh) * p.group + hg) * D;
+        vr.scale_log2 = scale_log2;
+        vr.qp = __builtin_amdgcn_readlane(qp, rr);
+        vr.ql = BAND ? __builtin_amdgcn_readlane(ql, rr) : INT32_MIN;
+        int sh = z_shard, idx = 0;
+        for (int c = b_begin; c < b_end; c += 64) {   // the blocks walked above
+          uint64_t mask = __builtin_amdgcn_ballot_w64(
+              c + lane < b_end && visible(block_bounds(min(c + lane, b_end - 1))));
+          for (; mask != 0; mask &= mask - 1, ++idx) {
+            if (idx < part_lo || idx >= part_hi) continue;
+            const int b = c + __builtin_ctzll(mask);
+            while (!one_shard && b >= p.t.blk_begin[sh + 1]) ++sh;
+            const int key0 = (b - p.t.blk_begin[sh]) * BLOCK;
+            const int64_t off = ((int64_t)key0 * p.n_kv_heads + kvh) * D;
+            vr.keys((const bf16_t*)p.t.k[sh] + off, (const bf16_t*)p.t.v[sh] + off,
+                    p.t.kv_pos[sh] + key0, min(BLOCK, p.t.n_kv[sh] - key0),
+                    (uint32_t)p.n_kv_heads * D, lane);
+          }
+        }
+        const float f = __shfl(share_of_row, rr, 64) / vr.l;
+#pragma unroll
+        for (int c = 0; c < D / 64; ++c)
+          ((float*)(stage + rr * G::OUT_STRIDE))[lane * (D / 64) + c] = vr.acc[c] * f;
+        wave_lds_fence();
+      }
+    }
     // (rows in order: row rr of the wavefront exists iff its lane's does)
     const uint64_t rows_ok = __builtin_amdgcn_ballot_w64(row_ok);
     auto row_address = [&](int rr) -> char* {

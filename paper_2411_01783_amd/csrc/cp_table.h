@@ -42,5 +42,55 @@ __device__ __forceinline__ int rank_of_token(const AttnTable& t, int tok) {
   return a;
 }
 
+// One query row on the vector pipe, a wavefront for it, reading V of the visible keys only. The
+// matrix pipe multiplies the V of a hidden key by a probability of zero, which is no zero if that
+// V is infinite or NaN: the kernels look at their finished rows (one test per row and walk) and
+// compute again, with this, those whose sum of probabilities is finite and whose O is not.
+template <typename T, int D>
+struct VectorRow {
+  const T* q;
+  float scale_log2;
+  int32_t qp, ql;   // visible: ql <= kv_pos <= qp
+  float m = -INFINITY, l = 0.f;
+  float acc[D / 64] = {};   // channels lane * (D / 64) ..
+
+  // `count` <= 64 keys; `stride`: elements between keys
+  __device__ void keys(const T* k, const T* v, const int32_t* pos, int count, uint32_t stride,
+                       int lane) {
+    const int32_t x = pos[min(lane, count - 1)];
+    const bool vis = lane < count && x <= qp && x >= ql;
+    float s = -INFINITY;
+    if (vis) {
+      const T* const kj = k + (int64_t)lane * stride;
+      float dot = 0.f;
+#pragma unroll 4
+      for (int c = 0; c < D; ++c) dot = fmaf(to_float(q[c]), to_float(kj[c]), dot);
+      s = dot * scale_log2;
+    }
+    float bm = s;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) bm = fmaxf(bm, __shfl_xor(bm, o, 64));
+    const float m_new = fmaxf(m, bm);
+    if (m_new == -INFINITY) return;
+    const float old = __builtin_amdgcn_exp2f(m - m_new);
+    const float pr = vis ? __builtin_amdgcn_exp2f(s - m_new) : 0.f;
+    float sum = pr;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+    l = fmaf(l, old, sum);
+    m = m_new;
+#pragma unroll
+    for (int c = 0; c < D / 64; ++c) acc[c] *= old;
+    for (int t = 0; t < count; ++t) {
+      const float pt = __builtin_bit_cast(
+          float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, pr), t));
+      if (pt == 0.f) continue;
+      const T* const vj = v + (int64_t)t * stride + lane * (D / 64);
+#pragma unroll
+      for (int c = 0; c < D / 64; ++c) acc[c] = fmaf(pt, to_float(vj[c]), acc[c]);
+    }
+  }
+};
+
 }  // namespace
 }  // namespace cp

@@ -137,3 +137,33 @@ def test_a_hidden_bad_key_changes_nothing(name, value):
         blind |= torch.arange(len(c.q_pos), device="cuda") < 150
     assert blind.any() and not blind.all()
     assert same(o2[blind], o[blind]) and same(l2[blind], l[blind])
+
+
+# A V that a row does not see: the row is computed again, on the vector pipe and with fp32
+# probabilities, so it agrees to the rounding of the path's own probabilities: none in fp32 and at
+# head_dim 64 (fp32 sums of at most 2048 terms: 2^-24 sqrt(2048) of values of unit size), bf16 at
+# head_dim 128. The walk behind flags asks for finite V (it has no second look).
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+@pytest.mark.parametrize("name", [n for n in CASES if n != "walk"])
+def test_a_hidden_bad_value_changes_nothing(name, value):
+    c = Case(name)
+    total = len(c.kv_pos)
+    atol = 2e-2 if c.q.shape[2] == 128 and c.q.dtype == torch.bfloat16 else 1e-5
+    hidden = [5, 40, total // 2 + 3, total - 1]     # padded slots: no row sees them
+    c.kv_pos = c.kv_pos.copy()
+    c.kv_pos[hidden] = B.CP_POS_PAD_KV
+    late = total - total // 4                       # a key that the later rows see
+    o, l = c.run()
+    c.v = c.v.clone()
+    c.v[hidden] = value
+    o2, l2 = c.run()
+    assert same(l2, l) and float((o2 - o).abs().max()) <= atol
+    c.v[late, 0, 1] = value
+    o2, l2 = c.run()
+    blind = torch.as_tensor(c.q_pos < c.kv_pos[late]).to("cuda")
+    if name == "packed":
+        blind |= torch.arange(len(c.q_pos), device="cuda") < 150
+    assert same(l2, l) and float((o2[blind] - o[blind]).abs().max()) <= atol
+    assert not torch.isfinite(o2[~blind]).all()     # (the rows that see it have it)
+    o3, _ = c.run(torch.bfloat16)
+    assert float((o3[blind].float() - o[blind]).abs().max()) <= 2e-2
