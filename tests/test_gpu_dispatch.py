@@ -242,3 +242,23 @@ def test_head_dim_64_takes_negative_positions(oracle):
     o, l = B.cp_attn_partial(dev(q), dev(k), dev(v), i32(qp), i32(kp), out_dtype=torch.float32)
     torch.cuda.synchronize()
     check(o, l, *oracle.attn(q64, k64, v64, qp, kp))
+
+
+# The flat decode kernel holds a probability to 16 bits (two bf16 terms) or better: each errs by up
+# to 2^-17 of itself, independently, and the fp32 sums by 2^-24 sqrt(keys); with one term it would be
+# 2^-9. (Error of a whole result, of which the probabilities' is the root mean square: below 2^-17.)
+def test_flat_decode_keeps_probabilities_to_16_bits(oracle):
+    lens, nh = [40, 3000, 700], 16
+    cu = np.concatenate([[0], np.cumsum(lens)])
+    q, q64 = randn(4801, (3, nh, 128))
+    k, k64 = randn(4802, (sum(lens), 1, 128))
+    v, v64 = randn(4803, (sum(lens), 1, 128))
+    pos = np.concatenate([np.arange(n) for n in lens])
+    o, _ = B.cp_attn_decode(dev(q), dev(k), dev(v), i32(np.array(lens) - 1), i32(pos), i32(cu),
+                            i32(np.arange(3)), out_dtype=torch.float32, unique_bid=True)
+    torch.cuda.synchronize()
+    ref = np.concatenate([oracle.attn(q64[b:b + 1], k64[cu[b]:cu[b + 1]], v64[cu[b]:cu[b + 1]],
+                                      np.array([n - 1]), np.arange(n))[0]
+                          for b, n in enumerate(lens)])
+    err = rel_l2(o, ref)
+    assert err < 2.0 ** -17, err
