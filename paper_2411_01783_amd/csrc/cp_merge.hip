@@ -115,35 +115,52 @@ __global__ __launch_bounds__(256) void merge_kernel(MergePtrs ptrs, int n_parts_
 // on many; in both a thread wants all its requests out at once: it asks for the LSE values of
 // all parts and for up to 16 data vectors back to back, and the arithmetic is branch-free (a
 // branch on the weights would pull the loads behind the wait for the LSE values). NP is the
-// part count rounded up; parts past the end repeat the last one with weight zero.
-// ONE: a single rank, and indices within 32 bits. Its pointers are scalar loads with the other
-// arguments; looked up by rank they are a vector load that everything else waits for, which with
-// the 64-bit division of the row costs 0.35 us a call (decode of 32 sequences of 2K to 8K keys
-// without the unique-id promise: 22.9 -> 22.6 us).
-template <typename TP, typename TO, int VEC, int NP, bool ONE>
-__global__ __launch_bounds__(256) void merge_table_kernel(const MergeTable m, int head_dim) {
+// part count rounded up; parts past the end repeat the last one with weight zero. The addresses
+// step from part to part: as products of the part's index they do not fit the scalar registers at
+// 64 parts (one sequence of 131072 keys: 7.6 -> MEASURE us). A single rank's pointers are scalar
+// loads with the other arguments; looked up by rank they are a vector load that everything else
+// waits for.
+template <typename TP, typename TO, int VEC, int NP>
+__global__ __launch_bounds__(256) void merge_table_kernel(const MergeTable m, int row_shift) {
   constexpr int BATCH = NP < 16 ? NP : 16;
-  const int vec_per_row = head_dim / VEC;
-  using Idx = std::conditional_t<ONE, uint32_t, int64_t>;
-  const Idx idx = (Idx)blockIdx.x * (Idx)blockDim.x + (Idx)threadIdx.x;
-  const Idx row = idx / (Idx)vec_per_row;
-  if ((int64_t)row >= m.row_begin[ONE ? 1 : m.n_ranks]) return;
-  const int col = (int)(idx - row * (Idx)vec_per_row) * VEC;
-  int a = 0;
-  if constexpr (!ONE) {
+  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t row = idx >> row_shift;                          // head_dim / VEC threads per row
+  const int col = ((int)idx & ((1 << row_shift) - 1)) * VEC;
+  const int head_dim = VEC << row_shift;
+  if (row >= m.row_begin[m.n_ranks]) return;
+  const void* part = m.part[0];
+  const float* part_lse = m.part_lse[0];
+  void* out = m.out[0];
+  float* lse_out = m.lse[0];
+  int64_t r = row;
+  if (m.n_ranks > 1) {
+    int a = 0;
 #pragma unroll 8
     for (int i = 1; i < m.n_ranks; ++i) a += row >= m.row_begin[i];
+    part = m.part[a];
+    part_lse = m.part_lse[a];
+    out = m.out[a];
+    lse_out = m.lse[a];
+    r -= m.row_begin[a];
   }
-  const int64_t r = (int64_t)row - m.row_begin[a];
   const int n_parts = m.n_parts;
   const int64_t first = (int64_t)blockIdx.y * n_parts;
-  const float* const lse = m.part_lse[a] + first * m.part_lse_elems + r;
-  const char* const src = (const char*)m.part[a] + first * m.part_bytes +
-                          (r * head_dim + col) * (int64_t)sizeof(TP);
+  const float* lse = part_lse + first * m.part_lse_elems + r;
+  const char* src = (const char*)part + first * m.part_bytes +
+                    (r * head_dim + col) * (int64_t)sizeof(TP);
+  // (the part count anew for every use: the comparisons with it, kept, would fill the scalar
+  // registers)
+  auto count = [n_parts] {
+    int n = n_parts;
+    asm volatile("" : "+s"(n));
+    return n;
+  };
   float lv[NP];
 #pragma unroll
-  for (int s = 0; s < NP; ++s)
-    lv[s] = lse[(int64_t)min(s, n_parts - 1) * m.part_lse_elems];
+  for (int s = 0; s < NP; ++s) {
+    lv[s] = *lse;
+    lse += s + 1 < count() ? m.part_lse_elems : 0;
+  }
   float acc[VEC];
 #pragma unroll
   for (int i = 0; i < VEC; ++i) acc[i] = 0.f;
@@ -152,14 +169,15 @@ __global__ __launch_bounds__(256) void merge_table_kernel(const MergeTable m, in
   for (int b = 0; b < NP / BATCH; ++b) {
     float xs[BATCH][VEC];
 #pragma unroll
-    for (int i = 0; i < BATCH; ++i)
-      load_vec<TP, VEC>((const TP*)(src + (int64_t)min(b * BATCH + i, n_parts - 1) * m.part_bytes),
-                        xs[i]);
+    for (int i = 0; i < BATCH; ++i) {
+      load_vec<TP, VEC>((const TP*)src, xs[i]);
+      src += b * BATCH + i + 1 < count() ? m.part_bytes : 0;
+    }
     __builtin_amdgcn_sched_barrier(0);  // keep the requests together, ahead of the arithmetic
     if (b == 0) {
 #pragma unroll
       for (int s = 0; s < NP; ++s) {
-        if (s >= n_parts) lv[s] = -INFINITY;
+        if (s >= count()) lv[s] = -INFINITY;
         lmax = fmaxf(lmax, lv[s]);
       }
     }
@@ -175,10 +193,10 @@ __global__ __launch_bounds__(256) void merge_table_kernel(const MergeTable m, in
   const float inv = den > 0.f ? 1.f / den : 0.f;
 #pragma unroll
   for (int c = 0; c < VEC; ++c) acc[c] *= inv;
-  char* const o = (char*)m.out[a] + (int64_t)blockIdx.y * m.group_out_bytes;
+  char* const o = (char*)out + (int64_t)blockIdx.y * m.group_out_bytes;
   store_vec<TO, VEC>((TO*)o + r * head_dim + col, acc);
-  if (m.lse[a] != nullptr && col == 0)
-    m.lse[a][(int64_t)blockIdx.y * m.group_lse_elems + r] =
+  if (lse_out != nullptr && col == 0)
+    lse_out[(int64_t)blockIdx.y * m.group_lse_elems + r] =
         den > 0.f ? lmax + __logf(den) : -INFINITY;
 }
 
@@ -228,24 +246,19 @@ namespace {
 
 template <typename TP, typename TO, int VEC>
 int launch_table_t(const MergeTable& m, int32_t head_dim, hipStream_t stream) {
-  const int64_t n_vec = m.row_begin[m.n_ranks] * (head_dim / VEC);
+  const int per_row = head_dim / VEC;   // 64 or 128 channels: a power of two
+  if (per_row < 1 || (per_row & (per_row - 1)) != 0 || head_dim % VEC != 0)
+    return CP_ERR_UNSUPPORTED;
+  const int64_t n_vec = m.row_begin[m.n_ranks] * per_row;
   if (n_vec == 0) return CP_OK;
   // one wavefront per workgroup while that is what spreads the rows over the 256 CUs
   const int threads = n_vec * m.n_groups < 256 * 4 * 256 ? 64 : 256;
   const int64_t blocks = (n_vec + threads - 1) / threads;
   if (blocks > 0x7fffffffLL) return CP_ERR_SHAPE;
   const dim3 grid((unsigned)blocks, m.n_groups);
-  // (the last workgroup's threads past the end have an index as well)
-  const bool one = m.n_ranks == 1 && n_vec + threads <= 0x7fffffffLL;
-#define CP_MERGE_TABLE(NP)                                                                      \
-  do {                                                                                          \
-    if (one)                                                                                    \
-      hipLaunchKernelGGL((merge_table_kernel<TP, TO, VEC, NP, true>), grid, dim3(threads), 0,   \
-                         stream, m, head_dim);                                                  \
-    else                                                                                        \
-      hipLaunchKernelGGL((merge_table_kernel<TP, TO, VEC, NP, false>), grid, dim3(threads), 0,  \
-                         stream, m, head_dim);                                                  \
-  } while (0)
+#define CP_MERGE_TABLE(NP)                                                                     \
+  hipLaunchKernelGGL((merge_table_kernel<TP, TO, VEC, NP>), grid, dim3(threads), 0, stream, m, \
+                     __builtin_ctz((unsigned)per_row))
   if (m.n_parts <= 2) CP_MERGE_TABLE(2);
   else if (m.n_parts <= 4) CP_MERGE_TABLE(4);
   else if (m.n_parts <= 8) CP_MERGE_TABLE(8);
