@@ -1007,13 +1007,21 @@ __global__ __launch_bounds__(MW * 64) void decode_flat_merge_kernel(const FlatMe
         typedef float floatx2_t __attribute__((ext_vector_type(2)));
         float wj[FM_U];
         floatx2_t x[FM_U];
+        // (weights and sources are read whatever the index: a branch around one puts its load
+        // behind the others'. One sequence of 131072 keys, 512 parts a row: 24.7 -> 18.0 us)
+        int src[FM_U];
 #pragma unroll
         for (int u = 0; u < FM_U; ++u) {
           const int ee = min(e + u * MW, cnt - 1);
-          wj[u] = e + u * MW < cnt ? w_of[ee] : 0.f;
+          wj[u] = w_of[ee];
+          src[u] = src_of[ee];
+        }
+#pragma unroll
+        for (int u = 0; u < FM_U; ++u) {
           // a part with zero weight may hold anything (it is read, then dropped)
           x[u] = __builtin_nontemporal_load(
-              (const floatx2_t*)(mp.part_out + (int64_t)src_of[ee] * D) + lane);
+              (const floatx2_t*)(mp.part_out + (int64_t)src[u] * D) + lane);
+          if (e + u * MW >= cnt) wj[u] = 0.f;
         }
 #pragma unroll
         for (int u = 0; u < FM_U; ++u) {
