@@ -606,6 +606,7 @@ int ring_one_launch(const cp_ring_desc* d, hipStream_t st) {
     m.out[a] = d->out[a]; m.lse[a] = d->lse != nullptr ? d->lse[a] : nullptr;
     m.row_begin[a + 1] = m.row_begin[a] + d->n_q[a] * d->n_q_heads;
   }
+  m.rows = m.row_begin[n];
   return launch_merge_table(m, d->head_dim, d->part_dtype, d->out_dtype, st);
 }
 

@@ -153,16 +153,17 @@ int launch_merge(int64_t rows, int32_t head_dim, int32_t n_parts, const void* co
 // Equation 4 over partials at a constant stride, for the rows of several ranks (row_begin: rows
 // are (token, head) pairs) and, in grid.y, for n_groups runs of n_parts partials each.
 struct MergeTable {
+  int32_t n_ranks, n_parts, n_groups;
+  int64_t rows;                      // of all ranks
+  int64_t part_bytes;                // bytes from one part to the next
+  int64_t part_lse_elems;
+  int64_t group_out_bytes;           // bytes between the outputs of two groups
+  int64_t group_lse_elems;
   const void* part[kMaxTable];       // part 0 of the rank's rows
   const float* part_lse[kMaxTable];
   void* out[kMaxTable];
   float* lse[kMaxTable];             // entries may be NULL
   int64_t row_begin[kMaxTable + 1];
-  int64_t part_bytes;                // bytes from one part to the next
-  int64_t part_lse_elems;
-  int64_t group_out_bytes;           // bytes between the outputs of two groups
-  int64_t group_lse_elems;
-  int32_t n_ranks, n_parts, n_groups;
 };
 int launch_merge_table(const MergeTable& m, int32_t head_dim, int32_t part_dtype,
                        int32_t out_dtype, hipStream_t stream);

@@ -1231,7 +1231,7 @@ int launch_decode(const cp_shape& s, float scale, const void* q, const void* k, 
   m.n_ranks = m.n_groups = 1;
   m.n_parts = splits;
   m.part[0] = p.part_out; m.part_lse[0] = p.part_lse; m.out[0] = out; m.lse[0] = lse;
-  m.row_begin[1] = (int64_t)rows;
+  m.rows = m.row_begin[1] = (int64_t)rows;
   m.part_bytes = (int64_t)rows * D * 4;
   m.part_lse_elems = (int64_t)rows;
   return launch_merge_table(m, D, CP_FP32, out_dtype, stream);

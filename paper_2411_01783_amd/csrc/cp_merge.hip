@@ -127,7 +127,7 @@ __global__ __launch_bounds__(256) void merge_table_kernel(const MergeTable m, in
   const int64_t row = idx >> row_shift;                          // head_dim / VEC threads per row
   const int col = ((int)idx & ((1 << row_shift) - 1)) * VEC;
   const int head_dim = VEC << row_shift;
-  if (row >= m.row_begin[m.n_ranks]) return;
+  if (row >= m.rows) return;
   const void* part = m.part[0];
   const float* part_lse = m.part_lse[0];
   void* out = m.out[0];
@@ -249,7 +249,7 @@ int launch_table_t(const MergeTable& m, int32_t head_dim, hipStream_t stream) {
   const int per_row = head_dim / VEC;   // 64 or 128 channels: a power of two
   if (per_row < 1 || (per_row & (per_row - 1)) != 0 || head_dim % VEC != 0)
     return CP_ERR_UNSUPPORTED;
-  const int64_t n_vec = m.row_begin[m.n_ranks] * per_row;
+  const int64_t n_vec = m.rows * per_row;
   if (n_vec == 0) return CP_OK;
   // one wavefront per workgroup while that is what spreads the rows over the 256 CUs
   const int threads = n_vec * m.n_groups < 256 * 4 * 256 ? 64 : 256;

@@ -59,23 +59,26 @@ constexpr float kOverflowSum = 1099511627776.f;    // 2^40: a block sum beyond i
 constexpr float kDeadRowRef = INFINITY;            // reference of a row that sees no key
 
 struct Params {
-  AttnTable t;            // queries and outputs per rank, KV per shard
-  const int32_t* arrived[kMaxTable];  // RING: per rank [n_shards], nonzero once step j's shard
-                                      // may be read
-  int32_t rb_begin[kMaxTable + 1];    // RING: first row block of every rank
+  // The first rank and shard of the table, beside the sizes: a single call reads its arguments from
+  // a few cache lines, in one go. (Spread over the table they were eight latencies one after the
+  // other, 2 us of every call.)
+  const void* q;
+  const int32_t* q_pos;
+  void* out;
+  float* lse;
+  const void* k;
+  const void* v;
+  const int32_t* kv_pos;
   const int2* bounds;     // (min, max) of kv_pos per block, shard after shard (not PLAN)
   const int32_t* q_lo;    // BAND only: smallest visible key position per query token
   float* part_out;        // SPLIT: [grid.z][rows_all_heads][D] fp32; PLAN: [2 slots per wg][BM][D]
   float* part_lse;        // likewise, without D
-  int2* plan_rec;         // PLAN: (unit, begin in it) of every share, for plan_merge_kernel
-  float* acc;             // ACC: running O, fp32 [rows_all_heads][D] (running LSE: t.lse[0])
-  void* final_out;        // ACC: where the merged O goes on the last step (else NULL)
-  float* final_lse;       // ACC: optional copy of the merged LSE
-  int32_t* ring_error;    // RING: per rank; bit j is set when the wait of step j gave up
-  int64_t rows;           // R = total_q * G
   int64_t rows_all_heads; // total_q * n_q_heads
   int64_t out_shard_stride;  // per_shard: bytes between the outputs of two shards
   int64_t lse_shard_stride;  // and elements between their LSE
+  int32_t n_ranks, n_shards;
+  int32_t n_kv;           // of the first shard
+  int32_t rows;           // R = total_q * G
   int32_t group;          // G
   int32_t n_kv_heads;
   int32_t n_row_blocks;
@@ -87,6 +90,15 @@ struct Params {
   int32_t cut_units;      // PLAN: equal shares (else a workgroup per unit)
   int32_t spin_limit;     // RING: polls per shard before giving up
   float scale_log2;       // softmax scale * log2(e)
+  int2* plan_rec;         // PLAN: (unit, begin in it) of every share, for plan_merge_kernel
+  float* acc;             // ACC: running O, fp32 [rows_all_heads][D] (running LSE: lse)
+  void* final_out;        // ACC: where the merged O goes on the last step (else NULL)
+  float* final_lse;       // ACC: optional copy of the merged LSE
+  int32_t* ring_error;    // RING: per rank; bit j is set when the wait of step j gave up
+  AttnTable t;            // queries and outputs per rank, KV per shard
+  const int32_t* arrived[kMaxTable];  // RING: per rank [n_shards], nonzero once step j's shard
+                                      // may be read
+  int32_t rb_begin[kMaxTable + 1];    // RING: first row block of every rank
 };
 
 // (min, max) of kv_pos per 32-key block (or, coarse, per four), for the shards of a whole call
@@ -99,13 +111,19 @@ __global__ __launch_bounds__(256) void kv_bounds_kernel(const AttnTable t, int32
   const int b = (blockIdx.x * 4 + (threadIdx.x >> 6)) * 4 + (lane >> 4);
   int lo = INT32_MAX, hi = INT32_MIN;
   if (b < n_blocks) {
-    int j = 0;
-    for (int i = 1; i < t.n_shards; ++i) j += b >= t.blk_begin[i];
-    const int32_t* __restrict__ kv_pos = t.kv_pos[j];
-    const int total_kv = t.n_kv[j];
+    // (one shard: scalar loads)
+    int first = 0, total_kv = t.n_kv[0];
+    const int32_t* __restrict__ kv_pos = t.kv_pos[0];
+    if (t.n_shards > 1) {
+      int j = 0;
+      for (int i = 1; i < t.n_shards; ++i) j += b >= t.blk_begin[i];
+      kv_pos = t.kv_pos[j];
+      total_kv = t.n_kv[j];
+      first = t.blk_begin[j];
+    }
 #pragma unroll
     for (int h = 0; h < BLOCK; h += 16) {
-      const int idx = (b - t.blk_begin[j]) * BLOCK + h + (lane & 15);
+      const int idx = (b - first) * BLOCK + h + (lane & 15);
       if (idx < total_kv) {
         const int32_t x = kv_pos[idx];
         lo = min(lo, x);
@@ -262,10 +280,14 @@ int check_rows(const AttnShape& s) {
 
 void fill_params(const AttnShape& s, const AttnTable& t, Params& p) {
   p.t = t;
+  p.q = t.q[0]; p.q_pos = t.q_pos[0]; p.out = t.out[0]; p.lse = t.lse[0];
+  p.k = t.k[0]; p.v = t.v[0]; p.kv_pos = t.kv_pos[0];
+  p.n_kv = t.n_kv[0];
+  p.n_ranks = t.n_ranks; p.n_shards = t.n_shards;
   p.group = s.n_q_heads / s.n_kv_heads;
-  p.rows = s.total_q * p.group;
+  p.rows = (int32_t)(s.total_q * p.group);   // (check_rows)
   p.rows_all_heads = s.total_q * s.n_q_heads;
-  p.n_row_blocks = (int32_t)((p.rows + BM - 1) / BM);
+  p.n_row_blocks = (int32_t)(((int64_t)p.rows + BM - 1) / BM);
   p.n_kv_heads = s.n_kv_heads;
   p.n_blocks = s.n_blocks;
   p.n_sub = p.n_z = 1;
@@ -372,7 +394,7 @@ int launch_attn_mfma(const AttnShape& s, const AttnTable& t, const AttnOut& o,
     m.out[a] = t.out[a];
     m.lse[a] = t.lse[a];
   }
-  m.row_begin[t.n_ranks] = p.rows_all_heads;
+  m.rows = m.row_begin[t.n_ranks] = p.rows_all_heads;
   return launch_merge_table(m, s.head_dim, CP_FP32, o.dtype, stream);
 }
 

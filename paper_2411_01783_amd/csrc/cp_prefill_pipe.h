@@ -396,7 +396,7 @@ __device__ __forceinline__ bool ring_enter(const Params& p, int rank, int step, 
     if (!ok) atomicOr(p.ring_error + rank, 1 << step);  // which step gave up (n_shards <= 32)
     *slot = ok;
     // a look at the next step's flag, used when the walk gets there
-    peek = step + 1 < p.t.n_shards ? ring_flag(p, rank, step + 1) : 0;
+    peek = step + 1 < p.n_shards ? ring_flag(p, rank, step + 1) : 0;
   }
   lds_barrier();
   const int ok = __builtin_amdgcn_readfirstlane(*slot);
@@ -439,6 +439,20 @@ __device__ inline int plan_workgroups(uint32_t total, int max_wgs) {
 }
 __device__ inline int share_begin(int i, uint32_t total, int n_wgs) {
   return (int)((uint32_t)i * total / (uint32_t)n_wgs);
+}
+
+// A pointer to global memory, said so: chosen in a branch or looked up in LDS it loses what the
+// compiler knows of a kernel argument, and is accessed with flat instructions. Those count as LDS
+// operations too, so that every later LDS read waits for memory (2000 cycles of an epilogue).
+template <typename T>
+using Glb = CP_GLB_AS T*;
+// A kernel argument as a value of its own: where it is one of two that a branch chooses from, the
+// compiler otherwise chooses between their addresses, and copies the arguments to scratch for it.
+template <typename T>
+__device__ __forceinline__ Glb<T> argument(T* x) {
+  Glb<T> y = (Glb<T>)x;
+  asm volatile("" : "+s"(y));
+  return y;
 }
 
 struct Share {
@@ -510,13 +524,13 @@ __device__ __forceinline__ void plan_bounds(const Params& p, int2* lds_bounds, c
     for (int u = 0; u < PER; ++u) {
       if (b0 + u * STEP < p.n_blocks) {   // uniform
         const int b = min(b0 + u * STEP + (tid >> 3), p.n_blocks - 1);
-        int first = 0, n_kv = p.t.n_kv[0];
-        const int32_t* pos = p.t.kv_pos[0];
-        if (p.t.n_shards > 1) {
+        int first = 0, n_kv = p.n_kv;
+        Glb<const int32_t> pos = argument(p.kv_pos);
+        if (p.n_shards > 1) {
           while (b >= L.blk_begin[sh + 1]) ++sh;
           first = L.blk_begin[sh];
           n_kv = L.n_kv[sh];
-          pos = L.kv_pos[sh];
+          pos = (Glb<const int32_t>)L.kv_pos[sh];
         }
         const int key0 = (b - first) * BLOCK + (tid & 7);
 #pragma unroll
@@ -556,11 +570,11 @@ __device__ __forceinline__ Share plan_share(const Params& p, int2* lds_bounds, u
                                             int tid) {
   const int lane = tid & 63, wave = tid >> 6;
   Share sh = {0, 0, 0};
-  if (tid >= 64 && tid < 64 + p.t.n_shards) {
+  if (p.n_shards > 1 && tid >= 64 && tid < 64 + p.n_shards) {
     const int i = tid - 64;
     shards[i] = {p.t.k[i], p.t.v[i], p.t.kv_pos[i], p.t.n_kv[i], p.t.blk_begin[i]};
   }
-  if (p.t.n_ranks > 1 || p.t.n_shards > 1) {
+  if (p.n_ranks > 1 || p.n_shards > 1) {
     if (tid <= kMaxTable) {
       L.tok_begin[tid] = p.t.tok_begin[tid];
       L.blk_begin[tid] = p.t.blk_begin[tid];
@@ -577,7 +591,7 @@ __device__ __forceinline__ Share plan_share(const Params& p, int2* lds_bounds, u
     __syncthreads();
     const int i = blockIdx.x / p.n_kv_heads, kvh = blockIdx.x - i * p.n_kv_heads;
     const int z = p.n_z > 1 ? i / p.n_row_blocks : 0;
-    const int rb = ordered_row_block(i - z * p.n_row_blocks, p.n_row_blocks, p.t.n_ranks, lane);
+    const int rb = ordered_row_block(i - z * p.n_row_blocks, p.n_row_blocks, p.n_ranks, lane);
     sh.unit = (kvh * p.n_z + z) * p.n_row_blocks + rb;
     return sh;
   }
@@ -596,14 +610,14 @@ __device__ __forceinline__ Share plan_share(const Params& p, int2* lds_bounds, u
       int a = 0;
 #pragma unroll
       for (int e = 0; e < 2; ++e) {
-        const int64_t row = e == 0 ? (int64_t)rb * BM : min<int64_t>((int64_t)rb * BM + BM, p.rows) - 1;
+        const int64_t row = e == 0 ? (int64_t)rb * BM : min<int64_t>((int64_t)rb * BM + BM, (int64_t)p.rows) - 1;
         const int t = (int)((uint32_t)row / (uint32_t)p.group);
         int32_t x;
-        if (p.t.n_ranks > 1) {
+        if (p.n_ranks > 1) {
           while (t >= L.tok_begin[a + 1]) ++a;
-          x = L.q_pos[a][t - L.tok_begin[a]];
+          x = ((Glb<const int32_t>)L.q_pos[a])[t - L.tok_begin[a]];
         } else {
-          x = p.t.q_pos[0][t];
+          x = ((Glb<const int32_t>)p.q_pos)[t];
         }
         mx[k] = max(mx[k], x);
         if (BAND) lo[k] = min(lo[k], x >= 0 ? p.q_lo[t] : INT32_MAX);
@@ -752,7 +766,7 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
     // the memory channels.
     const int i = blockIdx.x / p.n_kv_heads;
     kvh = blockIdx.x - i * p.n_kv_heads;
-    row_block = ordered_row_block(i, p.n_row_blocks, p.t.n_ranks, threadIdx.x & 63);
+    row_block = ordered_row_block(i, p.n_row_blocks, p.n_ranks, threadIdx.x & 63);
     // grid.z: the n_sub parts of the KV axis, of every shard in turn when shards are kept apart
     z_shard = p.per_shard ? blockIdx.z / p.n_sub : 0;
     z_sub = blockIdx.z - z_shard * p.n_sub;
@@ -779,17 +793,18 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
     // ---- blocks of this workgroup (the ring walk moves on from shard to shard) ----
     int cur_shard = MODE == RING ? rank : z_shard;
     const bool one_shard = MODE == RING || p.per_shard;
-    int b_begin = one_shard ? p.t.blk_begin[cur_shard] : 0;
-    int b_end = one_shard ? p.t.blk_begin[cur_shard + 1] : p.n_blocks;
+    int b_begin = one_shard && p.n_shards > 1 ? p.t.blk_begin[cur_shard] : 0;
+    int b_end = one_shard && p.n_shards > 1 ? p.t.blk_begin[cur_shard + 1] : p.n_blocks;
     auto block_bounds = [&](int b) -> int2 {
       return MODE == PLAN ? lds_bounds[b] : p.bounds[b >> p.bounds_shift];
     };
 
     // ---- this lane's query row ----
-    // (rows fit 31 bits: checked by the launcher)
-    const int64_t r = (int64_t)row_block * BM + wave * 32 + n;
-    const bool row_ok = r < (MODE == RING ? p.t.tok_begin[rank + 1] - p.t.tok_begin[rank]
-                                          : p.t.tok_begin[p.t.n_ranks]) * (int64_t)p.group;
+    // (rows and row blocks of 256 fit 31 bits: checked by the launcher)
+    const int n_rows = MODE == RING ? (p.t.tok_begin[rank + 1] - p.t.tok_begin[rank]) * p.group
+                                    : p.rows;
+    const int r0 = row_block * BM + wave * 32;   // of the wavefront
+    const bool row_ok = (uint32_t)(r0 + n) < (uint32_t)n_rows;
     // The start-up chain is q_pos -> visible blocks -> first tile; the bounds of the first 512
     // blocks are requested now so that they arrive together with q_pos, and the Q fragments
     // (needed last) are requested after both and waited for only before the first product.
@@ -798,22 +813,23 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
     int32_t qp = CP_POS_PAD_Q, ql = INT32_MIN;
     bf16x8_t qf[G::NKS];
     {
+      const int r = r0 + n;
       int token = row_ok ? (int)((uint32_t)r / (uint32_t)p.group) : 0;
-      const int hg = row_ok ? (int)(r - (int64_t)token * p.group) : 0;
-      const bf16_t* q = (const bf16_t*)p.t.q[MODE == RING ? rank : 0];
-      const int32_t* q_pos = p.t.q_pos[MODE == RING ? rank : 0];
+      const int hg = row_ok ? r - token * p.group : 0;
+      auto q = (Glb<const bf16_t>)argument(MODE == RING ? p.t.q[rank] : p.q);
+      auto q_pos = argument(MODE == RING ? p.t.q_pos[rank] : p.q_pos);
       if (BAND && row_ok) ql = p.q_lo[token];
-      if (MODE != RING && p.t.n_ranks > 1) {
+      if (MODE != RING && p.n_ranks > 1) {
         // (scalar loads where the row block lies within one rank, which it mostly does)
         const int t0 = (int)((uint32_t)(row_block * BM) / (uint32_t)p.group);
         const int a0 = rank_of_token(p.t, t0);
-        q = (const bf16_t*)p.t.q[a0];
-        q_pos = p.t.q_pos[a0];
+        q = (Glb<const bf16_t>)p.t.q[a0];
+        q_pos = (Glb<const int32_t>)p.t.q_pos[a0];
         int first = p.t.tok_begin[a0];
         if ((int64_t)row_block * BM + BM > (int64_t)p.t.tok_begin[a0 + 1] * p.group) {
           const int a = rank_of_token(p.t, token);
-          q = (const bf16_t*)p.t.q[a];
-          q_pos = p.t.q_pos[a];
+          q = (Glb<const bf16_t>)p.t.q[a];
+          q_pos = (Glb<const int32_t>)p.t.q_pos[a];
           first = p.t.tok_begin[a];
         }
         token -= row_ok ? first : token;
@@ -822,8 +838,8 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
       const int64_t row = ((int64_t)token * p.n_kv_heads + kvh) * p.group + hg;
 #pragma unroll
       for (int ks = 0; ks < G::NKS; ++ks) {
-        uint4 x = make_uint4(0, 0, 0, 0);
-        if (row_ok) x = *(const uint4*)(q + row * D + ks * 16 + g * 8);
+        u32x4_t x = {0u, 0u, 0u, 0u};
+        if (row_ok) x = *(Glb<const u32x4_t>)(q + row * D + ks * 16 + g * 8);
         qf[ks] = __builtin_bit_cast(bf16x8_t, x);
       }
     }
@@ -918,8 +934,9 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
     if constexpr (MODE == SPLIT || MODE == PLAN) {
       int total = 0;
       if (MODE == SPLIT || p.cut_units) {
-        int cnt = 0;
-        for (int b = b_begin + tid; b < b_end; b += NTHREADS) cnt += visible(block_bounds(b)) ? 1 : 0;
+        int cnt = b_begin + tid < b_end && visible(first_bounds) ? 1 : 0;
+        for (int b = b_begin + NTHREADS + tid; b < b_end; b += NTHREADS)
+          cnt += visible(block_bounds(b)) ? 1 : 0;
         cnt = wave_sum(cnt);
         lds_barrier();
         if (lane == 0) wg_scratch[wave] = cnt;
@@ -929,9 +946,11 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
         total = __builtin_amdgcn_readfirstlane(total);
       }
       if constexpr (MODE == SPLIT) {
-        const int tiles = (total + 3) >> 2;
-        part_lo = 4 * (int)((int64_t)tiles * z_sub / p.n_sub);
-        part_hi = 4 * (int)((int64_t)tiles * (z_sub + 1) / p.n_sub);
+        // (in 32 bits, which the tiles of a memory full of keys fit 64 times: a 64-bit division is
+        // 500 cycles of every start)
+        const uint32_t tiles = (uint32_t)(total + 3) >> 2;
+        part_lo = 4 * (int)(tiles * (uint32_t)z_sub / (uint32_t)p.n_sub);
+        part_hi = 4 * (int)(tiles * (uint32_t)(z_sub + 1) / (uint32_t)p.n_sub);
       } else if (p.cut_units) {
         const int units = p.n_row_blocks * p.n_z;
         const int planned = __builtin_amdgcn_readfirstlane((int)weight[share.unit % units]);
@@ -948,11 +967,11 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
     }
 
     int flag_peek = 0;
-    const int n_steps = MODE == RING ? p.t.n_shards : 1;
+    const int n_steps = MODE == RING ? p.n_shards : 1;
     for (int step = 0; step < n_steps; ++step) {
       if constexpr (MODE == RING) {
         if (step > 0) {
-          cur_shard = cur_shard > 0 ? cur_shard - 1 : p.t.n_shards - 1;
+          cur_shard = cur_shard > 0 ? cur_shard - 1 : p.n_shards - 1;
           b_begin = p.t.blk_begin[cur_shard];
           b_end = p.t.blk_begin[cur_shard + 1];
         }
@@ -987,14 +1006,24 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
           const int lo = max(part_lo, seen), hi = min(part_hi, seen + total);
           const int idx = seen + base + __builtin_popcountll(mask & ((1ull << lane) - 1ull));
           if (lv && idx >= lo && idx < hi) {
-            int sh = cur_shard;
-            if (!one_shard) {
-#pragma unroll 8
-              for (int i = 1; i < p.t.n_shards; ++i) sh += b >= p.t.blk_begin[i];
-            }
+            // (the shard through scalar loads where there is one; a lookup per lane is a memory
+            // latency more)
             LdsShard e;
-            if constexpr (MODE == PLAN) e = shards[sh];
-            else e = {p.t.k[sh], p.t.v[sh], p.t.kv_pos[sh], p.t.n_kv[sh], p.t.blk_begin[sh]};
+            if (p.n_shards == 1) {
+              e = {(const void*)argument(p.k), (const void*)argument(p.v),
+                   (const int32_t*)argument(p.kv_pos), p.n_kv, 0};
+            } else if (MODE != PLAN && one_shard) {
+              e = {p.t.k[cur_shard], p.t.v[cur_shard], p.t.kv_pos[cur_shard],
+                   p.t.n_kv[cur_shard], p.t.blk_begin[cur_shard]};
+            } else {
+              int sh = cur_shard;
+              if (!one_shard) {
+#pragma unroll 8
+                for (int i = 1; i < p.n_shards; ++i) sh += b >= p.t.blk_begin[i];
+              }
+              if constexpr (MODE == PLAN) e = shards[sh];
+              else e = {p.t.k[sh], p.t.v[sh], p.t.kv_pos[sh], p.t.n_kv[sh], p.t.blk_begin[sh]};
+            }
             const int key0 = (b - e.blk_begin) * BLOCK;
             const int valid = min(BLOCK, e.n_kv - key0);
             const uint64_t off = (uint64_t)key0 * stride_b + (uint32_t)kvh * ROW;
@@ -1044,8 +1073,8 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
             const int4 own = live_pos[i + (tid >> 5)];
             next_pos = CP_POS_PAD_KV;
             if ((tid & 31) < own.z) {
-              const int32_t* const pos = (const int32_t*)((uint64_t)(uint32_t)own.x |
-                                                          (uint64_t)(uint32_t)own.y << 32);
+              const auto pos = (Glb<const int32_t>)((uint64_t)(uint32_t)own.x |
+                                                    (uint64_t)(uint32_t)own.y << 32);
               next_pos = pos[tid & 31];
             }
           }
@@ -1156,6 +1185,12 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
     }
 
     // ---- epilogue ----
+    // (The lane's row again: kept over the walk, it and what is made of it took more registers than
+    // there are, and a kernel with two spilled registers started 2 us later.)
+    int tid_e = threadIdx.x;
+    asm volatile("" : "+v"(tid_e));
+    const int lane_e = tid_e & 63, n_e = lane_e & 31, g_e = lane_e >> 5;
+    const int r = r0 + n_e;
     const float l_sum = R.l_run + xor32(R.l_run);
     const float l_tot = sees ? l_sum : 0.f;
     const bool no_key = l_tot == 0.f;
@@ -1166,29 +1201,29 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
     // workspace, in fp32.
     const bool partial = MODE == SPLIT || (MODE == PLAN && !whole);
     int64_t row_lin;        // row of [tokens, N_H] in the buffer written to
-    char* o_row;
-    float* lse_row = nullptr;
+    Glb<char> o_row;
+    Glb<float> lse_row = nullptr;
     if (MODE == PLAN && partial) {
       const int slot = 2 * blockIdx.x + (first_piece ? 1 : 0);
-      row_lin = (int64_t)slot * BM + wave * 32 + n;
-      o_row = (char*)(p.part_out + row_lin * D);
-      lse_row = p.part_lse + row_lin;
+      row_lin = (int64_t)slot * BM + wave * 32 + n_e;
+      o_row = (Glb<char>)(p.part_out + row_lin * D);
+      lse_row = (Glb<float>)(p.part_lse + row_lin);
     } else {
       int token = row_ok ? (int)((uint32_t)r / (uint32_t)p.group) : 0;
-      const int hg = row_ok ? (int)(r - (int64_t)token * p.group) : 0;
-      char* o = (char*)p.t.out[MODE == RING ? rank : 0];
-      float* l = p.t.lse[MODE == RING ? rank : 0];
-      if (MODE != SPLIT && MODE != RING && p.t.n_ranks > 1) {
+      const int hg = row_ok ? r - token * p.group : 0;
+      auto o = (Glb<char>)argument(MODE == RING ? p.t.out[rank] : p.out);
+      auto l = argument(MODE == RING ? p.t.lse[rank] : p.lse);
+      if (MODE != SPLIT && MODE != RING && p.n_ranks > 1) {
         const int a = rank_of_token(p.t, token);
         token -= p.t.tok_begin[a];
-        o = (char*)p.t.out[a];
-        l = p.t.lse[a];
+        o = (Glb<char>)p.t.out[a];
+        l = (Glb<float>)p.t.lse[a];
       }
       row_lin = ((int64_t)token * p.n_kv_heads + kvh) * p.group + hg;
       if (MODE == SPLIT) {
         row_lin += (int64_t)blockIdx.z * p.rows_all_heads;
-        o = (char*)p.part_out;
-        l = p.part_lse;
+        o = (Glb<char>)p.part_out;
+        l = (Glb<float>)p.part_lse;
       } else {
         o += (int64_t)z_shard * p.out_shard_stride;
         if (l != nullptr) l += (int64_t)z_shard * p.lse_shard_stride;
@@ -1200,14 +1235,17 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
     // loop would pay for it with 200 spilled registers.
     uint32_t spoiled = 0;
     if constexpr (MODE != RING) {
-      float spoil = 0.f;   // stays zero if O is finite
+      float most = 0.f;   // finite if O is (the maximum of a NaN is NaN)
 #pragma unroll
       for (int db = 0; db < G::NDB; ++db)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) spoil = fmaf(R.o[db][i], 0.f, spoil);
-      spoil += xor32(spoil);
+        for (int i = 0; i < 16; i += 2)
+          most = __builtin_elementwise_maximum(
+              __builtin_elementwise_maximum(__builtin_fabsf(R.o[db][i]),
+                                            __builtin_fabsf(R.o[db][i + 1])), most);
+      most = __builtin_elementwise_maximum(most, xor32(most));
       spoiled = (uint32_t)__builtin_amdgcn_ballot_w64(
-          row_ok && l_tot > 0.f && l_tot < INFINITY && !(spoil == 0.f));
+          row_ok && l_tot > 0.f && l_tot < INFINITY && !(most < INFINITY));
     }
     float share_of_row = 1.f;   // ACC: weight of this step
     // ACC: weights of Equation 4 for the pair (running result, this step). a_old scales the
@@ -1226,12 +1264,12 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
       share_of_row = w_cur * rden;
       inv *= share_of_row;
       const float lse_new = den > 0.f ? m + __logf(den) : -INFINITY;
-      if (row_ok && g == 0) {
+      if (row_ok && g_e == 0) {
         if (l_tot > 0.f) *lse_row = lse_new;
         if (p.final_lse != nullptr) p.final_lse[row_lin] = lse_new;
       }
     } else {
-      if (row_ok && g == 0 && lse_row != nullptr) *lse_row = lse_val;
+      if (row_ok && g_e == 0 && lse_row != nullptr) *lse_row = lse_val;
     }
 
     // Transpose through LDS (the tile buffers are dead once every wavefront has left the walk;
@@ -1243,12 +1281,17 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
     for (int db = 0; db < G::NDB; ++db)
 #pragma unroll
       for (int i4 = 0; i4 < 4; ++i4) {
-        const int d0 = db * 32 + i4 * 8 + g * 4;
+        const int d0 = db * 32 + i4 * 8 + g_e * 4;
         floatx4_t w = {R.o[db][i4 * 4 + 0] * inv, R.o[db][i4 * 4 + 1] * inv,
                        R.o[db][i4 * 4 + 2] * inv, R.o[db][i4 * 4 + 3] * inv};
-        if (no_key) w = floatx4_t{0.f, 0.f, 0.f, 0.f};   // (O may be NaN there)
-        *(floatx4_t*)(stage + n * G::OUT_STRIDE + d0 * 4) = w;
+        *(floatx4_t*)(stage + n_e * G::OUT_STRIDE + d0 * 4) = w;
       }
+    if (no_key) {   // (O may be NaN there)
+#pragma unroll
+      for (int i = 0; i < D / 8; ++i)
+        *(floatx4_t*)(stage + n_e * G::OUT_STRIDE + (i * 8 + g_e * 4) * 4) =
+            floatx4_t{0.f, 0.f, 0.f, 0.f};
+    }
     wave_lds_fence();
     if constexpr (MODE != RING) {
       while (__builtin_expect(spoiled != 0, 0)) {
@@ -1257,7 +1300,7 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
         const int row = row_block * BM + wave * 32 + rr;
         int token = (int)((uint32_t)row / (uint32_t)p.group);
         const int hg = row - token * p.group;
-        const int a = p.t.n_ranks > 1 ? rank_of_token(p.t, token) : 0;
+        const int a = p.n_ranks > 1 ? rank_of_token(p.t, token) : 0;
         token -= p.t.tok_begin[a];
         VectorRow<bf16_t, D> vr;
         vr.q = (const bf16_t*)p.t.q[a] + (((int64_t)token * p.n_kv_heads + kvh) * p.group + hg) * D;
@@ -1267,7 +1310,7 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
         int sh = z_shard, idx = 0;
         for (int c = b_begin; c < b_end; c += 64) {   // the blocks walked above
           uint64_t mask = __builtin_amdgcn_ballot_w64(
-              c + lane < b_end && visible(block_bounds(min(c + lane, b_end - 1))));
+              c + lane_e < b_end && visible(block_bounds(min(c + lane_e, b_end - 1))));
           for (; mask != 0; mask &= mask - 1, ++idx) {
             if (idx < part_lo || idx >= part_hi) continue;
             const int b = c + __builtin_ctzll(mask);
@@ -1276,23 +1319,23 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
             const int64_t off = ((int64_t)key0 * p.n_kv_heads + kvh) * D;
             vr.keys((const bf16_t*)p.t.k[sh] + off, (const bf16_t*)p.t.v[sh] + off,
                     p.t.kv_pos[sh] + key0, min(BLOCK, p.t.n_kv[sh] - key0),
-                    (uint32_t)p.n_kv_heads * D, lane);
+                    (uint32_t)p.n_kv_heads * D, lane_e);
           }
         }
         const float f = __shfl(share_of_row, rr, 64) / vr.l;
 #pragma unroll
         for (int c = 0; c < D / 64; ++c)
-          ((float*)(stage + rr * G::OUT_STRIDE))[lane * (D / 64) + c] = vr.acc[c] * f;
+          ((float*)(stage + rr * G::OUT_STRIDE))[lane_e * (D / 64) + c] = vr.acc[c] * f;
         wave_lds_fence();
       }
     }
     // (rows in order: row rr of the wavefront exists iff its lane's does)
     const uint64_t rows_ok = __builtin_amdgcn_ballot_w64(row_ok);
-    auto row_address = [&](int rr) -> char* {
+    auto row_address = [&](int rr) -> Glb<char> {
       const uint64_t x = (uint64_t)o_row;
       const uint32_t lo = (uint32_t)__shfl((int)(uint32_t)x, rr, 64);
       const uint32_t hi = (uint32_t)__shfl((int)(uint32_t)(x >> 32), rr, 64);
-      return (char*)((uint64_t)hi << 32 | lo);
+      return (Glb<char>)((uint64_t)hi << 32 | lo);
     };
     if constexpr (MODE == ACC) {
       // The stored row (fp32) times its weight is added to the step's row, 4 channels per
@@ -1302,7 +1345,7 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
       constexpr int LPR = D / 4, RPP = 64 / LPR;     // lanes per row, rows per pass
 #pragma unroll
       for (int pass = 0; pass < 32 / RPP; ++pass) {
-        const int rr = pass * RPP + lane / LPR, c = (lane % LPR) * 4;
+        const int rr = pass * RPP + lane_e / LPR, c = (lane_e % LPR) * 4;
         const int64_t rl = __shfl(row_lin, rr, 64);
         float* const old_row = p.acc + rl * D + c;
         const float ao = __shfl(a_old, rr, 64);
@@ -1333,8 +1376,8 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
       constexpr int LPR = D / 8, RPP = 64 / LPR;
 #pragma unroll
       for (int pass = 0; pass < 32 / RPP; ++pass) {
-        const int rr = pass * RPP + lane / LPR, c = (lane % LPR) * 8;
-        char* const o = row_address(rr);
+        const int rr = pass * RPP + lane_e / LPR, c = (lane_e % LPR) * 8;
+        const Glb<char> o = row_address(rr);
         const floatx4_t a = *(const floatx4_t*)(stage + rr * G::OUT_STRIDE + c * 4);
         const floatx4_t b = *(const floatx4_t*)(stage + rr * G::OUT_STRIDE + c * 4 + 16);
         bf16x8_t w;
@@ -1343,16 +1386,16 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
           w[x] = static_cast<bf16_t>(a[x]);
           w[4 + x] = static_cast<bf16_t>(b[x]);
         }
-        if (rows_ok >> rr & 1) *(bf16x8_t*)(o + c * 2) = w;
+        if (rows_ok >> rr & 1) *(Glb<bf16x8_t>)(o + c * 2) = w;
       }
     } else {
       constexpr int LPR = D / 4, RPP = 64 / LPR;
 #pragma unroll
       for (int pass = 0; pass < 32 / RPP; ++pass) {
-        const int rr = pass * RPP + lane / LPR, c = (lane % LPR) * 4;
-        char* const o = row_address(rr);
+        const int rr = pass * RPP + lane_e / LPR, c = (lane_e % LPR) * 4;
+        const Glb<char> o = row_address(rr);
         const floatx4_t a = *(const floatx4_t*)(stage + rr * G::OUT_STRIDE + c * 4);
-        if (rows_ok >> rr & 1) *(floatx4_t*)(o + c * 4) = a;
+        if (rows_ok >> rr & 1) *(Glb<floatx4_t>)(o + c * 4) = a;
       }
     }
     if constexpr (MODE != PLAN) return;
@@ -1438,7 +1481,7 @@ __global__ __launch_bounds__(256) void plan_merge_kernel(const Params p) {
     const float inv = den[k] > 0.f ? 1.f / den[k] : 0.f;
     const int token = (int)((uint32_t)r / (uint32_t)p.group);
     const int hg = (int)(r - (int64_t)token * p.group);
-    const int a = p.t.n_ranks > 1 ? rank_of_token(p.t, token) : 0;
+    const int a = p.n_ranks > 1 ? rank_of_token(p.t, token) : 0;
     const int64_t lin = ((int64_t)(token - p.t.tok_begin[a]) * p.n_kv_heads + kvh) * p.group + hg;
     TO* const o = (TO*)((char*)p.t.out[a] + z * p.out_shard_stride) + lin * D + col;
     if constexpr (sizeof(TO) == 4) {
