@@ -44,7 +44,7 @@ AttnShape single_shape(const cp_shape& s) {
   AttnShape a = {};
   a.dtype = s.dtype; a.head_dim = s.head_dim;
   a.n_q_heads = s.n_q_heads; a.n_kv_heads = s.n_kv_heads;
-  a.total_q = s.total_q; a.n_blocks = kv_blocks(s.total_kv); a.n_shards = 1;
+  a.total_q = s.total_q; a.n_blocks = kv_blocks(s.total_kv); a.n_shards = 1; a.batch = s.batch;
   return a;
 }
 
@@ -402,6 +402,7 @@ static AttnShape ring_attn_shape(const cp_ring_desc* d) {
   s.dtype = d->dtype; s.head_dim = d->head_dim;
   s.n_q_heads = d->n_q_heads; s.n_kv_heads = d->n_kv_heads;
   s.n_shards = d->n_ranks;
+  s.batch = ring_is_packed(d, false) ? d->batch : 1;
   for (int r = 0; r < d->n_ranks; ++r) {
     s.total_q += d->n_q[r];
     s.n_blocks += kv_blocks(d->n_kv[r]);

@@ -66,6 +66,7 @@ struct AttnShape {
   int64_t total_q;      // tokens of all ranks
   int32_t n_blocks;     // blocks of all shards
   int32_t n_shards;
+  int32_t batch;        // packed sequences
   bool per_shard;       // keep the shards' results apart: one (O, LSE) per rank and shard
   float scale;
 };

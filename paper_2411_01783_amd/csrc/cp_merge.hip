@@ -271,10 +271,27 @@ int launch_table_t(const MergeTable& m, int32_t head_dim, hipStream_t stream) {
 
 }  // namespace
 
+constexpr int64_t kStreamRows = 4096;
+
 int launch_merge_table(const MergeTable& m, int32_t head_dim, int32_t part_dtype,
                        int32_t out_dtype, hipStream_t stream) {
   if (m.n_parts < 1 || m.n_parts > CP_MAX_PARTS || m.n_groups < 1 || m.n_groups > 65535)
     return CP_ERR_SHAPE;
+  // Many rows of one rank: bound by bandwidth and not by latency, and the streaming kernel with its
+  // compile-time part counts moves them faster (a call of 1000 queries of 16 heads, 4 parts of 16000
+  // rows: 30.3 us with the kernel above, 28.4).
+  const int n = m.n_parts;
+  if (m.n_ranks == 1 && m.n_groups == 1 && m.rows >= kStreamRows &&
+      (n == 2 || n == 4 || n == 8 || n == 16)) {
+    const void* outs[CP_MAX_PARTS];
+    const float* lses[CP_MAX_PARTS];
+    for (int i = 0; i < n; ++i) {
+      outs[i] = (const char*)m.part[0] + i * m.part_bytes;
+      lses[i] = m.part_lse[0] + i * m.part_lse_elems;
+    }
+    return launch_merge(m.rows, head_dim, n, outs, lses, part_dtype, m.out[0], out_dtype, m.lse[0],
+                        stream);
+  }
   if (part_dtype == CP_FP32)
     return out_dtype == CP_FP32 ? launch_table_t<float, float, 4>(m, head_dim, stream)
                                 : launch_table_t<float, bf16_t, 4>(m, head_dim, stream);

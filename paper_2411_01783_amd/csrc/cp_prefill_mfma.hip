@@ -54,6 +54,8 @@ constexpr int PLAN_MAX_BLOCKS = 960;      // PLAN: block bounds kept in LDS (30K
 constexpr int PLAN_MAX_UNITS = 1024;      // PLAN: units per KV head
 constexpr int kPlanWorkgroups = 256;      // one per CU
 constexpr int kUnitCost = 3;              // start-up and epilogue of a unit, in tile steps
+constexpr int kCutCost = 12;              // partials of a cut at head_dim 128, in tile steps
+constexpr int kUncutTiles = 6;            // units up to this long are not worth a cut
 constexpr float kRescaleSlack = 8.f;               // log2 units
 constexpr float kOverflowSum = 1099511627776.f;    // 2^40: a block sum beyond it is redone
 constexpr float kDeadRowRef = INFINITY;            // reference of a row that sees no key
@@ -86,6 +88,7 @@ struct Params {
   int32_t n_blocks;       // of all shards
   int32_t bounds_shift;   // blocks per entry of `bounds`: 1 << bounds_shift
   int32_t n_sub;          // SPLIT: parts of the KV axis (of every shard's, if per_shard)
+  int32_t sub_blocks;     // SPLIT: blocks per part, by their index; 0: equal parts of the visible ones
   int32_t per_shard;      // the shards' results are kept apart
   int32_t cut_units;      // PLAN: equal shares (else a workgroup per unit)
   int32_t spin_limit;     // RING: polls per shard before giving up
@@ -191,6 +194,7 @@ int choose_splits(int64_t wgs, int tiles, double rows, int head_dim, int max_spl
 struct Plan {
   Mode mode;
   int n_row_blocks, n_blocks, n_sub, n_z;  // n_z: shards kept apart
+  int sub_blocks;                          // see Params
   bool cut, coarse;
   size_t bounds_bytes, part_out_bytes, part_lse_bytes, rec_bytes;
   size_t total() const { return bounds_bytes + part_out_bytes + part_lse_bytes + rec_bytes; }
@@ -214,15 +218,34 @@ Plan make_plan(const AttnShape& s) {
   // (the planned launch has its bounds in LDS, but cp_attn_partial_accumulate, which shares the
   // workspace query, does not)
   pl.bounds_bytes = round256(std::max<size_t>(entries, 1) * sizeof(int2));
-  if (!single_large && s.n_blocks <= PLAN_MAX_BLOCKS && units <= PLAN_MAX_UNITS &&
-      wgs <= 8 * PLAN_MAX_UNITS &&
-      // (the line of all units times 256, and token rows, within 32 bits)
-      wgs * (24 + s.n_blocks / 4) < (1ll << 23)) {
+  // tiles of the average walk, if every query saw everything
+  const int tiles = (int)((s.n_blocks / pl.n_z + 3) / 4);
+  const bool one_call = s.n_shards == 1 && !s.per_shard;
+  bool plan = !single_large && s.n_blocks <= PLAN_MAX_BLOCKS && units <= PLAN_MAX_UNITS &&
+              wgs <= 8 * PLAN_MAX_UNITS &&
+              // (the line of all units times 256, and token rows, within 32 bits)
+              wgs * (24 + s.n_blocks / 4) < (1ll << 23);
+  if (one_call) {
+    // A call of one rank against one shard, as a rank of a real ring makes it. Up to two tiles, or
+    // up to six with four times as many row blocks: a workgroup per row block in one launch (400
+    // queries of 16 heads on 500 keys 22 us, with the KV axis split in three launches 25; 64
+    // queries 22 against 18). Equal shares from 128 row blocks on: with fewer, parts of the KV axis
+    // fill the CUs as well and write a smaller partial (1000 queries on their own 1000 keys 28 us
+    // against 40). From 86 row blocks on two parts are all that fits one round, and equal shares
+    // are better if the walks are long (3100 queries of 8 heads on 2 KV heads, later half of them
+    // seeing all keys: 53 us against 64). At head_dim 64 a partial is half as large and parts win
+    // earlier (700 queries of 16 heads on 2 25 us against 31).
+    const int seen = tiles / s.batch;
+    const bool uncut = seen <= 2 || (seen <= kUncutTiles &&
+                                     wgs >= (s.head_dim == 64 ? 128 : 4 * seen));
+    const bool cut = seen > kUncutTiles && (wgs >= 128 || (3 * wgs > 256 && seen >= 16));
+    plan = plan && (uncut || cut);
+  }
+  if (plan) {
     pl.mode = PLAN;
     // Up to six tiles a unit there is nothing worth cutting (the plan and the merge launch take
     // as long as three tile steps).
-    const int64_t tiles = (s.n_blocks / pl.n_z + 3) / 4;
-    pl.cut = tiles > 6;
+    pl.cut = (one_call ? tiles / s.batch : tiles) > kUncutTiles;
     if (pl.cut) {
       pl.part_out_bytes = (size_t)2 * kPlanWorkgroups * BM * s.head_dim * 4;
       pl.part_lse_bytes = (size_t)2 * kPlanWorkgroups * BM * 4;
@@ -232,11 +255,17 @@ Plan make_plan(const AttnShape& s) {
   }
   // Otherwise the KV axis is split where the workgroups alone leave CUs idle: for every shard
   // kept apart by the size of the average shard.
-  const int tiles = (int)((s.n_blocks / pl.n_z + 3) / 4);
   pl.n_sub = choose_splits(wgs, tiles, (double)rows_all * pl.n_z, s.head_dim,
                            s.per_shard ? 16 : CP_MAX_PARTS);
   pl.mode = pl.n_sub > 1 ? SPLIT : WHOLE;
   if (pl.mode == SPLIT) {
+    // One shard of more blocks than a workgroup lists at once: parts by index, since counting and
+    // passing over the blocks of the others takes longer than equal parts gain.
+    if (one_call && s.n_blocks > MAX_LIVE) {
+      const int per = (tiles + pl.n_sub - 1) / pl.n_sub;
+      pl.n_sub = (tiles + per - 1) / per;
+      pl.sub_blocks = 4 * per;
+    }
     pl.part_out_bytes = round256((size_t)pl.n_z * pl.n_sub * rows_all * s.head_dim * 4);
     pl.part_lse_bytes = round256((size_t)pl.n_z * pl.n_sub * rows_all * 4);
   }
@@ -349,6 +378,7 @@ int launch_attn_mfma(const AttnShape& s, const AttnTable& t, const AttnOut& o,
   p.plan_rec = (int2*)(ws + pl.bounds_bytes + pl.part_out_bytes + pl.part_lse_bytes);
   p.q_lo = q_lo;
   p.n_sub = pl.n_sub;
+  p.sub_blocks = pl.sub_blocks;
   p.n_z = pl.n_z;
   p.per_shard = s.per_shard ? 1 : 0;
   p.cut_units = pl.cut ? 1 : 0;

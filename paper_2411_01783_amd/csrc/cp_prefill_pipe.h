@@ -425,7 +425,10 @@ __device__ __forceinline__ bool ring_enter(const Params& p, int rank, int step, 
 // units and 350 blocks, so the weight comes from its first and last query and from at most 32
 // blocks, 128 in a packed batch; a cut is made at the same fraction of the unit's true list of
 // tiles.) What a share cuts goes to the workspace as fp32 partials (at most two per
-// workgroup) and is merged by plan_merge_kernel. Only for calls whose positions and unit list
+// workgroup) and is merged by plan_merge_kernel. Those partials are up to 67 MB each way, as much
+// time as 12 tile steps (6 at head_dim 64), so units of nearly equal length that fit one round are
+// left whole (2100 queries of 16 heads that all see the same 1050 keys: 53 us cut, 41 whole; where
+// half of them see 2100 and half none: 53 cut, 67 whole). Only for calls whose positions and unit list
 // fit LDS; larger ones have row blocks enough to keep every CU busy. Six packed prompts of 200 to
 // 3000 tokens over 4 ranks: 241 us with a workgroup per row block and 128-key tiles, 115 us in
 // equal shares of 32-key blocks.
@@ -564,7 +567,7 @@ struct LdsShard {
 };
 
 // Bounds of all blocks, and this workgroup's share. `weight`: the units' planned tiles (LDS).
-template <bool BAND>
+template <int D, bool BAND>
 __device__ __forceinline__ Share plan_share(const Params& p, int2* lds_bounds, uint16_t* weight,
                                             PlanLds& L, LdsShard* shards, int* wg_scratch,
                                             int tid) {
@@ -652,37 +655,58 @@ __device__ __forceinline__ Share plan_share(const Params& p, int2* lds_bounds, u
   }
   __syncthreads();
   // prefix sums
-  int x[PER], sum = 0;
+  int x[PER], sum = 0, most = 0;
 #pragma unroll
   for (int i = 0; i < PER; ++i) {
     const int u = tid * PER + i;
-    sum += u < n_units ? kUnitCost + (int)weight[u] : 0;
+    const int c = u < n_units ? kUnitCost + (int)weight[u] : 0;
+    most = max(most, c);
+    sum += c;
     x[i] = sum;
   }
+  most = wave_max(most);
   int scan = sum;
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
     const int y = __shfl_up(scan, o, 64);
     if (lane >= o) scan += y;
   }
-  if (lane == 63) wg_scratch[wave] = scan;
+  if (lane == 63) {
+    wg_scratch[wave] = scan;
+    wg_scratch[NWAVE + wave] = most;
+  }
   __syncthreads();
-  int before = scan - sum, total1 = 0;
+  int before = scan - sum, total1 = 0, longest = 0;
 #pragma unroll
   for (int w = 0; w < NWAVE; ++w) {
     const int c = wg_scratch[w];
     if (w < wave) before += c;
     total1 += c;
+    longest = max(longest, wg_scratch[NWAVE + w]);
   }
 #pragma unroll
   for (int i = 0; i < PER; ++i) x[i] += before;
   total1 = __builtin_amdgcn_readfirstlane(total1);
+  longest = __builtin_amdgcn_readfirstlane(longest);
   // the line of units, KV head after KV head
   const uint32_t total = (uint32_t)total1 * (uint32_t)p.n_kv_heads;
-  const int n_wgs = plan_workgroups(total, gridDim.x);
-  const int i = blockIdx.x;
+  const int i = blockIdx.x, all = n_units * p.n_kv_heads;
+  // Whole units where a cut gains less than its partials cost: one round of workgroups, and the
+  // longest unit not much longer than a share.
+  const bool keep_whole = all <= (int)gridDim.x &&
+                          longest <= (int)(total / gridDim.x) + kCutCost * (D / 64) / 2;
+  const int n_wgs = keep_whole ? all : plan_workgroups(total, gridDim.x);
   if (i >= n_wgs) {
     if (tid == 0) p.plan_rec[i + 1] = make_int2(-1, 0);
+    return sh;
+  }
+  if (keep_whole) {
+    sh.unit = i;
+    sh.length = kUnitCost + __builtin_amdgcn_readfirstlane((int)weight[i % n_units]);
+    if (tid == 0) {
+      p.plan_rec[i] = make_int2(i, 0);
+      if (i == n_wgs - 1) p.plan_rec[n_wgs] = make_int2(-1, 0);
+    }
     return sh;
   }
   // A boundary in the start-up of a unit moves to its begin: nothing is cut there. (Moving those
@@ -756,7 +780,7 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
   int row_block = 0, kvh = 0, z_shard = 0, z_sub = 0, rank = 0;
   Share share = {0, 0, 0};
   if constexpr (MODE == PLAN) {
-    share = plan_share<BAND>(p, lds_bounds, weight, *(PlanLds*)smem, shards, wg_scratch,
+    share = plan_share<D, BAND>(p, lds_bounds, weight, *(PlanLds*)smem, shards, wg_scratch,
                                 threadIdx.x);
     if (p.cut_units && share.length == 0) return;
     __syncthreads();   // the planning arrays are dead
@@ -795,6 +819,10 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
     const bool one_shard = MODE == RING || p.per_shard;
     int b_begin = one_shard && p.n_shards > 1 ? p.t.blk_begin[cur_shard] : 0;
     int b_end = one_shard && p.n_shards > 1 ? p.t.blk_begin[cur_shard + 1] : p.n_blocks;
+    if (MODE == SPLIT && p.sub_blocks > 0) {
+      b_begin = z_sub * p.sub_blocks;
+      b_end = min(b_end, b_begin + p.sub_blocks);
+    }
     auto block_bounds = [&](int b) -> int2 {
       return MODE == PLAN ? lds_bounds[b] : p.bounds[b >> p.bounds_shift];
     };
@@ -933,7 +961,7 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
     bool whole = true, first_piece = true;  // PLAN: the unit is not cut; its first piece
     if constexpr (MODE == SPLIT || MODE == PLAN) {
       int total = 0;
-      if (MODE == SPLIT || p.cut_units) {
+      if (MODE == SPLIT ? p.sub_blocks == 0 : p.cut_units != 0) {
         int cnt = b_begin + tid < b_end && visible(first_bounds) ? 1 : 0;
         for (int b = b_begin + NTHREADS + tid; b < b_end; b += NTHREADS)
           cnt += visible(block_bounds(b)) ? 1 : 0;
@@ -946,11 +974,13 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
         total = __builtin_amdgcn_readfirstlane(total);
       }
       if constexpr (MODE == SPLIT) {
-        // (in 32 bits, which the tiles of a memory full of keys fit 64 times: a 64-bit division is
-        // 500 cycles of every start)
-        const uint32_t tiles = (uint32_t)(total + 3) >> 2;
-        part_lo = 4 * (int)(tiles * (uint32_t)z_sub / (uint32_t)p.n_sub);
-        part_hi = 4 * (int)(tiles * (uint32_t)(z_sub + 1) / (uint32_t)p.n_sub);
+        if (p.sub_blocks == 0) {
+          // (in 32 bits, which the tiles of a memory full of keys fit 64 times: a 64-bit division is
+          // 500 cycles of every start)
+          const uint32_t tiles = (uint32_t)(total + 3) >> 2;
+          part_lo = 4 * (int)(tiles * (uint32_t)z_sub / (uint32_t)p.n_sub);
+          part_hi = 4 * (int)(tiles * (uint32_t)(z_sub + 1) / (uint32_t)p.n_sub);
+        }
       } else if (p.cut_units) {
         const int units = p.n_row_blocks * p.n_z;
         const int planned = __builtin_amdgcn_readfirstlane((int)weight[share.unit % units]);

@@ -1,10 +1,12 @@
 """GPU parity at the edges of the launch rules: which kernel or work split a call gets depends on
-its sizes, and these are the sizes on either side of each rule, against the fp64 oracle.
+its sizes, and these are the sizes on either side of each rule.
 
-Tolerances: those of gpu_util (2e-2 max-abs on O and 1e-3 on LSE for bf16 inputs of unit scale,
-1e-4 and 1e-5 for fp32), which bound the rounding of the inputs' products and of the probabilities
-whatever the split; a key counted twice or left out of the few hundred a short row sees is a
-relative change of 1 / keys of its denominator, above the LSE bound."""
+Against the fp64 oracle, with the tolerances of gpu_util (2e-2 max-abs on O and 1e-3 on LSE for bf16
+inputs of unit scale, 1e-4 and 1e-5 for fp32): they bound the rounding of the products and of the
+probabilities whatever the split, but a key left out or counted twice among a few thousand stays
+below them. So the rules of the attention launches are also taken with keys of zero
+(check_counts): every visible key then has the same weight, LSE is the logarithm of their number
+and O the share of each class of keys, and both come out exact, so that a single key is seen."""
 import numpy as np
 import pytest
 import torch
@@ -51,6 +53,90 @@ def check_ring(oracle, ring, out, lse, case, keep, atol=2e-2, rtol=1e-3):
                 continue
             o, l = oracle.attn(q64[r], k64[p], v64[p], q_all[r], p)
             check(po, pl, o, l, atol, rtol, "partial %d, %d" % (a, b))
+
+
+def counts_case(kv_sizes, q_sizes, nh, nkv, d, q_pos, cu=None):
+    """Zero keys; the value of key j is 1 in channel (j // 32 + j) % d, so that O tells which
+    blocks and which keys in them were counted."""
+    total, t = sum(kv_sizes), sum(q_sizes)
+    pos = np.arange(total)
+    k = torch.zeros((total, nkv, d), dtype=torch.bfloat16, device="cuda")
+    v = torch.zeros((total, nkv, d), dtype=torch.bfloat16, device="cuda")
+    cls = (pos // 32 + pos) % d
+    v[torch.arange(total), :, torch.as_tensor(cls)] = 1.0
+    q, _ = randn(4900, (t, nh, d))
+    cut = lambda x, n: [y.contiguous() for y in torch.tensor_split(x, np.cumsum(n)[:-1].tolist())]
+    args = (cut(dev(q), q_sizes), cut(k, kv_sizes), cut(v, kv_sizes), cut(i32(q_pos), q_sizes),
+            cut(i32(pos), kv_sizes))
+    return args, cls
+
+
+def check_counts(out, lse, q_pos, cls, d, lo=0, hi=None):
+    """Every row saw exactly the keys lo <= j < hi with j <= its position. Sums of ones are exact in
+    fp32; the division and the logarithm err by a few 2^-24 of their result, below half a key for
+    the at most 2^16 keys here."""
+    hi = len(cls) if hi is None else hi
+    classes = np.zeros((hi - lo + 1, d))
+    classes[1:] = np.cumsum(np.eye(d)[cls[lo:hi]], 0)
+    n = np.clip(np.asarray(q_pos) + 1 - lo, 0, hi - lo)
+    ref = torch.as_tensor(classes[n], device="cuda")[:, None, :]
+    nt = torch.as_tensor(n, device="cuda")[:, None]
+    got = out.double() * nt[..., None].double()
+    assert float((got - ref).abs().max()) < 0.5
+    seen = (nt > 0).expand(lse.shape)
+    assert torch.equal(torch.isneginf(lse), ~seen)
+    err = (torch.exp(lse.double()) - nt.double()).abs()[seen]
+    assert err.numel() == 0 or float(err.max()) < 0.5
+
+
+# One rank against one shard, the sizes on either side of each rule: tiles 2 and 3, 6 and 7; row
+# blocks 4 per tile; 85 and 86 with 15 and 16 tiles, 127 and 128, 255 and 256 row blocks; 512 and 513
+# blocks of a split KV axis, 960 and 961 of the plan; queries that all see the same keys (left whole),
+# that see everything or little (cut), in order.
+@pytest.mark.parametrize("tq,tk,nh,nkv,d", [
+    (30, 256, 8, 2, 128), (30, 257, 8, 2, 128), (300, 768, 16, 1, 128), (300, 769, 16, 1, 128),
+    (383, 768, 16, 1, 128), (385, 768, 16, 1, 128), (2032, 769, 64, 4, 64), (2050, 640, 16, 4, 64),
+    (1360, 2048, 16, 1, 128), (1361, 1920, 16, 1, 128), (1361, 2017, 16, 1, 128),
+    (2032, 900, 16, 1, 128), (2033, 900, 16, 1, 128), (4080, 800, 16, 1, 128),
+    (4081, 800, 16, 1, 128), (1500, 2500, 8, 8, 64), (4081, 800, 16, 1, 64),
+    (70, 16384, 16, 1, 128), (70, 16385, 16, 1, 64), (600, 30720, 64, 4, 128),
+    (600, 30721, 64, 4, 128), (1, 5000, 3, 1, 128),
+])
+def test_single_call_launch_rules_count_every_key(tq, tk, nh, nkv, d):
+    rng = np.random.default_rng(tq + tk)
+    half = np.where(np.arange(tq) < tq // 2, 40, tk)
+    for q_pos in (np.full(tq, tk // 2), half, np.sort(rng.integers(-1, tk, size=tq))):
+        args, cls = counts_case([tk], [tq], nh, nkv, d, q_pos)
+        o, l = B.cp_attn_partial(*(x[0] for x in args), out_dtype=torch.float32)
+        torch.cuda.synchronize()
+        check_counts(o, l, q_pos, cls, d)
+
+
+# Rings in one launch: the sizes of test_ring_launch_rules.
+@pytest.mark.parametrize("kv_sizes,q_sizes,nh,nkv,d", [
+    ([768, 0], [97, 1], 16, 1, 128), ([800, 1], [97, 2], 16, 1, 128), ([769, 31], [40, 57], 16, 1, 64),
+    ([15360, 15360], [33, 16], 4, 1, 128), ([15361, 15360], [33, 16], 4, 1, 128),
+    ([10239, 10273, 10209], [8, 0, 41], 8, 2, 64), ([1500, 0, 33, 1], [0, 300, 1, 17], 3, 1, 128),
+    ([2000, 2100], [2000, 2080], 16, 1, 128), ([2000, 2100], [2000, 2090], 16, 1, 128),
+])
+def test_ring_launch_rules_count_every_key(kv_sizes, q_sizes, nh, nkv, d):
+    total, t = sum(kv_sizes), sum(q_sizes)
+    rng = np.random.default_rng(total + t)
+    ends = np.concatenate([[0], np.cumsum(kv_sizes)])
+    for q_pos in (np.full(t, total // 2), np.sort(rng.integers(-1, total, size=t))):
+        args, cls = counts_case(kv_sizes, q_sizes, nh, nkv, d, q_pos)
+        for keep in (False, True):
+            ring = B.Ring(*args, out_dtype=torch.float32, keep_partials=keep)
+            out, lse = B.cp_ring_passkv(ring)
+            torch.cuda.synchronize()
+            check_counts(torch.cat(out), torch.cat(lse), q_pos, cls, d)
+            if not keep:
+                continue
+            rows = np.split(q_pos, np.cumsum(q_sizes)[:-1])
+            for a, r in enumerate(rows):
+                for b in range(len(kv_sizes)):
+                    if len(r) > 0:
+                        check_counts(*ring.partial(a, b), r, cls, d, ends[b], ends[b + 1])
 
 
 # kv sizes, query sizes, heads, kv heads, d:
