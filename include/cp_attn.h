@@ -288,9 +288,10 @@ typedef struct {
   const int32_t* const* cu_seqlens_kv; /* (host) -> (device) int32 [batch+1] per rank */
   const int32_t* const* bid;           /* (host) -> (device) int32 [n_q[k]] per rank */
   /*
-   * A second HIP stream (default priority), or NULL. Accepted and not used: a prefill ring is
-   * one launch over all ranks and shards, so there are no calls of a rank to overlap. Everything
-   * a driver enqueues goes to `stream`.
+   * A second HIP stream (default priority), or NULL. A prefill ring of up to 32 ranks is one launch
+   * over all ranks and shards and does not use it. The N x N calls of a larger one (bf16) alternate
+   * between the two streams if none of them needs scratch for a split of its KV axis; what the
+   * driver enqueues on `stream` after a rank's calls waits for both.
    */
   void* aux_stream;
   /*

@@ -182,7 +182,7 @@ int cp_attn_partial(const cp_shape* shape, const void* q, const void* k, const v
       if (rc != CP_OK) return rc;
     }
     return launch_attn_mfma(as, t, ao, q_lo, (char*)workspace + enc,
-                            workspace_bytes - enc, st);
+                            workspace_bytes - enc, nullptr, st);
   }
   if (s.dtype == CP_FP32 && cu_seqlens_q == nullptr) return launch_attn_fp32(as, t, ao, st);
   return launch_partial_generic(s, scale, q, k, v, q_pos, kv_pos, cu_seqlens_q, cu_seqlens_kv,
@@ -215,7 +215,7 @@ int cp_attn_partial_accumulate(const cp_shape* shape, const void* q, const void*
     return CP_ERR_WORKSPACE;
   const AttnTable t = single_table(s, q, k, v, q_pos, kv_pos, nullptr, acc_lse);
   const PrefillAccumulate acc = {acc_out, acc_lse, final_out, final_lse, final_dtype};
-  return launch_attn_mfma_accumulate(as, t, acc, workspace, workspace_bytes,
+  return launch_attn_mfma_accumulate(as, t, acc, workspace, workspace_bytes, nullptr,
                                      (hipStream_t)stream);
 }
 
@@ -375,8 +375,8 @@ static cp_shape ring_shape(const cp_ring_desc* d, int q_rank, int kv_rank, bool 
 
 // Prefill drivers: a ring is one attention launch over all its ranks and shards (AttnTable)
 // wherever the kernels take it: up to kMaxTable ranks, bf16 in one sequence or packed with
-// head_dim 128, fp32 in one sequence. Otherwise (and in this build only then) it is N x N
-// partial-attention calls into the slots and a merge per rank.
+// head_dim 128, fp32 in one sequence. Otherwise it is N x N partial-attention calls into the slots
+// (N with gathered queries) and a merge per rank.
 static bool ring_is_one_launch(const cp_ring_desc* d) {
   if (d->n_ranks > kMaxTable) return false;
   const bool packed = ring_is_packed(d, false);
@@ -422,9 +422,24 @@ static size_t ring_varseq_bytes(const cp_ring_desc* d) {
   return varseq_workspace_bytes(d->batch, tokens, keys);
 }
 
-// Shape of the one decode call KV holder b answers with when the queries are gathered.
-static cp_shape gathered_decode_shape(const cp_ring_desc* d, int b) {
-  cp_shape s = ring_shape(d, 0, b, true);
+// The N x N calls of a ring on the MFMA kernel read every shard N times: its position bounds are
+// made once, at the head of the ring's workspace. (Not of a packed batch, whose positions are
+// shifted for every call.)
+static bool ring_shares_bounds(const cp_ring_desc* d, bool decode) {
+  return !decode && !ring_is_packed(d, decode) && mfma_applies(ring_shape(d, 0, 0, false));
+}
+
+// One of those calls, to the attention launch.
+static AttnShape step_shape(const cp_shape& s) {
+  AttnShape a = single_shape(s);
+  a.has_bounds = true;
+  a.scale = resolve_scale(s.softmax_scale, s.head_dim);
+  return a;
+}
+
+// Shape of the one call KV holder b answers with when the queries are gathered.
+static cp_shape gathered_shape(const cp_ring_desc* d, int b, bool decode) {
+  cp_shape s = ring_shape(d, 0, b, decode);
   s.total_q = 0;
   for (int a = 0; a < d->n_ranks; ++a) s.total_q += d->n_q[a];
   return s;
@@ -437,17 +452,23 @@ extern "C" size_t cp_ring_workspace_bytes(const cp_ring_desc* d, int32_t decode)
            : d->fused_merge == 2 && d->arrived != nullptr
                ? attn_mfma_ring_workspace_bytes(ring_attn_shape(d))
                : attn_mfma_workspace_bytes(ring_attn_shape(d)) + ring_varseq_bytes(d);
+  const bool shared = ring_shares_bounds(d, decode != 0);
+  auto call_bytes = [&](const cp_shape& s) -> size_t {
+    if (!shared) return cp_workspace_bytes(&s, decode ? CP_WS_DECODE : CP_WS_PARTIAL);
+    return check_shape(&s) == CP_OK ? attn_mfma_workspace_bytes(step_shape(s)) : 0;
+  };
   size_t need = 0;
   for (int a = 0; a < d->n_ranks; ++a)
-    for (int b = 0; b < d->n_ranks; ++b) {
-      cp_shape s = ring_shape(d, a, b, decode != 0);
-      need = std::max(need, cp_workspace_bytes(&s, decode ? CP_WS_DECODE : CP_WS_PARTIAL));
-    }
+    for (int b = 0; b < d->n_ranks; ++b)
+      need = std::max(need, call_bytes(ring_shape(d, a, b, decode != 0)));
+  if (!decode && d->gathered_q)
+    for (int b = 0; b < d->n_ranks; ++b) need = std::max(need, call_bytes(gathered_shape(d, b, false)));
+  if (shared) need += kv_bounds_ring_bytes(d->n_ranks, d->n_kv);
   if (d->gathered_q && decode) {
     cp_shape shapes[CP_MAX_PARTS];
     bool flat = true;
     for (int b = 0; b < d->n_ranks; ++b) {
-      shapes[b] = gathered_decode_shape(d, b);
+      shapes[b] = gathered_shape(d, b, true);
       need = std::max(need, cp_workspace_bytes(&shapes[b], CP_WS_DECODE));
       flat = flat && decode_flat_applies(shapes[b]);
     }
@@ -546,6 +567,39 @@ int ring_merge(const cp_ring_desc* d, const RingSlots& slots, int a, hipStream_t
                        d->part_dtype, d->out[a], d->out_dtype, lse_out, st);
 }
 
+// The ranks' outputs lie back to back, as gathered queries do.
+bool outputs_are_gathered(const cp_ring_desc* d) {
+  const size_t out_row = (size_t)d->n_q_heads * d->head_dim * elem_size(d->out_dtype);
+  bool one = true;
+  for (int a = 1; a < d->n_ranks && one; ++a) {
+    one = (char*)d->out[a] == (char*)d->out[a - 1] + d->n_q[a - 1] * out_row;
+    if (d->lse != nullptr)
+      one = one && d->lse[a] != nullptr && d->lse[0] != nullptr &&
+            d->lse[a] == d->lse[a - 1] + d->n_q[a - 1] * d->n_q_heads;
+  }
+  return one;
+}
+
+// The All2All with gathered queries: source rank a merges slot k * n + a of every holder k. With
+// the outputs back to back the N merges are one launch over the holders' whole blocks.
+int ring_merge_gathered(const cp_ring_desc* d, const RingSlots& slots, hipStream_t st) {
+  const int n = d->n_ranks;
+  int rc = CP_OK;
+  if (!outputs_are_gathered(d)) {
+    for (int a = 0; a < n && rc == CP_OK; ++a) rc = ring_merge(d, slots, a, st);
+    return rc;
+  }
+  const void* outs[CP_MAX_PARTS];
+  const float* lses[CP_MAX_PARTS];
+  for (int k = 0; k < n; ++k) {
+    outs[k] = slots.out(slot_of(d, 0, k));
+    lses[k] = slots.lse(slot_of(d, 0, k));
+  }
+  return cp_attn_merge((int64_t)n * d->n_q[0] * d->n_q_heads, d->head_dim, n, outs, lses,
+                       d->part_dtype, d->out[0], d->out_dtype,
+                       d->lse != nullptr ? d->lse[0] : nullptr, st);
+}
+
 // The whole ring as one attention launch (plus the tile-bound pre-pass and, where the KV axis is
 // split or the partials are kept, a merge launch over all ranks).
 int ring_one_launch(const cp_ring_desc* d, hipStream_t st) {
@@ -595,7 +649,7 @@ int ring_one_launch(const cp_ring_desc* d, hipStream_t st) {
       return launch_attn_mfma_ring(s, t, d->arrived, d->ring_error, d->spin_limit, d->out_dtype,
                                    ws, left, st);
     }
-    rc = launch_attn_mfma(s, t, o, q_lo, ws, left, st);
+    rc = launch_attn_mfma(s, t, o, q_lo, ws, left, nullptr, st);
   }
   if (rc != CP_OK || !d->keep_partials) return rc;
   MergeTable m = {};
@@ -611,27 +665,80 @@ int ring_one_launch(const cp_ring_desc* d, hipStream_t st) {
   return launch_merge_table(m, d->head_dim, d->part_dtype, d->out_dtype, st);
 }
 
+// What the steps of a ring that is not one launch share.
+struct RingSteps {
+  bool bounds = false;                  // of every shard, made once
+  size_t bounds_off[CP_MAX_PARTS] = {};
+  char* call_ws = nullptr;
+  size_t call_ws_bytes = 0;
+  hipStream_t aux = nullptr;            // the calls of a rank alternate between two streams
+  hipEvent_t fork = nullptr, join = nullptr;
+  ~RingSteps() {
+    if (fork != nullptr) (void)hipEventDestroy(fork);
+    if (join != nullptr) (void)hipEventDestroy(join);
+  }
+};
+
+int prepare_steps(const cp_ring_desc* d, hipStream_t st, RingSteps& w) {
+  w.bounds = ring_shares_bounds(d, false);
+  const size_t head = w.bounds ? kv_bounds_ring_bytes(d->n_ranks, d->n_kv) : 0;
+  w.call_ws = (char*)d->workspace + head;
+  w.call_ws_bytes = d->workspace_bytes - head;   // (check_ring_workspace)
+  if (!w.bounds) return CP_OK;
+  const int rc = launch_kv_bounds_ring(d->n_ranks, d->kv_pos, d->n_kv, d->workspace, w.bounds_off,
+                                       st);
+  if (rc != CP_OK || d->aux_stream == nullptr || d->fused_merge || d->gathered_q) return rc;
+  // Two streams only if no call writes partials to the workspace that all of them share.
+  for (int a = 0; a < d->n_ranks; ++a)
+    for (int b = 0; b < d->n_ranks; ++b)
+      if (d->n_q[a] > 0 && attn_mfma_has_partials(step_shape(ring_shape(d, a, b, false))))
+        return CP_OK;
+  if (hipEventCreateWithFlags(&w.fork, hipEventDisableTiming) != hipSuccess ||
+      hipEventCreateWithFlags(&w.join, hipEventDisableTiming) != hipSuccess)
+    return CP_ERR_LAUNCH;
+  w.aux = (hipStream_t)d->aux_stream;
+  return CP_OK;
+}
+
+// Queries of rank a (s.total_q of them) against the KV of rank b; `acc`: merged into a running
+// result.
+int step_call(const cp_ring_desc* d, const RingSteps& w, const cp_shape& s, int a, int b, void* out,
+              float* lse, int32_t dtype, const PrefillAccumulate* acc, hipStream_t st) {
+  const bool packed = ring_is_packed(d, false);
+  if (!w.bounds)   // (fused_merge is refused there)
+    return cp_attn_partial(&s, d->q[a], d->k[b], d->v[b], d->q_pos[a], d->kv_pos[b],
+                           packed ? d->cu_seqlens_q[a] : nullptr,
+                           packed ? d->cu_seqlens_kv[b] : nullptr, out, lse, dtype, w.call_ws,
+                           w.call_ws_bytes, st);
+  if (!aligned16(d->q[a]) || !aligned16(d->k[b]) || !aligned16(d->v[b])) return CP_ERR_ALIGN;
+  if (s.total_q == 0) return CP_OK;
+  if (s.total_q > INT32_MAX) return CP_ERR_SHAPE;
+  const AttnShape as = step_shape(s);
+  const AttnTable t = single_table(s, d->q[a], d->k[b], d->v[b], d->q_pos[a], d->kv_pos[b], out,
+                                   lse);
+  const char* const bounds = (const char*)d->workspace + w.bounds_off[b];
+  if (acc != nullptr)
+    return launch_attn_mfma_accumulate(as, t, *acc, w.call_ws, w.call_ws_bytes, bounds, st);
+  return launch_attn_mfma(as, t, AttnOut{dtype, 0, 0}, nullptr, w.call_ws, w.call_ws_bytes, bounds,
+                          st);
+}
+
 // fused_merge of a rank of such a ring, which has one slot for its partials: step 0 writes a
 // running (O, LSE) there, the following steps merge into it in their epilogues and the last one
 // writes the rank's output.
 template <typename KvOf>
-int ring_rank_fused(const cp_ring_desc* d, const RingSlots& slots, int a, hipStream_t st,
-                    KvOf kv_of_step) {
+int ring_rank_fused(const cp_ring_desc* d, const RingSteps& w, const RingSlots& slots, int a,
+                    hipStream_t st, KvOf kv_of_step) {
   float* const acc_out = (float*)slots.out(0);
   float* const acc_lse = slots.lse(0);
   for (int j = 0; j < d->n_ranks; ++j) {
     const int b = kv_of_step(a, j);
-    const cp_shape s = ring_shape(d, a, b, false);
     const bool last = j == d->n_ranks - 1;
-    const int rc =
-        j == 0 ? cp_attn_partial(&s, d->q[a], d->k[b], d->v[b], d->q_pos[a], d->kv_pos[b], nullptr,
-                                 nullptr, acc_out, acc_lse, CP_FP32, d->workspace,
-                                 d->workspace_bytes, st)
-               : cp_attn_partial_accumulate(&s, d->q[a], d->k[b], d->v[b], d->q_pos[a],
-                                            d->kv_pos[b], acc_out, acc_lse,
-                                            last ? d->out[a] : nullptr, d->out_dtype,
-                                            last && d->lse != nullptr ? d->lse[a] : nullptr,
-                                            d->workspace, d->workspace_bytes, st);
+    const PrefillAccumulate acc = {acc_out, acc_lse, last ? d->out[a] : nullptr,
+                                   last && d->lse != nullptr ? d->lse[a] : nullptr, d->out_dtype};
+    if (last && d->n_q[a] > 0 && !aligned16(d->out[a])) return CP_ERR_ALIGN;
+    const int rc = step_call(d, w, ring_shape(d, a, b, false), a, b, acc_out, acc_lse, CP_FP32,
+                             j == 0 ? nullptr : &acc, st);
     if (rc != CP_OK) return rc;
   }
   return CP_OK;
@@ -643,25 +750,38 @@ template <typename KvOf>
 int ring_steps(const cp_ring_desc* d, hipStream_t st, KvOf kv_of_step) {
   const RingSlots slots = make_slots(d);
   const int n = d->n_ranks;
-  const bool packed = ring_is_packed(d, false);
+  RingSteps w;
+  int rc = prepare_steps(d, st, w);
+  if (rc != CP_OK) return rc;
+  if (d->gathered_q) {   // one call per KV holder, whose slots are one block
+    for (int b = 0; b < n; ++b) {
+      const int64_t slot = slot_of(d, 0, b);
+      rc = step_call(d, w, gathered_shape(d, b, false), 0, b, slots.out(slot), slots.lse(slot),
+                     d->part_dtype, nullptr, st);
+      if (rc != CP_OK) return rc;
+    }
+    return ring_merge_gathered(d, slots, st);
+  }
   for (int a = 0; a < n; ++a) {
     if (d->fused_merge && n > 1) {
-      const int rc = ring_rank_fused(d, slots, a, st, kv_of_step);
+      rc = ring_rank_fused(d, w, slots, a, st, kv_of_step);
       if (rc != CP_OK) return rc;
       continue;
     }
-    for (int j = 0; j < n; ++j) {
+    // (the aux stream starts behind the previous rank's merge, which reads the slots)
+    if (w.aux != nullptr && (hipEventRecord(w.fork, st) != hipSuccess ||
+                             hipStreamWaitEvent(w.aux, w.fork, 0) != hipSuccess))
+      return CP_ERR_LAUNCH;
+    for (int j = 0; j < n && rc == CP_OK; ++j) {
       const int b = kv_of_step(a, j);
-      const cp_shape s = ring_shape(d, a, b, false);
       const int64_t slot = slot_of(d, a, b);
-      const int rc = cp_attn_partial(&s, d->q[a], d->k[b], d->v[b], d->q_pos[a], d->kv_pos[b],
-                                     packed ? d->cu_seqlens_q[a] : nullptr,
-                                     packed ? d->cu_seqlens_kv[b] : nullptr, slots.out(slot),
-                                     slots.lse(slot), d->part_dtype, d->workspace,
-                                     d->workspace_bytes, st);
-      if (rc != CP_OK) return rc;
+      rc = step_call(d, w, ring_shape(d, a, b, false), a, b, slots.out(slot), slots.lse(slot),
+                     d->part_dtype, nullptr, w.aux != nullptr && (j & 1) ? w.aux : st);
     }
-    const int rc = ring_merge(d, slots, a, st);
+    if (w.aux != nullptr && (hipEventRecord(w.join, w.aux) != hipSuccess ||
+                             hipStreamWaitEvent(st, w.join, 0) != hipSuccess))
+      return CP_ERR_LAUNCH;
+    if (rc == CP_OK) rc = ring_merge(d, slots, a, st);
     if (rc != CP_OK) return rc;
   }
   return CP_OK;
@@ -726,23 +846,15 @@ static int ring_decode_gathered(const cp_ring_desc* d, hipStream_t st) {
   cp_shape shapes[CP_MAX_PARTS];
   bool flat = true;
   for (int k = 0; k < n; ++k) {
-    shapes[k] = gathered_decode_shape(d, k);
+    shapes[k] = gathered_shape(d, k, true);
     flat = flat && decode_flat_applies(shapes[k]);
     if (!aligned16(d->k[k]) || !aligned16(d->v[k])) return CP_ERR_ALIGN;
   }
   if (!aligned16(d->q[0])) return CP_ERR_ALIGN;
-  const size_t out_row = (size_t)d->n_q_heads * d->head_dim * elem_size(d->out_dtype);
-  bool one = true;   // the ranks' outputs lie back to back as the queries do
-  for (int a = 1; a < n && one; ++a) {
-    one = (char*)d->out[a] == (char*)d->out[a - 1] + d->n_q[a - 1] * out_row;
-    if (d->lse != nullptr)
-      one = one && d->lse[a] != nullptr && d->lse[0] != nullptr &&
-            d->lse[a] == d->lse[a - 1] + d->n_q[a - 1] * d->n_q_heads;
-  }
-  float* const lse0 = d->lse != nullptr ? d->lse[0] : nullptr;
   if (flat) {
     // every holder's split-KV partials in one launch, one merge over splits x holders
     const int64_t all = (int64_t)n * d->n_q[0];
+    const bool one = outputs_are_gathered(d);
     return launch_decode_flat(n, shapes, resolve_scale(d->softmax_scale, d->head_dim), d->q[0],
                               d->k, d->v, d->q_pos[0], d->kv_pos, d->cu_seqlens_kv, d->bid[0],
                               one ? 1 : n, one ? &all : d->n_q, d->out, d->out_dtype, d->lse,
@@ -755,20 +867,7 @@ static int ring_decode_gathered(const cp_ring_desc* d, hipStream_t st) {
                         d->part_dtype, d->workspace, d->workspace_bytes, st);
     if (rc != CP_OK) return rc;
   }
-  // The All2All: source rank a merges slot k * n + a of every holder k. With the outputs back to
-  // back the N merges are one launch over the holders' whole blocks.
-  if (one) {
-    const void* outs[CP_MAX_PARTS];
-    const float* lses[CP_MAX_PARTS];
-    for (int k = 0; k < n; ++k) {
-      outs[k] = slots.out(slot_of(d, 0, k));
-      lses[k] = slots.lse(slot_of(d, 0, k));
-    }
-    return cp_attn_merge((int64_t)n * d->n_q[0] * d->n_q_heads, d->head_dim, n, outs, lses,
-                         d->part_dtype, d->out[0], d->out_dtype, lse0, st);
-  }
-  for (int a = 0; a < n && rc == CP_OK; ++a) rc = ring_merge(d, slots, a, st);
-  return rc;
+  return ring_merge_gathered(d, slots, st);
 }
 
 // Algorithm 4: N x N decode calls, grouped by source rank, and a merge per source.

@@ -67,6 +67,7 @@ struct AttnShape {
   int32_t n_blocks;     // blocks of all shards
   int32_t n_shards;
   int32_t batch;        // packed sequences
+  bool has_bounds;      // one rank, one shard: its position bounds are there already
   bool per_shard;       // keep the shards' results apart: one (O, LSE) per rank and shard
   float scale;
 };
@@ -82,10 +83,19 @@ struct AttnOut {
 // `q_lo`: packed batches (head_dim 128), smallest visible key position per token, all ranks back
 // to back.
 bool attn_mfma_applies(int dtype, int head_dim, int n_q_heads, int n_kv_heads);
+// `bounds`: the shard's position bounds, if they are there already (kv_bounds_ring; one rank, one
+// shard), else NULL.
 size_t attn_mfma_workspace_bytes(const AttnShape& s);
+bool attn_mfma_has_partials(const AttnShape& s);   // writes to the workspace besides the bounds
 int launch_attn_mfma(const AttnShape& s, const AttnTable& t, const AttnOut& o,
                      const int32_t* q_lo, void* workspace, size_t workspace_bytes,
-                     hipStream_t stream);
+                     const void* bounds, hipStream_t stream);
+
+// Position bounds of n_shards shards for the calls that each take one of them, in at most two
+// launches. offset[b]: where those of shard b begin in the region of kv_bounds_ring_bytes.
+size_t kv_bounds_ring_bytes(int n_shards, const int64_t* n_kv);
+int launch_kv_bounds_ring(int n_shards, const int32_t* const* kv_pos, const int64_t* n_kv,
+                          void* region, size_t* offset, hipStream_t stream);
 
 // "Merge into a running result": (out, lse) are read and updated (Equation 4), and if final_out
 // is not NULL the merged O goes there in final_dtype instead of back to out. One rank, one
@@ -100,7 +110,7 @@ struct PrefillAccumulate {
 bool attn_mfma_merging_applies(const AttnShape& s);
 int launch_attn_mfma_accumulate(const AttnShape& s, const AttnTable& t,
                                 const PrefillAccumulate& acc, void* workspace,
-                                size_t workspace_bytes, hipStream_t stream);
+                                size_t workspace_bytes, const void* bounds, hipStream_t stream);
 
 // One launch for all ring steps of all ranks (pass-KV), rank k walking the shards in the order
 // k, k - 1, ... (mod n_ranks) with one running softmax state per row, each shard behind its

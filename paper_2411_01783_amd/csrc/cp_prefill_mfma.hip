@@ -239,7 +239,9 @@ Plan make_plan(const AttnShape& s) {
     const bool uncut = seen <= 2 || (seen <= kUncutTiles &&
                                      wgs >= (s.head_dim == 64 ? 128 : 4 * seen));
     const bool cut = seen > kUncutTiles && (wgs >= 128 || (3 * wgs > 256 && seen >= 16));
-    plan = plan && (uncut || cut);
+    // (With the position bounds there already, planning costs more than it saves: 33 ranks of 60
+    // tokens 14.4 us a call against 12.3; and equal shares leave no room for a second stream.)
+    plan = plan && (uncut || cut) && !s.has_bounds;
   }
   if (plan) {
     pl.mode = PLAN;
@@ -358,9 +360,42 @@ bool attn_mfma_merging_applies(const AttnShape& s) {
                        CP_MAX_PARTS) == 1;
 }
 
+bool attn_mfma_has_partials(const AttnShape& s) { return make_plan(s).part_out_bytes > 0; }
+
+size_t kv_bounds_ring_bytes(int n_shards, const int64_t* n_kv) {
+  size_t entries = 0;
+  for (int b = 0; b < n_shards; ++b) entries += (size_t)((n_kv[b] + TILE - 1) / TILE);
+  return round256(std::max<size_t>(entries, 1) * sizeof(int2));
+}
+
+int launch_kv_bounds_ring(int n_shards, const int32_t* const* kv_pos, const int64_t* n_kv,
+                          void* region, size_t* offset, hipStream_t stream) {
+  int2* out = (int2*)region;
+  for (int first = 0; first < n_shards; first += kMaxTable) {
+    AttnTable t = {};
+    t.n_shards = std::min(n_shards - first, kMaxTable);
+    int64_t blocks = 0;
+    for (int j = 0; j < t.n_shards; ++j) {   // (a shard begins with a new entry, of four blocks)
+      const int b = first + j;
+      if (n_kv[b] > INT32_MAX - TILE) return CP_ERR_SHAPE;
+      t.kv_pos[j] = kv_pos[b];
+      t.n_kv[j] = (int32_t)n_kv[b];
+      t.blk_begin[j] = (int32_t)blocks;
+      offset[b] = (size_t)(out + blocks / 4 - (int2*)region) * sizeof(int2);
+      blocks += (n_kv[b] + TILE - 1) / TILE * 4;
+      if (blocks > INT32_MAX - 16) return CP_ERR_SHAPE;
+    }
+    t.blk_begin[t.n_shards] = (int32_t)blocks;
+    const int rc = launch_kv_bounds(t, (int)blocks, true, out, stream);
+    if (rc != CP_OK) return rc;
+    out += blocks / 4;
+  }
+  return CP_OK;
+}
+
 int launch_attn_mfma(const AttnShape& s, const AttnTable& t, const AttnOut& o,
                      const int32_t* q_lo, void* workspace, size_t workspace_bytes,
-                     hipStream_t stream) {
+                     const void* bounds, hipStream_t stream) {
   const Plan pl = make_plan(s);
   if (workspace_bytes < pl.total()) return CP_ERR_WORKSPACE;
   if (pl.n_row_blocks == 0) return CP_OK;
@@ -371,7 +406,7 @@ int launch_attn_mfma(const AttnShape& s, const AttnTable& t, const AttnOut& o,
   char* ws = (char*)workspace;
   Params p = {};
   fill_params(s, t, p);
-  p.bounds = (const int2*)ws;
+  p.bounds = (const int2*)(bounds != nullptr ? bounds : ws);
   p.bounds_shift = pl.coarse ? 2 : 0;
   p.part_out = (float*)(ws + pl.bounds_bytes);
   p.part_lse = (float*)(ws + pl.bounds_bytes + pl.part_out_bytes);
@@ -384,7 +419,7 @@ int launch_attn_mfma(const AttnShape& s, const AttnTable& t, const AttnOut& o,
   p.cut_units = pl.cut ? 1 : 0;
   p.out_shard_stride = o.shard_out_bytes;
   p.lse_shard_stride = o.shard_lse_elems;
-  if (pl.mode != PLAN) {
+  if (pl.mode != PLAN && bounds == nullptr) {
     rc = launch_kv_bounds(t, s.n_blocks, pl.coarse, ws, stream);
     if (rc != CP_OK) return rc;
   }
@@ -430,17 +465,19 @@ int launch_attn_mfma(const AttnShape& s, const AttnTable& t, const AttnOut& o,
 
 int launch_attn_mfma_accumulate(const AttnShape& s, const AttnTable& t,
                                 const PrefillAccumulate& acc, void* workspace,
-                                size_t workspace_bytes, hipStream_t stream) {
+                                size_t workspace_bytes, const void* bounds, hipStream_t stream) {
   if (!attn_mfma_merging_applies(s)) return CP_ERR_UNSUPPORTED;
-  const size_t bounds = round256((size_t)std::max((s.n_blocks + 3) / 4, 1) * sizeof(int2));
-  if (workspace_bytes < bounds) return CP_ERR_WORKSPACE;
+  const size_t need = round256((size_t)std::max((s.n_blocks + 3) / 4, 1) * sizeof(int2));
+  if (bounds == nullptr && workspace_bytes < need) return CP_ERR_WORKSPACE;
   int rc = check_rows(s);
   if (rc != CP_OK) return rc;
-  rc = launch_kv_bounds(t, s.n_blocks, true, workspace, stream);
-  if (rc != CP_OK) return rc;
+  if (bounds == nullptr) {
+    rc = launch_kv_bounds(t, s.n_blocks, true, workspace, stream);
+    if (rc != CP_OK) return rc;
+  }
   Params p = {};
   fill_params(s, t, p);
-  p.bounds = (const int2*)workspace;
+  p.bounds = (const int2*)(bounds != nullptr ? bounds : workspace);
   p.bounds_shift = 2;
   p.acc = acc.out;
   p.final_out = acc.final_out;

@@ -176,6 +176,32 @@ def test_ring_of_more_ranks_than_one_launch_takes(oracle):
         check_ring(oracle, ring, out, lse, case, keep)
 
 
+# 33 ranks are N x N calls whose shards' position bounds are made once, in two launches (32 and 1):
+# two streams, gathered queries (a call per holder, one merge), every option with keys of zero so
+# that a bound of the wrong shard shows. 2050 tokens and 16 heads a rank are enough row blocks for
+# two streams (no split of the KV axis), 64 are not.
+@pytest.mark.parametrize("per,d", [(64, 128), (2050, 128), (40, 64)])
+def test_ring_of_calls_counts_every_key(per, d):
+    n = 33
+    kv = [70] * 30 + [0, 145, 70]
+    total = sum(kv)
+    q_pos = np.sort(np.random.default_rng(per).integers(-1, total, size=n * per))
+    for opts in (dict(), dict(aux_stream=torch.cuda.Stream()),
+                 dict(aux_stream=torch.cuda.Stream(), keep_partials=True),
+                 dict(keep_partials=True, gathered_q=True)):
+        args, cls = counts_case(kv, [per] * n, 16, 1, d, q_pos)
+        if "gathered_q" in opts:   # back to back in one buffer
+            for i in (0, 3):
+                whole = torch.cat(args[i])
+                args[i][:] = [whole[r * per:(r + 1) * per] for r in range(n)]
+        ring = B.Ring(*args, out_dtype=torch.float32, **opts)
+        for order in ([B.cp_ring_passq] if "gathered_q" in opts else
+                      [B.cp_ring_passkv, B.cp_ring_passq]):
+            out, lse = order(ring)
+            torch.cuda.synchronize()
+            check_counts(torch.cat(out), torch.cat(lse), q_pos, cls, d)
+
+
 # merged step by step in one slot: nothing behind the slot is written
 def test_fused_ring_of_more_ranks_than_one_launch_takes(oracle):
     case = ring_case(4200, [9] * 33, [5] * 32 + [0], 4, 2, 128)
