@@ -196,6 +196,34 @@ def _raw(stream) -> Optional[int]:
     return None if stream is None else _stream(stream)
 
 
+def _elsewhere(stream, like: torch.Tensor):
+    """The torch stream of a stream argument if it is not torch's current one, else None."""
+    if not like.is_cuda:
+        return None
+    raw = _stream(stream)
+    if raw == torch.cuda.current_stream(like.device).cuda_stream:
+        return None
+    if isinstance(stream, torch.cuda.Stream):
+        return stream
+    return torch.cuda.ExternalStream(raw, device=like.device) if raw \
+        else torch.cuda.default_stream(like.device)
+
+
+def _allocated_there(other, like: torch.Tensor, call, *results):
+    """`call` allocates what its kernels on the stream `other` use. That memory comes from the pool of
+    `other`: a block of the current stream's pool may still be in use there, and would be given out
+    again there when it is released, while the kernels are queued. `results`: what the caller
+    brought; what the call made in place of a None is the caller's on the current stream."""
+    here = torch.cuda.current_stream(like.device)
+    with torch.cuda.stream(other):
+        made = call()
+    if type(made) is tuple:
+        for given, t in zip(results, made):
+            if given is None and t is not None:
+                t.record_stream(here)
+    return made
+
+
 def make_shape(dtype: int, head_dim: int, n_q_heads: int, n_kv_heads: int, total_q: int,
                total_kv: int, batch: int = 1, softmax_scale: float = 0.0,
                flags: int = 0) -> cp_shape:
@@ -256,8 +284,13 @@ def cp_attn_partial(q, k, v, q_pos, kv_pos, cu_seqlens_q=None, cu_seqlens_kv=Non
                     out_dtype: Optional[torch.dtype] = None, softmax_scale: float = 0.0,
                     out=None, lse=None, workspace=None, stream=None):
     """(O, LSE) of q [Tq, N_H, d] against k, v [Tkv, N_KV, d] under kv_pos <= q_pos."""
-    r = (_native or _calls()).partial(q, k, v, q_pos, kv_pos, cu_seqlens_q, cu_seqlens_kv,
-                                      out_dtype, softmax_scale, out, lse, workspace, _raw(stream))
+    args = (q, k, v, q_pos, kv_pos, cu_seqlens_q, cu_seqlens_kv, out_dtype, softmax_scale, out, lse,
+            workspace, _raw(stream))
+    call = (_native or _calls()).partial
+    other = None
+    if stream is not None and (out is None or lse is None or workspace is None):
+        other = _elsewhere(stream, q)
+    r = call(*args) if other is None else _allocated_there(other, q, lambda: call(*args), out, lse)
     if type(r) is int:
         raise CpError(r, "cp_attn_partial")
     return r
@@ -273,7 +306,9 @@ def cp_attn_partial_accumulate(q, k, v, q_pos, kv_pos, acc_out, acc_lse, final_o
     shape = make_shape(dtype_code(q.dtype), d, nh, nkv, tq, tkv, 1, softmax_scale)
     assert acc_out.dtype == torch.float32 and acc_lse.dtype == torch.float32
     if workspace is None:
-        workspace = _workspace(cp_workspace_bytes(shape, CP_WS_PARTIAL), q.device)
+        other = None if stream is None else _elsewhere(stream, q)
+        make = lambda: _workspace(cp_workspace_bytes(shape, CP_WS_PARTIAL), q.device)
+        workspace = make() if other is None else _allocated_there(other, q, make)
     wp, wn = _ws_ptr(workspace)
     fdt = dtype_code(final_out.dtype) if final_out is not None else CP_FP32
     _check(lib.cp_attn_partial_accumulate(ctypes.byref(shape), _ptr(q), _ptr(k), _ptr(v),
@@ -288,8 +323,13 @@ def cp_attn_decode(q, k, v, q_pos, kv_pos, cu_seqlens_kv, bid,
                    out=None, lse=None, workspace=None, stream=None, unique_bid: bool = False):
     """Decode step: query i attends to KV segment bid[i] of the packed k, v. `unique_bid`:
     the caller's promise that no sequence id occurs twice (CP_SHAPE_UNIQUE_BID)."""
-    r = (_native or _calls()).decode(q, k, v, q_pos, kv_pos, cu_seqlens_kv, bid, out_dtype,
-                                     softmax_scale, out, lse, workspace, _raw(stream), unique_bid)
+    args = (q, k, v, q_pos, kv_pos, cu_seqlens_kv, bid, out_dtype, softmax_scale, out, lse,
+            workspace, _raw(stream), unique_bid)
+    call = (_native or _calls()).decode
+    other = None
+    if stream is not None and (out is None or lse is None or workspace is None):
+        other = _elsewhere(stream, q)
+    r = call(*args) if other is None else _allocated_there(other, q, lambda: call(*args), out, lse)
     if type(r) is int:
         raise CpError(r, "cp_attn_decode")
     return r
@@ -316,11 +356,17 @@ class KVCache:
         self.slots = int(cu[-1])
         self.cu_host = cu.astype(np.int32)
         self.cu = torch.as_tensor(self.cu_host).to(device)
-        self.k = torch.empty((self.slots, n_kv_heads, head_dim), dtype=dtype, device=device)
-        self.v = torch.empty_like(self.k)
-        self.kv_pos = torch.empty((self.slots,), dtype=torch.int32, device=device)
-        self.used = torch.empty((self.batch + 1,), dtype=torch.int32, device=device)  # + ticket word
-        self.dropped = torch.empty((1,), dtype=torch.int32, device=device)
+
+        def buffers():
+            k = torch.empty((self.slots, n_kv_heads, head_dim), dtype=dtype, device=device)
+            return (k, torch.empty_like(k),
+                    torch.empty((self.slots,), dtype=torch.int32, device=device),
+                    torch.empty((self.batch + 1,), dtype=torch.int32, device=device),  # + ticket word
+                    torch.empty((1,), dtype=torch.int32, device=device))
+        other = None if stream is None else _elsewhere(stream, self.cu)
+        made = buffers() if other is None \
+            else _allocated_there(other, self.cu, buffers, *[None] * 5)
+        self.k, self.v, self.kv_pos, self.used, self.dropped = made
         shape = make_shape(dtype_code(dtype), head_dim, n_kv_heads, n_kv_heads, 0, self.slots,
                            self.batch)
         _check(load().cp_kv_cache_reset(ctypes.byref(shape), _ptr(self.k), _ptr(self.v),
@@ -353,7 +399,13 @@ def cp_attn_merge(outs: Sequence[torch.Tensor], lses: Sequence[torch.Tensor],
                   out_dtype: Optional[torch.dtype] = None, out=None, lse_out=None,
                   want_lse: bool = True, stream=None):
     """Equation 4 over partial outputs outs[s] [..., d] with lses[s] [...]."""
-    r = (_native or _calls()).merge(outs, lses, out_dtype, out, lse_out, want_lse, _raw(stream))
+    args = (outs, lses, out_dtype, out, lse_out, want_lse, _raw(stream))
+    call = (_native or _calls()).merge
+    other = None
+    if stream is not None and (out is None or (want_lse and lse_out is None)) and len(outs) > 0:
+        other = _elsewhere(stream, outs[0])
+    r = call(*args) if other is None \
+        else _allocated_there(other, outs[0], lambda: call(*args), out, lse_out)
     if type(r) is int:
         raise CpError(r, "cp_attn_merge")
     return r
