@@ -191,6 +191,13 @@ int choose_splits(int64_t wgs, int tiles, double rows, int head_dim, int max_spl
   return splits;
 }
 
+// The most parts that a launch of `wgs` workgroups cuts `tiles` tiles into: three rounds of
+// workgroups, beyond which there is 2 % to gain and the partials grow without end.
+int max_parts(int64_t wgs, int tiles, bool per_shard) {
+  const int64_t three_rounds = wgs > 0 && wgs < 256 ? 768 / wgs : 1;
+  return (int)std::min<int64_t>({three_rounds, tiles, per_shard ? 16 : CP_MAX_PARTS});
+}
+
 struct Plan {
   Mode mode;
   int n_row_blocks, n_blocks, n_sub, n_z;  // n_z: shards kept apart
@@ -258,7 +265,7 @@ Plan make_plan(const AttnShape& s) {
   // Otherwise the KV axis is split where the workgroups alone leave CUs idle: for every shard
   // kept apart by the size of the average shard.
   pl.n_sub = choose_splits(wgs, tiles, (double)rows_all * pl.n_z, s.head_dim,
-                           s.per_shard ? 16 : CP_MAX_PARTS);
+                           max_parts(wgs, tiles, s.per_shard));
   pl.mode = pl.n_sub > 1 ? SPLIT : WHOLE;
   if (pl.mode == SPLIT) {
     // One shard of more blocks than a workgroup lists at once: parts by index, since counting and
@@ -332,19 +339,32 @@ bool attn_mfma_applies(int dtype, int head_dim, int n_q_heads, int n_kv_heads) {
          n_q_heads / n_kv_heads <= 64;
 }
 
-// A program may keep one workspace, sized for its largest KV, and call with less: what fewer keys
-// would be cut into equal shares for fits as well.
+// A program may keep one workspace, sized for its largest KV, and call with less. Fewer keys can
+// need more (other part counts, equal shares), so the size covers every smaller KV: the shares if
+// any of them is cut into shares, and the most parts that any of them is split into.
 size_t attn_mfma_workspace_bytes(const AttnShape& s) {
   const Plan pl = make_plan(s);
-  size_t need = pl.total();
+  if (pl.mode == PLAN && !pl.cut) return pl.total();   // and so is every smaller KV
+  size_t need = pl.total() - pl.bounds_bytes;
   AttnShape fewer = s;
   fewer.n_blocks = std::min(s.n_blocks, PLAN_MAX_BLOCKS);
-  if (fewer.n_blocks < s.n_blocks) {
-    Plan q = make_plan(fewer);
-    q.bounds_bytes = pl.bounds_bytes;
-    need = std::max(need, q.total());
-  }
-  return need;
+  const Plan shares = make_plan(fewer);
+  if (shares.cut) need = std::max(need, shares.total() - shares.bounds_bytes);
+  // (Short walks one by one, longer ones by the bound. Where equal shares take over, from 16 tiles
+  // per sequence on at the latest, there are none of those up to the plan's limit.)
+  const int kShort = s.batch <= 8 ? 16 * std::max(s.batch, 1) : 0;
+  const int tiles = (int)((s.n_blocks / pl.n_z + 3) / 4);
+  const int64_t wgs = (int64_t)pl.n_row_blocks * pl.n_z * s.n_kv_heads;
+  const size_t rows = (size_t)pl.n_z * s.total_q * s.n_q_heads;
+  int parts = 1;
+  for (int t = 2; t <= std::min(tiles, kShort); ++t)
+    parts = std::max(parts, choose_splits(wgs, t, (double)rows, s.head_dim,
+                                          max_parts(wgs, t, s.per_shard)));
+  if (tiles > kShort && !(s.n_blocks <= PLAN_MAX_BLOCKS && shares.cut))
+    parts = std::max(parts, max_parts(wgs, tiles, s.per_shard));
+  if (parts > 1)
+    need = std::max(need, round256(parts * rows * s.head_dim * 4) + round256(parts * rows * 4));
+  return pl.bounds_bytes + need;
 }
 
 size_t attn_mfma_ring_workspace_bytes(const AttnShape& s) {

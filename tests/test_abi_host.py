@@ -255,6 +255,21 @@ def test_workspace_of_the_largest_kv_serves_smaller_calls(lib):
                                                    total_kv=n), B.CP_WS_PARTIAL) >= max(small)
 
 
+# and over all KV sizes for one set of queries, through every rule of the launch: uncut, parts of
+# the KV axis, equal shares, whole
+@pytest.mark.parametrize("nh,nkv,head_dim", [(16, 1, 128), (8, 2, 128), (8, 8, 64), (64, 4, 64)])
+def test_prefill_workspace_grows_with_the_kv(lib, nh, nkv, head_dim):
+    sizes = sorted({1, 256, 257, 768, 769, 1920, 2048, 16384, 16385, 30720, 30721,
+                    *(128 * t + d for t in (3, 5, 7, 9, 11, 13, 17, 23, 40, 100, 200, 241, 300,
+                                            417, 1000, 3000) for d in (0, 1))})
+    for total_q in (1, 16, 100, 400, 1000, 1359, 1400, 1500, 2040, 2100, 4000, 4096, 9000):
+        for batch in (1, 3):
+            need = [B.cp_workspace_bytes(_shape(n_q_heads=nh, n_kv_heads=nkv, head_dim=head_dim,
+                                                total_q=total_q, total_kv=n, batch=batch),
+                                         B.CP_WS_PARTIAL) for n in sizes]
+            assert need == sorted(need), (total_q, batch)
+
+
 def test_ring_descriptor_validation(lib):
     d = B.cp_ring_desc()
     assert lib.cp_ring_passkv(None, None) == -1
