@@ -191,9 +191,12 @@ __device__ __forceinline__ void pipe_body(PipeRegs<D>& R, const bf16x8_t (&qf)[D
   // has seen, so nothing underflows that should not, and a block whose exponentials sum to more
   // than kOverflowSum (a score 40 log2 units above the reference) is detected from its sum and
   // redone in the full form, for the rows concerned. A block that straddles a query position is
-  // masked first (need_mask), and so is, without a look at its positions, one that no row of this
-  // wavefront can see (dead: the workgroup's other wavefronts can): whatever form the block takes,
-  // a score that its row must not see is -inf in it.
+  // masked first (need_mask). One that no row of this wavefront can see (dead: the workgroup's
+  // other wavefronts can) is taken against an infinite reference, i.e. as zeros; if that gives a NaN
+  // (a score that is not finite) it is redone like the others, and masked there: in no form does a
+  // score enter that its row must not see. (Masking it at once, 16 moves and a maximum a block, made
+  // a wavefront of blind rows hold its workgroup back: 5000 queries, the later half seeing all of
+  // 5000 keys, 114.5 -> 127 us.)
   // Full form (until every row of the wavefront has a reference): block maximum, and the
   // reference is raised when the maximum exceeds it by more than kRescaleSlack. O and l are
   // rescaled at the end of the step, after the MFMAs that still belong to the old reference. The
@@ -236,35 +239,36 @@ __device__ __forceinline__ void pipe_body(PipeRegs<D>& R, const bf16x8_t (&qf)[D
       m_use = R.m_run;
       if (__builtin_expect(need_mask | !have_ref, 0)) {  // wave-uniform, rare: off the hot path
         if (dead) {
+          m_use = INFINITY;
+        } else {
+          if (need_mask) {
+            // The kv_pos reads are simply waited for (which also completes every older LDS read,
+            // so the counted waits hold).
+            u32x4_t kp0 = lds_read_b128<POFF + 0>(paddr), kp1 = lds_read_b128<POFF + 32>(paddr);
+            u32x4_t kp2 = lds_read_b128<POFF + 64>(paddr), kp3 = lds_read_b128<POFF + 96>(paddr);
+            lgkm_wait<0>(kp0, kp1, kp2, kp3);
 #pragma unroll
-          for (int i = 0; i < 16; ++i) s[i] = -INFINITY;
-        } else if (need_mask) {
-          // The kv_pos reads are simply waited for (which also completes every older LDS read,
-          // so the counted waits hold).
-          u32x4_t kp0 = lds_read_b128<POFF + 0>(paddr), kp1 = lds_read_b128<POFF + 32>(paddr);
-          u32x4_t kp2 = lds_read_b128<POFF + 64>(paddr), kp3 = lds_read_b128<POFF + 96>(paddr);
-          lgkm_wait<0>(kp0, kp1, kp2, kp3);
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int32_t k0 = (int32_t)kp0[r], k1 = (int32_t)kp1[r];
-            const int32_t k2 = (int32_t)kp2[r], k3 = (int32_t)kp3[r];
-            if (k0 > qp || (BAND && k0 < ql)) s[0 + r] = -INFINITY;
-            if (k1 > qp || (BAND && k1 < ql)) s[4 + r] = -INFINITY;
-            if (k2 > qp || (BAND && k2 < ql)) s[8 + r] = -INFINITY;
-            if (k3 > qp || (BAND && k3 < ql)) s[12 + r] = -INFINITY;
+            for (int r = 0; r < 4; ++r) {
+              const int32_t k0 = (int32_t)kp0[r], k1 = (int32_t)kp1[r];
+              const int32_t k2 = (int32_t)kp2[r], k3 = (int32_t)kp3[r];
+              if (k0 > qp || (BAND && k0 < ql)) s[0 + r] = -INFINITY;
+              if (k1 > qp || (BAND && k1 < ql)) s[4 + r] = -INFINITY;
+              if (k2 > qp || (BAND && k2 < ql)) s[8 + r] = -INFINITY;
+              if (k3 > qp || (BAND && k3 < ql)) s[12 + r] = -INFINITY;
+            }
           }
-        }
-        if (!have_ref) {
-          const float m_step = block_max() * scale_log2;
-          // true on the first visible block, also if its scores are NaN: such a row is lost, and
-          // must not keep the others of its wavefront on the full form
-          raise = !(m_step <= R.m_run + kRescaleSlack);
-          const float m_new = raise ? m_step : R.m_run;
-          alpha = __builtin_amdgcn_exp2f(R.m_run - (m_new == -INFINITY ? 0.f : m_new));
-          R.l_run *= alpha;
-          R.m_run = m_new;
-          m_use = m_new == -INFINITY ? 0.f : m_new;
-          have_ref = __builtin_amdgcn_ballot_w64(m_new == -INFINITY) == 0;
+          if (!have_ref) {
+            const float m_step = block_max() * scale_log2;
+            // true on the first visible block, also if its scores are NaN: such a row is lost, and
+            // must not keep the others of its wavefront on the full form
+            raise = !(m_step <= R.m_run + kRescaleSlack);
+            const float m_new = raise ? m_step : R.m_run;
+            alpha = __builtin_amdgcn_exp2f(R.m_run - (m_new == -INFINITY ? 0.f : m_new));
+            R.l_run *= alpha;
+            R.m_run = m_new;
+            m_use = m_new == -INFINITY ? 0.f : m_new;
+            have_ref = __builtin_amdgcn_ballot_w64(m_new == -INFINITY) == 0;
+          }
         }
       }
       pin(m_use);
@@ -342,6 +346,10 @@ __device__ __forceinline__ void pipe_body(PipeRegs<D>& R, const bf16x8_t (&qf)[D
   if (__builtin_expect(__builtin_amdgcn_ballot_w64(over) != 0, 0)) {
     const float over_f = over ? 1.f : 0.f;
     const bool row_over = over_f + xor32(over_f) > 0.f;   // in either half of the row's keys
+    if (dead) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s[i] = -INFINITY;
+    }
     const float m_step = block_max() * scale_log2;
     const float m_new = row_over ? fmaxf(R.m_run, m_step) : R.m_run;
     m_use = m_new == -INFINITY ? 0.f : m_new;
