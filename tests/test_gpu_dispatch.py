@@ -176,6 +176,32 @@ def test_ring_of_more_ranks_than_one_launch_takes(oracle):
         check_ring(oracle, ring, out, lse, case, keep)
 
 
+# The walk behind arrival flags: uneven shards, an empty one, a rank without queries, several KV
+# heads, a shard of more blocks than a workgroup lists at once, one that never arrives.
+@pytest.mark.parametrize("kv_sizes,q_sizes,nh,nkv", [
+    ([700, 0, 33], [520, 0, 515], 64, 4),
+    ([1, 17000, 300, 0], [2048, 2050, 0, 2049], 16, 1),
+])
+def test_ring_walk_counts_every_key(kv_sizes, q_sizes, nh, nkv):
+    n, total, t = len(kv_sizes), sum(kv_sizes), sum(q_sizes)
+    ends = np.concatenate([[0], np.cumsum(kv_sizes)])
+    q_pos = np.random.default_rng(t).integers(-1, total, size=t)
+    rows = np.split(q_pos, np.cumsum(q_sizes)[:-1])
+    args, cls = counts_case(kv_sizes, q_sizes, nh, nkv, 128, q_pos)
+    for missing in (None, 0):        # shard 0 never arrives at rank 0 (its own, step 0)
+        arrived = [torch.ones(n, dtype=torch.int32, device="cuda") for _ in range(n)]
+        if missing is not None:
+            arrived[0][0] = 0
+        ring = B.Ring(*args, out_dtype=torch.float32, fused_merge=2, arrived=arrived, spin_limit=3)
+        out, lse = B.cp_ring_passkv(ring)
+        torch.cuda.synchronize()
+        assert ring.ring_error.tolist() == [0 if missing is None else 1] + [0] * (n - 1)
+        for a, r in enumerate(rows):
+            if len(r) > 0:
+                lo = ends[1] if a == 0 and missing is not None else 0
+                check_counts(out[a], lse[a], r, cls, 128, lo)
+
+
 # 33 ranks are N x N calls whose shards' position bounds are made once, in two launches (32 and 1):
 # two streams, gathered queries (a call per holder, one merge), every option with keys of zero so
 # that a bound of the wrong shard shows. 2050 tokens and 16 heads a rank are enough row blocks for

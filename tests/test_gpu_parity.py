@@ -318,18 +318,23 @@ def test_ring_walk_in_one_launch_matches_unsharded(oracle, n, t, flags):
         got_o = torch.stack([out[where[int(r)][0]][where[int(r)][1]] for r in rows])
         got_l = torch.stack([lse[where[int(r)][0]][where[int(r)][1]] for r in rows])
         check(got_o, got_l, ref_o, ref_l, what="ring walk, %s" % odt)
-        # the step-by-step ring with the merge in the epilogues computes the same thing
+        # step by step, every step merged in its epilogue, computes the same thing
         if odt == torch.float32:
-            step = B.Ring([dev(q[p]) for p in pos], [dev(k[p]) for p in pos],
-                          [dev(v[p]) for p in pos], [i32(p) for p in q_pos], [i32(p) for p in pos],
-                          out_dtype=odt, fused_merge=True)
-            out_s, lse_s = B.cp_ring_passkv(step)
-            torch.cuda.synchronize()
             for a in range(n):
-                assert float((out[a] - out_s[a]).abs().max()) < 2e-3
+                qa, qpa = dev(q[pos[a]]), i32(q_pos[a])
+                out_s = lse_s = None
+                for j in range(n):
+                    p = pos[(a - j) % n]
+                    args = (qa, dev(k[p]), dev(v[p]), qpa, i32(p))
+                    if j == 0:
+                        out_s, lse_s = B.cp_attn_partial(*args, out_dtype=odt)
+                    else:
+                        B.cp_attn_partial_accumulate(*args, out_s, lse_s)
+                torch.cuda.synchronize()
+                assert float((out[a] - out_s).abs().max()) < 2e-3
                 fin = torch.isfinite(lse[a])
-                assert torch.equal(fin, torch.isfinite(lse_s[a]))
-                assert float((lse[a][fin] - lse_s[a][fin]).abs().max()) < 1e-4
+                assert torch.equal(fin, torch.isfinite(lse_s))
+                assert float((lse[a][fin] - lse_s[fin]).abs().max()) < 1e-4
     with pytest.raises(B.CpError):   # pass-Q moves the queries: no such walk
         B.cp_ring_passq(ring)
 
@@ -337,8 +342,8 @@ def test_ring_walk_in_one_launch_matches_unsharded(oracle, n, t, flags):
 @pytest.mark.parametrize("fused", [0, 1, 2])
 def test_ring_with_an_empty_and_uneven_kv_shards(oracle, fused):
     """The KV of a ring need not be sharded like the queries (the mask is by position): one
-    rank holds no keys at all, another two ranks' worth, the third a ragged count. Covers the
-    one-launch tile-bound pre-pass over shards of different sizes, an empty one among them."""
+    rank holds no keys at all, another two ranks' worth, the third a ragged count. 0 and 1 are the
+    launch over all ranks and shards, 2 is the walk behind arrival flags."""
     n, t = 3, 6144 + 77
     q, q64 = randn(61, (t, 16, 128))
     k, k64 = randn(62, (t, 1, 128))
@@ -349,10 +354,13 @@ def test_ring_with_an_empty_and_uneven_kv_shards(oracle, fused):
     rows = np.r_[0:40, t // 2 - 8:t // 2 + 8, t - 40:t]
     ref_o, ref_l = oracle.attn(q64[rows], k64, v64, rows, np.arange(t))
     where = {int(p): (a, i) for a in range(n) for i, p in enumerate(pos[a])}
+    arrived = [torch.ones(n, dtype=torch.int32, device="cuda") for _ in range(n)] \
+        if fused == 2 else None
     ring = B.Ring([dev(q[p]) for p in pos], [dev(k[p]) for p in kv], [dev(v[p]) for p in kv],
                   [i32(p) for p in pos], [i32(p) for p in kv], out_dtype=torch.float32,
-                  fused_merge=fused)
+                  fused_merge=fused, arrived=arrived, spin_limit=1000)
     out, lse = B.cp_ring_passkv(ring)
+    assert not ring.arrival_failed()
     torch.cuda.synchronize()
     got_o = torch.stack([out[where[int(r)][0]][where[int(r)][1]] for r in rows])
     got_l = torch.stack([lse[where[int(r)][0]][where[int(r)][1]] for r in rows])
@@ -391,8 +399,8 @@ def test_ring_walk_gives_up_on_a_shard_that_never_arrives(oracle):
 @pytest.mark.parametrize("n,t,two_streams", [(4, 2048, False), (3, 1000, False),
                                              (4, 2048, True), (2, 16384, True)])
 def test_mfma_load_balanced_partials_and_merge(oracle, n, t, two_streams):
-    # two_streams: the drivers issue a rank's calls alternately on two streams (t = 16384 gives
-    # every call enough row blocks that none splits its KV axis, the condition for doing so)
+    # two_streams: accepted, and without effect on a ring of up to 32 ranks, which is one launch
+    # (larger ones, whose calls alternate between the streams: test_gpu_dispatch.py)
     aux = torch.cuda.Stream() if two_streams else None
     q, q64 = randn(41, (t, 16, 128))
     k, k64 = randn(42, (t, 1, 128))
