@@ -107,7 +107,9 @@ int cp_shard_positions(int64_t total, int64_t offset, int32_t n_ranks, int32_t r
 /*
  * Bytes of device workspace a call of the given kind needs for this shape
  * (an upper bound valid for any positions). 0 if none. Returns 0 for an
- * invalid shape (the call itself will report the error).
+ * invalid shape (the call itself will report the error). For CP_WS_PARTIAL the
+ * size does not shrink as total_kv grows: what serves the largest KV serves
+ * every smaller one with the same queries.
  */
 size_t cp_workspace_bytes(const cp_shape* shape, int32_t kind);
 
@@ -128,9 +130,14 @@ size_t cp_workspace_bytes(const cp_shape* shape, int32_t kind);
  *   workspace     (device) >= cp_workspace_bytes(shape, CP_WS_PARTIAL), 256-byte
  *                 aligned; may be NULL when that size is 0
  *
- * bf16 inputs with head_dim 128 run on the MFMA kernel (fully masked KV tiles
- * are skipped; short query shards are split over the KV axis through the
- * workspace). Other combinations run on an fp32 vector kernel.
+ * Matrix cores: bf16 with head_dim 128, packed or not; bf16 with head_dim 64 in one sequence;
+ * fp32 in one sequence; all for groups of up to 64 query heads on a KV head. Blocks of keys that
+ * no query sees are skipped. bf16 calls that would leave compute units idle are cut along the
+ * KV axis, with the parts in the workspace, and merged by a second launch. What is left (packed
+ * fp32, packed head_dim 64, larger groups) runs on the vector pipe and needs no workspace.
+ * Precision: scores, sums and accumulators are fp32 everywhere. Probabilities are rounded to
+ * bf16 with head_dim 128 bf16 inputs only; with head_dim 64 they keep 24 bits (three bf16 terms),
+ * with fp32 inputs they stay fp32.
  *
  * Packed batches (the fused variable-length inputs of Algorithm 2, Section 3.4):
  * query i of sequence b sees key j iff j belongs to sequence b and
@@ -159,8 +166,8 @@ int cp_attn_partial(const cp_shape* shape, const void* q, const void* k, const v
  *   final_lse  (device) fp32 or NULL: a copy of the merged LSE.
  *   other arguments as cp_attn_partial.
  * Rows of which this step sees no key are not touched (with final_out: copied from acc_out).
- * Errors: as cp_attn_partial; CP_ERR_UNSUPPORTED unless the call runs on the MFMA kernel
- * without a KV split (bf16, head_dim 128, batch 1, at least 128 row blocks of 256 rows).
+ * Errors: as cp_attn_partial; CP_ERR_UNSUPPORTED unless the call is large enough that its row
+ * blocks fill the compute units by themselves (bf16, head_dim 128, batch 1, at least 128 row blocks of 256 rows).
  */
 int cp_attn_partial_accumulate(const cp_shape* shape, const void* q, const void* k,
                                const void* v, const int32_t* q_pos, const int32_t* kv_pos,
@@ -320,6 +327,9 @@ typedef struct {
    * leaves that shard out and sets bit j of ring_error[k] (device int32 [n_ranks], required
    * with arrived; the caller zeroes it): which steps of which ranks gave up can be read off it.
    * The outputs of such a rank are then not meaningful, but every kernel ends.
+   * Only K and V may arrive behind a flag. Every kv_pos[k] must be complete in stream order
+   * before the call: the launch reads the positions of all shards first, to leave out the blocks
+   * that no query sees.
    * Limit of the contract: it relies on no line of a step's buffer being in a cache of this
    * GPU when its flag is seen. Within one launch that holds because the buffer is read only
    * after its flag. From one launch to the next (the next layer, the next call) it holds if
@@ -336,7 +346,9 @@ typedef struct {
    * Pass-Q drivers only. 1: the query shards of all ranks lie back to back in one buffer
    * (q[s + 1] == q[s] + n_q[s] rows, the same for q_pos and, for decode, bid; all n_q equal
    * and nonzero) - the small Q all-gathered instead of passed round the ring - and every KV
-   * holder k answers all N steps with ONE call over the gathered queries. Requires
+   * holder k answers all N steps at once, over the gathered queries. The holders are one attention
+   * launch in prefill rings of up to 32 ranks and in decode with unique_bid, a call each
+   * otherwise. Requires
    * keep_partials (n_ranks * n_ranks slots), in which the partial of the queries of rank a
    * against the KV of rank b is then in slot b * n_ranks + a: the N slots a holder writes
    * are contiguous, its All2All send buffer in destination order. Not with message_layout
@@ -387,7 +399,9 @@ int cp_ring_passq(const cp_ring_desc* desc, void* stream);
 /*
  * Batched ring pass-Q decode, Algorithm 4: as cp_ring_passq with one query token
  * per sequence, batch ids travelling with the queries, and KV_k[bid] lookups
- * through cu_seqlens_kv[k]. Uses cp_attn_decode for every step.
+ * through cu_seqlens_kv[k]. Every step is one cp_attn_decode call; with gathered_q a holder's N
+ * steps are one call, and with unique_bid as well all holders' steps are one launch, followed by
+ * one merge.
  */
 int cp_ring_passq_decode(const cp_ring_desc* desc, void* stream);
 

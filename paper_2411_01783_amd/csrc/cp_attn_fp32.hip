@@ -17,7 +17,7 @@
 //
 // Bound: the matrix pipe's fp32 rate (157 TFLOP/s) for long shards, launch and the chain
 // positions -> list -> K -> V for short ones. A ring of 512 tokens over 2 ranks (4 heads of 64)
-// takes 18.5 us; on the vector pipe, with a launch per ring step and a merge, it took 189 us.
+// takes 18.8 us; on the vector pipe, with a launch per ring step and a merge, it took 189 us.
 #include "cp_common.h"
 #include "cp_table.h"
 

@@ -347,7 +347,7 @@ __global__ __launch_bounds__(NTHREADS, 2) void decode_kernel(Params p) {
 // their ramp and tail 16 times, and left 85 MB of partials of short ranges to merge: 32 sequences
 // of 32K to 128K keys over 16 holders took 300 us and take 240). A range is
 // at least 64 keys, one unit per wavefront: shorter ones take as long and only make partials
-// (four conversations of 300 to 1800 keys 15.2 -> 11.2 us).
+// (four conversations of 300 to 1800 keys 15.2 -> 11.0 us).
 // ---------------------------------------------------------------------------
 constexpr int FW = 4;                           // wavefronts per workgroup
 constexpr int F_WG_PER_CU = 2;                  // (8 wavefronts per CU: 4 x 2 was faster than 8 x 1)

@@ -117,7 +117,7 @@ __global__ __launch_bounds__(256) void merge_kernel(MergePtrs ptrs, int n_parts_
 // branch on the weights would pull the loads behind the wait for the LSE values). NP is the
 // part count rounded up; parts past the end repeat the last one with weight zero. The addresses
 // step from part to part: as products of the part's index they do not fit the scalar registers at
-// 64 parts (one sequence of 131072 keys: 7.6 -> MEASURE us). A single rank's pointers are scalar
+// 64 parts (one sequence of 131072 keys: 7.6 -> 5.4 us). A single rank's pointers are scalar
 // loads with the other arguments; looked up by rank they are a vector load that everything else
 // waits for.
 template <typename TP, typename TO, int VEC, int NP>

@@ -1,9 +1,10 @@
 // fp32 vector-ALU partial attention: one wavefront per (query token, query head).
 //
-// Serves the shapes the MFMA kernel does not take (fp32 inputs, head_dim 64,
-// packed batches). It follows Appendix B directly: scores of 64 keys at a time,
-// a running maximum and denominator (online softmax), and a running weighted
-// sum of values. Correctness path; not tuned.
+// Serves the shapes the matrix-pipe kernels do not take: packed batches of fp32 or of
+// head_dim 64, and groups of more than 64 query heads on a KV head. It follows
+// Appendix B directly: scores of 64 keys at a time, a running maximum and
+// denominator (online softmax), and a running weighted sum of values.
+// Correctness path; not tuned.
 #include "cp_common.h"
 
 namespace cp {

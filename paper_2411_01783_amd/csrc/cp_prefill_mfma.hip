@@ -26,12 +26,14 @@
 //     shards, so that Equation 4 over the ring steps happens inside the online softmax. (A
 //     launch per ring step costs 12 to 17 us at small query shards whatever its work: 256
 //     launches and 256 split merges for 16 ranks, 6.08 ms at 1024 new tokens on 131072 cached
-//     ones, where one launch takes 0.94 ms; 4096 tokens of head_dim 64 over 4 ranks 45 us.)
+//     ones, where one launch takes 0.94 ms; 4096 tokens of head_dim 64 over 4 ranks 3.8 ms
+//     on the vector pipe, 62 us here.)
 //   - Small and middling calls, whose row blocks would leave compute units idle or with very
-//     different walks, are cut into equal shares by the workgroups themselves (PLAN). Where
-//     their positions do not fit LDS and the row blocks leave CUs idle, the KV axis is split over
-//     grid.z (SPLIT). Both write fp32 partials of what they cut to the workspace, which a second
-//     launch merges with Eq. 4.
+//     different walks, plan in the workgroups themselves (PLAN), if their positions fit LDS: a
+//     workgroup per row block where walks are short, equal shares of all the work elsewhere. Where
+//     positions do not fit, and in single calls with few row blocks, the KV axis is split over
+//     grid.z (SPLIT). What is cut goes to the workspace as fp32 partials, which a second launch
+//     merges with Eq. 4.
 //   - The epilogue transposes the accumulators through LDS so that every output
 //     row leaves as one contiguous 4 D byte (fp32) or 2 D byte (bf16) run.
 //   - The same body also merges into a running (O, LSE) in its epilogue (ACC), and walks the

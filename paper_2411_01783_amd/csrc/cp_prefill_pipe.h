@@ -383,9 +383,10 @@ __device__ __forceinline__ int ring_flag(const Params& p, int rank, int step) {
 }
 // Makes sure that the shard of ring step `step` of rank `rank` may be read: `peek` is what thread
 // 0 read of the step's flag while the previous shard was being walked (so a shard that arrived in
-// time costs no round trip here); if that was zero it polls (uncached loads, a short sleep between them, at most p.spin_limit of them).
-// The whole workgroup learns the outcome through LDS; false = the flag never came up:
-// bit `step` of the rank's error word is set and the caller leaves the shard out. Every wait ends.
+// time costs no round trip here); if that was zero it polls (uncached loads, a short sleep between
+// them, at most p.spin_limit of them). The whole workgroup learns the outcome through LDS; false =
+// the flag never came up: bit `step` of the rank's error word is set and the caller leaves the shard
+// out. Every wait ends.
 __device__ __forceinline__ bool ring_enter(const Params& p, int rank, int step, int tid,
                                            int* wg_scratch, int& peek) {
   int* const slot = wg_scratch + 20 + (step & 1);  // two slots: a wavefront may lag one step
@@ -408,12 +409,13 @@ __device__ __forceinline__ bool ring_enter(const Params& p, int rank, int step, 
   }
   lds_barrier();
   const int ok = __builtin_amdgcn_readfirstlane(*slot);
-  // The shard's data is read after its flag: every load of it is issued after this barrier,
-  // which thread 0 reaches only with the flag's value in hand. No cache invalidation: the
+  // The shard's K and V are read after its flag (its positions before: those are complete when the
+  // call is enqueued, and the blocks to walk are chosen from them): every load is issued after this
+  // barrier, which thread 0 reaches only with the flag's value in hand. No cache invalidation: the
   // caller gives every step a buffer of its own that is complete before its flag is set and
-  // is not written again while the kernel runs, so no line of it can be in a cache before the
-  // flag is seen. (An agent-scope acquire here invalidates the XCD's L2 once per workgroup and
-  // shard and costs 3.5 % of the walk.)
+  // is not written again while the kernel runs, so no line of its K and V can be in a cache
+  // before the flag is seen. (An agent-scope acquire here invalidates the XCD's L2 once per workgroup
+  // and shard and costs 3.5 % of the walk.)
   return ok != 0;
 }
 
@@ -438,7 +440,7 @@ __device__ __forceinline__ bool ring_enter(const Params& p, int rank, int step, 
 // left whole (2100 queries of 16 heads that all see the same 1050 keys: 53 us cut, 41 whole; where
 // half of them see 2100 and half none: 53 cut, 67 whole). Only for calls whose positions and unit list
 // fit LDS; larger ones have row blocks enough to keep every CU busy. Six packed prompts of 200 to
-// 3000 tokens over 4 ranks: 241 us with a workgroup per row block and 128-key tiles, 115 us in
+// 3000 tokens over 4 ranks: 241 us with a workgroup per row block and 128-key tiles, 112 us in
 // equal shares of 32-key blocks.
 // ---------------------------------------------------------------------------
 
