@@ -424,10 +424,10 @@ def bench_partial_prefill(names, reps: int = 5, cpu: bool = False):
                       [_i32(pp) for pp in kvpos], out_dtype=torch.bfloat16)
         flop = 4.0 * w.head_dim * w.n_q_heads * (t_new * p_cached + t_new * (t_new + 1) // 2)
         row = {"workload": name, "t_new": t_new, "p_cached": p_cached}
-        # (one and the same launch: two calls of warm-up left the first of the two on a clock that
-        # had not come up, and they seemed to differ)
+        # (one and the same launch: after a few calls of warm-up the first of the two still ran on a
+        # clock that had not come up, and they seemed to differ)
         for label, fn in (("passq", B.cp_ring_passq), ("passkv", B.cp_ring_passkv)):
-            sec = time_steps(lambda: fn(ring), reps, 20)
+            sec = time_steps(lambda: fn(ring), 4 * reps, 100)
             row[label + "_ms_per_ring"] = round(sec * 1e3, 3)
             row[label + "_tflops"] = round(flop / sec / 1e12, 1)
         # pass-Q with the (small) query shards gathered: every KV holder answers all 16 steps, the

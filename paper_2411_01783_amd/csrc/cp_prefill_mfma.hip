@@ -236,9 +236,9 @@ Plan make_plan(const AttnShape& s) {
               wgs * (24 + s.n_blocks / 4) < (1ll << 23);
   if (one_call) {
     // A call of one rank against one shard, as a rank of a real ring makes it. Up to two tiles, or
-    // up to six with four times as many row blocks: a workgroup per row block in one launch (400
-    // queries of 16 heads on 500 keys 22 us, with the KV axis split in three launches 25; 64
-    // queries 22 against 18). Equal shares from 128 row blocks on: with fewer, parts of the KV axis
+    // up to six with three times as many row blocks: a workgroup per row block in one launch (400
+    // queries of 16 heads on 500 keys 22 us, with the KV axis split in three launches 25; 200
+    // queries, 13 row blocks on 4 tiles, 22.7 and 22.3; 64 queries 22 against 18). Equal shares from 128 row blocks on: with fewer, parts of the KV axis
     // fill the CUs as well and write a smaller partial (1000 queries on their own 1000 keys 28 us
     // against 40). From 86 row blocks on two parts are all that fits one round, and equal shares
     // are better if the walks are long (3100 queries of 8 heads on 2 KV heads, later half of them
@@ -246,7 +246,7 @@ Plan make_plan(const AttnShape& s) {
     // earlier (700 queries of 16 heads on 2 25 us against 31).
     const int seen = tiles / s.batch;
     const bool uncut = seen <= 2 || (seen <= kUncutTiles &&
-                                     wgs >= (s.head_dim == 64 ? 128 : 4 * seen));
+                                     wgs >= (s.head_dim == 64 ? 128 : 3 * seen));
     const bool cut = seen > kUncutTiles && (wgs >= 128 || (3 * wgs > 256 && seen >= 16));
     // (With the position bounds there already, planning costs more than it saves: 33 ranks of 60
     // tokens 14.4 us a call against 12.3; and equal shares leave no room for a second stream.)
