@@ -440,7 +440,7 @@ __device__ __forceinline__ bool ring_enter(const Params& p, int rank, int step, 
 // left whole (2100 queries of 16 heads that all see the same 1050 keys: 53 us cut, 41 whole; where
 // half of them see 2100 and half none: 53 cut, 67 whole). Only for calls whose positions and unit list
 // fit LDS; larger ones have row blocks enough to keep every CU busy. Six packed prompts of 200 to
-// 3000 tokens over 4 ranks: 241 us with a workgroup per row block and 128-key tiles, 112 us in
+// 3000 tokens over 4 ranks: 241 us with a workgroup per row block and 128-key tiles, 114 us in
 // equal shares of 32-key blocks.
 // ---------------------------------------------------------------------------
 

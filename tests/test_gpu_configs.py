@@ -40,16 +40,23 @@ def _shard(w, q, k, v):
 
 @pytest.mark.parametrize("fused_merge", [2, True, False])
 def test_prefill_128k_passkv_ring_sampled(oracle, fused_merge):
-    # 2 walks a rank's 16 ring steps in one launch; True merges in the epilogues of 16
-    # launches; False keeps 16 partials per rank and merges them with the merge kernel
+    # 2 walks a rank's 16 ring steps behind arrival flags; True merges in the softmax of one launch
+    # over all ranks and shards; False keeps 16 partials per rank and merges them with the merge
+    # kernel (17 GB)
     w = W.WORKLOADS["prefill_128k"]
     q, k, v = W.qkv(w, device="cuda")
     pos, qs, ks, vs = _shard(w, q, k, v)
     ps = [i32(p) for p in pos]
+    opts = {}
+    if fused_merge is False:
+        opts["keep_partials"] = True
+    elif fused_merge == 2:
+        opts["arrived"] = [torch.ones(w.n_ranks, dtype=torch.int32, device="cuda") for _ in ps]
     ring = B.Ring(qs, ks, vs, ps, ps, out_dtype=torch.bfloat16, part_dtype=torch.float32,
-                  fused_merge=fused_merge)
+                  fused_merge=fused_merge, **opts)
     out, lse = B.cp_ring_passkv(ring)
     torch.cuda.synchronize()
+    assert fused_merge != 2 or not ring.arrival_failed()
     k64, v64 = W.to_f64(k), W.to_f64(v)
     rng = np.random.default_rng(w.seed)
     chunk = w.t_new // (2 * w.n_ranks)
