@@ -59,7 +59,9 @@ struct Geo {
   static constexpr int SMEM = OFF_BOUNDS;                        // bounds from global memory
   static constexpr int OFF_WEIGHT = OFF_BOUNDS + PLAN_MAX_BLOCKS * 8;  // PLAN: bounds kept in LDS
   static constexpr int OFF_SHARDS = OFF_WEIGHT + PLAN_MAX_UNITS * 2;   // units' weights
-  static constexpr int SMEM_PLAN = OFF_SHARDS + kMaxTable * 32;        // and the shards
+  static constexpr int OFF_INDEX = OFF_SHARDS + kMaxTable * 32;        // and the shards
+  static constexpr int SMEM_PLAN = OFF_INDEX + 16;                     // which share this is
+  static_assert(NWAVE * 32 * (D * 4 + 16) <= OFF_INDEX, "the epilogue's staging leaves it alone");
   static constexpr int OUT_STRIDE = D * 4 + 16;  // epilogue staging: one fp32 output row + pad
   static_assert(NWAVE * 32 * OUT_STRIDE <= SMEM, "epilogue staging fits in the allocation");
   static_assert(SMEM_PLAN <= 160 * 1024, "LDS budget of one CU");
@@ -576,11 +578,12 @@ struct LdsShard {
   int32_t n_kv, blk_begin;
 };
 
-// Bounds of all blocks, and this workgroup's share. `weight`: the units' planned tiles (LDS).
+// Bounds of all blocks, and this workgroup's share. `weight`: the units' planned tiles, `index`: which
+// share this is (LDS).
 template <int D, bool BAND>
 __device__ __forceinline__ Share plan_share(const Params& p, int2* lds_bounds, uint16_t* weight,
-                                            PlanLds& L, LdsShard* shards, int* wg_scratch,
-                                            int tid) {
+                                            PlanLds& L, LdsShard* shards, int* index,
+                                            int* wg_scratch, int tid) {
   const int lane = tid & 63, wave = tid >> 6;
   Share sh = {0, 0, 0};
   if (p.n_shards > 1 && tid >= 64 && tid < 64 + p.n_shards) {
@@ -700,12 +703,18 @@ __device__ __forceinline__ Share plan_share(const Params& p, int2* lds_bounds, u
   longest = __builtin_amdgcn_readfirstlane(longest);
   // the line of units, KV head after KV head
   const uint32_t total = (uint32_t)total1 * (uint32_t)p.n_kv_heads;
-  const int i = blockIdx.x, all = n_units * p.n_kv_heads;
+  const int all = n_units * p.n_kv_heads;
   // Whole units where a cut gains less than its partials cost: one round of workgroups, and the
   // longest unit not much longer than a share.
   const bool keep_whole = all <= (int)gridDim.x &&
                           longest <= (int)(total / gridDim.x) + kCutCost * (D / 64) / 2;
   const int n_wgs = keep_whole ? all : plan_workgroups(total, gridDim.x);
+  // Neighbouring shares, which walk the same keys, on one XCD (workgroups go to the 8 XCDs in turn),
+  // if every XCD gets its part of them.
+  const int i = n_wgs == kPlanWorkgroups
+                    ? (int)(blockIdx.x & 7) * (kPlanWorkgroups / 8) + (int)(blockIdx.x >> 3)
+                    : (int)blockIdx.x;
+  if (tid == 0) *index = i;
   if (i >= n_wgs) {
     if (tid == 0) p.plan_rec[i + 1] = make_int2(-1, 0);
     return sh;
@@ -764,6 +773,21 @@ enum Mode {
           // happens inside the online softmax
 };
 
+// Workgroup (x, z) of a grid whose z are different keys: those of one z onto as few XCDs as there
+// are to share out. Workgroups go to the 8 XCDs in turn, in the order of x + gridDim.x * z, and an
+// XCD's L2 fetches a tile of keys once for all that walk it there; as dispatched, 8 row blocks
+// against 16 holders in two parts each put every key on every XCD. g = gcd(gridDim.z, 8) classes of
+// z, an eighth of the workgroups for each XCD: class xcd % g, and every (8 / g)-th x. The order of x
+// (longest walks first) is kept.
+__device__ __forceinline__ void xcd_slice(int& x, int& z) {
+  const int nz = gridDim.z, g = nz & -nz & 7 ? nz & -nz : 8, s = 8 / g;
+  if (g == 1 || gridDim.x % s != 0) return;
+  const int line = x + gridDim.x * z, xcd = line & 7, idx = line >> 3, per = nz / g;
+  const int k = (uint32_t)idx / (uint32_t)per;
+  z = xcd % g + g * (idx - k * per);
+  x = k * s + xcd / g;
+}
+
 // A workgroup's walk: 256 consecutive (token, head-in-group) rows of one KV head, over the
 // queries of all ranks of the table back to back, against the visible blocks of the KV shards.
 // BAND: packed batch. Positions are shifted per sequence and a query also has a lower bound
@@ -784,26 +808,31 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
   int2* const lds_bounds = (int2*)(smem + G::OFF_BOUNDS);
   uint16_t* const weight = (uint16_t*)(smem + G::OFF_WEIGHT);
   LdsShard* const shards = (LdsShard*)(smem + G::OFF_SHARDS);
+  int* const share_index = (int*)(smem + G::OFF_INDEX);
   const uint32_t smem_lds = (uint32_t)(size_t)(CP_LDS_AS char*)smem;
 
   // ---- what this workgroup does first ----
   int row_block = 0, kvh = 0, z_shard = 0, z_sub = 0, rank = 0;
   Share share = {0, 0, 0};
   if constexpr (MODE == PLAN) {
-    share = plan_share<D, BAND>(p, lds_bounds, weight, *(PlanLds*)smem, shards, wg_scratch,
-                                threadIdx.x);
+    share = plan_share<D, BAND>(p, lds_bounds, weight, *(PlanLds*)smem, shards, share_index,
+                                wg_scratch, threadIdx.x);
     if (p.cut_units && share.length == 0) return;
     __syncthreads();   // the planning arrays are dead
   } else {
     // The KV heads of a row block are neighbours in dispatch order: the rows of one head are
     // n_kv_heads * 2 D bytes apart, so workgroups that all read the same head use only some of
     // the memory channels.
-    const int i = blockIdx.x / p.n_kv_heads;
-    kvh = blockIdx.x - i * p.n_kv_heads;
-    row_block = ordered_row_block(i, p.n_row_blocks, p.n_ranks, threadIdx.x & 63);
     // grid.z: the n_sub parts of the KV axis, of every shard in turn when shards are kept apart
-    z_shard = p.per_shard ? blockIdx.z / p.n_sub : 0;
-    z_sub = blockIdx.z - z_shard * p.n_sub;
+    int x = blockIdx.x, z = blockIdx.z;
+    if constexpr (MODE == WHOLE || MODE == SPLIT) {
+      if (gridDim.z > 1) xcd_slice(x, z);
+    }
+    const int i = x / p.n_kv_heads;
+    kvh = x - i * p.n_kv_heads;
+    row_block = ordered_row_block(i, p.n_row_blocks, p.n_ranks, threadIdx.x & 63);
+    z_shard = p.per_shard ? z / p.n_sub : 0;
+    z_sub = z - z_shard * p.n_sub;
     if constexpr (MODE == RING) {   // row blocks do not straddle ranks here
       while (p.rb_begin[rank + 1] <= row_block) ++rank;
       row_block -= p.rb_begin[rank];
@@ -1244,7 +1273,8 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
     Glb<char> o_row;
     Glb<float> lse_row = nullptr;
     if (MODE == PLAN && partial) {
-      const int slot = 2 * blockIdx.x + (first_piece ? 1 : 0);
+      const int slot =
+          2 * __builtin_amdgcn_readfirstlane(*share_index) + (first_piece ? 1 : 0);
       row_lin = (int64_t)slot * BM + wave * 32 + n_e;
       o_row = (Glb<char>)(p.part_out + row_lin * D);
       lse_row = (Glb<float>)(p.part_lse + row_lin);
@@ -1261,7 +1291,7 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
       }
       row_lin = ((int64_t)token * p.n_kv_heads + kvh) * p.group + hg;
       if (MODE == SPLIT) {
-        row_lin += (int64_t)blockIdx.z * p.rows_all_heads;
+        row_lin += (int64_t)(z_shard * p.n_sub + z_sub) * p.rows_all_heads;
         o = (Glb<char>)p.part_out;
         l = (Glb<float>)p.part_lse;
       } else {
