@@ -13,9 +13,9 @@
 //     SM(i):   mask, row maximum, exponentials of block i   (vector pipe)
 //     Q(i+1):  S^T = K Q^T of the next block                (D / 16 MFMA, matrix pipe)
 // The three are independent, so the vector work is issued between the MFMAs of its
-// neighbours, one slice per MFMA (two at D = 64), in source order (scheduling fences keep
-// that order). LDS fragment reads are inline assembly with hand-counted lgkmcnt waits, issued
-// D / 16 MFMAs before their use: the compiler would otherwise wait for the tile prefetch
+// neighbours, one slice per MFMA, in source order (scheduling fences keep that order). LDS
+// fragment reads are inline assembly with hand-counted lgkmcnt waits, issued D / 16 MFMAs (of one
+// term) before their use: the compiler would otherwise wait for the tile prefetch
 // (vmcnt(0)) in front of every LDS read that follows a direct-to-LDS load, and would not
 // keep reads in flight across its own waits.
 //
@@ -175,7 +175,6 @@ __device__ __forceinline__ void pipe_body(PipeRegs<D>& R, const bf16x8_t (&qf)[D
   constexpr int KOFF = ((BLK + 1) & 3) * G::BLK;
   constexpr int VOFF = BLK * G::BLK;
   constexpr int H = G::NKS;          // MFMAs per half step
-  constexpr int SL = 8 / H;          // vector slices per MFMA
   constexpr int POFF = BLK * 32 * 4;
   // exponentials started by vector slice 1 + k: values [kBound[k], kBound[k + 1]); they are
   // summed and packed one slice later (a transcendental result has a wait state)
@@ -221,11 +220,11 @@ __device__ __forceinline__ void pipe_body(PipeRegs<D>& R, const bf16x8_t (&qf)[D
 #pragma unroll
       for (int t = 0; t < G::TERMS; ++t) {
         unsigned pk = pack_bf16(a, b);
+        pin(pk);   // (here: the compiler otherwise converts a once more for its half of pk)
         if (t + 1 < G::TERMS) {   // what the term leaves over (exact)
           a -= __builtin_bit_cast(float, pk << 16);
           b -= __builtin_bit_cast(float, pk & 0xffff0000u);
         }
-        pin(pk);
         R.pb[CUR][t][v >> 3][(v & 7) >> 1] = pk;
       }
       pin(lsum1);
@@ -289,11 +288,6 @@ __device__ __forceinline__ void pipe_body(PipeRegs<D>& R, const bf16x8_t (&qf)[D
     }
   };
 
-  auto slices = [&](auto mc) __attribute__((always_inline)) {
-    constexpr int M = decltype(mc)::value;
-    valu(IntC<M * SL>{});
-    if constexpr (SL == 2) valu(IntC<M * SL + 1>{});
-  };
 
   // ---- first half: P(i-1) on the matrix pipe, K fragments of block i+1 requested ----
   auto first = [&](auto mc) __attribute__((always_inline)) {
@@ -302,15 +296,21 @@ __device__ __forceinline__ void pipe_body(PipeRegs<D>& R, const bf16x8_t (&qf)[D
       // LDS operations issued after V fragment M: H - 1 - M later V fragments (two reads each)
       // and M K fragments
       lgkm_wait<2 * (H - 1 - M) + M>(R.vf[M]);
-#pragma unroll
-      for (int t = 0; t < G::TERMS; ++t)
-        R.o[M % G::NDB] = mfma32(__builtin_bit_cast(bf16x8_t, R.vf[M]),
-                                 __builtin_bit_cast(bf16x8_t, R.pb[NXT][t][M / G::NDB]),
-                                 R.o[M % G::NDB]);
-      R.kf[M] = lds_read_b128<KOFF>(kaddr[M]);
-      hook(IntC<M>{});
-      slices(IntC<M>{});
-      __builtin_amdgcn_sched_barrier(0);
+      auto term = [&](auto tc) __attribute__((always_inline)) {
+        constexpr int T = decltype(tc)::value;
+        if constexpr (T < G::TERMS) {
+          R.o[M % G::NDB] = mfma32(__builtin_bit_cast(bf16x8_t, R.vf[M]),
+                                   __builtin_bit_cast(bf16x8_t, R.pb[NXT][T][M / G::NDB]),
+                                   R.o[M % G::NDB]);
+          if constexpr (T + 1 == G::TERMS) {
+            R.kf[M] = lds_read_b128<KOFF>(kaddr[M]);
+            hook(IntC<M>{});
+          }
+          valu(IntC<M * G::TERMS + T>{});
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      };
+      term(IntC<0>{}); term(IntC<1>{}); term(IntC<2>{});
     }
   };
   first(IntC<0>{}); first(IntC<1>{}); first(IntC<2>{}); first(IntC<3>{});
@@ -332,7 +332,7 @@ __device__ __forceinline__ void pipe_body(PipeRegs<D>& R, const bf16x8_t (&qf)[D
       }
       R.vf[M] = lds_read_vt_frag<VOFF + (M / G::NDB) * 16 * G::ROW, G::ROW>(vaddr[M % G::NDB]);
       hook(IntC<H + M>{});
-      slices(IntC<H + M>{});
+      valu(IntC<H * G::TERMS + M>{});
       __builtin_amdgcn_sched_barrier(0);
     }
   };
