@@ -8,27 +8,26 @@
 // per 16-byte load of K; the channel order of the second is free as well, so a lane's 16-byte
 // load of V serves four channel blocks.
 //
-// A workgroup of 4 wavefronts owns 16 * NR rows (token, head-in-group) of one KV head; the
+// A workgroup of 4 or 8 wavefronts owns 16 * NR rows (token, head-in-group) of one KV head; the
 // 16-key blocks that any of its queries can see are listed in LDS and dealt out over the
 // wavefronts, whose results are combined in LDS at the end. Splitting the keys and not the rows
 // over the wavefronts keeps small problems (the 512-token configuration has 2048 rows) on many
 // CUs with a short serial chain each. NR = 2 (head_dim 64, many rows) halves the K/V traffic
 // from L2.
 //
-// Bound: the matrix pipe's fp32 rate (157 TFLOP/s) for long shards, launch and the chain
-// positions -> list -> K -> V for short ones. A ring of 512 tokens over 2 ranks (4 heads of 64)
-// takes 18.2 us; on the vector pipe, with a launch per ring step and a merge, it took 189 us.
+// Bound: the matrix pipe's fp32 rate (157 TFLOP/s) for long shards, launch
+// and the chain positions -> list -> K -> V for short ones. A ring of 512 tokens over 2 ranks (4
+// heads of 64) takes 14.2 us: 128 workgroups, of whose 14 us the matrix pipe needs 3.4. It took 18.1
+// with 4 wavefronts a workgroup and the key positions asked for after the queries' had come.
 #include "cp_common.h"
 #include "cp_table.h"
 
 namespace cp {
 namespace {
 
-constexpr int NWAVE = 4;
-constexpr int NTHREADS = NWAVE * 64;
 constexpr int BLK = 16;                     // keys per block
 constexpr int PER = kAttnBlock / BLK;       // blocks here per block of the table
-constexpr int MAX_LIST = NTHREADS;          // blocks looked at per chunk
+constexpr int kMaxList = 512;              // blocks looked at per chunk: a thread each, at most
 
 struct Params {
   AttnTable t;
@@ -57,12 +56,14 @@ struct BlockRegs {
   int last;
 };
 
-template <int D, int NR, typename TO>
-__global__ __launch_bounds__(NTHREADS) void attn_fp32_kernel(const Params p) {
+template <int D, int NR, int NWAVE, typename TO>
+__global__ __launch_bounds__(NWAVE * 64) void attn_fp32_kernel(const Params p) {
+  constexpr int NTHREADS = NWAVE * 64;
+  constexpr int MAX_LIST = NTHREADS;                    // blocks looked at per chunk
   constexpr int ROWS = 16 * NR;
   constexpr int STRIDE = D + 4;
   __shared__ int2 list[MAX_LIST];                       // (shard, first key)
-  __shared__ int wg_scratch[8];
+  __shared__ int wg_scratch[NWAVE];
   __shared__ __align__(16) float comb[NWAVE][ROWS][STRIDE];
   __shared__ float comb_m[NWAVE][ROWS], comb_l[NWAVE][ROWS];
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -70,6 +71,35 @@ __global__ __launch_bounds__(NTHREADS) void attn_fp32_kernel(const Params p) {
   const int row_block = ordered_row_block(blockIdx.x, gridDim.x, p.t.n_ranks, lane);
   const int kvh = blockIdx.y;
   const int z_shard = p.per_shard ? blockIdx.z : 0;
+
+  // This thread's block of the chunk at b0 and its smallest position (none: above every query's).
+  // The first chunk's positions are asked for before the queries, so that the two travel together.
+  const int b_begin = (p.per_shard ? p.t.blk_begin[z_shard] : 0) * PER;
+  const int b_end = (p.per_shard ? p.t.blk_begin[z_shard + 1] : p.n_blocks) * PER;
+  int sh = z_shard, key0 = 0;
+  int64_t lo = INT64_MAX;
+  auto look = [&](int b0) {
+    const int b = b0 + tid;
+    sh = z_shard;
+    lo = INT64_MAX;
+    if (b < b_end) {
+      const int blk = b / PER;
+      if (!p.per_shard) {
+#pragma unroll 8
+        for (int i = 1; i < p.t.n_shards; ++i) sh += blk >= p.t.blk_begin[i];
+      }
+      key0 = (blk - p.t.blk_begin[sh]) * kAttnBlock + (b % PER) * BLK;
+      const int last = p.t.n_kv[sh] - 1 - key0;
+      if (last >= 0) {
+        const int32_t* pt = p.t.kv_pos[sh] + key0;
+        int m = INT32_MAX;
+#pragma unroll
+        for (int i = 0; i < BLK; ++i) m = min(m, pt[min(i, last)]);
+        lo = m;
+      }
+    }
+  };
+  look(b_begin);
 
   // ---- queries: row r of column group c is this lane's column n ----
   floatx4_t qf[NR][D / 16];
@@ -93,7 +123,7 @@ __global__ __launch_bounds__(NTHREADS) void attn_fp32_kernel(const Params p) {
   }
 #pragma unroll
   for (int o = 8; o > 0; o >>= 1) qmax = max(qmax, __shfl_xor(qmax, o, 64));
-  qmax = __builtin_amdgcn_readfirstlane(qmax);  // (the four wavefronts hold the same rows)
+  qmax = __builtin_amdgcn_readfirstlane(qmax);  // (the wavefronts hold the same rows)
 
   float m_run[NR], l_run[NR];
   floatx4_t acc[NR][D / 16];
@@ -174,29 +204,10 @@ __global__ __launch_bounds__(NTHREADS) void attn_fp32_kernel(const Params p) {
     }
   };
 
-  const int b_begin = (p.per_shard ? p.t.blk_begin[z_shard] : 0) * PER;
-  const int b_end = (p.per_shard ? p.t.blk_begin[z_shard + 1] : p.n_blocks) * PER;
   for (int b0 = b_begin; b0 < b_end; b0 += MAX_LIST) {
     // list of the blocks some query of the workgroup can see
-    const int b = b0 + tid;
-    bool live = false;
-    int sh = z_shard, key0 = 0;
-    if (b < b_end) {
-      const int blk = b / PER;
-      if (!p.per_shard) {
-#pragma unroll 8
-        for (int i = 1; i < p.t.n_shards; ++i) sh += blk >= p.t.blk_begin[i];
-      }
-      key0 = (blk - p.t.blk_begin[sh]) * kAttnBlock + (b % PER) * BLK;
-      const int last = p.t.n_kv[sh] - 1 - key0;
-      if (last >= 0) {
-        const int32_t* pt = p.t.kv_pos[sh] + key0;
-        int lo = INT32_MAX;
-#pragma unroll
-        for (int i = 0; i < BLK; ++i) lo = min(lo, pt[min(i, last)]);
-        live = lo <= qmax;
-      }
-    }
+    if (b0 != b_begin) look(b0);
+    const bool live = lo <= qmax;
     const uint64_t mask = __builtin_amdgcn_ballot_w64(live);
     __syncthreads();  // the previous list is no longer read
     if (lane == 0) wg_scratch[wave] = __builtin_popcountll(mask);
@@ -247,7 +258,8 @@ __global__ __launch_bounds__(NTHREADS) void attn_fp32_kernel(const Params p) {
     }
   }
   __syncthreads();
-  constexpr int TPR = 16, CPT = D / TPR;   // threads per row, channels per thread
+  constexpr int TPR = NTHREADS / 16, CPT = D / TPR;   // threads per row, channels per thread
+  static_assert(TPR <= 64 && CPT >= 1, "a row is in one wavefront");
 #pragma unroll
   for (int c = 0; c < NR; ++c) {
     const int row = c * 16 + tid / TPR, ch = (tid % TPR) * CPT;
@@ -284,10 +296,11 @@ __global__ __launch_bounds__(NTHREADS) void attn_fp32_kernel(const Params p) {
     for (int i = 0; i < CPT; ++i) spoil = fmaf(x[i], 0.f, spoil);
     uint64_t spoiled = __builtin_amdgcn_ballot_w64(row_ok && den > 0.f && den < INFINITY &&
                                                    !(spoil == 0.f));
-    const bool mine = (spoiled >> (lane & ~(TPR - 1)) & ((1u << TPR) - 1)) != 0;
+    constexpr uint64_t kRowLanes = TPR == 64 ? ~0ull : (1ull << (TPR & 63)) - 1;
+    const bool mine = (spoiled >> (lane & ~(TPR - 1)) & kRowLanes) != 0;
     while (__builtin_expect(spoiled != 0, 0)) {
       const int rl = __builtin_ctzll(spoiled) & ~(TPR - 1);   // first lane of the row
-      spoiled &= ~(((1ull << TPR) - 1) << rl);
+      spoiled &= ~(kRowLanes << rl);
       const int ra = __builtin_amdgcn_readlane(a, rl);
       const int64_t rlin = (int64_t)(
           (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)lin, rl) |
@@ -320,22 +333,37 @@ __global__ __launch_bounds__(NTHREADS) void attn_fp32_kernel(const Params p) {
   }
 }
 
-template <int D, int NR, typename TO>
+template <int D, int NR, int NWAVE, typename TO>
 int launch_t(const AttnShape& s, Params& p, hipStream_t stream) {
   const int64_t blocks = (p.rows + 16 * NR - 1) / (16 * NR);
   if (blocks > 0x7fffffffLL) return CP_ERR_SHAPE;
-  hipLaunchKernelGGL((attn_fp32_kernel<D, NR, TO>),
+  hipLaunchKernelGGL((attn_fp32_kernel<D, NR, NWAVE, TO>),
                      dim3((unsigned)blocks, s.n_kv_heads, s.per_shard ? s.n_shards : 1),
-                     dim3(NTHREADS), 0, stream, p);
+                     dim3(NWAVE * 64), 0, stream, p);
   return check_launch();
 }
 
+// head_dim 128: a workgroup of 8 wavefronts holds as many registers as two of 4 would need to be on
+// a CU together, and those do not fit (one wavefront a SIMD): 4096 tokens of 8 heads over 2 ranks
+// 580 -> 486 us, 8192 on 2 KV heads 2198 -> 1779, 512 of 4 heads 26 -> 23.
+// head_dim 64, by workgroups of 16 rows (2 ranks; us):
+//   up to 512, two a CU: the walk of the longest row block is what the call waits for, and 8
+//     wavefronts halve it (512 tokens of 4 heads 17.5 -> 14.2, 1400 38.4 -> 26.5, 2048 54.2 -> 43.1)
+//   up to 768: three workgroups of 4 wavefronts are on a CU at once, all of them run together (1400
+//     tokens of 8 heads on 2 KV heads, 700: 44.3; 8 wavefronts 49.1, 32 rows as below 58)
+//   up to 1024: a fourth would wait for a CU; 32 rows by 8 wavefronts are two even rounds (875: 145
+//     -> 89, 900: 64 -> 56, 950: 87 -> 61, 1000: 135 -> 111; at 750 79 -> 108)
+//   beyond: 32 rows by 4 wavefronts, half the K/V traffic from L2 (1250: 203; 8 wavefronts 225; 2048:
+//     221 and 228, 16 rows by 8 wavefronts 285)
 template <typename TO>
 int launch_o(const AttnShape& s, Params& p, hipStream_t stream) {
-  if (s.head_dim == 128) return launch_t<128, 1, TO>(s, p, stream);
-  // 32 rows per workgroup once 16 would give every CU more than four workgroups
-  if (p.rows * s.n_kv_heads > 16 * 4 * 256) return launch_t<64, 2, TO>(s, p, stream);
-  return launch_t<64, 1, TO>(s, p, stream);
+  if (s.head_dim == 128) return launch_t<128, 1, 8, TO>(s, p, stream);
+  const int64_t wgs = (p.rows + 15) / 16 * s.n_kv_heads;
+  const int64_t all = wgs * (s.per_shard ? s.n_shards : 1);
+  if (all <= 2 * 256) return launch_t<64, 1, 8, TO>(s, p, stream);
+  if (wgs > 4 * 256) return launch_t<64, 2, 4, TO>(s, p, stream);
+  if (all > 3 * 256 && all <= 4 * 256) return launch_t<64, 2, 8, TO>(s, p, stream);
+  return launch_t<64, 1, 4, TO>(s, p, stream);
 }
 
 }  // namespace
@@ -345,7 +373,7 @@ int launch_attn_fp32(const AttnShape& s, const AttnTable& t, const AttnOut& o,
   if (s.head_dim != 64 && s.head_dim != 128) return CP_ERR_UNSUPPORTED;
   if (s.n_kv_heads > 65535) return CP_ERR_SHAPE;
   // block indices are kept in 31 bits; so are row indices
-  if (s.n_blocks > 0x7fffffff / PER - MAX_LIST) return CP_ERR_SHAPE;
+  if (s.n_blocks > 0x7fffffff / PER - kMaxList) return CP_ERR_SHAPE;
   Params p = {};
   p.t = t;
   p.group = s.n_q_heads / s.n_kv_heads;

@@ -286,6 +286,28 @@ def test_fp32_ring(oracle, kv_sizes, q_sizes, nh, nkv, d, keep):
     check_ring(oracle, ring, out, lse, case, keep, O_ATOL_FP32, LSE_RTOL_FP32)
 
 
+# fp32, 8 wavefronts a workgroup: workgroups of 16 rows on either side of 512 (two a CU), 768 and 1024
+# (head_dim 64), and lists of more than 512 blocks of 16 keys, the last of them of one key
+@pytest.mark.parametrize("kv_sizes,q_sizes,nh,nkv,d", [
+    ([70, 59], [1000, 1048], 4, 1, 64),
+    ([70, 59], [1000, 1049], 4, 1, 64),
+    ([33, 300], [1536, 1536], 4, 1, 64),
+    ([33, 300], [1536, 1537], 4, 1, 64),
+    ([1, 64], [2048, 2048], 4, 1, 64),
+    ([1, 64], [2049, 2048], 4, 1, 64),
+    ([8193, 8209], [5, 3], 4, 1, 64),
+    ([8193, 40], [5, 3], 4, 1, 128),
+    ([15, 16, 17], [0, 1, 9], 8, 2, 128),
+])
+@pytest.mark.parametrize("keep", [False, True])
+def test_fp32_ring_of_eight_wavefronts(oracle, kv_sizes, q_sizes, nh, nkv, d, keep):
+    case = ring_case(4450, kv_sizes, q_sizes, nh, nkv, d, "fp32")
+    ring = B.Ring(*case[0], keep_partials=keep)
+    out, lse = B.cp_ring_passkv(ring)
+    torch.cuda.synchronize()
+    check_ring(oracle, ring, out, lse, case, keep, O_ATOL_FP32, LSE_RTOL_FP32)
+
+
 # batches on either side of the 1024 sequences whose spans the encode kernel scans by itself
 @pytest.mark.parametrize("batch", [1023, 1024, 1025])
 def test_packed_batch_of_many_sequences(oracle, batch):
