@@ -12,8 +12,9 @@
 // saturates and the later sequences see nothing.
 //
 // The ranks of a ring are shifted together: sequence b's span is taken over all ranks' shares of
-// it, so that one launch attends from any rank's queries to any shard's keys. Three small
-// launches (a launch costs more than the work), two for batches of up to kScanHere sequences.
+// it, so that one launch attends from any rank's queries to any shard's keys. One small launch (a
+// launch costs more than the work) for what fits kBatchHere and kTokensHere, two for batches of up to
+// kScanHere sequences, else three.
 #include "cp_common.h"
 
 namespace cp {
@@ -22,6 +23,11 @@ namespace {
 inline size_t round256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 constexpr int kScanHere = 1024;  // batches up to this size: the encode kernel scans the spans
+// One launch up to this many sequences (a lane each scans their spans) and tokens, queries and keys
+// of all ranks. Every workgroup reads all positions: at 65536 tokens that is what the launch saved
+// costs (1500 tokens on average: 12 sequences over 4 ranks 535.8 -> 534.7 us).
+constexpr int kBatchHere = 64;
+constexpr int64_t kTokensHere = 65536;
 
 struct SeqTable {
   const int32_t* q_pos[kMaxTable];
@@ -80,6 +86,94 @@ __device__ __forceinline__ int seq_of(const int32_t* __restrict__ cu, int batch,
   return lo;
 }
 
+__device__ __forceinline__ void encode_q(int32_t x, int64_t base, int32_t* hi, int32_t* lo) {
+  const bool ok = x >= 0 && base + x < INT32_MAX;
+  *hi = ok ? (int32_t)(base + x) : CP_POS_PAD_Q;
+  *lo = ok ? (int32_t)base : 0;
+}
+__device__ __forceinline__ int32_t encode_kv(int32_t x, int64_t base) {
+  return (x == CP_POS_PAD_KV || base + x >= INT32_MAX) ? CP_POS_PAD_KV : (int32_t)(base + x);
+}
+
+// Spans and encoded positions in one launch: every workgroup takes the spans of all sequences
+// itself, from positions that lie in L2 after the first workgroup, and encodes its 1024 tokens. A
+// wavefront takes every 16th piece (a sequence's share on one rank); the boundaries of its next 64
+// pieces are fetched by its lanes together, so that a piece costs one round trip per 512 positions.
+// Bound by those round trips. Two prompts of 32 to 64 tokens 21.2 -> 18.4 us a call, six of 200 to 3000
+// over 4 ranks 113.7 -> 109.2, twelve of 200 to 600 over 2 ranks 69.0 -> 66.6 (two launches before).
+__global__ __launch_bounds__(1024) void seq_encode_all_kernel(const SeqTable t,
+                                                               int32_t* __restrict__ q_hi,
+                                                               int32_t* __restrict__ q_lo,
+                                                               int32_t* __restrict__ kv_enc) {
+  __shared__ int32_t top[kBatchHere];   // largest position, then base
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (tid < kBatchHere) top[tid] = -1;
+  const int n_lists = t.n_shards + t.n_ranks, n_pieces = n_lists * t.batch;
+  const int i = blockIdx.x * 1024 + tid;
+  // this thread's own tokens, asked for before anything is waited for
+  int qa = 0, ka = 0, ql = 0, kl = 0;
+  int32_t qx = 0, kx = 0;
+  const bool has_q = i < t.tok_begin[t.n_ranks], has_k = i < t.key_begin[t.n_shards];
+  if (has_q) {
+    for (int r = 1; r < t.n_ranks; ++r) qa += i >= t.tok_begin[r];
+    ql = i - t.tok_begin[qa];
+    qx = t.q_pos[qa][ql];
+  }
+  if (has_k) {
+    for (int r = 1; r < t.n_shards; ++r) ka += i >= t.key_begin[r];
+    kl = i - t.key_begin[ka];
+    kx = t.kv_pos[ka][kl];
+  }
+  __syncthreads();
+  for (int p0 = wave; p0 < n_pieces; p0 += 16 * 64) {
+    const int mine = p0 + lane * 16;
+    int lo = 0, hi = 0, list = 0, seq = 0;
+    if (mine < n_pieces) {
+      list = mine / t.batch;
+      seq = mine - list * t.batch;
+      const int32_t* const cu =
+          list < t.n_shards ? t.cu_kv[list] : t.cu_q[list - t.n_shards];
+      lo = cu[seq];
+      hi = cu[seq + 1];
+    }
+    const int n = min(64, (n_pieces - p0 + 15) / 16);
+    for (int j = 0; j < n; ++j) {
+      const int l = __builtin_amdgcn_readlane(list, j), b = __builtin_amdgcn_readlane(seq, j);
+      const int first = __builtin_amdgcn_readlane(lo, j), end = __builtin_amdgcn_readlane(hi, j);
+      const bool keys = l < t.n_shards;
+      const int32_t* const pos = keys ? t.kv_pos[l] : t.q_pos[l - t.n_shards];
+      int m = -1;
+for (int k = first; k < end; k += 8 * 64) {
+        int32_t x[8];   // (clamped, not skipped: all eight are on their way at once)
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = pos[min(k + u * 64 + lane, end - 1)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          if (!keys || x[u] != CP_POS_PAD_KV) m = max(m, x[u]);
+      }
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o, 64));
+      if (lane == 0) atomicMax(&top[b], m);   // (LDS)
+    }
+  }
+  __syncthreads();
+  // exclusive prefix of the spans, saturating: a sequence per lane of the first wavefront
+  if (wave == 0) {
+    const int64_t span = lane < t.batch ? (int64_t)top[lane] + 1 : 0;
+    int64_t sum = span;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int64_t y = __shfl_up(sum, o, 64);
+      if (lane >= o) sum += y;
+    }
+    top[lane] = (int32_t)min<int64_t>(sum - span, INT32_MAX - 1);
+  }
+  __syncthreads();
+  if (has_q) encode_q(qx, top[seq_of(t.cu_q[qa], t.batch, ql)], q_hi + i, q_lo + i);
+  if (has_k) kv_enc[i] = encode_kv(kx, top[seq_of(t.cu_kv[ka], t.batch, kl)]);
+}
+
 // SCAN: `base` is span, and every workgroup forms the prefix sums in LDS.
 template <bool SCAN>
 __global__ __launch_bounds__(256) void seq_encode_kernel(const SeqTable t,
@@ -118,10 +212,7 @@ __global__ __launch_bounds__(256) void seq_encode_kernel(const SeqTable t,
     const int li = i - t.tok_begin[a];
     const int32_t x = t.q_pos[a][li];
     const int b = seq_of(t.cu_q[a], t.batch, li);
-    const int64_t s = SCAN ? pre[b] : base[b];
-    const bool ok = x >= 0 && s + x < INT32_MAX;
-    q_hi[i] = ok ? (int32_t)(s + x) : CP_POS_PAD_Q;
-    q_lo[i] = ok ? (int32_t)s : 0;
+    encode_q(x, SCAN ? pre[b] : base[b], q_hi + i, q_lo + i);
   }
   if (i < t.key_begin[t.n_shards]) {
     int a = 0;
@@ -129,8 +220,7 @@ __global__ __launch_bounds__(256) void seq_encode_kernel(const SeqTable t,
     const int li = i - t.key_begin[a];
     const int32_t x = t.kv_pos[a][li];
     const int b = seq_of(t.cu_kv[a], t.batch, li);
-    const int64_t s = SCAN ? pre[b] : base[b];
-    kv_enc[i] = (x == CP_POS_PAD_KV || s + x >= INT32_MAX) ? CP_POS_PAD_KV : (int32_t)(s + x);
+    kv_enc[i] = encode_kv(x, SCAN ? pre[b] : base[b]);
   }
 }
 
@@ -180,8 +270,14 @@ int launch_varseq_encode(int32_t batch, int64_t total_kv, AttnTable& t, const in
     keys += t.n_kv[b];
   }
   s.key_begin[t.n_shards] = keys;
-  hipLaunchKernelGGL(seq_span_kernel, dim3(batch), dim3(256), 0, stream, s, span);
   const int64_t n = std::max<int64_t>(total_q, keys);
+  if (batch <= kBatchHere && total_q + keys <= kTokensHere) {
+    if (n > 0)
+      hipLaunchKernelGGL(seq_encode_all_kernel, dim3((unsigned)((n + 1023) / 1024)), dim3(1024), 0,
+                         stream, s, q_hi, (int32_t*)*q_lo, kv_enc);
+    return check_launch();
+  }
+  hipLaunchKernelGGL(seq_span_kernel, dim3(batch), dim3(256), 0, stream, s, span);
   const dim3 grid((unsigned)((n + 255) / 256));
   if (batch <= kScanHere) {
     if (n > 0)

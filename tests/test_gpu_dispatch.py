@@ -308,6 +308,53 @@ def test_fp32_ring_of_eight_wavefronts(oracle, kv_sizes, q_sizes, nh, nkv, d, ke
     check_ring(oracle, ring, out, lse, case, keep, O_ATOL_FP32, LSE_RTOL_FP32)
 
 
+# positions encoded in one launch (up to 64 sequences and 65536 tokens, a workgroup per 1024): edges
+# of both, sequences that are empty on every rank, padding on both sides, more pieces than one fetch of
+# the boundaries takes (64 per wavefront)
+@pytest.mark.parametrize("n,batch,length", [
+    (1, 1, 1), (1, 2, 512), (3, 5, 700), (2, 63, 9), (2, 64, 9), (2, 65, 9), (17, 64, 34),
+    (1, 2, 16384), (1, 2, 16385),
+])
+def test_packed_positions_in_one_launch(oracle, n, batch, length):
+    nh, rng = 2, np.random.default_rng(4500 + batch)
+    lens = np.maximum(length - np.arange(batch) % 3 * (length // 3), 0)
+    if batch == 2 and length >= 16384:
+        lens[:] = length            # on either side of 65536 tokens
+    elif batch > 2:
+        lens[1] = 0
+    qs, ks, vs, ps, pk, cus = [], [], [], [], [], []
+    for r in range(n):
+        pos = [B.cp_shard_positions(int(x), n, r) for x in lens]
+        cu = np.concatenate([[0], np.cumsum([len(p) for p in pos])]).astype(np.int32)
+        p = np.concatenate(pos).astype(np.int32)
+        kp, qp = p.copy(), p.copy()
+        kp[rng.random(len(p)) < 0.05] = B.CP_POS_PAD_KV
+        qp[rng.random(len(p)) < 0.05] = B.CP_POS_PAD_Q
+        for xs, h, i in ((qs, nh, 0), (ks, 1, 1), (vs, 1, 2)):
+            xs.append(randn(4510 + 3 * r + i, (len(p), h, 128)))
+        ps.append(qp)
+        pk.append(kp)
+        cus.append(cu)
+    ring = B.Ring([dev(x[0]) for x in qs], [dev(x[0]) for x in ks], [dev(x[0]) for x in vs],
+                  [i32(x) for x in ps], [i32(x) for x in pk], out_dtype=torch.float32,
+                  cu_seqlens_q=[i32(c) for c in cus], cu_seqlens_kv=[i32(c) for c in cus])
+    out, lse = B.cp_ring_passkv(ring)
+    torch.cuda.synchronize()
+    for b in range(batch):
+        of = [slice(c[b], c[b + 1]) for c in cus]
+        kp = np.concatenate([x[s] for x, s in zip(pk, of)])
+        k, v = (np.concatenate([x[1][s] for x, s in zip(xs, of)]) for xs in (ks, vs))
+        for r in range(n):
+            rows = np.arange(of[r].start, of[r].stop)
+            if len(rows) > 200:     # (the oracle is the slow side)
+                rows = np.unique(np.concatenate([rows[:40], rows[-40:], rng.choice(rows, 40)]))
+            if len(rows) == 0:
+                continue
+            ref_o, ref_l = oracle.attn(qs[r][1][rows], k, v, ps[r][rows], kp)
+            at = torch.as_tensor(rows).cuda()
+            check(out[r][at], lse[r][at], ref_o, ref_l, what="rank %d sequence %d" % (r, b))
+
+
 # batches on either side of the 1024 sequences whose spans the encode kernel scans by itself
 @pytest.mark.parametrize("batch", [1023, 1024, 1025])
 def test_packed_batch_of_many_sequences(oracle, batch):
