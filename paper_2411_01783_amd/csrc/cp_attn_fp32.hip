@@ -343,11 +343,11 @@ int launch_t(const AttnShape& s, Params& p, hipStream_t stream) {
   return check_launch();
 }
 
-// head_dim 128: a workgroup of 8 wavefronts holds as many registers as two of 4 would need to be on
-// a CU together, and those do not fit (one wavefront a SIMD): 4096 tokens of 8 heads over 2 ranks
+// head_dim 128: 8 wavefronts keep a SIMD's two within its registers; left to itself the kernel of 4
+// takes more than half of them and runs one wavefront a SIMD: 4096 tokens of 8 heads over 2 ranks
 // 580 -> 486 us, 8192 on 2 KV heads 2198 -> 1779, 512 of 4 heads 26 -> 23.
 // head_dim 64, by workgroups of 16 rows (2 ranks; us):
-//   up to 512, two a CU: the walk of the longest row block is what the call waits for, and 8
+//   up to 512, two rounds: the walk of the longest row block is what the call waits for, and 8
 //     wavefronts halve it (512 tokens of 4 heads 17.5 -> 14.2, 1400 38.4 -> 26.5, 2048 54.2 -> 43.1)
 //   up to 768: three workgroups of 4 wavefronts are on a CU at once, all of them run together (1400
 //     tokens of 8 heads on 2 KV heads, 700: 44.3; 8 wavefronts 49.1, 32 rows as below 58)
