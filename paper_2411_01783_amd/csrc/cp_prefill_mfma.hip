@@ -40,6 +40,7 @@
 //     shards of every rank's ring steps in ring order, each behind an arrival flag (RING,
 //     prefill_ring_walk_kernel).
 #include "cp_common.h"
+#include "cp_launch_rules.h"
 #include "cp_table.h"
 
 namespace cp {
@@ -92,6 +93,7 @@ struct Params {
   int32_t n_sub;          // SPLIT: parts of the KV axis (of every shard's, if per_shard)
   int32_t sub_blocks;     // SPLIT: blocks per part, by their index; 0: equal parts of the visible ones
   int32_t per_shard;      // the shards' results are kept apart
+  int32_t xcd_slice;      // WHOLE, SPLIT: workgroups are placed by xcd_slice
   int32_t cut_units;      // PLAN: equal shares (else a workgroup per unit)
   int32_t spin_limit;     // RING: polls per shard before giving up
   float scale_log2;       // softmax scale * log2(e)
@@ -453,6 +455,7 @@ int launch_attn_mfma(const AttnShape& s, const AttnTable& t, const AttnOut& o,
   const unsigned wgs = (unsigned)(pl.n_row_blocks * s.n_kv_heads);
   const dim3 grid = pl.mode == PLAN ? dim3(pl.cut ? kPlanWorkgroups : wgs * pl.n_z)
                                     : dim3(wgs, 1, pl.n_z * pl.n_sub);
+  p.xcd_slice = xcd_slice_applies(grid.x, grid.z, s.n_blocks) ? 1 : 0;
   rc = launch_body(kern, smem, grid, p, stream);
   if (rc != CP_OK) return rc;
 

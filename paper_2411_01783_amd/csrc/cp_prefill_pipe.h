@@ -773,21 +773,6 @@ enum Mode {
           // happens inside the online softmax
 };
 
-// Workgroup (x, z) of a grid whose z are different keys: those of one z onto as few XCDs as there
-// are to share out. Workgroups go to the 8 XCDs in turn, in the order of x + gridDim.x * z, and an
-// XCD's L2 fetches a tile of keys once for all that walk it there; as dispatched, 8 row blocks
-// against 16 holders in two parts each put every key on every XCD. g = gcd(gridDim.z, 8) classes of
-// z, an eighth of the workgroups for each XCD: class xcd % g, and every (8 / g)-th x. The order of x
-// (longest walks first) is kept.
-__device__ __forceinline__ void xcd_slice(int& x, int& z) {
-  const int nz = gridDim.z, g = nz & -nz & 7 ? nz & -nz : 8, s = 8 / g;
-  if (g == 1 || gridDim.x % s != 0) return;
-  const int line = x + gridDim.x * z, xcd = line & 7, idx = line >> 3, per = nz / g;
-  const int k = (uint32_t)idx / (uint32_t)per;
-  z = xcd % g + g * (idx - k * per);
-  x = k * s + xcd / g;
-}
-
 // A workgroup's walk: 256 consecutive (token, head-in-group) rows of one KV head, over the
 // queries of all ranks of the table back to back, against the visible blocks of the KV shards.
 // BAND: packed batch. Positions are shifted per sequence and a query also has a lower bound
@@ -826,7 +811,11 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
     // grid.z: the n_sub parts of the KV axis, of every shard in turn when shards are kept apart
     int x = blockIdx.x, z = blockIdx.z;
     if constexpr (MODE == WHOLE || MODE == SPLIT) {
-      if (gridDim.z > 1) xcd_slice(x, z);
+      if (p.xcd_slice) {
+        const GridPos at = xcd_slice(x, z, gridDim.x, gridDim.z);
+        x = at.x;
+        z = at.z;
+      }
     }
     const int i = x / p.n_kv_heads;
     kvh = x - i * p.n_kv_heads;

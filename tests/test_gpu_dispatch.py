@@ -74,7 +74,7 @@ def counts_case(kv_sizes, q_sizes, nh, nkv, d, q_pos, cu=None):
 def check_counts(out, lse, q_pos, cls, d, lo=0, hi=None):
     """Every row saw exactly the keys lo <= j < hi with j <= its position. Sums of ones are exact in
     fp32; the division and the logarithm err by a few 2^-24 of their result, below half a key for
-    the at most 2^16 keys here."""
+    the at most 2^17.3 keys here (LSE below 12: 2^17.3 * 12 * 2^-24 is 0.12)."""
     hi = len(cls) if hi is None else hi
     classes = np.zeros((hi - lo + 1, d))
     classes[1:] = np.cumsum(np.eye(d)[cls[lo:hi]], 0)
@@ -137,6 +137,52 @@ def test_ring_launch_rules_count_every_key(kv_sizes, q_sizes, nh, nkv, d):
                 for b in range(len(kv_sizes)):
                     if len(r) > 0:
                         check_counts(*ring.partial(a, b), r, cls, d, ends[b], ends[b + 1])
+
+
+# Which workgroup runs where (xcd_slice), with every output and partial full of NaN before, so that a
+# row block that nobody takes shows. Shards kept apart, as row blocks x parts of all shards: 8 x 32 from
+# 4096 blocks of keys on (2 and 4 KV heads, head_dim 64), 4 x 64, and what stays as dispatched: 4095
+# blocks, 12 x 42, 64 x 4, 8 x 30, more than a round (84 x 4).
+@pytest.mark.parametrize("kv_sizes,total_q,nh,nkv,d", [
+    ([8192] * 16, 128, 16, 1, 128), ([8192] * 15 + [8160], 128, 16, 1, 128),
+    ([65536 + 33, 65536], 64, 32, 2, 64), ([131072, 1, 0, 0], 128, 16, 4, 128),
+    ([20000] * 5 + [31073], 192, 16, 1, 128), ([40000] * 3 + [11073], 64, 16, 1, 128),
+    ([32768] * 4, 1024, 16, 4, 128), ([43692] * 3, 126, 16, 1, 128), ([40000] * 4, 672, 32, 1, 128),
+])
+def test_kept_shards_placed_on_xcds_count_every_key(kv_sizes, total_q, nh, nkv, d):
+    n, total = len(kv_sizes), sum(kv_sizes)
+    q_sizes = [total_q // n] * n
+    q_pos = np.sort(np.random.default_rng(n + total_q).integers(-1, total, size=total_q))
+    args, cls = counts_case(kv_sizes, q_sizes, nh, nkv, d, q_pos)
+    ring = B.Ring(*args, out_dtype=torch.float32, keep_partials=True)
+    for x in [ring.partial_out, ring.partial_lse] + ring.out + ring.lse:
+        x.fill_(float("nan"))
+    ring.workspace.fill_(255)
+    out, lse = B.cp_ring_passkv(ring)
+    torch.cuda.synchronize()
+    check_counts(torch.cat(out), torch.cat(lse), q_pos, cls, d)
+    ends = np.concatenate([[0], np.cumsum(kv_sizes)])
+    for a, r in enumerate(np.split(q_pos, n)):
+        for b in range(n):
+            check_counts(*ring.partial(a, b), r, cls, d, ends[b], ends[b + 1])
+
+
+# one shard in parts: 8 x 32 and 4 x 64 placed, 40 x 6 and three rounds (192 x 4) as dispatched
+@pytest.mark.parametrize("tq,tk,nh,nkv", [
+    (128, 131072, 16, 1), (64, 131072, 16, 1), (128, 131041, 16, 4), (640, 8000, 16, 1),
+    (49152, 49152, 1, 1),
+])
+def test_parts_placed_on_xcds_count_every_key(tq, tk, nh, nkv):
+    q_pos = np.sort(np.random.default_rng(tq).integers(-1, tk, size=tq))
+    args, cls = counts_case([tk], [tq], nh, nkv, 128, q_pos)
+    shape = B.make_shape(B.CP_BF16, 128, nh, nkv, tq, tk)
+    ws = torch.full((B.cp_workspace_bytes(shape, B.CP_WS_PARTIAL) + 256,), 255, dtype=torch.uint8,
+                    device="cuda")
+    out = torch.full((tq, nh, 128), float("nan"), device="cuda")
+    lse = torch.full((tq, nh), float("nan"), device="cuda")
+    B.cp_attn_partial(*(x[0] for x in args), out=out, lse=lse, workspace=ws)
+    torch.cuda.synchronize()
+    check_counts(out, lse, q_pos, cls, 128)
 
 
 # kv sizes, query sizes, heads, kv heads, d:

@@ -1,0 +1,82 @@
+"""The launch rules of csrc/cp_launch_rules.h, compiled for the host and checked over ranges of sizes
+that a few calls on a GPU cannot cover. No GPU needed."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
+                    "paper_2411_01783_amd", "csrc")
+
+SHIM = r"""
+#include "cp_launch_rules.h"
+extern "C" {
+// where the workgroups of a grid nx x nz run: x + nx * z of each, in dispatch order
+int placed(int nx, int nz, int n_blocks, int32_t* out) {
+  const bool slice = cp::xcd_slice_applies(nx, nz, n_blocks);
+  for (int i = 0; i < nx * nz; ++i) {
+    cp::GridPos at = {i % nx, i / nx};
+    if (slice) at = cp::xcd_slice(at.x, at.z, nx, nz);
+    out[i] = at.x < 0 || at.x >= nx || at.z < 0 || at.z >= nz ? -1 : at.x + nx * at.z;
+  }
+  return slice;
+}
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rules")
+    src, lib = str(d / "rules.cpp"), str(d / "rules.so")
+    with open(src, "w") as f:
+        f.write(SHIM)
+    subprocess.check_call([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-Wall", "-Werror",
+                           "-fPIC", "-shared", "-I", CSRC, src, "-o", lib])
+    return ctypes.CDLL(lib)
+
+
+def placed(rules, nx, nz, n_blocks):
+    out = np.empty(nx * nz, dtype=np.int32)
+    moved = rules.placed(nx, nz, n_blocks, out.ctypes.data_as(ctypes.c_void_p))
+    return out, bool(moved)
+
+
+def test_every_workgroup_of_a_grid_runs_once(rules):
+    any_moved = 0
+    for nz in list(range(1, 41)) + [48, 64, 69, 128, 256]:
+        for nx in list(range(1, 70)) + [96, 128, 139, 256]:
+            for n_blocks in (100, 4095, 4096, 100000):
+                out, moved = placed(rules, nx, nz, n_blocks)
+                assert np.array_equal(np.sort(out), np.arange(nx * nz)), (nx, nz)
+                any_moved += moved
+    assert any_moved > 0
+
+
+# Work per z in proportion: holders with more keys, contiguous shards under a causal mask, shards
+# that no query sees. Workgroups go to the eight XCDs in turn, and the time is that of the busiest one:
+# it has no more to do than in the order of dispatch, up to one z's row blocks.
+@pytest.mark.parametrize("shares", [
+    [1] * 7 + [2], [1] * 15 + [2], [3, 1], [1, 1, 1, 4], list(range(8, 0, -1)), [7, 5, 3, 1], [1, 0],
+    [4] * 8 + [1] * 8, [1, 1, 0, 0], [1] * 8 + [0] * 8, [1] * 4 + [0] * 12, [5] + [1] * 31,
+])
+def test_no_xcd_gets_more_than_its_part(rules, shares):
+    for parts in (1, 2, 3, 4, 8, 16):
+        work = np.repeat(np.array(shares, dtype=np.int64), parts)
+        nz = len(work)
+        for nx in (1, 2, 4, 8, 12, 16, 32, 64, 128, 192, 256, 512):
+            out, moved = placed(rules, nx, nz, 1 << 20)
+            load = np.array([work[out[x::8] // nx].sum() for x in range(8)])
+            plain = np.array([work[np.arange(x, nx * nz, 8) // nx].sum() for x in range(8)])
+            assert load.max() <= plain.max() + (8 * work.max() if moved else 0), (nx, nz)
+
+
+# and what the placement is for
+@pytest.mark.parametrize("nx,nz", [(8, 32), (4, 64), (1, 256)])
+def test_workgroups_on_the_same_keys_share_an_xcd(rules, nx, nz):
+    out, moved = placed(rules, nx, nz, 4096)
+    assert moved
+    for z in range(nz):
+        assert len(set(np.flatnonzero(out // nx == z) % 8)) == 1
