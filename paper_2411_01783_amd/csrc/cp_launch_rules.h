@@ -45,4 +45,19 @@ CP_RULE bool xcd_slice_applies(int64_t nx, int64_t nz, int64_t n_blocks) {
   return nx * nz == kCus && nx <= 8 && n_blocks >= 4096;
 }
 
+// ---- packed batches: spans found and positions encoded in one launch, or in two ----
+
+// `lists`: of positions, the queries of every rank and the keys of every shard. In one launch the 16
+// wavefronts of a workgroup walk batch * lists / 16 pieces each, one after the other; in two, every
+// sequence has a workgroup of its own, which walks the lists, and the second launch costs as much as
+// 3 to 4 pieces. The line is where the two take the same, by the sweep of 1 to 64 sequences over 1 to
+// 32 ranks (whole call, us, one launch and two): over 1 rank 28 sequences of 256 tokens 28.6 and
+// 29.2, 40 46.0 and 44.7; over 4 ranks 8 33.3 and 34.8, 12 37.2 and 37.0, 64 104 and 82; over 16 ranks
+// 5 63.2 and 64.4, 8 56.1 and 52.9, 64 236 and 144; over 32 ranks 4 73.1 and 75.6, 8 87 and 78.
+// Every workgroup reads all positions, up to 65536 tokens: that is as far as it was measured (one
+// sequence of 32768 1869 and 1889, 8 of 4096 over 4 ranks 352.5 and 355.5).
+CP_RULE bool encode_in_one_launch(int64_t batch, int64_t lists, int64_t tokens) {
+  return (batch - 5) * lists <= 48 && tokens <= 65536;
+}
+
 }  // namespace cp

@@ -13,9 +13,10 @@
 //
 // The ranks of a ring are shifted together: sequence b's span is taken over all ranks' shares of
 // it, so that one launch attends from any rank's queries to any shard's keys. One small launch (a
-// launch costs more than the work) for what fits kBatchHere and kTokensHere, two for batches of up to
+// launch costs more than the work) for few sequences (encode_in_one_launch), two for batches of up to
 // kScanHere sequences, else three.
 #include "cp_common.h"
+#include "cp_launch_rules.h"
 
 namespace cp {
 namespace {
@@ -23,11 +24,7 @@ namespace {
 inline size_t round256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 constexpr int kScanHere = 1024;  // batches up to this size: the encode kernel scans the spans
-// One launch up to this many sequences (a lane each scans their spans) and tokens, queries and keys
-// of all ranks. Every workgroup reads all positions: at 65536 tokens that is what the launch saved
-// costs (1500 tokens on average: 12 sequences over 4 ranks 535.8 -> 534.7 us).
-constexpr int kBatchHere = 64;
-constexpr int64_t kTokensHere = 65536;
+constexpr int kBatchHere = 64;   // a lane each scans the spans (encode_in_one_launch takes fewer)
 
 struct SeqTable {
   const int32_t* q_pos[kMaxTable];
@@ -97,9 +94,9 @@ __device__ __forceinline__ int32_t encode_kv(int32_t x, int64_t base) {
 
 // Spans and encoded positions in one launch: every workgroup takes the spans of all sequences
 // itself, from positions that lie in L2 after the first workgroup, and encodes its 1024 tokens. A
-// wavefront takes every 16th piece (a sequence's share on one rank); the boundaries of its next 64
-// pieces are fetched by its lanes together, so that a piece costs one round trip per 512 positions.
-// Bound by those round trips. Two prompts of 32 to 64 tokens 21.2 -> 18.4 us a call, six of 200 to 3000
+// wavefront takes every 16th piece (a sequence's share on one rank), one after the other; the
+// boundaries of its pieces are fetched by its lanes together (the rule leaves it 23 at most), so that a
+// piece costs one round trip per 512 positions. Bound by those round trips. Two prompts of 32 to 64 tokens 21.2 -> 18.4 us a call, six of 200 to 3000
 // over 4 ranks 113.7 -> 109.2, twelve of 200 to 600 over 2 ranks 69.0 -> 66.6 (two launches before).
 __global__ __launch_bounds__(1024) void seq_encode_all_kernel(const SeqTable t,
                                                                int32_t* __restrict__ q_hi,
@@ -126,36 +123,33 @@ __global__ __launch_bounds__(1024) void seq_encode_all_kernel(const SeqTable t,
     kx = t.kv_pos[ka][kl];
   }
   __syncthreads();
-  for (int p0 = wave; p0 < n_pieces; p0 += 16 * 64) {
-    const int mine = p0 + lane * 16;
-    int lo = 0, hi = 0, list = 0, seq = 0;
-    if (mine < n_pieces) {
-      list = mine / t.batch;
-      seq = mine - list * t.batch;
-      const int32_t* const cu =
-          list < t.n_shards ? t.cu_kv[list] : t.cu_q[list - t.n_shards];
-      lo = cu[seq];
-      hi = cu[seq + 1];
+  const int mine = wave + lane * 16;
+  int lo = 0, hi = 0, list = 0, seq = 0;
+  if (mine < n_pieces) {
+    list = mine / t.batch;
+    seq = mine - list * t.batch;
+    const int32_t* const cu = list < t.n_shards ? t.cu_kv[list] : t.cu_q[list - t.n_shards];
+    lo = cu[seq];
+    hi = cu[seq + 1];
+  }
+  const int n = (n_pieces - wave + 15) / 16;
+  for (int j = 0; j < n; ++j) {
+    const int l = __builtin_amdgcn_readlane(list, j), b = __builtin_amdgcn_readlane(seq, j);
+    const int first = __builtin_amdgcn_readlane(lo, j), end = __builtin_amdgcn_readlane(hi, j);
+    const bool keys = l < t.n_shards;
+    const int32_t* const pos = keys ? t.kv_pos[l] : t.q_pos[l - t.n_shards];
+    int m = -1;
+    for (int k = first; k < end; k += 8 * 64) {
+      int32_t x[8];   // (clamped, not skipped: all eight are on their way at once)
+#pragma unroll
+      for (int u = 0; u < 8; ++u) x[u] = pos[min(k + u * 64 + lane, end - 1)];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (!keys || x[u] != CP_POS_PAD_KV) m = max(m, x[u]);
     }
-    const int n = min(64, (n_pieces - p0 + 15) / 16);
-    for (int j = 0; j < n; ++j) {
-      const int l = __builtin_amdgcn_readlane(list, j), b = __builtin_amdgcn_readlane(seq, j);
-      const int first = __builtin_amdgcn_readlane(lo, j), end = __builtin_amdgcn_readlane(hi, j);
-      const bool keys = l < t.n_shards;
-      const int32_t* const pos = keys ? t.kv_pos[l] : t.q_pos[l - t.n_shards];
-      int m = -1;
-for (int k = first; k < end; k += 8 * 64) {
-        int32_t x[8];   // (clamped, not skipped: all eight are on their way at once)
 #pragma unroll
-        for (int u = 0; u < 8; ++u) x[u] = pos[min(k + u * 64 + lane, end - 1)];
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-          if (!keys || x[u] != CP_POS_PAD_KV) m = max(m, x[u]);
-      }
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o, 64));
-      if (lane == 0) atomicMax(&top[b], m);   // (LDS)
-    }
+    for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o, 64));
+    if (lane == 0) atomicMax(&top[b], m);   // (LDS)
   }
   __syncthreads();
   // exclusive prefix of the spans, saturating: a sequence per lane of the first wavefront
@@ -271,7 +265,7 @@ int launch_varseq_encode(int32_t batch, int64_t total_kv, AttnTable& t, const in
   }
   s.key_begin[t.n_shards] = keys;
   const int64_t n = std::max<int64_t>(total_q, keys);
-  if (batch <= kBatchHere && total_q + keys <= kTokensHere) {
+  if (encode_in_one_launch(batch, t.n_ranks + t.n_shards, total_q + keys)) {
     if (n > 0)
       hipLaunchKernelGGL(seq_encode_all_kernel, dim3((unsigned)((n + 1023) / 1024)), dim3(1024), 0,
                          stream, s, q_hi, (int32_t*)*q_lo, kv_enc);

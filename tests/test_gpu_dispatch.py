@@ -354,12 +354,14 @@ def test_fp32_ring_of_eight_wavefronts(oracle, kv_sizes, q_sizes, nh, nkv, d, ke
     check_ring(oracle, ring, out, lse, case, keep, O_ATOL_FP32, LSE_RTOL_FP32)
 
 
-# positions encoded in one launch (up to 64 sequences and 65536 tokens, a workgroup per 1024): edges
-# of both, sequences that are empty on every rank, padding on both sides, more pieces than one fetch of
-# the boundaries takes (64 per wavefront)
+# positions encoded in one launch (a workgroup per 1024 tokens) and in two: (sequences - 5) * lists on
+# either side of 48 for 1, 2, 8 and 32 ranks, 65536 tokens and more, sequences that are empty on every
+# rank, padding on both sides; many sequences over many ranks
 @pytest.mark.parametrize("n,batch,length", [
     (1, 1, 1), (1, 2, 512), (3, 5, 700), (2, 63, 9), (2, 64, 9), (2, 65, 9), (17, 64, 34),
     (1, 2, 16384), (1, 2, 16385),
+    (1, 29, 40), (1, 30, 40), (2, 17, 130), (2, 18, 130), (8, 8, 90), (8, 9, 90), (32, 5, 70),
+    (32, 6, 70),
 ])
 def test_packed_positions_in_one_launch(oracle, n, batch, length):
     nh, rng = 2, np.random.default_rng(4500 + batch)

@@ -23,6 +23,9 @@ int placed(int nx, int nz, int n_blocks, int32_t* out) {
   }
   return slice;
 }
+int encode_in_one_launch(int64_t batch, int64_t lists, int64_t tokens) {
+  return cp::encode_in_one_launch(batch, lists, tokens);
+}
 }
 """
 
@@ -80,3 +83,29 @@ def test_workgroups_on_the_same_keys_share_an_xcd(rules, nx, nz):
     assert moved
     for z in range(nz):
         assert len(set(np.flatnonzero(out // nx == z) % 8)) == 1
+
+
+# Ranks, sequences, and the time of a whole packed call with its positions encoded in one launch over
+# that in two (prompts of 64 or 256 tokens, MI355X): whatever loses 2 % or more takes two, whatever
+# gains 4 % or more takes one. (In one launch a wavefront walks sequences * ranks / 8 pieces one by one.)
+@pytest.mark.parametrize("ranks,batch,ratio", [
+    (1, 1, .89), (1, 8, .88), (1, 16, .92), (1, 24, .96), (1, 40, 1.03), (1, 64, 1.12),
+    (2, 6, .92), (2, 12, .96), (2, 24, 1.04), (3, 8, .96), (4, 2, .87), (4, 8, .96), (4, 14, 1.02),
+    (4, 32, 1.21), (4, 64, 1.54), (8, 2, .87), (8, 5, .96), (16, 1, .84), (16, 4, .96), (16, 8, 1.07),
+    (16, 16, 1.31), (16, 64, 2.59), (32, 1, .84), (32, 5, .96), (32, 8, 1.12), (32, 64, 3.23),
+])
+def test_positions_of_many_pieces_take_two_launches(rules, ranks, batch, ratio):
+    one = rules.encode_in_one_launch
+    one.argtypes = [ctypes.c_int64] * 3
+    assert ratio >= 1.02 or ratio <= 0.96
+    assert bool(one(batch, 2 * ranks, batch * 128)) == (ratio < 1)
+    assert not one(1, 2 * ranks, 65537)
+
+
+def test_pieces_of_one_launch_fit_a_wavefront(rules):
+    one = rules.encode_in_one_launch
+    one.argtypes = [ctypes.c_int64] * 3
+    for lists in range(2, 65):       # kMaxTable ranks and shards
+        for batch in range(1, 2000):
+            if one(batch, lists, 1):   # a lane per sequence, a lane per piece of 16 wavefronts
+                assert batch <= 64 and -(-batch * lists // 16) <= 64
