@@ -75,7 +75,8 @@ __global__ __launch_bounds__(NWAVE * 64) void attn_fp32_kernel(const Params p) {
   __shared__ float comb_m[NWAVE][ROWS], comb_l[NWAVE][ROWS];
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int n = lane & 15, kg = lane >> 4;
-  const int row_block = ordered_row_block(blockIdx.x, gridDim.x, p.t.n_ranks, lane);
+  const int row_block = ordered_row_block(blockIdx.x, gridDim.x, p.t.n_ranks, lane,
+                                          p.rows % ROWS != 0 ? kLatePartial : kLate);
   const int kvh = blockIdx.y;
   const int z_shard = p.per_shard ? blockIdx.z : 0;
 

@@ -2,6 +2,7 @@
 #pragma once
 
 #include "cp_common.h"
+#include "cp_launch_rules.h"
 
 namespace cp {
 namespace {
@@ -10,19 +11,17 @@ namespace {
 // short. In one rank's shard (chunk r of the sequence, then chunk 2N-1-r) later rows see more
 // keys. Over N ranks back to back the late chunks of all ranks go first, rank 0's (the last of
 // the sequence) at their head, then the early chunks, rank 0's (the first of the sequence) last.
-// The boundaries are those of equal shards; shards of other sizes only lose some of the order.
-__device__ __forceinline__ int ordered_row_block(int i, int B, int n_ranks, int lane) {
+__device__ __forceinline__ int ordered_row_block(int i, int B, int n_ranks, int lane,
+                                                 ChunkRule rule) {
   if (n_ranks == 1) return B - 1 - i;
-  // lane l < N: second half of rank l; N <= l < 2N: first half of rank 2N-1-l  (N <= 32)
+  // lane l < N: late chunk of rank l; N <= l < 2N: early chunk of rank 2N-1-l  (N <= 32)
   const bool late = lane < n_ranks;
   const int r = late ? lane : 2 * n_ranks - 1 - lane;
   int lo = 0, hi = 0;
-  if (r >= 0) {
-    const int h = late ? 2 * r + 1 : 2 * r;
-    // (B < 2^26: that many row blocks of 16 rows do not fit the memory; 64-bit divisions took
-    // 1000 cycles of every start)
-    lo = (int)((uint32_t)h * (uint32_t)B / (uint32_t)(2 * n_ranks));
-    hi = (int)((uint32_t)(h + 1) * (uint32_t)B / (uint32_t)(2 * n_ranks));
+  if (r >= 0) {   // (in 32 bits: 64-bit divisions took 1000 cycles of every start)
+    const int j = late ? 2 * r + 1 : 2 * r;
+    lo = chunk_begin(j, B, n_ranks, rule);
+    hi = chunk_begin(j + 1, B, n_ranks, rule);
   }
   int end = hi - lo;  // inclusive prefix sum of the lengths
 #pragma unroll

@@ -26,6 +26,9 @@ int placed(int nx, int nz, int n_blocks, int32_t* out) {
 int encode_in_one_launch(int64_t batch, int64_t lists, int64_t tokens) {
   return cp::encode_in_one_launch(batch, lists, tokens);
 }
+int chunk_begin(int j, int B, int N, int rule) {
+  return cp::chunk_begin(j, B, N, (cp::ChunkRule)rule);
+}
 }
 """
 
@@ -109,3 +112,43 @@ def test_pieces_of_one_launch_fit_a_wavefront(rules):
         for batch in range(1, 2000):
             if one(batch, lists, 1):   # a lane per sequence, a lane per piece of 16 wavefronts
                 assert batch <= 64 and -(-batch * lists // 16) <= 64
+
+
+ENDS_IN, LATE, LATE_PARTIAL = range(3)
+
+
+def dispatch_order(rules, B, N, rule):
+    """Row blocks as ordered_row_block hands them out: the late chunks of ranks 0, 1, .., then the
+    early ones of ranks N - 1, .., 0, each from its end."""
+    begin = [rules.chunk_begin(j, B, N, rule) for j in range(2 * N + 1)]
+    assert begin[0] == 0 and begin[-1] == B and np.all(np.diff(begin) >= 0)
+    chunks = [2 * r + 1 for r in range(N)] + [2 * r for r in reversed(range(N))]
+    return np.concatenate([np.arange(begin[j], begin[j + 1])[::-1] for j in chunks])
+
+
+# Equal chunks of any length, so that row blocks of `rows` rows straddle them or not.
+@pytest.mark.parametrize("rows", [16, 32])
+def test_fp32_row_blocks_with_late_rows_go_first(rules, rows):
+    for N in (2, 3, 4, 7, 8, 16, 32):
+        for chunk in list(range(1, 60)) + [128, 165, 225, 256, 450, 1000]:     # rows
+            R = 2 * N * chunk
+            B = -(-R // rows)
+            order = dispatch_order(rules, B, N, LATE_PARTIAL if R % rows else LATE)
+            assert np.array_equal(np.sort(order), np.arange(B))
+            if B < 4 * N:           # (all of them run at once)
+                continue
+            late = np.arange(R) // chunk % 2 == 1
+            has_late = np.array([late[b * rows:(b + 1) * rows].any() for b in range(B)])
+            last_late = np.flatnonzero(has_late[order]).max()
+            # (a partial last block puts the boundaries up to a block too early)
+            assert last_late < has_late.sum() + (2 * N if R % rows else 0), (N, chunk)
+
+
+def test_row_blocks_are_all_handed_out(rules):
+    for N in range(2, 33):
+        for B in list(range(1, 300)) + [1000, 4095, 65537, (1 << 26) - 1]:
+            if B < 300:
+                assert np.array_equal(np.sort(dispatch_order(rules, B, N, ENDS_IN)), np.arange(B))
+            for rule in (ENDS_IN, LATE, LATE_PARTIAL):
+                begin = [rules.chunk_begin(j, B, N, rule) for j in range(2 * N + 1)]
+                assert begin[0] == 0 and begin[-1] == B and np.all(np.diff(begin) >= 0)
