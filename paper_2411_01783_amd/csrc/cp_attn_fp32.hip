@@ -20,6 +20,7 @@
 // heads of 64) takes 14.2 us: 128 workgroups, of whose 14 us the matrix pipe needs 3.4. It took 18.1
 // with 4 wavefronts a workgroup and the key positions asked for after the queries' had come.
 #include "cp_common.h"
+#include "cp_launch_rules.h"
 #include "cp_table.h"
 
 namespace cp {
@@ -63,8 +64,10 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// (head_dim 128: two wavefronts a SIMD asked for; left to itself the compiler takes 278 registers for
+// workgroups of 4, and one runs.)
 template <int D, int NR, int NWAVE, typename TO>
-__global__ __launch_bounds__(NWAVE * 64) void attn_fp32_kernel(const Params p) {
+__global__ __launch_bounds__(NWAVE * 64, D == 128 ? 2 : 1) void attn_fp32_kernel(const Params p) {
   constexpr int NTHREADS = NWAVE * 64;
   constexpr int MAX_LIST = NTHREADS;                    // blocks looked at per chunk
   constexpr int ROWS = 16 * NR;
@@ -154,8 +157,9 @@ __global__ __launch_bounds__(NWAVE * 64) void attn_fp32_kernel(const Params p) {
   }
   // The first block this wavefront takes if all of the first are visible, as they mostly are (else it
   // is not used): it travels with the queries, not behind the list. (head_dim 128, where a block is
-  // longest on its way: 512 tokens of 4 heads 23.0 -> 21.3 us, 4096 of 8 heads 488 -> 464. At
-  // head_dim 64 it gains nothing: 14.1 and 14.3, 2048 tokens of 4 heads 42.9 and 45.0.)
+  // longest on its way: 512 tokens of 4 heads 23.0 -> 21.3 us, 4096 of 8 heads 488 -> 464. A call that
+  // sees none of its keys waits for it in vain: 512 queries on 512 6.3 -> 8.3. At head_dim 64 it gains
+  // nothing: 14.1 and 14.3, 2048 tokens of 4 heads 42.9 and 45.0.)
   BlockRegs<D> cur, nxt;
   const int guess = wave * BLK;   // of the first shard
   const bool guessed = D == 128 && guess < p.t.n_kv[z_shard];
@@ -365,27 +369,17 @@ int launch_t(const AttnShape& s, Params& p, hipStream_t stream) {
   return check_launch();
 }
 
-// head_dim 128: 8 wavefronts keep a SIMD's two within its registers; left to itself the kernel of 4
-// takes more than half of them and runs one wavefront a SIMD: 4096 tokens of 8 heads over 2 ranks
-// 580 -> 486 us, 8192 on 2 KV heads 2198 -> 1779, 512 of 4 heads 26 -> 23.
-// head_dim 64, by workgroups of 16 rows (2 ranks; us):
-//   up to 512, two rounds: the walk of the longest row block is what the call waits for, and 8
-//     wavefronts halve it (512 tokens of 4 heads 17.5 -> 14.2, 1400 38.4 -> 26.5, 2048 54.2 -> 43.1)
-//   up to 768: three workgroups of 4 wavefronts are on a CU at once, all of them run together (1400
-//     tokens of 8 heads on 2 KV heads, 700: 44.3; 8 wavefronts 49.1, 32 rows as below 58)
-//   up to 1024: a fourth would wait for a CU; 32 rows by 8 wavefronts are two even rounds (875: 145
-//     -> 89, 900: 64 -> 56, 950: 87 -> 61, 1000: 135 -> 111; at 750 79 -> 108)
-//   beyond: 32 rows by 4 wavefronts, half the K/V traffic from L2 (1250: 203; 8 wavefronts 225; 2048:
-//     221 and 228, 16 rows by 8 wavefronts 285)
 template <typename TO>
 int launch_o(const AttnShape& s, Params& p, hipStream_t stream) {
-  if (s.head_dim == 128) return launch_t<128, 1, 8, TO>(s, p, stream);
-  const int64_t wgs = (p.rows + 15) / 16 * s.n_kv_heads;
-  const int64_t all = wgs * (s.per_shard ? s.n_shards : 1);
-  if (all <= 2 * 256) return launch_t<64, 1, 8, TO>(s, p, stream);
-  if (wgs > 4 * 256) return launch_t<64, 2, 4, TO>(s, p, stream);
-  if (all > 3 * 256 && all <= 4 * 256) return launch_t<64, 2, 8, TO>(s, p, stream);
-  return launch_t<64, 1, 4, TO>(s, p, stream);
+  int64_t keys = 0;
+  for (int b = 0; b < s.n_shards; ++b) keys += p.t.n_kv[b];
+  const Fp32Form f = fp32_form(s.head_dim, p.rows, s.n_kv_heads, s.n_shards, s.per_shard, s.total_q,
+                               keys);
+  if (s.head_dim == 128)
+    return f.waves == 4 ? launch_t<128, 1, 4, TO>(s, p, stream) : launch_t<128, 1, 8, TO>(s, p, stream);
+  if (f.rows == 32)
+    return f.waves == 4 ? launch_t<64, 2, 4, TO>(s, p, stream) : launch_t<64, 2, 8, TO>(s, p, stream);
+  return f.waves == 4 ? launch_t<64, 1, 4, TO>(s, p, stream) : launch_t<64, 1, 8, TO>(s, p, stream);
 }
 
 }  // namespace

@@ -83,4 +83,49 @@ CP_RULE int chunk_begin(int j, int B, int N, ChunkRule rule) {
   return (int)(((uint32_t)j * b + up) / n2);
 }
 
+// ---- fp32 attention: rows and wavefronts of a workgroup ----
+
+struct Fp32Form {
+  int rows, waves;
+};
+
+// A workgroup's wavefronts share its keys, 16 at a time, and their results are combined in LDS. How
+// many workgroups a CU holds is the registers' doing: at head_dim 64 two of 4 wavefronts (175
+// registers) and one of 8, at head_dim 128 likewise. So the same wavefronts are at work either way, and
+// 8 a workgroup halve the longest walk where there is one workgroup a CU or less; beyond that they
+// run in two rounds, longest walks first, and win where walks differ in length (a whole prefill: as
+// many queries as keys), and lose a start and an end where they do not. `keys`: of a walk on average,
+// all of them or (kept_apart shards) those of a shard. us, 4 and 8 wavefronts:
+//   up to 128 keys: a block of 16 for each of 8 or none. head_dim 64: 512 tokens of 4 heads on 16
+//     6.0 and 6.6, 2048 6.8 and 11.1; head_dim 128, 8 shards of 64 kept apart, 2048 queries 87 and 137
+//   one workgroup of 16 rows a CU (256): 512 tokens of 4 heads over 2 ranks 17.5 and 14.2, at
+//     head_dim 128 26 and 21; 512 queries on 512 keys 17.4 and 13.6, 26 and 21
+//   head_dim 64, up to 512 workgroups: 1320 tokens of 4 heads over 4 ranks 37 and 25, 2048 54 and 43,
+//     1500 queries on 3000 cached and new keys 78 and 67; but 2048 queries that all see 512 keys 21.4
+//     and 25.5, 1024 over 2 ranks, their partials kept apart, 25.6 and 26.8, 512 over 4 14.9 and 18.3.
+//     Sizes do not say who sees what, and 8 lose where all rows see as much: 2048 queries on 1024 keys
+//     36.9 and 39.5, the step of a ring in which a later rank's 1200 queries meet an earlier rank's keys
+//     24.9 and 28.7 (the step the other way round 33 and 23), a shard that no query sees 5.8 and 9.2.
+//   up to 768: 16 rows by 4: 2400 tokens of 4 heads 63.8 and 63.1, 3040 80 and 89, 700 workgroups of
+//     8 heads on 2 KV heads 44.4 and 49
+//   up to 1024: 32 rows, half the K/V traffic and half the workgroups: by 8, 3600 tokens of 4 heads
+//     over 2 ranks 93 (16 rows by 4: 113), 4096 queries on 512 keys 38 (41); by 4 up to 256 keys, which
+//     are one round: 4096 queries on 256 20.3 (16 rows by 4: 26.1, 32 by 8: 27.3), on 16 9.4 (11.2, 17)
+//   beyond: 32 rows by 4 (5000 tokens of 4 heads 203, by 8 224), 16 rows where it is the kept-apart
+//     shards that make the workgroups
+//   head_dim 128 (16 rows): beyond 256 workgroups 4 up to 256 keys: 2048 queries on 8 shards of 256
+//     kept apart 233 and 357; 2048 on 256 22 and 28. (On more, two workgroups of 4 a CU mostly win, 2048
+//     queries on 8 shards of 512 272 and 325, but a whole prefill of 1100 tokens of 4 heads 51 and 36.)
+CP_RULE Fp32Form fp32_form(int head_dim, int64_t rows, int64_t n_kv_heads, int64_t shards,
+                           bool kept_apart, int64_t total_q, int64_t total_keys) {
+  const int64_t apart = kept_apart ? shards : 1, keys = total_keys / apart;
+  const int64_t wgs = (rows + 15) / 16 * n_kv_heads, all = wgs * apart;   // of 16 rows
+  if (head_dim == 128) return {16, keys <= 128 || (keys <= 256 && all > kCus) ? 4 : 8};
+  if (wgs > 4 * kCus) return {32, 4};
+  if (all > 3 * kCus && all <= 4 * kCus) return {32, keys > 256 ? 8 : 4};
+  if (all > 2 * kCus || keys <= 128) return {16, 4};
+  if (all <= kCus) return {16, 8};
+  return {16, !kept_apart && (keys > 512 || total_q == total_keys) ? 8 : 4};
+}
+
 }  // namespace cp

@@ -332,8 +332,11 @@ def test_fp32_ring(oracle, kv_sizes, q_sizes, nh, nkv, d, keep):
     check_ring(oracle, ring, out, lse, case, keep, O_ATOL_FP32, LSE_RTOL_FP32)
 
 
-# fp32, 8 wavefronts a workgroup: workgroups of 16 rows on either side of 512 (two a CU), 768 and 1024
-# (head_dim 64), and lists of more than 512 blocks of 16 keys, the last of them of one key
+# fp32: workgroups of 16 rows on either side of 512, 768 and 1024 (head_dim 64), lists of more than 512
+# blocks of 16 keys, the last of them of one key; then the forms of fp32_form and the sizes on either side
+# of their rules: 16 rows by 8 (256 workgroups; up to 512 of a whole prefill, and on more than 512 keys),
+# 32 by 8 and by 4 (keys 257 and 256), head_dim 128 by 4 and by 8 (128 and 129 keys; 256 and 257 of more
+# than 256 workgroups)
 @pytest.mark.parametrize("kv_sizes,q_sizes,nh,nkv,d", [
     ([70, 59], [1000, 1048], 4, 1, 64),
     ([70, 59], [1000, 1049], 4, 1, 64),
@@ -344,6 +347,17 @@ def test_fp32_ring(oracle, kv_sizes, q_sizes, nh, nkv, d, keep):
     ([8193, 8209], [5, 3], 4, 1, 64),
     ([8193, 40], [5, 3], 4, 1, 128),
     ([15, 16, 17], [0, 1, 9], 8, 2, 128),
+    ([70, 59], [400, 624], 4, 1, 64),
+    ([70, 58], [400, 624], 4, 1, 64),
+    ([300, 320], [310, 310], 8, 2, 64),
+    ([300, 213], [600, 501], 4, 1, 64),
+    ([300, 212], [600, 501], 4, 1, 64),
+    ([200, 57], [1700, 1600], 4, 1, 64),
+    ([200, 56], [1700, 1601], 4, 1, 64),
+    ([64, 64], [5, 30], 4, 1, 128),
+    ([64, 65], [5, 30], 4, 1, 128),
+    ([200, 56], [500, 528], 4, 1, 128),
+    ([200, 57], [500, 528], 4, 1, 128),
 ])
 @pytest.mark.parametrize("keep", [False, True])
 def test_fp32_ring_of_eight_wavefronts(oracle, kv_sizes, q_sizes, nh, nkv, d, keep):

@@ -26,6 +26,12 @@ int placed(int nx, int nz, int n_blocks, int32_t* out) {
 int encode_in_one_launch(int64_t batch, int64_t lists, int64_t tokens) {
   return cp::encode_in_one_launch(batch, lists, tokens);
 }
+int fp32_form(int head_dim, int64_t rows, int64_t n_kv_heads, int64_t shards, int kept_apart,
+              int64_t total_q, int64_t total_keys) {
+  const cp::Fp32Form f = cp::fp32_form(head_dim, rows, n_kv_heads, shards, kept_apart != 0, total_q,
+                                       total_keys);
+  return f.rows * 10 + f.waves;
+}
 int chunk_begin(int j, int B, int N, int rule) {
   return cp::chunk_begin(j, B, N, (cp::ChunkRule)rule);
 }
@@ -152,3 +158,49 @@ def test_row_blocks_are_all_handed_out(rules):
             for rule in (ENDS_IN, LATE, LATE_PARTIAL):
                 begin = [rules.chunk_begin(j, B, N, rule) for j in range(2 * N + 1)]
                 assert begin[0] == 0 and begin[-1] == B and np.all(np.diff(begin) >= 0)
+
+
+# Calls of the fp32 kernel whose time with another form of workgroup (rows, wavefronts) was measured:
+# head_dim, queries, heads, KV heads, shards, kept apart, keys; the form that has to be taken, and one that
+# loses to it by 4 % or more (us of both, MI355X).
+FP32_FORMS = [
+    (64, 512, 4, 1, 1, 0, 16, (16, 4), (16, 8), 6.0, 6.6),
+    (64, 2048, 4, 1, 1, 0, 16, (16, 4), (16, 8), 6.8, 11.1),
+    (64, 2048, 4, 1, 1, 0, 512, (16, 4), (16, 8), 21.5, 25.5),
+    (64, 1024, 8, 2, 1, 0, 256, (16, 4), (16, 8), 13.9, 18.5),
+    (64, 512, 4, 1, 4, 1, 2048, (16, 4), (16, 8), 26.4, 30.9),
+    (64, 1024, 4, 1, 2, 1, 1024, (16, 4), (16, 8), 25.6, 26.8),
+    (64, 512, 8, 1, 2, 1, 512, (16, 4), (16, 8), 18.4, 22.3),
+    (64, 512, 4, 1, 1, 0, 512, (16, 8), (16, 4), 13.6, 17.2),
+    (64, 512, 4, 1, 2, 0, 512, (16, 8), (16, 4), 14.2, 17.5),
+    (64, 1320, 4, 1, 4, 0, 1320, (16, 8), (16, 4), 25.4, 37.0),
+    (64, 2048, 4, 1, 2, 0, 2048, (16, 8), (16, 4), 43.0, 54.3),
+    (64, 540, 8, 2, 1, 0, 540, (16, 8), (16, 4), 14.1, 19.0),
+    (64, 1500, 4, 1, 1, 0, 3000, (16, 8), (16, 4), 67.4, 77.7),
+    (64, 3040, 4, 1, 2, 0, 3040, (16, 4), (16, 8), 80.2, 89.0),
+    (64, 4096, 4, 1, 1, 0, 16, (32, 4), (16, 4), 9.4, 11.2),
+    (64, 4096, 4, 1, 1, 0, 256, (32, 4), (32, 8), 20.3, 27.3),
+    (64, 512, 4, 1, 8, 1, 512, (32, 4), (32, 8), 17.2, 25.1),
+    (64, 1024, 4, 1, 4, 1, 1024, (32, 4), (32, 8), 26.0, 30.3),
+    (64, 3600, 4, 1, 2, 0, 3600, (32, 8), (16, 4), 93.0, 112.7),
+    (64, 2048, 4, 1, 2, 1, 2048, (32, 8), (32, 4), 55.4, 60.3),
+    (64, 5000, 4, 1, 2, 0, 5000, (32, 4), (32, 8), 202.7, 224.1),
+    (64, 2048, 4, 1, 8, 1, 512, (16, 4), (32, 8), 64.0, 86.4),
+    (128, 512, 4, 1, 1, 0, 64, (16, 4), (16, 8), 7.5, 8.6),
+    (128, 2048, 4, 1, 8, 1, 512, (16, 4), (16, 8), 83.6, 136.8),
+    (128, 2048, 8, 1, 8, 1, 2048, (16, 4), (16, 8), 233.5, 357.0),
+    (128, 2048, 4, 1, 1, 0, 256, (16, 4), (16, 8), 22.2, 27.7),
+    (128, 512, 4, 1, 1, 0, 512, (16, 8), (16, 4), 20.6, 25.2),
+    (128, 1100, 4, 1, 2, 0, 1100, (16, 8), (16, 4), 35.8, 51.2),
+    (128, 512, 8, 2, 1, 0, 2048, (16, 8), (16, 4), 60.5, 84.1),
+]
+
+
+@pytest.mark.parametrize("case", FP32_FORMS)
+def test_fp32_workgroups_are_of_the_form_that_was_faster(rules, case):
+    d, q, nh, nkv, shards, apart, keys, form, other, us, us_other = case
+    assert us_other >= 1.04 * us and other != form
+    f = rules.fp32_form
+    f.argtypes = [ctypes.c_int] + [ctypes.c_int64] * 3 + [ctypes.c_int] + [ctypes.c_int64] * 2
+    rows, waves = divmod(f(d, q * (nh // nkv), nkv, shards, apart, q, keys), 10)
+    assert (rows, waves) == form
