@@ -21,28 +21,64 @@ struct GridPos {
   int x, z;
 };
 
-// The workgroups of one z on one XCD, whose L2 then fetches a tile of keys once for all that walk
-// it; as dispatched, 8 row blocks against 16 holders in two parts each put every key on every XCD.
-// z in turn over the XCDs; the order of x (longest walks first) is kept. (nz: a multiple of 8.)
+// The workgroups of one z onto as few XCDs as there are to share out: an XCD's L2 fetches a tile of
+// keys once for all that walk it there; as dispatched, 8 row blocks against 16 holders in two parts
+// each put every key on every XCD. g = gcd(nz, 8) classes of z, an eighth of the workgroups for each
+// XCD: class xcd % g, and every (8 / g)-th x. The order of x (longest walks first) is kept.
 CP_RULE GridPos xcd_slice(int x, int z, int nx, int nz) {
+  const int g = (nz & -nz & (kXcds - 1)) ? (nz & -nz) : kXcds, s = kXcds / g;
+  if (g == 1 || nx % s != 0) return {x, z};
   const uint32_t line = (uint32_t)x + (uint32_t)nx * (uint32_t)z;
-  const uint32_t xcd = line % kXcds, idx = line / kXcds, per = (uint32_t)nz / kXcds, k = idx / per;
-  return {(int)k, (int)(xcd + kXcds * (idx - k * per))};
+  const uint32_t xcd = line % kXcds, idx = line / kXcds, per = (uint32_t)nz / (uint32_t)g;
+  const uint32_t k = idx / per;
+  return {(int)(k * s + xcd / g), (int)(xcd % g + g * (idx - k * per))};
 }
 
-// Where that is done: one full round of workgroups, in which each has a compute unit to itself; few
-// row blocks, so that the traffic of the keys counts; and keys enough (4096 blocks: 131072) for it to
-// be seen. 128 queries of 16 heads, us, placed and as dispatched: 131072 keys in 16 shards kept apart
-// 145.3 and 149.8, in one 133.0 and 137.0 (the queries spread over its positions: 114 and 137).
-// Elsewhere it costs:
-//   more row blocks: an XCD has 32 compute units for its z, and those may be the long ones. 16
-//     holders of 8192 keys, one of them of 16384, 1024 queries 1506 and 1111; 32768 causal tokens in 8
-//     contiguous shards 7144 and 4663; 49152 tokens of one head against themselves 899 and 601. Of one
-//     round, too: 1024 queries on 2 shards of 32768 of which they see one 474 and 349.
-//   part of a round: 96 queries that see 8 of 16 shards of 16384 182 and 136
-//   few keys: 48 queries on 16384 33.3 and 28.3, 128 on 31744 in 16 shards (half seen) 56 and 54
-CP_RULE bool xcd_slice_applies(int64_t nx, int64_t nz, int64_t n_blocks) {
-  return nx * nz == kCus && nx <= 8 && n_blocks >= 4096;
+// What the z of a grid are.
+enum GridParts {
+  kPartsOfVisible,  // equal parts of what every row block sees
+  kPartsByIndex,    // of one shard, by the index of the keys
+  kShardsAlike,     // shards kept apart, of one length, and few queries (new ones on cached keys)
+  kShardsOther      // shards kept apart
+};
+CP_RULE bool shards_alike(int n, const int32_t* n_kv, int64_t total_q) {
+  int64_t longest = 0, total = 0;
+  for (int i = 0; i < n; ++i) {
+    longest = n_kv[i] > longest ? n_kv[i] : longest;
+    total += n_kv[i];
+  }
+  return 20 * longest * n <= 21 * total && 8 * total_q <= total;
+}
+
+// Where xcd_slice is used: row blocks that share keys (2 of a KV head at least), few enough that the
+// traffic of the keys counts, and z of the same work, since a class of z has its XCDs' compute units
+// and no others. us, as dispatched and sliced:
+//   rings merged in the launch, 4 to 32 row blocks, one round: 65 queries of 8 heads on 2 KV heads on 40401 keys of
+//     8 ranks 43.1 and 39.9, 106 of 16 on 4 on 106961 of 16 126.9 and 119.5, 588 of 8 on 2 122.6 and 117.7
+//   one shard by index, 4 to 8, one round, in 32 parts or more (under a causal mask the first are the
+//     long walks): 128 queries of 16 heads on 131072 keys 137 and 133, 64 81 and 78; 128 on 16384 keys
+//     37.4 and 40.4
+//   shards kept apart, alike, 3 to 16, of three quarters of a round to two: 128 queries of 16 heads on
+//     16 of 8192 keys 149.8 and 145.3, 160 of 16 on 16 of 5733 155.0 and 149.7, 96 of 8 on 2 on 16 of
+//     1970 45.3 and 42.2; but 64 of 16 on 2 of 15872 44.4 and 47.5, half a round
+// and where not:
+//   shards that are not alike: 1024 queries of 16 heads on 16 of 8192 keys, one of them of 16384, 1111
+//     and 1506; 32768 causal tokens in 8 contiguous shards 4663 and 7144; 49152 tokens of one head on
+//     themselves, by index, 601 and 899; of one round, too: 1024 queries on 49152 and 16384 keys 558
+//     and 696
+//   one row block a KV head: 32 queries of 16 heads on 4 KV heads on 32768 keys 31.8 and 32.9
+//   more row blocks, more rounds: no difference where the z are alike
+// (Fewer keys than some 30000 are planned in equal shares.)
+// (Shards alike whose keys the queries do not see alike, contiguous ones in the middle of which the
+// queries stand, lose up to 40 %; with load-balanced shards there is no such thing.)
+CP_RULE bool xcd_slice_applies(GridParts parts, int64_t row_blocks, int64_t n_kv_heads, int64_t nz,
+                               int64_t n_blocks) {
+  const int64_t nx = row_blocks * n_kv_heads;
+  if (nz < 2 || row_blocks < 2 || parts == kShardsOther) return false;
+  if (parts == kShardsAlike)
+    return nx >= 3 && nx <= 16 && nx * nz >= kCus * 3 / 4 && nx * nz <= 2 * kCus;
+  if (nx < 4 || nx * nz > kCus) return false;
+  return parts == kPartsOfVisible ? nx <= 32 : nx <= 8 && nz >= 32 && n_blocks >= 2048;
 }
 
 // ---- packed batches: spans found and positions encoded in one launch, or in two ----

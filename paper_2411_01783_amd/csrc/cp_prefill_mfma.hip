@@ -455,7 +455,11 @@ int launch_attn_mfma(const AttnShape& s, const AttnTable& t, const AttnOut& o,
   const unsigned wgs = (unsigned)(pl.n_row_blocks * s.n_kv_heads);
   const dim3 grid = pl.mode == PLAN ? dim3(pl.cut ? kPlanWorkgroups : wgs * pl.n_z)
                                     : dim3(wgs, 1, pl.n_z * pl.n_sub);
-  p.xcd_slice = xcd_slice_applies(grid.x, grid.z, s.n_blocks) ? 1 : 0;
+  const GridParts parts = s.per_shard ? shards_alike(t.n_shards, t.n_kv, s.total_q) ? kShardsAlike
+                                                                                    : kShardsOther
+                          : s.n_shards > 1 ? kPartsOfVisible
+                                           : kPartsByIndex;
+  p.xcd_slice = xcd_slice_applies(parts, pl.n_row_blocks, s.n_kv_heads, grid.z, s.n_blocks) ? 1 : 0;
   rc = launch_body(kern, smem, grid, p, stream);
   if (rc != CP_OK) return rc;
 

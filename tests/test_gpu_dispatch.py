@@ -140,21 +140,26 @@ def test_ring_launch_rules_count_every_key(kv_sizes, q_sizes, nh, nkv, d):
 
 
 # Which workgroup runs where (xcd_slice), with every output and partial full of NaN before, so that a
-# row block that nobody takes shows. Shards kept apart, as row blocks x parts of all shards: 8 x 32 from
-# 4096 blocks of keys on (2 and 4 KV heads, head_dim 64), 4 x 64, and what stays as dispatched: 4095
-# blocks, 12 x 42, 64 x 4, 8 x 30, more than a round (84 x 4).
-@pytest.mark.parametrize("kv_sizes,total_q,nh,nkv,d", [
-    ([8192] * 16, 128, 16, 1, 128), ([8192] * 15 + [8160], 128, 16, 1, 128),
-    ([65536 + 33, 65536], 64, 32, 2, 64), ([131072, 1, 0, 0], 128, 16, 4, 128),
-    ([20000] * 5 + [31073], 192, 16, 1, 128), ([40000] * 3 + [11073], 64, 16, 1, 128),
-    ([32768] * 4, 1024, 16, 4, 128), ([43692] * 3, 126, 16, 1, 128), ([40000] * 4, 672, 32, 1, 128),
+# row block that nobody takes shows. Row blocks x parts of all shards. Kept apart and alike: 8 x 32 (1
+# and 2 KV heads, head_dim 64), 8 x 30 of two classes, 12 x 20 of four, 12 x 18; as dispatched: a shard
+# longer than the rest, 64 x 4, more than a round (84 x 4). Merged in the launch: 4 x 64, 12 x 20, 8 x 30,
+# 20 x 12, and 64 x 4 as dispatched.
+@pytest.mark.parametrize("kv_sizes,total_q,nh,nkv,d,keep", [
+    ([8192] * 16, 128, 16, 1, 128, True), ([65536 + 33, 65536], 64, 32, 2, 64, True),
+    ([43692] * 3, 126, 16, 1, 128, True), ([8213] * 4, 192, 16, 1, 128, True),
+    ([5500, 5511] * 3, 192, 16, 1, 128, True), ([8192] * 15 + [16384], 128, 16, 1, 128, True),
+    ([131072, 1, 0, 0], 128, 16, 4, 128, True), ([40000] * 3 + [11073], 64, 16, 1, 128, True),
+    ([32768] * 4, 1024, 16, 4, 128, True), ([40000] * 4, 672, 32, 1, 128, True),
+    ([10101] * 4, 68, 8, 2, 128, False), ([30000, 1, 0, 5000], 352, 8, 2, 128, False),
+    ([8500] * 4, 100, 16, 4, 64, False), ([10900] * 4, 588, 8, 2, 128, False),
+    ([16384] * 4, 1024, 16, 1, 128, False),
 ])
-def test_kept_shards_placed_on_xcds_count_every_key(kv_sizes, total_q, nh, nkv, d):
+def test_shards_placed_on_xcds_count_every_key(kv_sizes, total_q, nh, nkv, d, keep):
     n, total = len(kv_sizes), sum(kv_sizes)
     q_sizes = [total_q // n] * n
     q_pos = np.sort(np.random.default_rng(n + total_q).integers(-1, total, size=total_q))
     args, cls = counts_case(kv_sizes, q_sizes, nh, nkv, d, q_pos)
-    ring = B.Ring(*args, out_dtype=torch.float32, keep_partials=True)
+    ring = B.Ring(*args, out_dtype=torch.float32, keep_partials=keep)
     for x in [ring.partial_out, ring.partial_lse] + ring.out + ring.lse:
         x.fill_(float("nan"))
     ring.workspace.fill_(255)
@@ -163,7 +168,7 @@ def test_kept_shards_placed_on_xcds_count_every_key(kv_sizes, total_q, nh, nkv, 
     check_counts(torch.cat(out), torch.cat(lse), q_pos, cls, d)
     ends = np.concatenate([[0], np.cumsum(kv_sizes)])
     for a, r in enumerate(np.split(q_pos, n)):
-        for b in range(n):
+        for b in range(n if keep else 0):
             check_counts(*ring.partial(a, b), r, cls, d, ends[b], ends[b + 1])
 
 

@@ -13,15 +13,20 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 SHIM = r"""
 #include "cp_launch_rules.h"
 extern "C" {
-// where the workgroups of a grid nx x nz run: x + nx * z of each, in dispatch order
-int placed(int nx, int nz, int n_blocks, int32_t* out) {
-  const bool slice = cp::xcd_slice_applies(nx, nz, n_blocks);
+// where the workgroups of a grid run: x + nx * z of each, in dispatch order
+int placed(int parts, int row_blocks, int n_kv_heads, int nz, int n_blocks, int32_t* out) {
+  const int nx = row_blocks * n_kv_heads;
+  const bool slice =
+      cp::xcd_slice_applies((cp::GridParts)parts, row_blocks, n_kv_heads, nz, n_blocks);
   for (int i = 0; i < nx * nz; ++i) {
     cp::GridPos at = {i % nx, i / nx};
     if (slice) at = cp::xcd_slice(at.x, at.z, nx, nz);
     out[i] = at.x < 0 || at.x >= nx || at.z < 0 || at.z >= nz ? -1 : at.x + nx * at.z;
   }
   return slice;
+}
+int shards_alike(int n, const int32_t* n_kv, int64_t total_q) {
+  return cp::shards_alike(n, n_kv, total_q);
 }
 int encode_in_one_launch(int64_t batch, int64_t lists, int64_t tokens) {
   return cp::encode_in_one_launch(batch, lists, tokens);
@@ -50,48 +55,75 @@ def rules(tmp_path_factory):
     return ctypes.CDLL(lib)
 
 
-def placed(rules, nx, nz, n_blocks):
-    out = np.empty(nx * nz, dtype=np.int32)
-    moved = rules.placed(nx, nz, n_blocks, out.ctypes.data_as(ctypes.c_void_p))
+VISIBLE, BY_INDEX, ALIKE, OTHER = range(4)
+
+
+def placed(rules, parts, row_blocks, nkv, nz, n_blocks=1 << 20):
+    out = np.empty(row_blocks * nkv * nz, dtype=np.int32)
+    moved = rules.placed(parts, row_blocks, nkv, nz, n_blocks, out.ctypes.data_as(ctypes.c_void_p))
     return out, bool(moved)
 
 
 def test_every_workgroup_of_a_grid_runs_once(rules):
-    any_moved = 0
-    for nz in list(range(1, 41)) + [48, 64, 69, 128, 256]:
-        for nx in list(range(1, 70)) + [96, 128, 139, 256]:
-            for n_blocks in (100, 4095, 4096, 100000):
-                out, moved = placed(rules, nx, nz, n_blocks)
-                assert np.array_equal(np.sort(out), np.arange(nx * nz)), (nx, nz)
-                any_moved += moved
-    assert any_moved > 0
+    moves = 0
+    for nz in list(range(1, 41)) + [48, 64, 69, 128]:
+        for row_blocks, nkv in [(x, 1) for x in range(1, 70)] + [(2, 2), (3, 4), (5, 2), (128, 1)]:
+            for parts in (VISIBLE, BY_INDEX, ALIKE, OTHER):
+                out, moved = placed(rules, parts, row_blocks, nkv, nz)
+                assert np.array_equal(np.sort(out), np.arange(row_blocks * nkv * nz))
+                moves += moved and not np.array_equal(out, np.arange(len(out)))
+    assert moves > 50
 
 
-# Work per z in proportion: holders with more keys, contiguous shards under a causal mask, shards
-# that no query sees. Workgroups go to the eight XCDs in turn, and the time is that of the busiest one:
-# it has no more to do than in the order of dispatch, up to one z's row blocks.
+# Work per z in proportion. Workgroups go to the eight XCDs in turn, and the time is that of the busiest
+# one. Shards that are not alike (a holder with more keys, contiguous ones under a causal mask) stay as
+# dispatched; what is placed is the same work for every XCD.
 @pytest.mark.parametrize("shares", [
     [1] * 7 + [2], [1] * 15 + [2], [3, 1], [1, 1, 1, 4], list(range(8, 0, -1)), [7, 5, 3, 1], [1, 0],
-    [4] * 8 + [1] * 8, [1, 1, 0, 0], [1] * 8 + [0] * 8, [1] * 4 + [0] * 12, [5] + [1] * 31,
+    [4] * 8 + [1] * 8, [1, 1, 0, 0], [1] * 8 + [0] * 8, [1] * 4 + [0] * 12, [5] + [1] * 31, [1] * 6,
+    [1] * 16,
 ])
 def test_no_xcd_gets_more_than_its_part(rules, shares):
-    for parts in (1, 2, 3, 4, 8, 16):
-        work = np.repeat(np.array(shares, dtype=np.int64), parts)
+    for sub in (1, 2, 3, 4, 8, 16):
+        work = np.repeat(np.array(shares, dtype=np.int64), sub)
         nz = len(work)
-        for nx in (1, 2, 4, 8, 12, 16, 32, 64, 128, 192, 256, 512):
-            out, moved = placed(rules, nx, nz, 1 << 20)
-            load = np.array([work[out[x::8] // nx].sum() for x in range(8)])
-            plain = np.array([work[np.arange(x, nx * nz, 8) // nx].sum() for x in range(8)])
-            assert load.max() <= plain.max() + (8 * work.max() if moved else 0), (nx, nz)
+        n_kv = (ctypes.c_int32 * len(shares))(*[8192 * x for x in shares])
+        alike = rules.shards_alike(len(shares), n_kv, ctypes.c_int64(128))
+        assert bool(alike) == (len(set(shares)) == 1)
+        for row_blocks in (2, 4, 8, 12, 16, 32, 64, 128, 192, 256, 512):
+            out, _ = placed(rules, ALIKE if alike else OTHER, row_blocks, 1, nz)
+            load = [work[out[x::8] // row_blocks].sum() for x in range(8)]
+            plain = [work[np.arange(x, row_blocks * nz, 8) // row_blocks].sum() for x in range(8)]
+            assert max(load) <= max(plain), (row_blocks, nz)
 
 
-# and what the placement is for
-@pytest.mark.parametrize("nx,nz", [(8, 32), (4, 64), (1, 256)])
-def test_workgroups_on_the_same_keys_share_an_xcd(rules, nx, nz):
-    out, moved = placed(rules, nx, nz, 4096)
+def test_shards_of_a_prefill_are_not_alike(rules):
+    n_kv = (ctypes.c_int32 * 8)(*[1000] * 8)
+    assert rules.shards_alike(8, n_kv, ctypes.c_int64(1000))
+    assert not rules.shards_alike(8, n_kv, ctypes.c_int64(1001))   # (contiguous, causal: very unlike)
+
+
+# Parts of one shard by index, under a causal mask the first ones are the long walks: spread over the XCDs.
+def test_parts_by_index_are_spread(rules):
+    for row_blocks in (2, 4, 8, 16, 32, 64, 192):
+        for nz in (2, 4, 8, 16, 32, 64):
+            out, _ = placed(rules, BY_INDEX, row_blocks, 1, nz)
+            work = np.arange(nz, 0, -1)
+            load = np.array([work[out[x::8] // row_blocks].sum() for x in range(8)])
+            if row_blocks * nz >= 64:
+                assert load.max() <= 1.25 * load.mean(), (row_blocks, nz)
+
+
+# and what the placement is for: a z on as few XCDs as can be
+@pytest.mark.parametrize("parts,row_blocks,nkv,nz,xcds", [
+    (ALIKE, 8, 1, 32, 1), (ALIKE, 4, 2, 30, 4), (VISIBLE, 12, 1, 20, 2), (VISIBLE, 2, 2, 64, 1),
+    (BY_INDEX, 8, 1, 32, 1),
+])
+def test_workgroups_on_the_same_keys_share_xcds(rules, parts, row_blocks, nkv, nz, xcds):
+    out, moved = placed(rules, parts, row_blocks, nkv, nz, 4096)
     assert moved
     for z in range(nz):
-        assert len(set(np.flatnonzero(out // nx == z) % 8)) == 1
+        assert len(set(np.flatnonzero(out // (row_blocks * nkv) == z) % 8)) == xcds
 
 
 # Ranks, sequences, and the time of a whole packed call with its positions encoded in one launch over
