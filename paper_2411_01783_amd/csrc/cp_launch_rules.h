@@ -81,6 +81,15 @@ CP_RULE bool xcd_slice_applies(GridParts parts, int64_t row_blocks, int64_t n_kv
   return parts == kPartsOfVisible ? nx <= 32 : nx <= 8 && nz >= 32 && n_blocks >= 2048;
 }
 
+// Equal shares of a planned call (256 of `units` row blocks, per KV head and shard kept apart): whether
+// neighbouring shares go to one XCD, as they walk the same keys. With few units neighbours are mostly
+// parts of one unit, that is other keys, and at head_dim 128 that costs. As dispatched and grouped, us:
+// 104 queries of 16 heads on 4 KV heads, 8 units, on 24208 keys 74.0 and 75.6, 12 units on 12649 62.3 and
+// 64.5, 20 on 20628 90.9 and 94.2; 28 on 12047 76.2 and 73.7 (28 to 100 are 0.95 to 1.05 of the time, 1.00
+// on average); packed prompts 111.5 and 110.7. Head_dim 64: 16 to 48 units 0.93 to 1.01 of the time, a
+// ring of 4096 tokens 62.4 and 61.3.
+CP_RULE bool shares_grouped(int head_dim, int units) { return head_dim == 64 || units >= 28; }
+
 // ---- packed batches: spans found and positions encoded in one launch, or in two ----
 
 // `lists`: of positions, the queries of every rank and the keys of every shard. In one launch the 16

@@ -709,9 +709,8 @@ __device__ __forceinline__ Share plan_share(const Params& p, int2* lds_bounds, u
   const bool keep_whole = all <= (int)gridDim.x &&
                           longest <= (int)(total / gridDim.x) + kCutCost * (D / 64) / 2;
   const int n_wgs = keep_whole ? all : plan_workgroups(total, gridDim.x);
-  // Neighbouring shares, which walk the same keys, on one XCD (workgroups go to the 8 XCDs in turn),
-  // if every XCD gets its part of them.
-  const int i = n_wgs == kPlanWorkgroups
+  // (workgroups go to the 8 XCDs in turn; only if every XCD gets its part of the shares)
+  const int i = n_wgs == kPlanWorkgroups && shares_grouped(D, all)
                     ? (int)(blockIdx.x & 7) * (kPlanWorkgroups / 8) + (int)(blockIdx.x >> 3)
                     : (int)blockIdx.x;
   if (tid == 0) *index = i;

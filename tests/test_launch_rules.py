@@ -25,6 +25,7 @@ int placed(int parts, int row_blocks, int n_kv_heads, int nz, int n_blocks, int3
   }
   return slice;
 }
+int shares_grouped(int head_dim, int units) { return cp::shares_grouped(head_dim, units); }
 int shards_alike(int n, const int32_t* n_kv, int64_t total_q) {
   return cp::shards_alike(n, n_kv, total_q);
 }
@@ -124,6 +125,15 @@ def test_workgroups_on_the_same_keys_share_xcds(rules, parts, row_blocks, nkv, n
     assert moved
     for z in range(nz):
         assert len(set(np.flatnonzero(out // (row_blocks * nkv) == z) % 8)) == xcds
+
+
+# head_dim, units, time with neighbouring shares on one XCD over that as dispatched (16384 to 29000 keys)
+@pytest.mark.parametrize("d,units,ratio", [
+    (128, 8, 1.03), (128, 12, 1.035), (128, 20, 1.03), (128, 24, 1.02), (128, 28, .97), (128, 64, .965),
+    (128, 320, .95), (64, 16, .97), (64, 48, .96),
+])
+def test_shares_of_few_units_are_not_grouped(rules, d, units, ratio):
+    assert bool(rules.shares_grouped(d, units)) == (ratio < 1)
 
 
 # Ranks, sequences, and the time of a whole packed call with its positions encoded in one launch over
