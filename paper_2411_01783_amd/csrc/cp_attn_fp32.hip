@@ -15,10 +15,10 @@
 // CUs with a short serial chain each. NR = 2 (head_dim 64, many rows) halves the K/V traffic
 // from L2.
 //
-// Bound: the matrix pipe's fp32 rate (157 TFLOP/s) for long shards, launch
-// and the chain positions -> list -> K -> V for short ones. A ring of 512 tokens over 2 ranks (4
-// heads of 64) takes 14.2 us: 128 workgroups, of whose 14 us the matrix pipe needs 3.4. It took 18.1
-// with 4 wavefronts a workgroup and the key positions asked for after the queries' had come.
+// Bound: the matrix pipe's fp32 rate (157 TFLOP/s) for long shards, launch and the chain positions ->
+// list -> K -> V for short ones. A ring of 512 tokens over 2 ranks (4 heads of 64) takes 14.2 us: 128
+// workgroups, of whose 14 us the matrix pipe needs 3.4. It took 17.5 with 4 wavefronts a workgroup, and
+// 18.1 with the key positions asked for after the queries' had come as well.
 #include "cp_common.h"
 #include "cp_launch_rules.h"
 #include "cp_table.h"
@@ -28,7 +28,7 @@ namespace {
 
 constexpr int BLK = 16;                     // keys per block
 constexpr int PER = kAttnBlock / BLK;       // blocks here per block of the table
-constexpr int kMaxList = 512;              // blocks looked at per chunk: a thread each, at most
+constexpr int kMaxList = 512;               // blocks looked at per chunk: a thread each, at most
 
 struct Params {
   AttnTable t;
@@ -56,13 +56,6 @@ struct BlockRegs {
   // order has it (2500 tokens of 4 heads of 64 67 to 74 us; 64.6 here).
   int last;
 };
-
-// Workgroup barrier that orders LDS traffic only: global loads stay in flight across it.
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
 
 // (head_dim 128: two wavefronts a SIMD asked for; left to itself the compiler takes 278 registers for
 // workgroups of 4, and one runs.)

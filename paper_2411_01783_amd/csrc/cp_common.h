@@ -33,6 +33,14 @@ __device__ __forceinline__ bf16_t from_float<bf16_t>(float x) {
   return static_cast<bf16_t>(x);
 }
 
+// Workgroup barrier that orders LDS traffic only: global loads issued before it stay in flight
+// across it.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // ---- launchers (each returns a cp_status; enqueue on `stream` only) ----
 
 // fp32 vector kernel: any supported dtype / head_dim, packed batches.

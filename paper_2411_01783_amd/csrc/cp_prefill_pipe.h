@@ -129,14 +129,6 @@ __device__ __forceinline__ unsigned pack_bf16(float a, float b) {
   return __builtin_bit_cast(unsigned, t);
 }
 
-// Workgroup barrier that orders LDS traffic only: global loads issued before it (the Q
-// fragments, the tile-bound prefetch) stay in flight across it.
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // Everything a wavefront carries from block to block. All indices are compile-time.
 template <int D>
 struct PipeRegs {
@@ -287,7 +279,6 @@ __device__ __forceinline__ void pipe_body(PipeRegs<D>& R, const bf16x8_t (&qf)[D
       }
     }
   };
-
 
   // ---- first half: P(i-1) on the matrix pipe, K fragments of block i+1 requested ----
   auto first = [&](auto mc) __attribute__((always_inline)) {
@@ -442,7 +433,7 @@ __device__ __forceinline__ bool ring_enter(const Params& p, int rank, int step, 
 // left whole (2100 queries of 16 heads that all see the same 1050 keys: 53 us cut, 41 whole; where
 // half of them see 2100 and half none: 53 cut, 67 whole). Only for calls whose positions and unit list
 // fit LDS; larger ones have row blocks enough to keep every CU busy. Six packed prompts of 200 to
-// 3000 tokens over 4 ranks: 241 us with a workgroup per row block and 128-key tiles, 114 us in
+// 3000 tokens over 4 ranks: 241 us with a workgroup per row block and 128-key tiles, 107 us in
 // equal shares of 32-key blocks.
 // ---------------------------------------------------------------------------
 
