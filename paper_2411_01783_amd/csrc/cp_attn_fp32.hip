@@ -38,6 +38,7 @@ struct Params {
   int32_t group;
   int32_t n_kv_heads;
   int32_t n_blocks;          // of the table
+  ChunkRule chunks;          // of ordered_row_block
   int32_t per_shard;
   float scale_log2;
 };
@@ -71,8 +72,7 @@ __global__ __launch_bounds__(NWAVE * 64, D == 128 ? 2 : 1) void attn_fp32_kernel
   __shared__ float comb_m[NWAVE][ROWS], comb_l[NWAVE][ROWS];
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int n = lane & 15, kg = lane >> 4;
-  const int row_block = ordered_row_block(blockIdx.x, gridDim.x, p.t.n_ranks, lane,
-                                          p.rows % ROWS != 0 ? kLatePartial : kLate);
+  const int row_block = ordered_row_block(blockIdx.x, gridDim.x, p.t.n_ranks, lane, p.chunks);
   const int kvh = blockIdx.y;
   const int z_shard = p.per_shard ? blockIdx.z : 0;
 
@@ -356,6 +356,7 @@ template <int D, int NR, int NWAVE, typename TO>
 int launch_t(const AttnShape& s, Params& p, hipStream_t stream) {
   const int64_t blocks = (p.rows + 16 * NR - 1) / (16 * NR);
   if (blocks > 0x7fffffffLL) return CP_ERR_SHAPE;
+  p.chunks = late_first((int)blocks, p.t.n_ranks, p.rows % (16 * NR) != 0);
   hipLaunchKernelGGL((attn_fp32_kernel<D, NR, NWAVE, TO>),
                      dim3((unsigned)blocks, s.n_kv_heads, s.per_shard ? s.n_shards : 1),
                      dim3(NWAVE * 64), 0, stream, p);

@@ -108,24 +108,26 @@ CP_RULE bool encode_in_one_launch(int64_t batch, int64_t lists, int64_t tokens) 
 // ---- the chunks of a ring's ranks among the row blocks, for ordered_row_block ----
 
 // First of the B row blocks (over the queries of N ranks back to back) of chunk j: rank j / 2's early
-// chunk (j even) or late chunk (j odd). A block with rows of two chunks:
-//   kEndsIn: is the chunk's that ends in it
-//   kLate, kLatePartial (the last block is not full): is the late chunk's, on either side of it, since
-//     its longest walk is a late row's
+// chunk (j even) or late chunk (j odd). A block with rows of two chunks is
+//   ends_in: the chunk's that ends in it
+//   late_first: the late chunk's, on either side of it, since its longest walk is a late row's
 // fp32: taken for early, such a block was dispatched last and the call waited for it alone: 1320 tokens
 // of 4 heads over 4 ranks 38.6 us, 25.4 with it in its place; 3600 157 and 96. The bf16 kernel has
-// kEndsIn: 20000 tokens of 16 heads over 4 ranks would gain 18 %, but 33333 over 8 lose 4 %. The
+// ends_in: 20000 tokens of 16 heads over 4 ranks would gain 18 %, but 33333 over 8 lose 4 %. The
 // boundaries are those of equal shards; shards of other sizes only lose some of the order. (B < 2^26:
 // that many row blocks of 16 rows do not fit the memory; N <= 32.)
-enum ChunkRule { kEndsIn, kLate, kLatePartial };
+struct ChunkRule {
+  uint32_t odd_blocks, up;
+};
+CP_RULE ChunkRule ends_in(int B) { return {(uint32_t)B, 0}; }
+// `partial`: the last block is not full (or boundaries come out up to a block too far)
+CP_RULE ChunkRule late_first(int B, int N, bool partial) {
+  if (B < 4 * N) return ends_in(B);   // (all of them run at once)
+  return {(uint32_t)B - (partial ? 1 : 0), 2 * (uint32_t)N - 1};
+}
 CP_RULE int chunk_begin(int j, int B, int N, ChunkRule rule) {
-  const uint32_t n2 = 2 * (uint32_t)N;
-  uint32_t b = (uint32_t)B, up = 0;
-  if (rule != kEndsIn && b >= 2 * n2) {   // (fewer all run at once)
-    if (j % 2 == 0) up = n2 - 1;
-    else if (rule == kLatePartial) b -= 1;   // (or the boundary comes out up to a block too far)
-  }
-  return (int)(((uint32_t)j * b + up) / n2);
+  return (int)(((uint32_t)j * (j % 2 ? rule.odd_blocks : (uint32_t)B) + (j % 2 ? 0 : rule.up)) /
+               (2 * (uint32_t)N));
 }
 
 // ---- fp32 attention: rows and wavefronts of a workgroup ----

@@ -598,7 +598,8 @@ __device__ __forceinline__ Share plan_share(const Params& p, int2* lds_bounds, u
     __syncthreads();
     const int i = blockIdx.x / p.n_kv_heads, kvh = blockIdx.x - i * p.n_kv_heads;
     const int z = p.n_z > 1 ? i / p.n_row_blocks : 0;
-    const int rb = ordered_row_block(i - z * p.n_row_blocks, p.n_row_blocks, p.n_ranks, lane, kEndsIn);
+    const int rb = ordered_row_block(i - z * p.n_row_blocks, p.n_row_blocks, p.n_ranks, lane,
+                                     ends_in(p.n_row_blocks));
     sh.unit = (kvh * p.n_z + z) * p.n_row_blocks + rb;
     return sh;
   }
@@ -809,7 +810,8 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
     }
     const int i = x / p.n_kv_heads;
     kvh = x - i * p.n_kv_heads;
-    row_block = ordered_row_block(i, p.n_row_blocks, p.n_ranks, threadIdx.x & 63, kEndsIn);
+    row_block = ordered_row_block(i, p.n_row_blocks, p.n_ranks, threadIdx.x & 63,
+                                  ends_in(p.n_row_blocks));
     z_shard = p.per_shard ? z / p.n_sub : 0;
     z_sub = z - z_shard * p.n_sub;
     if constexpr (MODE == RING) {   // row blocks do not straddle ranks here

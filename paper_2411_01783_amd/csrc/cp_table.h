@@ -19,9 +19,10 @@ __device__ __forceinline__ int ordered_row_block(int i, int B, int n_ranks, int 
   const int r = late ? lane : 2 * n_ranks - 1 - lane;
   int lo = 0, hi = 0;
   if (r >= 0) {   // (in 32 bits: 64-bit divisions took 1000 cycles of every start)
-    const int j = late ? 2 * r + 1 : 2 * r;
-    lo = chunk_begin(j, B, n_ranks, rule);
-    hi = chunk_begin(j + 1, B, n_ranks, rule);
+    const int middle = chunk_begin(2 * r + 1, B, n_ranks, rule);
+    const int side = chunk_begin(late ? 2 * r + 2 : 2 * r, B, n_ranks, rule);
+    lo = late ? middle : side;
+    hi = late ? side : middle;
   }
   int end = hi - lo;  // inclusive prefix sum of the lengths
 #pragma unroll

@@ -39,7 +39,7 @@ int fp32_form(int head_dim, int64_t rows, int64_t n_kv_heads, int64_t shards, in
   return f.rows * 10 + f.waves;
 }
 int chunk_begin(int j, int B, int N, int rule) {
-  return cp::chunk_begin(j, B, N, (cp::ChunkRule)rule);
+  return cp::chunk_begin(j, B, N, rule == 0 ? cp::ends_in(B) : cp::late_first(B, N, rule == 2));
 }
 }
 """
