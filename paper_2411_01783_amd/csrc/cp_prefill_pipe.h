@@ -54,12 +54,15 @@ struct Geo {
   static constexpr int OFF_SCRATCH = OFF_POS + 2 * POS_BYTES;
   static constexpr int OFF_LIVE = OFF_SCRATCH + 256;
   static constexpr int OFF_LIVE_POS = OFF_LIVE + MAX_LIVE * 16;
-  static constexpr int OFF_LIVE_RANGE = OFF_LIVE_POS + MAX_LIVE * 16;
+  static constexpr int OFF_LIVE_RANGE = OFF_LIVE_POS + MAX_LIVE * 8;
   static constexpr int OFF_BOUNDS = OFF_LIVE_RANGE + MAX_LIVE * 8;
   static constexpr int SMEM = OFF_BOUNDS;                        // bounds from global memory
   static constexpr int OFF_WEIGHT = OFF_BOUNDS + PLAN_MAX_BLOCKS * 8;  // PLAN: bounds kept in LDS
-  static constexpr int OFF_SHARDS = OFF_WEIGHT + PLAN_MAX_UNITS * 2;   // units' weights
-  static constexpr int OFF_INDEX = OFF_SHARDS + kMaxTable * 32;        // and the shards
+  static constexpr int OFF_SHARDS = OFF_WEIGHT + PLAN_MAX_UNITS * 2;   // units' weights,
+  static constexpr int OFF_RANKS = OFF_SHARDS + kMaxTable * 32;        // the shards
+  static constexpr int OFF_RANK_TOK = OFF_RANKS + kMaxTable * 32;      // and ranks, first token of each,
+  static constexpr int OFF_BLOCK_SHARD = OFF_RANK_TOK + 144;           // shard of every block
+  static constexpr int OFF_INDEX = OFF_BLOCK_SHARD + PLAN_MAX_BLOCKS;
   static constexpr int SMEM_PLAN = OFF_INDEX + 16;                     // which share this is
   static_assert(NWAVE * 32 * (D * 4 + 16) <= OFF_INDEX, "the epilogue's staging leaves it alone");
   static constexpr int OUT_STRIDE = D * 4 + 16;  // epilogue staging: one fp32 output row + pad
@@ -423,7 +426,7 @@ __device__ __forceinline__ bool ring_enter(const Params& p, int rank, int step, 
 // share ends. A unit is a row block of one KV head (against one shard, where shards are kept
 // apart); its weight is an estimate of its visible tiles plus kUnitCost for start-up and
 // epilogue. Every workgroup works the plan out for itself, from kv_pos and q_pos, in LDS: that
-// costs it 3 to 6 us, less than the launches that would hand it over, and replaces the
+// costs it 3 to 6 us (10 for packed prompts), less than the launches that would hand it over, and replaces the
 // position-bound pre-pass. (Counting a unit's visible blocks exactly took up to 45 us at 700
 // units and 350 blocks, so the weight comes from its first and last query and from at most 32
 // blocks, 128 in a packed batch; a cut is made at the same fraction of the unit's true list of
@@ -432,7 +435,10 @@ __device__ __forceinline__ bool ring_enter(const Params& p, int rank, int step, 
 // time as 12 tile steps (6 at head_dim 64), so units of nearly equal length that fit one round are
 // left whole (2100 queries of 16 heads that all see the same 1050 keys: 53 us cut, 41 whole; where
 // half of them see 2100 and half none: 53 cut, 67 whole). Only for calls whose positions and unit list
-// fit LDS; larger ones have row blocks enough to keep every CU busy. Six packed prompts of 200 to
+// fit LDS; larger ones have row blocks enough to keep every CU busy. What bounds a share of short
+// units are the latencies between the last tile of a unit and the first of the next, 9.9 us of packed
+// prompts' 91: with the next rows asked for behind the epilogue, tables in LDS and the blocks counted
+// and listed in one go 7.9, the call 109.4 -> 102.3 us, 4096 tokens at head_dim 64 59.3 -> 57.9. Six packed prompts of 200 to
 // 3000 tokens over 4 ranks: 241 us with a workgroup per row block and 128-key tiles, 107 us in
 // equal shares of 32-key blocks.
 // ---------------------------------------------------------------------------
@@ -467,14 +473,26 @@ struct Share {
   int length;
 };
 
-// Copies of the table that are looked up per lane while planning (over the tile buffers, which
-// are not in use yet).
+// Shards, ranks and the shard of every block, as PLAN looks them up (in LDS: per lane, and of every
+// unit, they would be chains of argument loads, 2 us of every start). Not filled for one rank or one
+// shard.
+struct LdsShard {
+  const void* k;
+  const void* v;
+  const int32_t* kv_pos;
+  int32_t n_kv, blk_begin;
+};
+struct LdsRank {
+  const void* q;
+  const int32_t* q_pos;
+  void* out;
+  float* lse;
+};
 struct PlanLds {
-  const int32_t* q_pos[kMaxTable];
-  const int32_t* kv_pos[kMaxTable];
-  int n_kv[kMaxTable];
-  int tok_begin[kMaxTable + 1];
-  int blk_begin[kMaxTable + 1];
+  LdsShard* shards;
+  LdsRank* ranks;
+  int32_t* tok_begin;     // kMaxTable + 1
+  uint8_t* block_shard;
 };
 
 // x rotated by N within each row of 16 lanes.
@@ -523,7 +541,6 @@ __device__ __forceinline__ void plan_bounds(const Params& p, int2* lds_bounds, c
                                             int tid) {
   // 8 threads per block, 4 positions per thread, up to 8 blocks per thread at a time
   constexpr int PER = 8, STEP = NTHREADS / 8;
-  int sh = 0;
   for (int b0 = 0; b0 < p.n_blocks; b0 += PER * STEP) {
     int32_t x[PER][4];
 #pragma unroll
@@ -533,10 +550,10 @@ __device__ __forceinline__ void plan_bounds(const Params& p, int2* lds_bounds, c
         int first = 0, n_kv = p.n_kv;
         Glb<const int32_t> pos = argument(p.kv_pos);
         if (p.n_shards > 1) {
-          while (b >= L.blk_begin[sh + 1]) ++sh;
-          first = L.blk_begin[sh];
-          n_kv = L.n_kv[sh];
-          pos = (Glb<const int32_t>)L.kv_pos[sh];
+          const LdsShard& e = L.shards[L.block_shard[b]];
+          first = e.blk_begin;
+          n_kv = e.n_kv;
+          pos = (Glb<const int32_t>)e.kv_pos;
         }
         const int key0 = (b - first) * BLOCK + (tid & 7);
 #pragma unroll
@@ -561,38 +578,58 @@ __device__ __forceinline__ void plan_bounds(const Params& p, int2* lds_bounds, c
   }
 }
 
-// A shard as the list of visible blocks looks it up per lane (PLAN: in LDS).
-struct LdsShard {
-  const void* k;
-  const void* v;
-  const int32_t* kv_pos;
-  int32_t n_kv, blk_begin;
-};
-
 // Bounds of all blocks, and this workgroup's share. `weight`: the units' planned tiles, `index`: which
 // share this is (LDS).
 template <int D, bool BAND>
 __device__ __forceinline__ Share plan_share(const Params& p, int2* lds_bounds, uint16_t* weight,
-                                            PlanLds& L, LdsShard* shards, int* index,
-                                            int* wg_scratch, int tid) {
+                                            const PlanLds& L, int* index, int* wg_scratch,
+                                            int tid) {
   const int lane = tid & 63, wave = tid >> 6;
   Share sh = {0, 0, 0};
-  if (p.n_shards > 1 && tid >= 64 && tid < 64 + p.n_shards) {
-    const int i = tid - 64;
-    shards[i] = {p.t.k[i], p.t.v[i], p.t.kv_pos[i], p.t.n_kv[i], p.t.blk_begin[i]};
-  }
+  const int n_rb = p.n_row_blocks, n_units = n_rb * p.n_z;
+  // Units of this thread (PER of them): their first and last query, and whose those are.
+  constexpr int PER = PLAN_MAX_UNITS / NTHREADS;
+  int tok[PER][2], of[PER][2] = {};
   if (p.n_ranks > 1 || p.n_shards > 1) {
-    if (tid <= kMaxTable) {
-      L.tok_begin[tid] = p.t.tok_begin[tid];
-      L.blk_begin[tid] = p.t.blk_begin[tid];
-      if (tid < kMaxTable) {
-        L.q_pos[tid] = p.t.q_pos[tid];
-        L.kv_pos[tid] = p.t.kv_pos[tid];
-        L.n_kv[tid] = p.t.n_kv[tid];
+    if (tid >= 64 && tid < 64 + p.n_shards) {
+      const int i = tid - 64;
+      L.shards[i] = {p.t.k[i], p.t.v[i], p.t.kv_pos[i], p.t.n_kv[i], p.t.blk_begin[i]};
+    }
+    if (tid >= 128 && tid < 128 + p.n_ranks) {
+      const int i = tid - 128;
+      L.ranks[i] = {p.t.q[i], p.t.q_pos[i], p.t.out[i], p.t.lse[i]};
+    }
+    if (tid >= 192 && tid <= 192 + p.n_ranks) L.tok_begin[tid - 192] = p.t.tok_begin[tid - 192];
+    if (p.n_shards > 1) {
+      for (int b = tid; b < p.n_blocks; b += NTHREADS) {
+        int sh = 0;
+#pragma unroll 8
+        for (int i = 1; i < p.n_shards; ++i) sh += b >= p.t.blk_begin[i];
+        L.block_shard[b] = (uint8_t)sh;
       }
     }
-    __syncthreads();
   }
+  if (p.cut_units) {
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const int u = min(k * NTHREADS + tid, n_units - 1);
+      const int rb = u - (p.n_z > 1 ? u / n_rb : 0) * n_rb;
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const uint32_t row = (uint32_t)rb * BM;
+        tok[k][e] = (int)((e == 0 ? row : min(row + BM, (uint32_t)p.rows) - 1) / (uint32_t)p.group);
+      }
+    }
+#pragma unroll 8
+    for (int i = 1; i < p.n_ranks; ++i) {
+      const int begin = p.t.tok_begin[i];
+#pragma unroll
+      for (int k = 0; k < PER; ++k)
+#pragma unroll
+        for (int e = 0; e < 2; ++e) of[k][e] += tok[k][e] >= begin;
+    }
+  }
+  if (p.n_ranks > 1 || p.n_shards > 1) __syncthreads();
   if (!p.cut_units) {  // a workgroup per unit
     plan_bounds(p, lds_bounds, L, tid);
     __syncthreads();
@@ -603,30 +640,19 @@ __device__ __forceinline__ Share plan_share(const Params& p, int2* lds_bounds, u
     sh.unit = (kvh * p.n_z + z) * p.n_row_blocks + rb;
     return sh;
   }
-  const int n_rb = p.n_row_blocks, n_units = n_rb * p.n_z;
-  // Position range of every row block as its first and its last query have it; PER blocks per
-  // thread, requested before the key positions.
-  constexpr int PER = PLAN_MAX_UNITS / NTHREADS;
+  // Position range of every row block as its first and its last query have it, requested before the
+  // key positions.
   int mx[PER], lo[PER];
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
     mx[k] = INT32_MIN;
     lo[k] = INT32_MAX;
     if (k * NTHREADS < n_units) {  // uniform
-      const int u = min(k * NTHREADS + tid, n_units - 1);
-      const int z = p.n_z > 1 ? u / n_rb : 0, rb = u - z * n_rb;
-      int a = 0;
 #pragma unroll
       for (int e = 0; e < 2; ++e) {
-        const int64_t row = e == 0 ? (int64_t)rb * BM : min<int64_t>((int64_t)rb * BM + BM, (int64_t)p.rows) - 1;
-        const int t = (int)((uint32_t)row / (uint32_t)p.group);
-        int32_t x;
-        if (p.n_ranks > 1) {
-          while (t >= L.tok_begin[a + 1]) ++a;
-          x = ((Glb<const int32_t>)L.q_pos[a])[t - L.tok_begin[a]];
-        } else {
-          x = ((Glb<const int32_t>)p.q_pos)[t];
-        }
+        const int t = tok[k][e], a = of[k][e];
+        const int32_t x = p.n_ranks > 1 ? ((Glb<const int32_t>)L.ranks[a].q_pos)[t - L.tok_begin[a]]
+                                        : ((Glb<const int32_t>)p.q_pos)[t];
         mx[k] = max(mx[k], x);
         if (BAND) lo[k] = min(lo[k], x >= 0 ? p.q_lo[t] : INT32_MAX);
       }
@@ -643,17 +669,21 @@ __device__ __forceinline__ Share plan_share(const Params& p, int2* lds_bounds, u
     if (k * NTHREADS < n_units) {
       const int u = min(k * NTHREADS + tid, n_units - 1);
       const int z = p.n_z > 1 ? u / n_rb : 0;
-      // (the table in LDS is only filled for several ranks or shards)
-      const int b0 = p.n_z > 1 ? L.blk_begin[z] : 0;
-      const int b1 = p.n_z > 1 ? L.blk_begin[z + 1] : p.n_blocks;
-      int cnt = 0;
-      for (int b = b0; b < b1; b += 8 * stride) {
+      const int b0 = p.n_z > 1 ? L.shards[z].blk_begin : 0;
+      const int b1 = p.n_z > 1 ? (z + 1 < p.n_z ? L.shards[z + 1].blk_begin : p.n_blocks) : p.n_blocks;
+      int cnt = 0, b = b0;
+      // (no test of the range in the groups that lie in it: 10 vector instructions a sample were 4.4 us
+      // of a packed call's start, for 98 samples)
+      for (; b + 7 * stride < b1; b += 8 * stride) {
         int2 x[8];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) x[i] = lds_bounds[min(b + i * stride, b1 - 1)];
+        for (int i = 0; i < 8; ++i) x[i] = lds_bounds[b + i * stride];
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
-          cnt += b + i * stride < b1 && x[i].x <= mx[k] && (!BAND || x[i].y >= lo[k]) ? 1 : 0;
+        for (int i = 0; i < 8; ++i) cnt += x[i].x <= mx[k] && (!BAND || x[i].y >= lo[k]) ? 1 : 0;
+      }
+      for (; b < b1; b += stride) {
+        const int2 x = lds_bounds[b];
+        cnt += x.x <= mx[k] && (!BAND || x.y >= lo[k]) ? 1 : 0;
       }
       weight[u] = (uint16_t)max(1, (cnt * stride + 3) >> 2);
     }
@@ -771,7 +801,6 @@ enum Mode {
 template <int D, typename TO, bool BAND, Mode MODE>
 __device__ __forceinline__ void prefill_body(const Params& p) {
   using G = Geo<D>;
-  static_assert(4 * G::KD >= (int)sizeof(PlanLds), "the planning arrays lie over the tile buffers");
   constexpr int ROW = G::ROW;
   extern __shared__ __align__(16) char smem[];
   char* const kbuf0 = smem;
@@ -779,22 +808,34 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
   int32_t* const posbuf0 = (int32_t*)(smem + G::OFF_POS);
   int* const wg_scratch = (int*)(smem + G::OFF_SCRATCH);
   int4* const live = (int4*)(smem + G::OFF_LIVE);            // addresses of K and V (below)
-  int4* const live_pos = (int4*)(smem + G::OFF_LIVE_POS);    // address of kv_pos, keys
+  int2* const live_pos = (int2*)(smem + G::OFF_LIVE_POS);    // address of kv_pos, keys above it
   int2* const live_range = (int2*)(smem + G::OFF_LIVE_RANGE);  // (min, max) of kv_pos
   int2* const lds_bounds = (int2*)(smem + G::OFF_BOUNDS);
   uint16_t* const weight = (uint16_t*)(smem + G::OFF_WEIGHT);
-  LdsShard* const shards = (LdsShard*)(smem + G::OFF_SHARDS);
+  const PlanLds L = {(LdsShard*)(smem + G::OFF_SHARDS), (LdsRank*)(smem + G::OFF_RANKS),
+                     (int32_t*)(smem + G::OFF_RANK_TOK), (uint8_t*)(smem + G::OFF_BLOCK_SHARD)};
   int* const share_index = (int*)(smem + G::OFF_INDEX);
   const uint32_t smem_lds = (uint32_t)(size_t)(CP_LDS_AS char*)smem;
 
+  // All lines of the arguments at once: as scalar loads, a few lines at a time, they are one cold
+  // memory latency after the other (128 queries of 16 heads on 16 of 8192 keys: 9.7 -> 6.9 us from the
+  // start to the first tile's requests).
+  int touched = 0;
+  if (threadIdx.x < (sizeof(Params) + 63) / 64)
+    touched = ((const __attribute__((address_space(4))) int*)__builtin_amdgcn_kernarg_segment_ptr())[threadIdx.x * 16];
   // ---- what this workgroup does first ----
   int row_block = 0, kvh = 0, z_shard = 0, z_sub = 0, rank = 0;
   Share share = {0, 0, 0};
   if constexpr (MODE == PLAN) {
-    share = plan_share<D, BAND>(p, lds_bounds, weight, *(PlanLds*)smem, shards, share_index,
-                                wg_scratch, threadIdx.x);
+    share = plan_share<D, BAND>(p, lds_bounds, weight, L, share_index, wg_scratch, threadIdx.x);
     if (p.cut_units && share.length == 0) return;
-    __syncthreads();   // the planning arrays are dead
+    const int units = p.n_row_blocks * p.n_z;
+    kvh = share.unit / units;
+    const int u = share.unit - kvh * units;
+    z_shard = p.n_z > 1 ? u / p.n_row_blocks : 0;
+    row_block = u - z_shard * p.n_row_blocks;
+    asm volatile("" ::"v"(touched));
+    lds_barrier();   // the plan's scratch is read
   } else {
     // The KV heads of a row block are neighbours in dispatch order: the rows of one head are
     // n_kv_heads * 2 D bytes apart, so workgroups that all read the same head use only some of
@@ -820,6 +861,59 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
     }
   }
 
+  // Rank of the query `token` of a lane's row, in a row block whose first query is t0 (PLAN, several
+  // ranks): most row blocks lie within one.
+  auto planned_rank = [&](int t0, int token, int lane) __attribute__((always_inline)) -> int {
+    const int begin = L.tok_begin[min(lane, p.n_ranks)];
+    int a = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < p.n_ranks && t0 >= begin)) - 1;
+    if (__builtin_amdgcn_ballot_w64(token >= __builtin_amdgcn_readlane(begin, a + 1)) != 0)
+      while (token >= L.tok_begin[a + 1]) ++a;
+    return a;
+  };
+  // Asks for what this lane needs of its query row in row block `rb`: position, lower bound, Q
+  // fragments. A row past the end takes the last one's (it is known by its index), so that nothing is
+  // waited for here: loads under a condition were, 1.2 us of every epilogue that makes them.
+  auto request_rows = [&](int rb, int head, int n_rows, int tid, int32_t& qp, int32_t& ql,
+                          u32x4_t (&qf)[G::NKS]) __attribute__((always_inline)) {
+    const int lane = tid & 63, g = lane >> 5;
+    const int r = min(rb * BM + (__builtin_amdgcn_readfirstlane(tid >> 6)) * 32 + (lane & 31), n_rows - 1);
+    int token = (int)((uint32_t)r / (uint32_t)p.group);
+    const int hg = r - token * p.group;
+    auto q = (Glb<const bf16_t>)argument(MODE == RING ? p.t.q[rank] : p.q);
+    auto q_pos = argument(MODE == RING ? p.t.q_pos[rank] : p.q_pos);
+    const int packed_token = token;
+    if (MODE != RING && p.n_ranks > 1) {
+      const int t0 = (int)((uint32_t)(rb * BM) / (uint32_t)p.group);
+      if constexpr (MODE == PLAN) {
+        const int a = planned_rank(t0, token, lane);
+        q = (Glb<const bf16_t>)L.ranks[a].q;
+        q_pos = (Glb<const int32_t>)L.ranks[a].q_pos;
+        token -= L.tok_begin[a];
+      } else {
+        // (scalar loads where the row block lies within one rank, which it mostly does)
+        const int a0 = rank_of_token(p.t, t0);
+        q = (Glb<const bf16_t>)p.t.q[a0];
+        q_pos = (Glb<const int32_t>)p.t.q_pos[a0];
+        int first = p.t.tok_begin[a0];
+        if ((int64_t)rb * BM + BM > (int64_t)p.t.tok_begin[a0 + 1] * p.group) {
+          const int a = rank_of_token(p.t, token);
+          q = (Glb<const bf16_t>)p.t.q[a];
+          q_pos = (Glb<const int32_t>)p.t.q_pos[a];
+          first = p.t.tok_begin[a];
+        }
+        token -= first;
+      }
+    }
+    q += (((int64_t)token * p.n_kv_heads + head) * p.group + hg) * D + g * 8;
+    qp = q_pos[token];
+    ql = BAND ? p.q_lo[packed_token] : INT32_MIN;
+#pragma unroll
+    for (int ks = 0; ks < G::NKS; ++ks) qf[ks] = *(Glb<const u32x4_t>)(q + ks * 16);
+  };
+  int32_t next_qp = 0, next_ql = 0;   // of the next unit's rows (PLAN: behind the epilogue of this one)
+  u32x4_t next_qf[G::NKS];
+  bool rows_requested = false;
+
   for (;;) {  // (PLAN: the units of the share, else once)
     // (The thread index is made opaque here: what is computed from it would otherwise be kept in
     // registers across the units, of which there are none to spare.)
@@ -827,13 +921,6 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
     if constexpr (MODE == PLAN) asm volatile("" : "+v"(tid));
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int n = lane & 31, g = lane >> 5;
-    if constexpr (MODE == PLAN) {
-      const int units = p.n_row_blocks * p.n_z;
-      kvh = share.unit / units;
-      const int u = share.unit - kvh * units;
-      z_shard = p.n_z > 1 ? u / p.n_row_blocks : 0;
-      row_block = u - z_shard * p.n_row_blocks;
-    }
     // ---- blocks of this workgroup (the ring walk moves on from shard to shard) ----
     int cur_shard = MODE == RING ? rank : z_shard;
     const bool one_shard = MODE == RING || p.per_shard;
@@ -858,41 +945,15 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
     // (needed last) are requested after both and waited for only before the first product.
     int2 first_bounds = make_int2(0, 0);
     if (b_begin + tid < b_end) first_bounds = block_bounds(b_begin + tid);
-    int32_t qp = CP_POS_PAD_Q, ql = INT32_MIN;
+    if (MODE != PLAN || !rows_requested)
+      request_rows(row_block, kvh, n_rows, tid, next_qp, next_ql, next_qf);
+    const int32_t qp = row_ok ? next_qp : CP_POS_PAD_Q, ql = row_ok ? next_ql : INT32_MIN;
     bf16x8_t qf[G::NKS];
-    {
-      const int r = r0 + n;
-      int token = row_ok ? (int)((uint32_t)r / (uint32_t)p.group) : 0;
-      const int hg = row_ok ? r - token * p.group : 0;
-      auto q = (Glb<const bf16_t>)argument(MODE == RING ? p.t.q[rank] : p.q);
-      auto q_pos = argument(MODE == RING ? p.t.q_pos[rank] : p.q_pos);
-      if (BAND && row_ok) ql = p.q_lo[token];
-      if (MODE != RING && p.n_ranks > 1) {
-        // (scalar loads where the row block lies within one rank, which it mostly does)
-        const int t0 = (int)((uint32_t)(row_block * BM) / (uint32_t)p.group);
-        const int a0 = rank_of_token(p.t, t0);
-        q = (Glb<const bf16_t>)p.t.q[a0];
-        q_pos = (Glb<const int32_t>)p.t.q_pos[a0];
-        int first = p.t.tok_begin[a0];
-        if ((int64_t)row_block * BM + BM > (int64_t)p.t.tok_begin[a0 + 1] * p.group) {
-          const int a = rank_of_token(p.t, token);
-          q = (Glb<const bf16_t>)p.t.q[a];
-          q_pos = (Glb<const int32_t>)p.t.q_pos[a];
-          first = p.t.tok_begin[a];
-        }
-        token -= row_ok ? first : token;
-      }
-      if (row_ok) qp = q_pos[token];
-      const int64_t row = ((int64_t)token * p.n_kv_heads + kvh) * p.group + hg;
 #pragma unroll
-      for (int ks = 0; ks < G::NKS; ++ks) {
-        u32x4_t x = {0u, 0u, 0u, 0u};
-        if (row_ok) x = *(Glb<const u32x4_t>)(q + row * D + ks * 16 + g * 8);
-        qf[ks] = __builtin_bit_cast(bf16x8_t, x);
-      }
-    }
+    for (int ks = 0; ks < G::NKS; ++ks) qf[ks] = __builtin_bit_cast(bf16x8_t, next_qf[ks]);
     const float scale_log2 = p.scale_log2;
 
+    if constexpr (MODE != PLAN) asm volatile("" ::"v"(touched));
     // ---- query position range of the wavefront and of the workgroup ----
     // rows that can see anything: a padded query (CP_POS_PAD_Q) and the rows past the end of
     // the shard cannot, and stay out of the ranges below
@@ -979,20 +1040,35 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
     // whole tiles of the list.
     int part_lo = 0, part_hi = INT32_MAX;
     bool whole = true, first_piece = true;  // PLAN: the unit is not cut; its first piece
+    // (the visible ones of the first chunk, counted here, are listed from the same count below)
+    uint64_t first_mask = 0;
+    int first_base = 0, first_total = 0;
     if constexpr (MODE == SPLIT || MODE == PLAN) {
       int total = 0;
-      if (MODE == SPLIT ? p.sub_blocks == 0 : p.cut_units != 0) {
-        int cnt = b_begin + tid < b_end && visible(first_bounds) ? 1 : 0;
+      const bool more = (MODE == SPLIT ? p.sub_blocks == 0 : p.cut_units != 0) &&
+                        b_end - b_begin > NTHREADS;   // chunks to count
+      int cnt = 0;
+      if (more) {
         for (int b = b_begin + NTHREADS + tid; b < b_end; b += NTHREADS)
           cnt += visible(block_bounds(b)) ? 1 : 0;
         cnt = wave_sum(cnt);
-        lds_barrier();
-        if (lane == 0) wg_scratch[wave] = cnt;
-        lds_barrier();
-#pragma unroll
-        for (int w = 0; w < NWAVE; ++w) total += wg_scratch[w];
-        total = __builtin_amdgcn_readfirstlane(total);
       }
+      first_mask = __builtin_amdgcn_ballot_w64(b_begin + tid < b_end && visible(first_bounds));
+      int* const counts = wg_scratch + 24;
+      if (lane == 0) {
+        counts[wave] = __builtin_popcountll(first_mask);
+        counts[NWAVE + wave] = cnt;
+      }
+      lds_barrier();
+#pragma unroll
+      for (int w = 0; w < NWAVE; ++w) {
+        const int c = counts[w];
+        if (w < wave) first_base += c;
+        first_total += c;
+        total += counts[NWAVE + w];
+      }
+      first_total = __builtin_amdgcn_readfirstlane(first_total);
+      total = __builtin_amdgcn_readfirstlane(total) + first_total;
       if constexpr (MODE == SPLIT) {
         if (p.sub_blocks == 0) {
           // (in 32 bits, which the tiles of a memory full of keys fit 64 times: a 64-bit division is
@@ -1002,8 +1078,8 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
           part_hi = 4 * (int)(tiles * (uint32_t)(z_sub + 1) / (uint32_t)p.n_sub);
         }
       } else if (p.cut_units) {
-        const int units = p.n_row_blocks * p.n_z;
-        const int planned = __builtin_amdgcn_readfirstlane((int)weight[share.unit % units]);
+        const int planned =
+            __builtin_amdgcn_readfirstlane((int)weight[z_shard * p.n_row_blocks + row_block]);
         const int end = min(kUnitCost + planned, share.begin + share.length);
         const int lo = max(0, share.begin - kUnitCost), hi = end - kUnitCost;
         share.length -= end - share.begin;
@@ -1032,27 +1108,36 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
       for (int c0 = b_begin; c0 < b_end; c0 += MAX_LIVE) {
         // Compact the blocks some query of the workgroup can see (smallest key position not
         // beyond the largest query position) into an ascending list in LDS.
-        lds_barrier();  // previous chunk (list, tile buffers) fully consumed
         int n_live;     // tiles
         {
           const int b = c0 + tid;
-          int2 bb = make_int2(0, 0);
-          bool lv = false;
-          if (b < b_end) {
-            bb = (c0 == b_begin && step == 0) ? first_bounds : block_bounds(b);
-            lv = visible(bb);
-          }
-          const uint64_t mask = __builtin_amdgcn_ballot_w64(lv);
-          if (lane == 0) wg_scratch[wave] = __builtin_popcountll(mask);
-          lds_barrier();
+          int2 bb = first_bounds;
+          bool lv;
+          uint64_t mask;
           int base = 0, total = 0;
+          if ((MODE == SPLIT || MODE == PLAN) && c0 == b_begin) {
+            lv = (first_mask >> lane & 1) != 0;
+            mask = first_mask;
+            base = first_base;
+            total = first_total;
+          } else {
+            lds_barrier();  // previous chunk (list, tile buffers) fully consumed
+            lv = false;
+            if (b < b_end) {
+              if (c0 != b_begin || step != 0) bb = block_bounds(b);
+              lv = visible(bb);
+            }
+            mask = __builtin_amdgcn_ballot_w64(lv);
+            if (lane == 0) wg_scratch[wave] = __builtin_popcountll(mask);
+            lds_barrier();
 #pragma unroll
-          for (int w = 0; w < NWAVE; ++w) {
-            const int c = wg_scratch[w];
-            if (w < wave) base += c;
-            total += c;
+            for (int w = 0; w < NWAVE; ++w) {
+              const int c = wg_scratch[w];
+              if (w < wave) base += c;
+              total += c;
+            }
+            total = __builtin_amdgcn_readfirstlane(total);
           }
-          total = __builtin_amdgcn_readfirstlane(total);
           const int lo = max(part_lo, seen), hi = min(part_hi, seen + total);
           const int idx = seen + base + __builtin_popcountll(mask & ((1ull << lane) - 1ull));
           if (lv && idx >= lo && idx < hi) {
@@ -1067,29 +1152,32 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
                    p.t.n_kv[cur_shard], p.t.blk_begin[cur_shard]};
             } else {
               int sh = cur_shard;
-              if (!one_shard) {
+              if constexpr (MODE == PLAN) {
+                if (!one_shard) sh = L.block_shard[b];
+                e = L.shards[sh];
+              } else {
 #pragma unroll 8
                 for (int i = 1; i < p.n_shards; ++i) sh += b >= p.t.blk_begin[i];
+                e = {p.t.k[sh], p.t.v[sh], p.t.kv_pos[sh], p.t.n_kv[sh], p.t.blk_begin[sh]};
               }
-              if constexpr (MODE == PLAN) e = shards[sh];
-              else e = {p.t.k[sh], p.t.v[sh], p.t.kv_pos[sh], p.t.n_kv[sh], p.t.blk_begin[sh]};
             }
             const int key0 = (b - e.blk_begin) * BLOCK;
             const int valid = min(BLOCK, e.n_kv - key0);
             const uint64_t off = (uint64_t)key0 * stride_b + (uint32_t)kvh * ROW;
             const uint64_t ka = (uint64_t)e.k + off, va = (uint64_t)e.v + off;
             const uint64_t pa = (uint64_t)(e.kv_pos + key0);
-            // (the last valid row travels in the upper 16 bits of V's address, which are zero)
+            // (the last valid row travels in the upper 16 bits of V's address, which are zero, and the
+            // count of keys in those of their positions')
             const int4 kv = make_int4((int)ka, (int)(ka >> 32), (int)va,
                                       (int)(va >> 32) | (valid - 1) << 16);
             live[idx - lo] = kv;
-            live_pos[idx - lo] = make_int4((int)pa, (int)(pa >> 32), valid, 0);
+            live_pos[idx - lo] = make_int2((int)pa, (int)(pa >> 32) | valid << 16);
             // (a ragged block always pays for the mask: its largest position is the pad's)
             live_range[idx - lo] = make_int2(bb.x, valid < BLOCK ? INT32_MAX : bb.y);
             if (idx == hi - 1) {  // fill the last tile with blocks of no keys
               for (int i = idx - lo + 1; (i & 3) != 0; ++i) {
                 live[i] = kv;
-                live_pos[i] = make_int4((int)pa, (int)(pa >> 32), 0, 0);
+                live_pos[i] = make_int2((int)pa, (int)(pa >> 32));
                 live_range[i] = make_int2(INT32_MAX, INT32_MAX);
               }
             }
@@ -1120,11 +1208,11 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
           const int mm = (int)(__builtin_amdgcn_ballot_w64(m) & 15);
           t.mask = mm | ((int)__builtin_amdgcn_ballot_w64(none) & mm) << 4;
           if (wave < TILE / 64) {   // kv_pos of the key tid
-            const int4 own = live_pos[i + (tid >> 5)];
+            const int2 own = live_pos[i + (tid >> 5)];
             next_pos = CP_POS_PAD_KV;
-            if ((tid & 31) < own.z) {
+            if ((tid & 31) < (int)((uint32_t)own.y >> 16)) {
               const auto pos = (Glb<const int32_t>)((uint64_t)(uint32_t)own.x |
-                                                    (uint64_t)(uint32_t)own.y << 32);
+                                                    (uint64_t)(uint32_t)(own.y & 0xffff) << 32);
               next_pos = pos[tid & 31];
             }
           }
@@ -1241,6 +1329,24 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
     asm volatile("" : "+v"(tid_e));
     const int lane_e = tid_e & 63, n_e = lane_e & 31, g_e = lane_e >> 5;
     const int r = r0 + n_e;
+    // PLAN: what the next unit needs of its rows travels behind this epilogue (its registers are the
+    // walk's: it costs none), and its address arithmetic is out of the next start.
+    int next_rb = row_block + 1, next_z = z_shard, next_kvh = kvh;
+    // (defined on every path: else the old ones are kept for the others)
+#pragma unroll
+    for (int ks = 0; ks < G::NKS; ++ks) next_qf[ks] = u32x4_t{0u, 0u, 0u, 0u};
+    if constexpr (MODE == PLAN) {
+      rows_requested = p.cut_units && share.length > 0;
+      if (next_rb == p.n_row_blocks) {
+        next_rb = 0;
+        if (++next_z == p.n_z) {
+          next_z = 0;
+          ++next_kvh;
+        }
+      }
+      if (rows_requested)
+        request_rows(next_rb, next_kvh, p.rows, tid_e, next_qp, next_ql, next_qf);
+    }
     const float l_sum = R.l_run + xor32(R.l_run);
     const float l_tot = sees ? l_sum : 0.f;
     const bool no_key = l_tot == 0.f;
@@ -1264,7 +1370,13 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
       const int hg = row_ok ? r - token * p.group : 0;
       auto o = (Glb<char>)argument(MODE == RING ? p.t.out[rank] : p.out);
       auto l = argument(MODE == RING ? p.t.lse[rank] : p.lse);
-      if (MODE != SPLIT && MODE != RING && p.n_ranks > 1) {
+      if (MODE == PLAN && p.n_ranks > 1) {
+        const int t0 = (int)((uint32_t)(row_block * BM) / (uint32_t)p.group);
+        const int a = planned_rank(t0, token, lane_e);
+        token -= row_ok ? L.tok_begin[a] : token;
+        o = (Glb<char>)L.ranks[a].out;
+        l = (Glb<float>)L.ranks[a].lse;
+      } else if (MODE != SPLIT && MODE != RING && p.n_ranks > 1) {
         const int a = rank_of_token(p.t, token);
         token -= p.t.tok_begin[a];
         o = (Glb<char>)p.t.out[a];
@@ -1450,8 +1562,10 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
       }
     }
     if constexpr (MODE != PLAN) return;
-    if (!p.cut_units || share.length <= 0) return;
-    share.unit += 1;
+    if (!rows_requested) return;
+    row_block = next_rb;
+    z_shard = next_z;
+    kvh = next_kvh;
     share.begin = 0;
     lds_barrier();   // the staging buffer is read before the next unit's tiles arrive (the
                      // stores need not have left)

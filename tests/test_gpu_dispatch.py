@@ -139,6 +139,28 @@ def test_ring_launch_rules_count_every_key(kv_sizes, q_sizes, nh, nkv, d):
                         check_counts(*ring.partial(a, b), r, cls, d, ends[b], ends[b + 1])
 
 
+# Equal shares of several units, whose rows are asked for one unit ahead: row blocks with rows of many
+# ranks (some without any), the last row block short, the step from one KV head to the next.
+@pytest.mark.parametrize("kv_sizes,q_sizes,nh,nkv,d", [
+    ([2000, 0, 33, 1], [1, 7, 0, 300], 16, 1, 128),
+    ([1500, 700], [700, 33], 12, 3, 128),
+    ([40] * 31 + [900], [3, 0, 16, 1, 90, 0, 0, 5] * 4, 16, 2, 128),
+    ([1500, 700], [1100, 1], 8, 4, 64),
+    ([1100], [2049], 16, 4, 64),
+])
+def test_shares_of_units_that_hold_rows_of_many_ranks(kv_sizes, q_sizes, nh, nkv, d):
+    n = max(len(kv_sizes), len(q_sizes))
+    kv_sizes, q_sizes = kv_sizes + [0] * (n - len(kv_sizes)), q_sizes + [0] * (n - len(q_sizes))
+    tq, tk = sum(q_sizes), sum(kv_sizes)
+    rng = np.random.default_rng(tq + tk)
+    for q_pos in (np.arange(tq) * tk // tq, np.sort(rng.integers(-1, tk, size=tq))):
+        args, cls = counts_case(kv_sizes, q_sizes, nh, nkv, d, q_pos)
+        ring = B.Ring(*args, out_dtype=torch.float32)
+        out, lse = B.cp_ring_passkv(ring)
+        torch.cuda.synchronize()
+        check_counts(torch.cat(out), torch.cat(lse), q_pos, cls, d)
+
+
 # Which workgroup runs where (xcd_slice), with every output and partial full of NaN before, so that a
 # row block that nobody takes shows. Row blocks x parts of all shards. Kept apart and alike: 8 x 32 (1
 # and 2 KV heads, head_dim 64), 8 x 30 of two classes, 12 x 20 of four, 12 x 18; as dispatched: a shard
