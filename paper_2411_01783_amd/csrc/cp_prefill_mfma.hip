@@ -56,7 +56,6 @@ constexpr int MAX_LIVE = NTHREADS;        // blocks looked at (and listed) per c
 constexpr int PLAN_MAX_BLOCKS = 960;      // PLAN: block bounds kept in LDS (30K keys; what fits)
 constexpr int PLAN_MAX_UNITS = 1024;      // PLAN: units per KV head
 constexpr int kPlanWorkgroups = 256;      // one per CU
-constexpr int kUnitCost = 3;              // start-up and epilogue of a unit, in tile steps
 constexpr int kCutCost = 12;              // partials of a cut at head_dim 128, in tile steps
 constexpr int kUncutTiles = 6;            // units up to this long are not worth a cut
 constexpr float kRescaleSlack = 8.f;               // log2 units
@@ -234,7 +233,7 @@ Plan make_plan(const AttnShape& s) {
   const bool one_call = s.n_shards == 1 && !s.per_shard;
   bool plan = !single_large && s.n_blocks <= PLAN_MAX_BLOCKS && units <= PLAN_MAX_UNITS &&
               wgs <= 8 * PLAN_MAX_UNITS &&
-              // (the line of all units times 256, and token rows, within 32 bits)
+              // (the line of all units, in half tiles, times 256, and token rows, within 32 bits)
               wgs * (24 + s.n_blocks / 4) < (1ll << 23);
   if (one_call) {
     // A call of one rank against one shard, as a rank of a real ring makes it. Up to two tiles, or

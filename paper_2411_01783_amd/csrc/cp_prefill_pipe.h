@@ -46,6 +46,14 @@ struct Geo {
   // bf16 terms of a probability. head_dim 64: three, which hold all 24 bits of the fp32 value (the
   // products with V are exact and summed in fp32: nothing is rounded to 16 bits). head_dim 128: one.
   static constexpr int TERMS = D == 64 ? 3 : 1;
+  // PLAN: blocks of a step of the line of units (cuts lie between two steps), and what start-up and
+  // epilogue of a unit cost, in steps. Half tiles and less for a unit at head_dim 64, where 7.5 us lie
+  // between the last tile of one unit and the first of the next, and a tile takes 3.7 (2 tiles: 900
+  // tokens of 16 heads on 2 33.3 us, 2600 of 8 48.3; 1.5: 31.5 and 45.7), and for packed calls (5 prompts
+  // of 700 to 3000 195.8 -> 189.2, 12 of 200 to 600 62.9 -> 59.9). At head_dim 128 otherwise whole tiles:
+  // 3000 tokens of 16 heads 70.4, in half tiles 72.1 to 78.
+  static constexpr int step_blocks(bool packed) { return D == 64 || packed ? 2 : 4; }
+  static constexpr int unit_cost(bool packed) { return D == 64 ? 3 : packed ? 6 : 3; }
   static constexpr int CHUNKS = ROW / 16;        // 16-byte chunks of a row
   static constexpr int LOAD_ROWS = 64 / CHUNKS;  // rows one 1 KiB load instruction brings
   static constexpr int PARTS = 16 / LOAD_ROWS;   // load instructions per wavefront for K (or V)
@@ -424,10 +432,10 @@ __device__ __forceinline__ bool ring_enter(const Params& p, int rank, int step, 
 // to 49 tiles: 204 us where the work is 70 us of all compute units). So the launch is 256
 // workgroups (one per CU) that take equal shares of the whole work, cutting row blocks where a
 // share ends. A unit is a row block of one KV head (against one shard, where shards are kept
-// apart); its weight is an estimate of its visible tiles plus kUnitCost for start-up and
+// apart); its weight is an estimate of its visible tiles plus unit_cost for start-up and
 // epilogue. Every workgroup works the plan out for itself, from kv_pos and q_pos, in LDS: that
-// costs it 3 to 6 us (10 for packed prompts), less than the launches that would hand it over, and replaces the
-// position-bound pre-pass. (Counting a unit's visible blocks exactly took up to 45 us at 700
+// costs it 3 to 6 us (10 for packed prompts), less than the launches that would hand it over, and
+// replaces the position-bound pre-pass. (Counting a unit's visible blocks exactly took up to 45 us at 700
 // units and 350 blocks, so the weight comes from its first and last query and from at most 32
 // blocks, 128 in a packed batch; a cut is made at the same fraction of the unit's true list of
 // tiles.) What a share cuts goes to the workspace as fp32 partials (at most two per
@@ -438,15 +446,15 @@ __device__ __forceinline__ bool ring_enter(const Params& p, int rank, int step, 
 // fit LDS; larger ones have row blocks enough to keep every CU busy. What bounds a share of short
 // units are the latencies between the last tile of a unit and the first of the next, 9.9 us of packed
 // prompts' 91: with the next rows asked for behind the epilogue, tables in LDS and the blocks counted
-// and listed in one go 7.9, the call 109.4 -> 102.3 us, 4096 tokens at head_dim 64 59.3 -> 57.9. Six packed prompts of 200 to
-// 3000 tokens over 4 ranks: 241 us with a workgroup per row block and 128-key tiles, 107 us in
-// equal shares of 32-key blocks.
+// and listed in one go 7.9, the call 109.4 -> 102.3 us, 4096 tokens at head_dim 64 59.3 -> 57.9.
+// Six packed prompts of 200 to 3000 tokens over 4 ranks: 241 us with a workgroup per row block and
+// 128-key tiles, 99 us in equal shares of 32-key blocks.
 // ---------------------------------------------------------------------------
 
 // Shares: workgroup i of W takes [share_begin(i), share_begin(i + 1)) of the line of all units
 // (the host keeps total * 256 within 32 bits).
-__device__ inline int plan_workgroups(uint32_t total, int max_wgs) {
-  const uint32_t w = total / (kUnitCost + 2);   // a share is worth its own start-up
+__device__ inline int plan_workgroups(uint32_t total, int own_start, int max_wgs) {
+  const uint32_t w = total / (uint32_t)own_start;   // a share is worth its own start-up
   return (int)(w < 1 ? 1 : w > (uint32_t)max_wgs ? (uint32_t)max_wgs : w);
 }
 __device__ inline int share_begin(int i, uint32_t total, int n_wgs) {
@@ -584,6 +592,9 @@ template <int D, bool BAND>
 __device__ __forceinline__ Share plan_share(const Params& p, int2* lds_bounds, uint16_t* weight,
                                             const PlanLds& L, int* index, int* wg_scratch,
                                             int tid) {
+  // (in steps of kStep blocks)
+  constexpr int kStep = Geo<D>::step_blocks(BAND), kTile = 4 / kStep;
+  constexpr int kUnitCost = Geo<D>::unit_cost(BAND);
   const int lane = tid & 63, wave = tid >> 6;
   Share sh = {0, 0, 0};
   const int n_rb = p.n_row_blocks, n_units = n_rb * p.n_z;
@@ -685,7 +696,7 @@ __device__ __forceinline__ Share plan_share(const Params& p, int2* lds_bounds, u
         const int2 x = lds_bounds[b];
         cnt += x.x <= mx[k] && (!BAND || x.y >= lo[k]) ? 1 : 0;
       }
-      weight[u] = (uint16_t)max(1, (cnt * stride + 3) >> 2);
+      weight[u] = (uint16_t)max(1, (cnt * stride + kStep - 1) / kStep);
     }
   }
   __syncthreads();
@@ -729,8 +740,8 @@ __device__ __forceinline__ Share plan_share(const Params& p, int2* lds_bounds, u
   // Whole units where a cut gains less than its partials cost: one round of workgroups, and the
   // longest unit not much longer than a share.
   const bool keep_whole = all <= (int)gridDim.x &&
-                          longest <= (int)(total / gridDim.x) + kCutCost * (D / 64) / 2;
-  const int n_wgs = keep_whole ? all : plan_workgroups(total, gridDim.x);
+                          longest <= (int)(total / gridDim.x) + kCutCost * (D / 64) * kTile / 2;
+  const int n_wgs = keep_whole ? all : plan_workgroups(total, kUnitCost + 2 * kTile, gridDim.x);
   // (workgroups go to the 8 XCDs in turn; only if every XCD gets its part of the shares)
   const int i = n_wgs == kPlanWorkgroups && shares_grouped(D, all)
                     ? (int)(blockIdx.x & 7) * (kPlanWorkgroups / 8) + (int)(blockIdx.x >> 3)
@@ -1037,7 +1048,7 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
       return b.x <= wg_qmax && (!BAND || b.y >= wg_lomin);
     };
     // The part of the list of visible blocks that is walked here: [part_lo, part_hi). Parts are
-    // whole tiles of the list.
+    // whole half tiles of the list.
     int part_lo = 0, part_hi = INT32_MAX;
     bool whole = true, first_piece = true;  // PLAN: the unit is not cut; its first piece
     // (the visible ones of the first chunk, counted here, are listed from the same count below)
@@ -1071,24 +1082,26 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
       total = __builtin_amdgcn_readfirstlane(total) + first_total;
       if constexpr (MODE == SPLIT) {
         if (p.sub_blocks == 0) {
-          // (in 32 bits, which the tiles of a memory full of keys fit 64 times: a 64-bit division is
-          // 500 cycles of every start)
-          const uint32_t tiles = (uint32_t)(total + 3) >> 2;
-          part_lo = 4 * (int)(tiles * (uint32_t)z_sub / (uint32_t)p.n_sub);
-          part_hi = 4 * (int)(tiles * (uint32_t)(z_sub + 1) / (uint32_t)p.n_sub);
+          // (in 32 bits, which the half tiles of a memory full of keys fit 32 times: a 64-bit division
+          // is 500 cycles of every start)
+          const uint32_t halves = (uint32_t)(total + 1) >> 1;
+          part_lo = 2 * (int)(halves * (uint32_t)z_sub / (uint32_t)p.n_sub);
+          part_hi = 2 * (int)(halves * (uint32_t)(z_sub + 1) / (uint32_t)p.n_sub);
         }
       } else if (p.cut_units) {
         const int planned =
             __builtin_amdgcn_readfirstlane((int)weight[z_shard * p.n_row_blocks + row_block]);
+        constexpr int kUnitCost = G::unit_cost(BAND);
         const int end = min(kUnitCost + planned, share.begin + share.length);
         const int lo = max(0, share.begin - kUnitCost), hi = end - kUnitCost;
         share.length -= end - share.begin;
         if (hi <= lo) return;  // the share ends within the unit's start-up
         whole = lo == 0 && hi == planned;
         first_piece = lo == 0;
-        const int tiles = (total + 3) >> 2;   // (pieces can come out empty: they are written as such)
-        part_lo = 4 * (int)((uint32_t)(tiles * lo) / (uint32_t)planned);
-        part_hi = 4 * (int)((uint32_t)(tiles * hi) / (uint32_t)planned);
+        constexpr int kStep = G::step_blocks(BAND);
+        const int steps = (total + kStep - 1) / kStep;   // (pieces can come out empty: they are written as such)
+        part_lo = kStep * (int)((uint32_t)(steps * lo) / (uint32_t)planned);
+        part_hi = kStep * (int)((uint32_t)(steps * hi) / (uint32_t)planned);
       }
     }
 
@@ -1108,7 +1121,8 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
       for (int c0 = b_begin; c0 < b_end; c0 += MAX_LIVE) {
         // Compact the blocks some query of the workgroup can see (smallest key position not
         // beyond the largest query position) into an ascending list in LDS.
-        int n_live;     // tiles
+        int n_live;       // tiles
+        bool half_tail;   // the last one has two blocks at most
         {
           const int b = c0 + tid;
           int2 bb = first_bounds;
@@ -1184,6 +1198,7 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
           }
           seen += total;
           n_live = (max(0, hi - lo) + 3) >> 2;
+          half_tail = (uint32_t)(hi - lo - 1) % 4 < 2;
         }
         lds_barrier();
         if (n_live == 0) continue;
@@ -1273,6 +1288,10 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
                                   if (M == 1 && __builtin_expect(has_next, 1)) issue_part(IntC<PPS>{}, next, nb);
                                   if (M == 9 && __builtin_expect(has_next, 1)) issue_part(IntC<3>{}, next, nb);
                                 });
+          // (the pipeline is at the same parity after two blocks as after four. Nothing of this tile is
+          // in flight then but the V fragments, which the drain waits for. 320 tokens at head_dim 64
+          // 19.1 -> 17.5 us, twelve prompts of 200 to 600 tokens 62.9 -> 59.9.)
+          if (__builtin_expect(half_tail && !has_next, 0)) break;
           pipe_body<D, 2, BAND>(R, qf, kaddr, vaddr, paddr, qp, ql, scale_log2, mask & 4,
                                 mask & 64, have_ref, no_hook);
           // barrier Y: the next tile has landed in every wavefront
@@ -1312,7 +1331,7 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
           __builtin_amdgcn_sched_barrier(0);
         }
         // back to buffer-0 addressing for the next chunk
-        if (n_live & 1) {
+        if ((n_live - (half_tail ? 1 : 0)) & 1) {
 #pragma unroll
           for (int ks = 0; ks < G::NKS; ++ks) kaddr[ks] ^= G::KD;
 #pragma unroll

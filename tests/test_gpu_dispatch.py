@@ -139,6 +139,32 @@ def test_ring_launch_rules_count_every_key(kv_sizes, q_sizes, nh, nkv, d):
                         check_counts(*ring.partial(a, b), r, cls, d, ends[b], ends[b + 1])
 
 
+# The last tile of a list ends after two blocks where no more than two have keys: one to five blocks,
+# cut lists (parts, equal shares) that end either way, a second chunk of one and of three blocks, and a
+# packed batch.
+@pytest.mark.parametrize("tq,tk,nh,d", [
+    (20, 32, 16, 128), (20, 64, 16, 64), (20, 65, 16, 128), (20, 96, 16, 64), (20, 129, 16, 128),
+    (70, 8192 + 64, 16, 128), (70, 8192 + 65, 16, 64), (2100, 2080, 16, 128), (2100, 2112, 16, 64),
+    (20, 16384 + 30, 16, 128), (20, 16384 + 96, 16, 64),
+])
+def test_tiles_of_two_blocks_count_every_key(tq, tk, nh, d):
+    rng = np.random.default_rng(tq + tk)
+    for q_pos in (np.full(tq, tk), np.sort(rng.integers(-1, tk, size=tq))):
+        args, cls = counts_case([tk], [tq], nh, 1, d, q_pos)
+        o, l = B.cp_attn_partial(*(x[0] for x in args), out_dtype=torch.float32)
+        torch.cuda.synchronize()
+        check_counts(o, l, q_pos, cls, d)
+        # as two sequences of one packed batch: the same lists one after the other
+        if d == 128 and tk < 4096:
+            two = [torch.cat([x[0], x[0]]) for x in args]
+            cu = [i32([0, n, 2 * n]) for n in (tq, tk)]
+            o, l = B.cp_attn_partial(*two, out_dtype=torch.float32, cu_seqlens_q=cu[0],
+                                     cu_seqlens_kv=cu[1])
+            torch.cuda.synchronize()
+            check_counts(o[:tq], l[:tq], q_pos, cls, d)
+            check_counts(o[tq:], l[tq:], q_pos, cls, d)
+
+
 # Equal shares of several units, whose rows are asked for one unit ahead: row blocks with rows of many
 # ranks (some without any), the last row block short, the step from one KV head to the next.
 @pytest.mark.parametrize("kv_sizes,q_sizes,nh,nkv,d", [
