@@ -16,9 +16,10 @@
 // from L2.
 //
 // Bound: the matrix pipe's fp32 rate (157 TFLOP/s) for long shards, launch and the chain positions ->
-// list -> K -> V for short ones. A ring of 512 tokens over 2 ranks (4 heads of 64) takes 14.2 us: 128
-// workgroups, of whose 14 us the matrix pipe needs 3.4. It took 17.5 with 4 wavefronts a workgroup, and
-// 18.1 with the key positions asked for after the queries' had come as well.
+// list -> K -> V for short ones. A ring of 512 tokens over 2 ranks (4 heads of 64) takes 13.5 us: 128
+// workgroups, of whose 13 us the matrix pipe needs 3.4. It took 17.5 with 4 wavefronts a workgroup,
+// 18.1 with the key positions asked for after the queries' had come as well, and 14.2 with the shard of
+// a block and the rank of a row looked up by lane, two latencies of arguments ahead of the positions.
 #include "cp_common.h"
 #include "cp_launch_rules.h"
 #include "cp_table.h"
@@ -59,9 +60,11 @@ struct BlockRegs {
 };
 
 // (head_dim 128: two wavefronts a SIMD asked for; left to itself the compiler takes 278 registers for
-// workgroups of 4, and one runs.)
+// workgroups of 4, and one runs. Two at most: with a third, which 168 registers allow, whole prefills of
+// 513 to 768 workgroups take their longest walks slower, 2500 tokens of 4 heads on 2 74 -> 79.6.)
 template <int D, int NR, int NWAVE, typename TO>
-__global__ __launch_bounds__(NWAVE * 64, D == 128 ? 2 : 1) void attn_fp32_kernel(const Params p) {
+__global__ __launch_bounds__(NWAVE * 64) __attribute__((amdgpu_waves_per_eu(D == 128 ? 2 : 1, 2)))
+void attn_fp32_kernel(const Params p) {
   constexpr int NTHREADS = NWAVE * 64;
   constexpr int MAX_LIST = NTHREADS;                    // blocks looked at per chunk
   constexpr int ROWS = 16 * NR;
@@ -70,6 +73,7 @@ __global__ __launch_bounds__(NWAVE * 64, D == 128 ? 2 : 1) void attn_fp32_kernel
   __shared__ int wg_scratch[NWAVE];
   __shared__ __align__(16) float comb[NWAVE][ROWS][STRIDE];
   __shared__ float comb_m[NWAVE][ROWS], comb_l[NWAVE][ROWS];
+  const int touched = touch_arguments<Params>();
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int n = lane & 15, kg = lane >> 4;
   const int row_block = ordered_row_block(blockIdx.x, gridDim.x, p.t.n_ranks, lane, p.chunks);
@@ -88,14 +92,25 @@ __global__ __launch_bounds__(NWAVE * 64, D == 128 ? 2 : 1) void attn_fp32_kernel
     lo = INT64_MAX;
     if (b < b_end) {
       const int blk = b / PER;
+      // (scalar loads and selects: looked up by lane, the shard's arguments are another latency)
+      int begin = p.t.blk_begin[z_shard], count = p.t.n_kv[z_shard];
+      const int32_t* pos = p.t.kv_pos[z_shard];
       if (!p.per_shard) {
-#pragma unroll 8
-        for (int i = 1; i < p.t.n_shards; ++i) sh += blk >= p.t.blk_begin[i];
+#pragma unroll 4
+        for (int i = 1; i < p.t.n_shards; ++i) {
+          const int x = p.t.blk_begin[i], c = p.t.n_kv[i];
+          const int32_t* const y = p.t.kv_pos[i];
+          const bool in = blk >= x;
+          sh = in ? i : sh;
+          begin = in ? x : begin;
+          count = in ? c : count;
+          pos = in ? y : pos;
+        }
       }
-      key0 = (blk - p.t.blk_begin[sh]) * kAttnBlock + (b % PER) * BLK;
-      const int last = p.t.n_kv[sh] - 1 - key0;
+      key0 = (blk - begin) * kAttnBlock + (b % PER) * BLK;
+      const int last = count - 1 - key0;
       if (last >= 0) {
-        const int32_t* pt = p.t.kv_pos[sh] + key0;
+        const int32_t* pt = pos + key0;
         int m = INT32_MAX;
 #pragma unroll
         for (int i = 0; i < BLK; ++i) m = min(m, pt[min(i, last)]);
@@ -129,6 +144,11 @@ __global__ __launch_bounds__(NWAVE * 64, D == 128 ? 2 : 1) void attn_fp32_kernel
     load_block(__builtin_amdgcn_readfirstlane(le.x), __builtin_amdgcn_readfirstlane(le.y), x);
   };
   // ---- queries: row r of column group c is this lane's column n ----
+  // (The rank of the first row, in scalar registers, is mostly that of all.)
+  const int t0 = (int)((uint32_t)(row_block * ROWS) / (uint32_t)p.group);
+  const int a0 = rank_of_token(p.t, t0);
+  const bool one_rank = (int64_t)row_block * ROWS + ROWS <= (int64_t)p.t.tok_begin[a0 + 1] * p.group ||
+                        a0 == p.t.n_ranks - 1;
   floatx4_t qf[NR][D / 16];
   int32_t qp[NR];
   int qmax = INT32_MIN;
@@ -138,11 +158,18 @@ __global__ __launch_bounds__(NWAVE * 64, D == 128 ? 2 : 1) void attn_fp32_kernel
     const bool ok = r < p.rows;
     const int token = ok ? (int)((uint32_t)r / (uint32_t)p.group) : 0;
     const int hg = ok ? (int)(r - (int64_t)token * p.group) : 0;
-    const int a = rank_of_token(p.t, token);
-    const int local = token - p.t.tok_begin[a];
-    const float* q = (const float*)p.t.q[a] +
-                     (((int64_t)local * p.n_kv_heads + kvh) * p.group + hg) * D + kg * 4;
-    qp[c] = ok ? p.t.q_pos[a][local] : CP_POS_PAD_Q;
+    const float* q = (const float*)p.t.q[a0];
+    const int32_t* q_pos = p.t.q_pos[a0];
+    int first = p.t.tok_begin[a0];
+    if (!one_rank) {
+      const int a = rank_of_token(p.t, token);
+      q = (const float*)p.t.q[a];
+      q_pos = p.t.q_pos[a];
+      first = p.t.tok_begin[a];
+    }
+    const int local = ok ? token - first : 0;
+    q += (((int64_t)local * p.n_kv_heads + kvh) * p.group + hg) * D + kg * 4;
+    qp[c] = ok ? q_pos[local] : CP_POS_PAD_Q;
 #pragma unroll
     for (int j = 0; j < D / 16; ++j)
       qf[c][j] = ok ? *(const floatx4_t*)(q + j * 16) : floatx4_t{0.f, 0.f, 0.f, 0.f};
@@ -161,6 +188,7 @@ __global__ __launch_bounds__(NWAVE * 64, D == 128 ? 2 : 1) void attn_fp32_kernel
   for (int o = 8; o > 0; o >>= 1) qmax = max(qmax, __shfl_xor(qmax, o, 64));
   qmax = __builtin_amdgcn_readfirstlane(qmax);  // (the wavefronts hold the same rows)
 
+  asm volatile("" ::"v"(touched));
   float m_run[NR], l_run[NR];
   floatx4_t acc[NR][D / 16];
 #pragma unroll
@@ -305,10 +333,17 @@ __global__ __launch_bounds__(NWAVE * 64, D == 128 ? 2 : 1) void attn_fp32_kernel
     const float inv = den > 0.f ? 1.f / den : 0.f;
     const int token = row_ok ? (int)((uint32_t)r / (uint32_t)p.group) : 0;
     const int hg = row_ok ? (int)(r - (int64_t)token * p.group) : 0;
-    const int a = rank_of_token(p.t, token);
-    const int64_t lin =
-        ((int64_t)(token - p.t.tok_begin[a]) * p.n_kv_heads + kvh) * p.group + hg;
-    char* const out0 = (char*)p.t.out[a] + z_shard * p.out_shard_bytes;
+    int a = a0, first = p.t.tok_begin[a0];
+    char* out0 = (char*)p.t.out[a0];
+    float* lse = p.t.lse[a0];
+    if (!one_rank) {
+      a = rank_of_token(p.t, token);
+      first = p.t.tok_begin[a];
+      out0 = (char*)p.t.out[a];
+      lse = p.t.lse[a];
+    }
+    const int64_t lin = ((int64_t)(token - first) * p.n_kv_heads + kvh) * p.group + hg;
+    out0 += z_shard * p.out_shard_bytes;
     // Rows that a V they do not see has spoiled (see VectorRow).
     float spoil = 0.f;   // stays zero if O is finite
 #pragma unroll
@@ -346,8 +381,8 @@ __global__ __launch_bounds__(NWAVE * 64, D == 128 ? 2 : 1) void attn_fp32_kernel
 #pragma unroll
       for (int i = 0; i < CPT; ++i) o[i] = from_float<TO>(den > 0.f ? x[i] * inv : 0.f);
     }
-    if (tid % TPR == 0 && p.t.lse[a] != nullptr)
-      p.t.lse[a][z_shard * p.lse_shard_elems + lin] =
+    if (tid % TPR == 0 && lse != nullptr)
+      lse[z_shard * p.lse_shard_elems + lin] =
           den > 0.f ? (mmax + __builtin_amdgcn_logf(den)) * kLn2 : -INFINITY;
   }
 }

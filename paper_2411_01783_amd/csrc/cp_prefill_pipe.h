@@ -828,12 +828,7 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
   int* const share_index = (int*)(smem + G::OFF_INDEX);
   const uint32_t smem_lds = (uint32_t)(size_t)(CP_LDS_AS char*)smem;
 
-  // All lines of the arguments at once: as scalar loads, a few lines at a time, they are one cold
-  // memory latency after the other (128 queries of 16 heads on 16 of 8192 keys: 9.7 -> 6.9 us from the
-  // start to the first tile's requests).
-  int touched = 0;
-  if (threadIdx.x < (sizeof(Params) + 63) / 64)
-    touched = ((const __attribute__((address_space(4))) int*)__builtin_amdgcn_kernarg_segment_ptr())[threadIdx.x * 16];
+  const int touched = touch_arguments<Params>();
   // ---- what this workgroup does first ----
   int row_block = 0, kvh = 0, z_shard = 0, z_sub = 0, rank = 0;
   Share share = {0, 0, 0};
