@@ -892,7 +892,7 @@ __host__ __device__ inline FlatParts flat_parts(int32_t a, int32_t b, int32_t wg
 // LSE); the largest LSE and the weights are reduced across the workgroup; then the wavefronts
 // share out the parts, every lane accumulating two channels of the parts its wavefront takes
 // (FM_U loads in flight per lane), and the MW sums are added up in LDS. Bound by its chain of
-// memory latencies (bid, cu_seqlens_kv, LSE, rows): one holder's slots need no table in LDS.
+// memory latencies (bid, cu_seqlens_kv, LSE, rows).
 struct FlatMergeParams {
   const int32_t* cu_kv[kMaxHolders];
   int32_t total_kv[kMaxHolders];
@@ -907,16 +907,16 @@ struct FlatMergeParams {
   int32_t n_q_heads;
 };
 
-// MW wavefronts per workgroup: 8 for a ring of holders, 4 for the few parts of one call.
+constexpr int MW = 8;       // wavefronts per workgroup
 constexpr int FM_U = 4;     // row loads in flight per lane
-template <typename TO, int MW, bool ONE>
+template <typename TO>
 __global__ __launch_bounds__(MW * 64) void decode_flat_merge_kernel(const FlatMergeParams mp,
                                                                      TO* __restrict__ out,
                                                                      float* __restrict__ lse_out) {
   constexpr int MTHREADS = MW * 64;
   static_assert(MTHREADS >= D, "one thread per channel writes the row");
-  __shared__ int part_begin[ONE ? 1 : kMaxHolders + 1];  // first part index of every holder
-  __shared__ int holder_lo[ONE ? 1 : kMaxHolders], holder_mains[ONE ? 1 : kMaxHolders];
+  __shared__ int part_begin[kMaxHolders + 1];  // first part index of every holder
+  __shared__ int holder_lo[kMaxHolders], holder_mains[kMaxHolders];
   __shared__ float red[MW];
   __shared__ float w_of[MTHREADS];
   __shared__ int src_of[MTHREADS];
@@ -925,38 +925,29 @@ __global__ __launch_bounds__(MW * 64) void decode_flat_merge_kernel(const FlatMe
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int qi = row / mp.n_q_heads, h = row - qi * mp.n_q_heads;
   const int s = mp.bid[qi];
-  int n_parts, one_lo = 0, one_mains = 0;
-  if constexpr (ONE) {
-    const FlatParts fp =
-        flat_parts(mp.cu_kv[0][s], mp.cu_kv[0][s + 1], mp.wg_keys, mp.total_kv[0]);
-    one_lo = fp.g_lo;
-    one_mains = max(0, fp.g_hi - fp.g_lo + 1);
-    n_parts = one_mains + (fp.tail ? FW : 0);
-  } else {
-    // lane k of the first wavefront looks up holder k's slots of this sequence (one round trip
-    // for all holders) and lines the holders' parts up
-    if (wave == 0) {
-      int c = 0;
-      if (lane < mp.n_holders) {
-        const FlatParts fp =
-            flat_parts(mp.cu_kv[lane][s], mp.cu_kv[lane][s + 1], mp.wg_keys, mp.total_kv[lane]);
-        const int mains = max(0, fp.g_hi - fp.g_lo + 1);
-        holder_lo[lane] = mp.wg_begin[lane] + fp.g_lo;
-        holder_mains[lane] = mains;
-        c = mains + (fp.tail ? FW : 0);
-      }
-      int end = c;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int y = __shfl_up(end, o, 64);
-        if (lane >= o) end += y;
-      }
-      if (lane < mp.n_holders) part_begin[lane] = end - c;
-      if (lane == mp.n_holders - 1) part_begin[mp.n_holders] = end;
+  // lane k of the first wavefront looks up holder k's slots of this sequence (one round trip
+  // for all holders) and lines the holders' parts up
+  if (wave == 0) {
+    int c = 0;
+    if (lane < mp.n_holders) {
+      const FlatParts fp =
+          flat_parts(mp.cu_kv[lane][s], mp.cu_kv[lane][s + 1], mp.wg_keys, mp.total_kv[lane]);
+      const int mains = max(0, fp.g_hi - fp.g_lo + 1);
+      holder_lo[lane] = mp.wg_begin[lane] + fp.g_lo;
+      holder_mains[lane] = mains;
+      c = mains + (fp.tail ? FW : 0);
     }
-    __syncthreads();
-    n_parts = part_begin[mp.n_holders];
+    int end = c;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int y = __shfl_up(end, o, 64);
+      if (lane >= o) end += y;
+    }
+    if (lane < mp.n_holders) part_begin[lane] = end - c;
+    if (lane == mp.n_holders - 1) part_begin[mp.n_holders] = end;
   }
+  __syncthreads();
+  const int n_parts = part_begin[mp.n_holders];
   float acc0 = 0.f, acc1 = 0.f, den = 0.f, lmax = -INFINITY;
   // (more than MTHREADS parts: several passes, each merged into the running result)
   for (int base = 0; base < n_parts; base += MTHREADS) {
@@ -964,17 +955,12 @@ __global__ __launch_bounds__(MW * 64) void decode_flat_merge_kernel(const FlatMe
     float my_lse = -INFINITY;
     int my_src = 0;     // row of the partials
     if (t < n_parts) {
-      int k = 0, j = t, lo = one_lo, mains = one_mains;
-      if constexpr (!ONE) {
-        int hi = mp.n_holders;   // the holder with part_begin[k] <= t < part_begin[k + 1]
-        while (hi - k > 1) {
-          const int mid = (k + hi) >> 1;
-          if (part_begin[mid] <= t) k = mid; else hi = mid;
-        }
-        j = t - part_begin[k];
-        lo = holder_lo[k];
-        mains = holder_mains[k];
+      int k = 0, hi = mp.n_holders;   // the holder with part_begin[k] <= t < part_begin[k + 1]
+      while (hi - k > 1) {
+        const int mid = (k + hi) >> 1;
+        if (part_begin[mid] <= t) k = mid; else hi = mid;
       }
+      const int j = t - part_begin[k], lo = holder_lo[k], mains = holder_mains[k];
       const int slot = j < mains ? lo + j : mp.n_main + (k * mp.batch + s) * FW + (j - mains);
       my_src = slot * mp.n_q_heads + h;
       my_lse = mp.part_lse[my_src];
@@ -1008,7 +994,7 @@ __global__ __launch_bounds__(MW * 64) void decode_flat_merge_kernel(const FlatMe
         float wj[FM_U];
         floatx2_t x[FM_U];
         // (weights and sources are read whatever the index: a branch around one puts its load
-        // behind the others'. One sequence of 131072 keys, 512 parts a row: 24.7 -> 18.0 us)
+        // behind the others')
         int src[FM_U];
 #pragma unroll
         for (int u = 0; u < FM_U; ++u) {
@@ -1049,6 +1035,102 @@ __global__ __launch_bounds__(MW * 64) void decode_flat_merge_kernel(const FlatMe
   if (lse_out != nullptr && tid == 0) lse_out[row] = den > 0.f ? lmax + __logf(den) : -INFINITY;
 }
 
+// The same over the partials of one call (one holder, whose slots need no table). A workgroup of OW
+// wavefronts takes 128 / CS channels of a row: 64 / CS lanes a part, CS parts a load, and every lane has
+// the rows of its share of 64 CS parts in flight before the parts' LSE are known. Bound by the chain
+// {bid, cu_seqlens_kv} -> {LSE, rows}: the boundaries of up to 63 sequences travel with the sequence's
+// number, a wavefront keeps the LSE of all parts itself, and there is one barrier. With few rows their
+// channels go to four workgroups: a row of 128 parts is 64 KB.
+constexpr int OW = 4;
+template <typename TO, int CS>
+__global__ __launch_bounds__(OW * 64) void decode_flat_merge_one_kernel(const FlatMergeParams mp,
+                                                                         TO* __restrict__ out,
+                                                                         float* __restrict__ lse_out) {
+  typedef float floatx2_t __attribute__((ext_vector_type(2)));
+  constexpr int U = 64 / OW;             // rows in flight per lane
+  constexpr int LPR = 64 / CS;           // lanes per row
+  __shared__ __align__(8) float sums[OW][2 * LPR];
+  const int row = blockIdx.x, col = blockIdx.y * 2 * LPR;   // row: query * n_q_heads + head
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int sub = lane / LPR, ch = (lane % LPR) * 2;
+  const int qi = row / mp.n_q_heads, h = row - qi * mp.n_q_heads;
+  int s, a, b;
+  if (mp.batch < 64) {
+    const int cu = mp.cu_kv[0][min(lane, mp.batch)];
+    s = mp.bid[qi];
+    a = __builtin_amdgcn_readlane(cu, s);
+    b = __builtin_amdgcn_readlane(cu, s + 1);
+  } else {
+    s = mp.bid[qi];
+    a = mp.cu_kv[0][s];
+    b = mp.cu_kv[0][s + 1];
+  }
+  const FlatParts fp = flat_parts(a, b, mp.wg_keys, mp.total_kv[0]);
+  const int mains = max(0, fp.g_hi - fp.g_lo + 1);
+  const int n_parts = mains + (fp.tail ? FW : 0);
+  auto part_row = [&](int e) -> int64_t {   // (past the end: the last part, with weight zero)
+    e = min(e, n_parts - 1);
+    const int slot = e < mains ? fp.g_lo + e : mp.n_main + s * FW + (e - mains);
+    return (int64_t)slot * mp.n_q_heads + h;
+  };
+  float acc0 = 0.f, acc1 = 0.f, den = 0.f, lmax = -INFINITY;
+  for (int base = 0; base < n_parts; base += 64 * CS) {
+    float w[CS];   // of the parts base + 64 i + lane
+    floatx2_t x[U];
+#pragma unroll
+    for (int i = 0; i < CS; ++i) w[i] = mp.part_lse[part_row(base + 64 * i + lane)];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (base + u * OW * CS < n_parts)   // uniform
+        x[u] = __builtin_nontemporal_load(
+            (const floatx2_t*)(mp.part_out + part_row(base + (u * OW + wave) * CS + sub) * D + col + ch));
+    float m = lmax;
+#pragma unroll
+    for (int i = 0; i < CS; ++i) {
+      if (base + 64 * i + lane >= n_parts) w[i] = -INFINITY;
+      m = fmaxf(m, w[i]);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+    const float old = lmax == -INFINITY ? 0.f : __expf(lmax - m);
+    acc0 *= old;
+    acc1 *= old;
+    lmax = m;
+    float sum = 0.f;
+#pragma unroll
+    for (int i = 0; i < CS; ++i) {
+      w[i] = m == -INFINITY ? 0.f : __expf(w[i] - m);   // exp(-inf) = 0: an empty part
+      sum += w[i];
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+    den = fmaf(den, old, sum);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (base + u * OW * CS < n_parts) {
+        // (a part of weight zero may hold anything)
+        const float f = __shfl(w[u * OW * CS / 64], u * OW * CS % 64 + wave * CS + sub, 64);
+        acc0 = fmaf(f, f != 0.f ? x[u][0] : 0.f, acc0);
+        acc1 = fmaf(f, f != 0.f ? x[u][1] : 0.f, acc1);
+      }
+  }
+#pragma unroll
+  for (int o = LPR; o < 64; o <<= 1) {
+    acc0 += __shfl_xor(acc0, o, 64);
+    acc1 += __shfl_xor(acc1, o, 64);
+  }
+  if (sub == 0) *(floatx2_t*)&sums[wave][ch] = floatx2_t{acc0, acc1};
+  __syncthreads();
+  if (tid < 2 * LPR) {
+    float r = 0.f;
+#pragma unroll
+    for (int w = 0; w < OW; ++w) r += sums[w][tid];
+    out[(int64_t)row * D + col + tid] = from_float<TO>(den > 0.f ? r / den : 0.f);
+  }
+  if (lse_out != nullptr && tid == 0 && col == 0)
+    lse_out[row] = den > 0.f ? lmax + __logf(den) : -INFINITY;
+}
+
 inline size_t round256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Power-of-two split count: about 512 workgroups in total (two per CU, all resident at
@@ -1074,6 +1156,11 @@ bool decode_flat_applies(const cp_shape& s) {
 }
 
 namespace {
+// Up to this many rows their channels go to four workgroups of the merge each. us, in one and in four
+// (and as it was, with the rows asked for behind the LSE): 16 rows of 470 parts 17.1 and 7.0 (17.3), of
+// 128 6.6 and 4.4 (7.3), 128 rows of 60 5.9 and 4.3 (5.9), 64 of 17 4.0 and 3.9 (4.6), 160 of 60 4.1 and
+// 4.0; 256 rows of 5 3.8 and 4.6 (4.3), 768 of 10 4.0 and 8.3 (4.4).
+constexpr int64_t kSplitRows = 160;
 constexpr int kMinRange = FW * UNIT;  // keys of a range: a unit per wavefront at least
 struct FlatPlan {
   int wg_keys, n_main;
@@ -1170,18 +1257,26 @@ int launch_decode_flat(int n_holders, const cp_shape* shapes, float scale, const
     if (rows == 0) continue;
     if (rows > 0x7fffffffLL) return CP_ERR_SHAPE;
     float* const l = lse != nullptr ? lse[a] : nullptr;
-    const dim3 grid((unsigned)rows);
-#define CP_FLAT_MERGE(TO, MW, ONE)                                                            \
-  hipLaunchKernelGGL((decode_flat_merge_kernel<TO, MW, ONE>), grid, dim3(MW * 64), 0, stream, \
-                     mp, (TO*)out[a], l)
-    if (n_holders == 1) {
-      if (out_dtype == CP_FP32) CP_FLAT_MERGE(float, 4, true);
-      else CP_FLAT_MERGE(bf16_t, 4, true);
+    if (n_holders > 1) {
+      if (out_dtype == CP_FP32)
+        hipLaunchKernelGGL(decode_flat_merge_kernel<float>, dim3((unsigned)rows), dim3(MW * 64), 0,
+                           stream, mp, (float*)out[a], l);
+      else
+        hipLaunchKernelGGL(decode_flat_merge_kernel<bf16_t>, dim3((unsigned)rows), dim3(MW * 64), 0,
+                           stream, mp, (bf16_t*)out[a], l);
     } else {
-      if (out_dtype == CP_FP32) CP_FLAT_MERGE(float, 8, false);
-      else CP_FLAT_MERGE(bf16_t, 8, false);
-    }
+#define CP_FLAT_MERGE(TO, CS)                                                                    \
+  hipLaunchKernelGGL((decode_flat_merge_one_kernel<TO, CS>), dim3((unsigned)rows, CS),            \
+                     dim3(OW * 64), 0, stream, mp, (TO*)out[a], l)
+      if (rows <= kSplitRows) {
+        if (out_dtype == CP_FP32) CP_FLAT_MERGE(float, 4);
+        else CP_FLAT_MERGE(bf16_t, 4);
+      } else {
+        if (out_dtype == CP_FP32) CP_FLAT_MERGE(float, 1);
+        else CP_FLAT_MERGE(bf16_t, 1);
+      }
 #undef CP_FLAT_MERGE
+    }
     if (check_launch() != CP_OK) return CP_ERR_LAUNCH;
   }
   return CP_OK;

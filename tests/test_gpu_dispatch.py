@@ -566,6 +566,37 @@ def test_head_dim_64_takes_negative_positions(oracle):
     check(o, l, *oracle.attn(q64, k64, v64, qp, kp))
 
 
+# The merge of a flat decode call: 256 and 257 parts of 64 keys, all 512 ranges, one part; 160 and 176
+# rows (four workgroups a row and one); 63, 64 and 65 sequences (whose boundaries fit a wavefront or not).
+@pytest.mark.parametrize("lengths,nh,nkv", [
+    ([16384], 16, 1), ([16385], 16, 1), ([130001], 3, 1), ([5, 1, 64, 63, 65], 16, 1),
+    ([700, 3000, 20, 64, 128, 900, 1, 333, 2000, 77], 16, 1),
+    ([700, 3000, 20, 64, 128, 900, 1, 333, 2000, 77, 5000], 16, 1),
+    ([9000, 8000], 8, 4), (list(range(1, 64)), 2, 1), (list(range(64, 0, -1)), 2, 1),
+    (list(range(3, 68)), 2, 2),
+])
+def test_flat_decode_merge_counts_every_key(lengths, nh, nkv):
+    batch, cu = len(lengths), np.concatenate([[0], np.cumsum(lengths)])
+    q, _ = randn(61, (batch, nh, 128))
+    k = torch.zeros((int(cu[-1]), nkv, 128), dtype=torch.bfloat16, device="cuda")
+    v = torch.zeros_like(k)
+    pos = np.concatenate([np.arange(n) for n in lengths])
+    cls = (pos // 16 + pos) % 128
+    v[torch.arange(len(pos)), :, torch.as_tensor(cls)] = 1.0
+    bid = np.random.default_rng(batch).permutation(batch)
+    q_pos = np.array([lengths[b] - 1 - (b % 3 == 2) * (lengths[b] // 2) for b in bid])
+    for dtype in (torch.float32, torch.bfloat16):
+        o, l = B.cp_attn_decode(dev(q), k, v, i32(q_pos), i32(pos), i32(cu), i32(bid),
+                                out_dtype=dtype, unique_bid=True)
+        torch.cuda.synchronize()
+        if dtype == torch.bfloat16:   # (rounded once)
+            assert torch.equal(o, whole.to(torch.bfloat16))
+            continue
+        whole = o
+        for i, b in enumerate(bid):
+            check_counts(o[i:i + 1], l[i:i + 1], q_pos[i:i + 1], cls[cu[b]:cu[b + 1]], 128)
+
+
 # The flat decode kernel holds a probability to 16 bits (two bf16 terms) or better: each errs by up
 # to 2^-17 of itself, independently, and the fp32 sums by 2^-24 sqrt(keys); with one term it would be
 # 2^-9. (Error of a whole result, of which the probabilities' is the root mean square: below 2^-17.)
