@@ -182,7 +182,7 @@ int cp_attn_partial(const cp_shape* shape, const void* q, const void* k, const v
       if (rc != CP_OK) return rc;
     }
     return launch_attn_mfma(as, t, ao, q_lo, (char*)workspace + enc,
-                            workspace_bytes - enc, nullptr, st);
+                            workspace_bytes - enc, nullptr, nullptr, st);
   }
   if (s.dtype == CP_FP32 && cu_seqlens_q == nullptr) return launch_attn_fp32(as, t, ao, st);
   return launch_partial_generic(s, scale, q, k, v, q_pos, kv_pos, cu_seqlens_q, cu_seqlens_kv,
@@ -628,6 +628,12 @@ int ring_one_launch(const cp_ring_desc* d, hipStream_t st) {
                                           : (int64_t)slots.lse_slot_elems;
   const AttnOut o = {d->keep_partials ? d->part_dtype : d->out_dtype,
                      slot_step * (int64_t)slots.out_stride, slot_step * slot_lse};
+  OverShards over = {};
+  over.dtype = d->out_dtype;
+  for (int a = 0; a < n; ++a) {
+    over.out[a] = d->out[a];
+    over.lse[a] = d->lse != nullptr ? d->lse[a] : nullptr;
+  }
   int rc;
   if (d->dtype == CP_FP32) {
     rc = launch_attn_fp32(s, t, o, st);
@@ -649,9 +655,9 @@ int ring_one_launch(const cp_ring_desc* d, hipStream_t st) {
       return launch_attn_mfma_ring(s, t, d->arrived, d->ring_error, d->spin_limit, d->out_dtype,
                                    ws, left, st);
     }
-    rc = launch_attn_mfma(s, t, o, q_lo, ws, left, nullptr, st);
+    rc = launch_attn_mfma(s, t, o, q_lo, ws, left, nullptr, d->keep_partials ? &over : nullptr, st);
   }
-  if (rc != CP_OK || !d->keep_partials) return rc;
+  if (rc != CP_OK || !d->keep_partials || over.done) return rc;
   MergeTable m = {};
   m.n_ranks = n; m.n_parts = n; m.n_groups = 1;
   m.part_bytes = o.shard_out_bytes;
@@ -720,7 +726,7 @@ int step_call(const cp_ring_desc* d, const RingSteps& w, const cp_shape& s, int 
   if (acc != nullptr)
     return launch_attn_mfma_accumulate(as, t, *acc, w.call_ws, w.call_ws_bytes, bounds, st);
   return launch_attn_mfma(as, t, AttnOut{dtype, 0, 0}, nullptr, w.call_ws, w.call_ws_bytes, bounds,
-                          st);
+                          nullptr, st);
 }
 
 // fused_merge of a rank of such a ring, which has one slot for its partials: step 0 writes a

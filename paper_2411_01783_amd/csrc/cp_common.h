@@ -99,6 +99,14 @@ struct AttnOut {
   int64_t shard_out_bytes;
   int64_t shard_lse_elems;
 };
+// Equation 4 over the shards' results (per_shard), rank by rank: where it goes. A launch whose own
+// merge can do it along the way does, and says so in `done`.
+struct OverShards {
+  int32_t dtype;
+  void* out[kMaxTable];
+  float* lse[kMaxTable];   // entries may be NULL
+  bool done;
+};
 
 // bf16 MFMA kernel, head_dim 128 and 64, groups of at most 64 heads.
 // `q_lo`: packed batches (head_dim 128), smallest visible key position per token, all ranks back
@@ -110,7 +118,7 @@ size_t attn_mfma_workspace_bytes(const AttnShape& s);
 bool attn_mfma_has_partials(const AttnShape& s);   // writes to the workspace besides the bounds
 int launch_attn_mfma(const AttnShape& s, const AttnTable& t, const AttnOut& o,
                      const int32_t* q_lo, void* workspace, size_t workspace_bytes,
-                     const void* bounds, hipStream_t stream);
+                     const void* bounds, OverShards* over, hipStream_t stream);   // over: or NULL
 
 // Position bounds of n_shards shards for the calls that each take one of them, in at most two
 // launches. offset[b]: where those of shard b begin in the region of kv_bounds_ring_bytes.
@@ -199,6 +207,10 @@ struct MergeTable {
 };
 int launch_merge_table(const MergeTable& m, int32_t head_dim, int32_t part_dtype,
                        int32_t out_dtype, hipStream_t stream);
+// The same over fp32 partials, and Equation 4 over the groups in the same launch.
+bool merge_over_groups_applies(const MergeTable& m);
+int launch_merge_over_groups(const MergeTable& m, int32_t head_dim, int32_t out_dtype,
+                             const OverShards& over, hipStream_t stream);
 
 inline int check_launch() {
   return hipGetLastError() == hipSuccess ? CP_OK : CP_ERR_LAUNCH;

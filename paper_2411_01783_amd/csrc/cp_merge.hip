@@ -200,6 +200,88 @@ __global__ __launch_bounds__(256) void merge_table_kernel(const MergeTable m, in
         den > 0.f ? lmax + __logf(den) : -INFINITY;
 }
 
+// fp32 partials of several groups (KV shards whose results are kept apart): the parts of every group
+// merged into the group's result, as merge_table_kernel does it, and Equation 4 over the groups along
+// the way. In two launches the groups' results are read again, and the second one starts behind the
+// first: 2048 rows of 16 groups of 2 parts 11.5 + 6.4 us, here 13.6 (traced). A thread has the 16 vectors of
+// 16 / NP groups in flight at once.
+struct GroupsOut {
+  void* out[kMaxTable];
+  float* lse[kMaxTable];
+};
+template <typename TS, typename TO, int NP>
+__global__ __launch_bounds__(256) void merge_over_groups_kernel(const MergeTable m, const GroupsOut f,
+                                                                int row_shift) {
+  constexpr int VEC = 4, GB = 16 / NP;
+  const int touched = touch_arguments<MergeTable>();
+  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t row = idx >> row_shift;                          // head_dim / VEC threads per row
+  const int col = ((int)idx & ((1 << row_shift) - 1)) * VEC;
+  const int head_dim = VEC << row_shift;
+  asm volatile("" ::"v"(touched));
+  if (row >= m.rows) return;
+  int a = 0;
+#pragma unroll 8
+  for (int i = 1; i < m.n_ranks; ++i) a += row >= m.row_begin[i];
+  const int64_t r = row - m.row_begin[a];
+  const float* const lse0 = m.part_lse[a] + r;
+  const char* const src0 = (const char*)m.part[a] + (r * head_dim + col) * (int64_t)sizeof(float);
+  char* const slot0 = (char*)m.out[a];
+  float* const slot_lse = m.lse[a];
+  float total[VEC] = {0.f, 0.f, 0.f, 0.f}, total_den = 0.f, total_max = -INFINITY;
+  for (int g0 = 0; g0 < m.n_groups; g0 += GB) {
+    float lv[GB][NP], x[GB][NP][VEC];
+#pragma unroll
+    for (int g = 0; g < GB; ++g)
+#pragma unroll
+      for (int s = 0; s < NP; ++s) {   // (clamped: past the end the last one, dropped below)
+        const int64_t k = (int64_t)min(g0 + g, m.n_groups - 1) * m.n_parts + min(s, m.n_parts - 1);
+        lv[g][s] = lse0[k * m.part_lse_elems];
+        load_vec<float, VEC>((const float*)(src0 + k * m.part_bytes), x[g][s]);
+      }
+    __builtin_amdgcn_sched_barrier(0);  // keep the requests together, ahead of the arithmetic
+#pragma unroll
+    for (int g = 0; g < GB; ++g) {
+      if (g0 + g >= m.n_groups) break;   // uniform
+      float lmax = -INFINITY;
+#pragma unroll
+      for (int s = 0; s < NP; ++s) {
+        if (s >= m.n_parts) lv[g][s] = -INFINITY;
+        lmax = fmaxf(lmax, lv[g][s]);
+      }
+      const bool any = lmax != -INFINITY;
+      float acc[VEC] = {0.f, 0.f, 0.f, 0.f}, den = 0.f;
+#pragma unroll
+      for (int s = 0; s < NP; ++s) {
+        const float w = any ? __expf(lv[g][s] - lmax) : 0.f;  // exp(-inf) = 0
+        den += w;
+#pragma unroll
+        for (int c = 0; c < VEC; ++c) acc[c] = fmaf(w, x[g][s][c], acc[c]);
+      }
+      const float inv = den > 0.f ? 1.f / den : 0.f;
+#pragma unroll
+      for (int c = 0; c < VEC; ++c) acc[c] *= inv;
+      const float lse = den > 0.f ? lmax + __logf(den) : -INFINITY;
+      store_vec<TS, VEC>((TS*)(slot0 + (int64_t)(g0 + g) * m.group_out_bytes) + r * head_dim + col, acc);
+      if (slot_lse != nullptr && col == 0) slot_lse[(int64_t)(g0 + g) * m.group_lse_elems + r] = lse;
+      // the group into the row's running result
+      const float top = fmaxf(total_max, lse);
+      const float old = top == -INFINITY ? 0.f : __expf(total_max - top);
+      const float w = top == -INFINITY ? 0.f : __expf(lse - top);
+      total_den = fmaf(total_den, old, w);
+#pragma unroll
+      for (int c = 0; c < VEC; ++c) total[c] = fmaf(total[c], old, w * acc[c]);
+      total_max = top;
+    }
+  }
+  const float inv = total_den > 0.f ? 1.f / total_den : 0.f;
+#pragma unroll
+  for (int c = 0; c < VEC; ++c) total[c] *= inv;
+  store_vec<TO, VEC>((TO*)f.out[a] + r * head_dim + col, total);
+  if (f.lse[a] != nullptr && col == 0)
+    f.lse[a][r] = total_den > 0.f ? total_max + __logf(total_den) : -INFINITY;
+}
+
 template <typename TP, typename TO, int VEC>
 int launch_np(const MergePtrs& ptrs, int n_parts, int64_t rows, int head_dim, void* out,
               float* lse_out, hipStream_t stream) {
@@ -272,6 +354,10 @@ int launch_table_t(const MergeTable& m, int32_t head_dim, hipStream_t stream) {
 }  // namespace
 
 constexpr int64_t kStreamRows = 4096;
+// A thread walks the groups: beyond 64 vectors that takes longer than the second launch (512 rows of 16
+// groups of 8 parts 13.4 us in two launches, 14.8 in one; 1024 rows of 16 of 4 14.0 and 12.0, 512 of 4 of
+// 16 10.0 and 7.9).
+constexpr int kMaxGroupParts = 64;
 
 int launch_merge_table(const MergeTable& m, int32_t head_dim, int32_t part_dtype,
                        int32_t out_dtype, hipStream_t stream) {
@@ -297,6 +383,50 @@ int launch_merge_table(const MergeTable& m, int32_t head_dim, int32_t part_dtype
                                 : launch_table_t<float, bf16_t, 4>(m, head_dim, stream);
   return out_dtype == CP_FP32 ? launch_table_t<bf16_t, float, 8>(m, head_dim, stream)
                               : launch_table_t<bf16_t, bf16_t, 8>(m, head_dim, stream);
+}
+
+bool merge_over_groups_applies(const MergeTable& m) {
+  return m.n_groups > 1 && m.n_parts > 1 && m.n_parts <= 16 && m.n_groups * m.n_parts <= kMaxGroupParts;
+}
+
+namespace {
+
+template <typename TS, typename TO>
+int launch_over_groups_t(const MergeTable& m, int32_t head_dim, const GroupsOut& f,
+                         hipStream_t stream) {
+  const int per_row = head_dim / 4;   // 64 or 128 channels: a power of two
+  if (per_row < 1 || (per_row & (per_row - 1)) != 0 || head_dim % 4 != 0) return CP_ERR_UNSUPPORTED;
+  const int64_t n_vec = m.rows * per_row;
+  if (n_vec == 0) return CP_OK;
+  // one wavefront per workgroup while that is what spreads the rows over the 256 CUs
+  const int threads = n_vec < 256 * 4 * 256 ? 64 : 256;
+  const int64_t blocks = (n_vec + threads - 1) / threads;
+  if (blocks > 0x7fffffffLL) return CP_ERR_SHAPE;
+#define CP_MERGE_GROUPS(NP)                                                                    \
+  hipLaunchKernelGGL((merge_over_groups_kernel<TS, TO, NP>), dim3((unsigned)blocks),            \
+                     dim3(threads), 0, stream, m, f, __builtin_ctz((unsigned)per_row))
+  if (m.n_parts <= 2) CP_MERGE_GROUPS(2);
+  else if (m.n_parts <= 4) CP_MERGE_GROUPS(4);
+  else if (m.n_parts <= 8) CP_MERGE_GROUPS(8);
+  else CP_MERGE_GROUPS(16);
+#undef CP_MERGE_GROUPS
+  return check_launch();
+}
+
+}  // namespace
+
+int launch_merge_over_groups(const MergeTable& m, int32_t head_dim, int32_t out_dtype,
+                             const OverShards& over, hipStream_t stream) {
+  GroupsOut f = {};
+  for (int a = 0; a < m.n_ranks; ++a) {
+    f.out[a] = over.out[a];
+    f.lse[a] = over.lse[a];
+  }
+  if (out_dtype == CP_FP32)
+    return over.dtype == CP_FP32 ? launch_over_groups_t<float, float>(m, head_dim, f, stream)
+                                 : launch_over_groups_t<float, bf16_t>(m, head_dim, f, stream);
+  return over.dtype == CP_FP32 ? launch_over_groups_t<bf16_t, float>(m, head_dim, f, stream)
+                               : launch_over_groups_t<bf16_t, bf16_t>(m, head_dim, f, stream);
 }
 
 }  // namespace cp

@@ -418,7 +418,7 @@ int launch_kv_bounds_ring(int n_shards, const int32_t* const* kv_pos, const int6
 
 int launch_attn_mfma(const AttnShape& s, const AttnTable& t, const AttnOut& o,
                      const int32_t* q_lo, void* workspace, size_t workspace_bytes,
-                     const void* bounds, hipStream_t stream) {
+                     const void* bounds, OverShards* over, hipStream_t stream) {
   const Plan pl = make_plan(s);
   if (workspace_bytes < pl.total()) return CP_ERR_WORKSPACE;
   if (pl.n_row_blocks == 0) return CP_OK;
@@ -488,6 +488,10 @@ int launch_attn_mfma(const AttnShape& s, const AttnTable& t, const AttnOut& o,
     m.lse[a] = t.lse[a];
   }
   m.rows = m.row_begin[t.n_ranks] = p.rows_all_heads;
+  if (over != nullptr && merge_over_groups_applies(m)) {
+    over->done = true;
+    return launch_merge_over_groups(m, s.head_dim, o.dtype, *over, stream);
+  }
   return launch_merge_table(m, s.head_dim, CP_FP32, o.dtype, stream);
 }
 
