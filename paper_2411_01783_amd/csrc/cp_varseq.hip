@@ -103,25 +103,50 @@ __global__ __launch_bounds__(1024) void seq_encode_all_kernel(const SeqTable t,
                                                                int32_t* __restrict__ q_lo,
                                                                int32_t* __restrict__ kv_enc) {
   __shared__ int32_t top[kBatchHere];   // largest position, then base
+  const int touched = touch_arguments<SeqTable>();
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   if (tid < kBatchHere) top[tid] = -1;
   const int n_lists = t.n_shards + t.n_ranks, n_pieces = n_lists * t.batch;
   const int i = blockIdx.x * 1024 + tid;
   // this thread's own tokens, asked for before anything is waited for
-  int qa = 0, ka = 0, ql = 0, kl = 0;
+  int ql = 0, kl = 0;
   int32_t qx = 0, kx = 0;
   const bool has_q = i < t.tok_begin[t.n_ranks], has_k = i < t.key_begin[t.n_shards];
+  // (scalar loads and selects: looked up by lane, the list's arguments are another latency. Five prompts
+  // of 100 to 900 tokens over 2 ranks 6.2 -> 5.3 us.)
+  const int32_t *q_cu = t.cu_q[0], *k_cu = t.cu_kv[0];
   if (has_q) {
-    for (int r = 1; r < t.n_ranks; ++r) qa += i >= t.tok_begin[r];
-    ql = i - t.tok_begin[qa];
-    qx = t.q_pos[qa][ql];
+    const int32_t* pos = t.q_pos[0];
+    int begin = 0;
+#pragma unroll 4
+    for (int r = 1; r < t.n_ranks; ++r) {
+      const int x = t.tok_begin[r];
+      const int32_t *const y = t.q_pos[r], *const c = t.cu_q[r];
+      const bool in = i >= x;
+      begin = in ? x : begin;
+      pos = in ? y : pos;
+      q_cu = in ? c : q_cu;
+    }
+    ql = i - begin;
+    qx = pos[ql];
   }
   if (has_k) {
-    for (int r = 1; r < t.n_shards; ++r) ka += i >= t.key_begin[r];
-    kl = i - t.key_begin[ka];
-    kx = t.kv_pos[ka][kl];
+    const int32_t* pos = t.kv_pos[0];
+    int begin = 0;
+#pragma unroll 4
+    for (int r = 1; r < t.n_shards; ++r) {
+      const int x = t.key_begin[r];
+      const int32_t *const y = t.kv_pos[r], *const c = t.cu_kv[r];
+      const bool in = i >= x;
+      begin = in ? x : begin;
+      pos = in ? y : pos;
+      k_cu = in ? c : k_cu;
+    }
+    kl = i - begin;
+    kx = pos[kl];
   }
+  asm volatile("" ::"v"(touched));
   __syncthreads();
   const int mine = wave + lane * 16;
   int lo = 0, hi = 0, list = 0, seq = 0;
@@ -164,8 +189,8 @@ __global__ __launch_bounds__(1024) void seq_encode_all_kernel(const SeqTable t,
     top[lane] = (int32_t)min<int64_t>(sum - span, INT32_MAX - 1);
   }
   __syncthreads();
-  if (has_q) encode_q(qx, top[seq_of(t.cu_q[qa], t.batch, ql)], q_hi + i, q_lo + i);
-  if (has_k) kv_enc[i] = encode_kv(kx, top[seq_of(t.cu_kv[ka], t.batch, kl)]);
+  if (has_q) encode_q(qx, top[seq_of(q_cu, t.batch, ql)], q_hi + i, q_lo + i);
+  if (has_k) kv_enc[i] = encode_kv(kx, top[seq_of(k_cu, t.batch, kl)]);
 }
 
 // SCAN: `base` is span, and every workgroup forms the prefix sums in LDS.
