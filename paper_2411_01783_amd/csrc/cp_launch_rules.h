@@ -111,11 +111,13 @@ CP_RULE bool encode_in_one_launch(int64_t batch, int64_t lists, int64_t tokens) 
 // chunk (j even) or late chunk (j odd). A block with rows of two chunks is
 //   ends_in: the chunk's that ends in it
 //   late_first: the late chunk's, on either side of it, since its longest walk is a late row's
-// fp32: taken for early, such a block was dispatched last and the call waited for it alone: 1320 tokens
-// of 4 heads over 4 ranks 38.6 us, 25.4 with it in its place; 3600 157 and 96. The bf16 kernel has
-// ends_in: 20000 tokens of 16 heads over 4 ranks would gain 18 %, but 33333 over 8 lose 4 %. The
-// boundaries are those of equal shards; shards of other sizes only lose some of the order. (B < 2^26:
-// that many row blocks of 16 rows do not fit the memory; N <= 32.)
+// Taken for early, such a block was dispatched last and the call waited for it alone. fp32: 1320 tokens
+// of 4 heads over 4 ranks 38.6 us, 25.4 with it in its place; 3600 157 and 96. bf16: 20000 tokens of 16
+// heads over 4 ranks 1699 and 1406, 33333 of 8 over 4 2542 and 1912, 33333 of 16 over 8 4103 and 3794,
+// 65000 of 8 at head_dim 64 over 8 10264 and 7967; 47777 of 16 over 2 7616 and 7627. The walk behind
+// flags, whose row blocks do not straddle ranks, has ends_in: 33333 of 16 over 2 4008 and 3999, 77777
+// over 16 21602 and 22070. The boundaries are those of equal shards; shards of other sizes only lose
+// some of the order. (B < 2^26: that many row blocks of 16 rows do not fit the memory; N <= 32.)
 struct ChunkRule {
   uint32_t odd_blocks, up;
 };

@@ -857,8 +857,7 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
     }
     const int i = x / p.n_kv_heads;
     kvh = x - i * p.n_kv_heads;
-    row_block = ordered_row_block(i, p.n_row_blocks, p.n_ranks, threadIdx.x & 63,
-                                  ends_in(p.n_row_blocks));
+    row_block = ordered_row_block(i, p.n_row_blocks, p.n_ranks, threadIdx.x & 63, p.chunks);
     z_shard = p.per_shard ? z / p.n_sub : 0;
     z_sub = z - z_shard * p.n_sub;
     if constexpr (MODE == RING) {   // row blocks do not straddle ranks here

@@ -177,6 +177,24 @@ def test_kept_shards_cut_into_parts_count_every_key(kv_sizes, q_sizes, nh, nkv, 
             assert torch.equal(kept[torch.float32][0][a], kept[torch.bfloat16][0][a])
 
 
+# A workgroup per row block over several ranks, the late chunks first: row blocks with rows of two
+# chunks, of two ranks, a last one that is short; shards of one length and of others.
+@pytest.mark.parametrize("kv_sizes,q_sizes,nh,nkv,d", [
+    ([10400, 10401, 10000], [1501, 1500, 1499], 16, 1, 128), ([8000] * 4, [1111] * 4, 16, 1, 64),
+    ([30000, 900], [700, 1401], 32, 2, 128), ([2000] * 16, [270] * 16, 16, 1, 128),
+])
+def test_rings_of_whole_row_blocks_count_every_key(kv_sizes, q_sizes, nh, nkv, d):
+    total, t = sum(kv_sizes), sum(q_sizes)
+    q_pos = np.sort(np.random.default_rng(total + t).integers(-1, total, size=t))
+    args, cls = counts_case(kv_sizes, q_sizes, nh, nkv, d, q_pos)
+    ring = B.Ring(*args, out_dtype=torch.float32)
+    for o in ring.out:
+        o.fill_(float("nan"))
+    out, lse = B.cp_ring_passkv(ring)
+    torch.cuda.synchronize()
+    check_counts(torch.cat(out), torch.cat(lse), q_pos, cls, d)
+
+
 # The last tile of a list ends after two blocks where no more than two have keys: one to five blocks,
 # cut lists (parts, equal shares) that end either way, a second chunk of one and of three blocks, and a
 # packed batch.
