@@ -449,7 +449,7 @@ def bench_partial_prefill(names, reps: int = 5, cpu: bool = False):
         kv_bytes_rank = sum(int(t.numel()) * 2 * 2 for t in ring.tensors[1]) / n
         io_bytes_rank = t_new * w.n_q_heads * w.head_dim * 2 + \
             (t_new // n) * w.n_q_heads * (w.head_dim * 2 + 4)
-        kern = "prefill_mfma_kernel (all holders in one launch) + merge_table_kernel"
+        kern = "prefill_mfma_kernel (all holders in one launch) + the merge of parts and holders"
         if t_new * 16 / n < 315:
             row["roofline"] = roofline_block("hbm", kern, kv_bytes_rank + io_bytes_rank,
                                              sec * 1e6 / n)
