@@ -310,7 +310,9 @@ typedef struct {
    * keep_partials in the pass-Q drivers, the N messages that rank s receives, from holders
    * k = 0..N-1 in order, are slots s * n_ranks + k, one contiguous range, and each is
    * written in place by the attention kernel and read in place by the merge: no pack,
-   * permute or unpack pass.
+   * permute or unpack pass. (Where shards are cut into parts, the launch that merges the parts
+   * writes the messages, and the result, bit by bit that of merging the messages, may come from
+   * the same launch.)
    */
   int32_t message_layout;
   /*

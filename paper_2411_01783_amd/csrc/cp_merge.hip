@@ -202,9 +202,17 @@ __global__ __launch_bounds__(256) void merge_table_kernel(const MergeTable m, in
 
 // fp32 partials of several groups (KV shards whose results are kept apart): the parts of every group
 // merged into the group's result, as merge_table_kernel does it, and Equation 4 over the groups along
-// the way. In two launches the groups' results are read again, and the second one starts behind the
-// first: 2048 rows of 16 groups of 2 parts 11.5 + 6.4 us, here 13.6 (traced). A thread has the 16 vectors of
-// 16 / NP groups in flight at once.
+// the way, over what is stored: a bf16 slot's values are rounded first, and every bit is that of two
+// launches. In those the groups' results are read again, and the second one starts behind the first.
+// Bound by its chain of arguments, LSE and vectors. A thread has the 16 vectors of 16 / NP groups in
+// flight at once. The LSE of all parts of a row are asked for ahead of them, by all threads of the row
+// together, which keep them in LDS; then they work out a group's weight or two each. us (traced), two
+// launches and one: 2048 rows of 16 groups of 2 parts 11.0 + 6.0 and 12.2, 1024 rows of 16 of 4 9.3 +
+// 4.8 and 11.6, of 8 of 8 8.3 + 4.3 and 9.2, of 4 of 16 7.9 + 4.7 and 8.6.
+// Up to 64 parts, for which the row's LSE have room (whole calls, us: 1008 rows of 7 groups of 9 46.7
+// and 42.5, of 9 of 7 45.7 and 41.4). A thread walks the groups: with more of them it loses to the
+// second launch sooner or later (512 rows of 16 of 8 13.4 and 14.8, in a form without LDS).
+constexpr int kMaxGroupParts = 64;
 struct GroupsOut {
   void* out[kMaxTable];
   float* lse[kMaxTable];
@@ -213,13 +221,17 @@ template <typename TS, typename TO, int NP>
 __global__ __launch_bounds__(256) void merge_over_groups_kernel(const MergeTable m, const GroupsOut f,
                                                                 int row_shift) {
   constexpr int VEC = 4, GB = 16 / NP;
+  constexpr int MIN_ROW = 16;                         // threads per row at least (64 channels)
+  constexpr int OWN = kMaxTable / MIN_ROW;            // groups a thread looks up at most
+  constexpr int OWN_PARTS = kMaxGroupParts / MIN_ROW; // and parts
+  __shared__ float lse_of[256 / MIN_ROW][kMaxGroupParts];
   const int touched = touch_arguments<MergeTable>();
   const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t row = idx >> row_shift;                          // head_dim / VEC threads per row
-  const int col = ((int)idx & ((1 << row_shift) - 1)) * VEC;
-  const int head_dim = VEC << row_shift;
+  const int per_row = 1 << row_shift, own = (int)threadIdx.x & (per_row - 1);
+  const int col = own * VEC, head_dim = VEC << row_shift;
   asm volatile("" ::"v"(touched));
-  if (row >= m.rows) return;
+  if (row >= m.rows) return;   // (all threads of a row: blocks hold whole rows)
   int a = 0;
 #pragma unroll 8
   for (int i = 1; i < m.n_ranks; ++i) a += row >= m.row_begin[i];
@@ -228,50 +240,84 @@ __global__ __launch_bounds__(256) void merge_over_groups_kernel(const MergeTable
   const char* const src0 = (const char*)m.part[a] + (r * head_dim + col) * (int64_t)sizeof(float);
   char* const slot0 = (char*)m.out[a];
   float* const slot_lse = m.lse[a];
+  const int n_all = m.n_groups * m.n_parts;
+  float* const lse_row = lse_of[threadIdx.x >> row_shift];   // (this wavefront's own)
+  float own_lse[OWN_PARTS];
+#pragma unroll
+  for (int k = 0; k < OWN_PARTS; ++k)
+    own_lse[k] = lse0[min(own + k * per_row, n_all - 1) * m.part_lse_elems];
+  // Weights of a group's parts from their LSE, and the sum of the weights; returns the group's LSE.
+  auto weights = [&](int g, float (&w)[NP], float& den) {
+    float lmax = -INFINITY;
+#pragma unroll
+    for (int s = 0; s < NP; ++s) {
+      const float x = lse_row[g * m.n_parts + min(s, m.n_parts - 1)];
+      w[s] = s < m.n_parts ? x : -INFINITY;
+      lmax = fmaxf(lmax, w[s]);
+    }
+    const bool any = lmax != -INFINITY;
+    den = 0.f;
+#pragma unroll
+    for (int s = 0; s < NP; ++s) {
+      w[s] = any ? __expf(w[s] - lmax) : 0.f;  // exp(-inf) = 0
+      den += w[s];
+    }
+    return den > 0.f ? lmax + __logf(den) : -INFINITY;
+  };
+  float group_w[OWN] = {};   // of the groups `own` and `own` + per_row
   float total[VEC] = {0.f, 0.f, 0.f, 0.f}, total_den = 0.f, total_max = -INFINITY;
   for (int g0 = 0; g0 < m.n_groups; g0 += GB) {
-    float lv[GB][NP], x[GB][NP][VEC];
+    float x[GB][NP][VEC];
 #pragma unroll
     for (int g = 0; g < GB; ++g)
 #pragma unroll
       for (int s = 0; s < NP; ++s) {   // (clamped: past the end the last one, dropped below)
         const int64_t k = (int64_t)min(g0 + g, m.n_groups - 1) * m.n_parts + min(s, m.n_parts - 1);
-        lv[g][s] = lse0[k * m.part_lse_elems];
         load_vec<float, VEC>((const float*)(src0 + k * m.part_bytes), x[g][s]);
       }
     __builtin_amdgcn_sched_barrier(0);  // keep the requests together, ahead of the arithmetic
+    if (g0 == 0) {
+#pragma unroll
+      for (int k = 0; k < OWN_PARTS; ++k)
+        if (own + k * per_row < n_all) lse_row[own + k * per_row] = own_lse[k];
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+#pragma unroll
+      for (int k = 0; k < OWN; ++k) {
+        const int g = own + k * per_row;
+        group_w[k] = -INFINITY;
+        if (g >= m.n_groups) continue;
+        float w[NP], den;
+        group_w[k] = weights(g, w, den);
+        if (slot_lse != nullptr) slot_lse[(int64_t)g * m.group_lse_elems + r] = group_w[k];
+        total_max = fmaxf(total_max, group_w[k]);
+      }
+      for (int o = per_row >> 1; o > 0; o >>= 1) total_max = fmaxf(total_max, __shfl_xor(total_max, o, 64));
+#pragma unroll
+      for (int k = 0; k < OWN; ++k)
+        group_w[k] = total_max != -INFINITY ? __expf(group_w[k] - total_max) : 0.f;
+    }
 #pragma unroll
     for (int g = 0; g < GB; ++g) {
-      if (g0 + g >= m.n_groups) break;   // uniform
-      float lmax = -INFINITY;
+      const int at = g0 + g;
+      if (at >= m.n_groups) break;   // uniform
+      float part_w[NP], den;
+      weights(at, part_w, den);
+      float acc[VEC] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int s = 0; s < NP; ++s) {
-        if (s >= m.n_parts) lv[g][s] = -INFINITY;
-        lmax = fmaxf(lmax, lv[g][s]);
-      }
-      const bool any = lmax != -INFINITY;
-      float acc[VEC] = {0.f, 0.f, 0.f, 0.f}, den = 0.f;
+      for (int s = 0; s < NP; ++s)
 #pragma unroll
-      for (int s = 0; s < NP; ++s) {
-        const float w = any ? __expf(lv[g][s] - lmax) : 0.f;  // exp(-inf) = 0
-        den += w;
-#pragma unroll
-        for (int c = 0; c < VEC; ++c) acc[c] = fmaf(w, x[g][s][c], acc[c]);
-      }
+        for (int c = 0; c < VEC; ++c) acc[c] = fmaf(part_w[s], x[g][s][c], acc[c]);
       const float inv = den > 0.f ? 1.f / den : 0.f;
+      const float w = __shfl(at < per_row ? group_w[0] : group_w[1], at & (per_row - 1), per_row);
+      total_den += w;
 #pragma unroll
-      for (int c = 0; c < VEC; ++c) acc[c] *= inv;
-      const float lse = den > 0.f ? lmax + __logf(den) : -INFINITY;
-      store_vec<TS, VEC>((TS*)(slot0 + (int64_t)(g0 + g) * m.group_out_bytes) + r * head_dim + col, acc);
-      if (slot_lse != nullptr && col == 0) slot_lse[(int64_t)(g0 + g) * m.group_lse_elems + r] = lse;
-      // the group into the row's running result
-      const float top = fmaxf(total_max, lse);
-      const float old = top == -INFINITY ? 0.f : __expf(total_max - top);
-      const float w = top == -INFINITY ? 0.f : __expf(lse - top);
-      total_den = fmaf(total_den, old, w);
-#pragma unroll
-      for (int c = 0; c < VEC; ++c) total[c] = fmaf(total[c], old, w * acc[c]);
-      total_max = top;
+      for (int c = 0; c < VEC; ++c) {
+        acc[c] = to_float(from_float<TS>(acc[c] * inv));   // (what the slot holds)
+        total[c] = fmaf(w, acc[c], total[c]);
+      }
+      store_vec<TS, VEC>((TS*)(slot0 + (int64_t)at * m.group_out_bytes) + r * head_dim + col, acc);
     }
   }
   const float inv = total_den > 0.f ? 1.f / total_den : 0.f;
@@ -354,10 +400,6 @@ int launch_table_t(const MergeTable& m, int32_t head_dim, hipStream_t stream) {
 }  // namespace
 
 constexpr int64_t kStreamRows = 4096;
-// A thread walks the groups: beyond 64 vectors that takes longer than the second launch (512 rows of 16
-// groups of 8 parts 13.4 us in two launches, 14.8 in one; 1024 rows of 16 of 4 14.0 and 12.0, 512 of 4 of
-// 16 10.0 and 7.9).
-constexpr int kMaxGroupParts = 64;
 
 int launch_merge_table(const MergeTable& m, int32_t head_dim, int32_t part_dtype,
                        int32_t out_dtype, hipStream_t stream) {
@@ -394,8 +436,8 @@ namespace {
 template <typename TS, typename TO>
 int launch_over_groups_t(const MergeTable& m, int32_t head_dim, const GroupsOut& f,
                          hipStream_t stream) {
-  const int per_row = head_dim / 4;   // 64 or 128 channels: a power of two
-  if (per_row < 1 || (per_row & (per_row - 1)) != 0 || head_dim % 4 != 0) return CP_ERR_UNSUPPORTED;
+  if (head_dim != 64 && head_dim != 128) return CP_ERR_UNSUPPORTED;
+  const int per_row = head_dim / 4;
   const int64_t n_vec = m.rows * per_row;
   if (n_vec == 0) return CP_OK;
   // one wavefront per workgroup while that is what spreads the rows over the 256 CUs

@@ -141,15 +141,15 @@ def test_ring_launch_rules_count_every_key(kv_sizes, q_sizes, nh, nkv, d):
 
 # Shards kept apart, cut into parts, with few queries: parts and shards merged in one launch (up to 64
 # parts in all: 14 of each of 3 shards, 16 of 4, 8 of 8, 4 and 2 of 16) and in two (13 of 5, 16 of 8);
-# ranks without queries, shards that not every query sees. With `one`, what is merged are the partials
-# before their rounding.
-@pytest.mark.parametrize("kv_sizes,q_sizes,nh,nkv,d,one", [
-    ([10400, 10401, 10000], [5, 0, 20], 16, 1, 128, True), ([8000] * 4, [9, 9, 9, 9], 16, 1, 64, True),
-    ([4000] * 8, [8] * 8, 16, 4, 128, True), ([2000] * 16, [0, 8] * 8, 16, 1, 128, True),
-    ([2000] * 16, [8] * 16, 16, 1, 64, True), ([6300] * 5, [3] * 5, 16, 1, 128, False),
-    ([4000] * 8, [4] * 8, 16, 1, 128, False),
+# ranks without queries, shards that not every query sees. The result is Equation 4 over what the slots
+# hold, bit by bit, whatever their type and in however many launches.
+@pytest.mark.parametrize("kv_sizes,q_sizes,nh,nkv,d", [
+    ([10400, 10401, 10000], [5, 0, 20], 16, 1, 128), ([8000] * 4, [9, 9, 9, 9], 16, 1, 64),
+    ([4000] * 8, [8] * 8, 16, 4, 128), ([2000] * 16, [0, 8] * 8, 16, 1, 128),
+    ([2000] * 16, [8] * 16, 16, 1, 64), ([6300] * 5, [3] * 5, 16, 1, 128),
+    ([4000] * 8, [4] * 8, 16, 1, 128),
 ])
-def test_kept_shards_cut_into_parts_count_every_key(kv_sizes, q_sizes, nh, nkv, d, one):
+def test_kept_shards_cut_into_parts_count_every_key(kv_sizes, q_sizes, nh, nkv, d):
     total, t = sum(kv_sizes), sum(q_sizes)
     rng = np.random.default_rng(total + t)
     ends = np.concatenate([[0], np.cumsum(kv_sizes)])
@@ -161,20 +161,26 @@ def test_kept_shards_cut_into_parts_count_every_key(kv_sizes, q_sizes, nh, nkv, 
         ring = B.Ring(*args, out_dtype=torch.float32, part_dtype=part, keep_partials=True)
         out, lse = B.cp_ring_passkv(ring)
         torch.cuda.synchronize()
-        kept[part] = ([o.clone() for o in out], [[ring.partial(a, b) for b in range(len(kv_sizes))]
-                                                 for a in range(len(rows))])
+        kept[part] = [[ring.partial(a, b) for b in range(len(kv_sizes))] for a in range(len(rows))]
         if part == torch.float32:
             check_counts(torch.cat(out), torch.cat(lse), q_pos, cls, d)
-            for a, r in enumerate(rows):
+        messages = B.Ring(*args, out_dtype=torch.float32, part_dtype=part, keep_partials=True,
+                          message_layout=True)
+        out_m, lse_m = B.cp_ring_passkv(messages)
+        for a, r in enumerate(rows):
+            if len(r) == 0:
+                continue
+            for ring_, o, l in ((ring, out[a], lse[a]), (messages, out_m[a], lse_m[a])):
+                slots = [ring_.partial(a, b) for b in range(len(kv_sizes))]
+                want_o, want_l = B.cp_attn_merge(*zip(*slots), out_dtype=torch.float32)
+                assert torch.equal(o, want_o) and torch.equal(l, want_l)
+            if part == torch.float32:
                 for b in range(len(kv_sizes)):
-                    if len(r) > 0:
-                        check_counts(*ring.partial(a, b), r, cls, d, ends[b], ends[b + 1])
+                    check_counts(*ring.partial(a, b), r, cls, d, ends[b], ends[b + 1])
     for a in range(len(rows)):
         for b in range(len(kv_sizes)):
-            (o32, l32), (o16, l16) = kept[torch.float32][1][a][b], kept[torch.bfloat16][1][a][b]
+            (o32, l32), (o16, l16) = kept[torch.float32][a][b], kept[torch.bfloat16][a][b]
             assert torch.equal(o32.to(torch.bfloat16), o16) and torch.equal(l32, l16)
-        if one:
-            assert torch.equal(kept[torch.float32][0][a], kept[torch.bfloat16][0][a])
 
 
 # A workgroup per row block over several ranks, the late chunks first: row blocks with rows of two
