@@ -56,6 +56,7 @@ constexpr int MAX_LIVE = NTHREADS;        // blocks looked at (and listed) per c
 constexpr int PLAN_MAX_BLOCKS = 960;      // PLAN: block bounds kept in LDS (30K keys; what fits)
 constexpr int PLAN_MAX_UNITS = 1024;      // PLAN: units per KV head
 constexpr int kPlanWorkgroups = 256;      // one per CU
+constexpr int kUnitCost = 3;              // start-up and epilogue of a unit, in steps (Geo::STEP_BLOCKS)
 constexpr int kCutCost = 12;              // partials of a cut at head_dim 128, in tile steps
 constexpr int kUncutTiles = 6;            // units up to this long are not worth a cut
 constexpr float kRescaleSlack = 8.f;               // log2 units

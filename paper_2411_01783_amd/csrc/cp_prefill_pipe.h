@@ -46,14 +46,15 @@ struct Geo {
   // bf16 terms of a probability. head_dim 64: three, which hold all 24 bits of the fp32 value (the
   // products with V are exact and summed in fp32: nothing is rounded to 16 bits). head_dim 128: one.
   static constexpr int TERMS = D == 64 ? 3 : 1;
-  // PLAN: blocks of a step of the line of units (cuts lie between two steps), and what start-up and
-  // epilogue of a unit cost, in steps. Half tiles and less for a unit at head_dim 64, where 7.5 us lie
-  // between the last tile of one unit and the first of the next, and a tile takes 3.7 (2 tiles: 900
-  // tokens of 16 heads on 2 33.3 us, 2600 of 8 48.3; 1.5: 31.5 and 45.7), and for packed calls (5 prompts
-  // of 700 to 3000 195.8 -> 189.2, 12 of 200 to 600 62.9 -> 59.9). At head_dim 128 otherwise whole tiles:
-  // 3000 tokens of 16 heads 70.4, in half tiles 72.1 to 78.
-  static constexpr int step_blocks(bool packed) { return D == 64 || packed ? 2 : 4; }
-  static constexpr int unit_cost(bool packed) { return D == 64 ? 3 : packed ? 6 : 3; }
+  // Blocks of a step: lists are cut between two of them (SPLIT, PLAN), and the line of units is counted
+  // in them. Head_dim 128: a tile. Results depend on where a list is cut there (a probability is rounded
+  // relative to the first block of its piece), and half tiles gain nothing (us, tiles and halves: 12
+  // packed prompts of 40 to 1200 tokens over 4 ranks 91.9 and 92.3, 2 of 1700 to 2100 66.9 and 63.4, 6 of
+  // 200 to 3000 97.6 and 99.1; 25 packed calls 1.00 of the time on average, 24 of pass-Q, too). Head_dim
+  // 64, where all 24 bits are kept: half a tile. 7.5 us lie between the last tile of one unit and the
+  // first of the next, and a tile takes 3.7 (987 tokens of 8 heads over 2 ranks 36.2 and 30.9, 4096 of 8
+  // on 2 over 4 59.6 and 57.7; 61 calls 0.96 of the time on average, the worst 1.03).
+  static constexpr int STEP_BLOCKS = D == 64 ? 2 : 4;
   static constexpr int CHUNKS = ROW / 16;        // 16-byte chunks of a row
   static constexpr int LOAD_ROWS = 64 / CHUNKS;  // rows one 1 KiB load instruction brings
   static constexpr int PARTS = 16 / LOAD_ROWS;   // load instructions per wavefront for K (or V)
@@ -432,7 +433,7 @@ __device__ __forceinline__ bool ring_enter(const Params& p, int rank, int step, 
 // to 49 tiles: 204 us where the work is 70 us of all compute units). So the launch is 256
 // workgroups (one per CU) that take equal shares of the whole work, cutting row blocks where a
 // share ends. A unit is a row block of one KV head (against one shard, where shards are kept
-// apart); its weight is an estimate of its visible tiles plus unit_cost for start-up and
+// apart); its weight is an estimate of its visible steps plus kUnitCost for start-up and
 // epilogue. Every workgroup works the plan out for itself, from kv_pos and q_pos, in LDS: that
 // costs it 3 to 6 us (10 for packed prompts), less than the launches that would hand it over, and
 // replaces the position-bound pre-pass. (Counting a unit's visible blocks exactly took up to 45 us at 700
@@ -593,8 +594,7 @@ __device__ __forceinline__ Share plan_share(const Params& p, int2* lds_bounds, u
                                             const PlanLds& L, int* index, int* wg_scratch,
                                             int tid) {
   // (in steps of kStep blocks)
-  constexpr int kStep = Geo<D>::step_blocks(BAND), kTile = 4 / kStep;
-  constexpr int kUnitCost = Geo<D>::unit_cost(BAND);
+  constexpr int kStep = Geo<D>::STEP_BLOCKS, kTile = 4 / kStep;
   const int lane = tid & 63, wave = tid >> 6;
   Share sh = {0, 0, 0};
   const int n_rb = p.n_row_blocks, n_units = n_rb * p.n_z;
@@ -1042,7 +1042,7 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
       return b.x <= wg_qmax && (!BAND || b.y >= wg_lomin);
     };
     // The part of the list of visible blocks that is walked here: [part_lo, part_hi). Parts are
-    // whole half tiles of the list.
+    // whole steps of the list.
     int part_lo = 0, part_hi = INT32_MAX;
     bool whole = true, first_piece = true;  // PLAN: the unit is not cut; its first piece
     // (the visible ones of the first chunk, counted here, are listed from the same count below)
@@ -1076,23 +1076,23 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
       total = __builtin_amdgcn_readfirstlane(total) + first_total;
       if constexpr (MODE == SPLIT) {
         if (p.sub_blocks == 0) {
-          // (in 32 bits, which the half tiles of a memory full of keys fit 32 times: a 64-bit division
-          // is 500 cycles of every start)
-          const uint32_t halves = (uint32_t)(total + 1) >> 1;
-          part_lo = 2 * (int)(halves * (uint32_t)z_sub / (uint32_t)p.n_sub);
-          part_hi = 2 * (int)(halves * (uint32_t)(z_sub + 1) / (uint32_t)p.n_sub);
+          // (in 32 bits: a memory full of keys has some 2^24 steps, and CP_MAX_PARTS is 64; a 64-bit
+          // division is 500 cycles of every start)
+          constexpr int kStep = G::STEP_BLOCKS;
+          const uint32_t steps = (uint32_t)(total + kStep - 1) / kStep;
+          part_lo = kStep * (int)(steps * (uint32_t)z_sub / (uint32_t)p.n_sub);
+          part_hi = kStep * (int)(steps * (uint32_t)(z_sub + 1) / (uint32_t)p.n_sub);
         }
       } else if (p.cut_units) {
         const int planned =
             __builtin_amdgcn_readfirstlane((int)weight[z_shard * p.n_row_blocks + row_block]);
-        constexpr int kUnitCost = G::unit_cost(BAND);
         const int end = min(kUnitCost + planned, share.begin + share.length);
         const int lo = max(0, share.begin - kUnitCost), hi = end - kUnitCost;
         share.length -= end - share.begin;
         if (hi <= lo) return;  // the share ends within the unit's start-up
         whole = lo == 0 && hi == planned;
         first_piece = lo == 0;
-        constexpr int kStep = G::step_blocks(BAND);
+        constexpr int kStep = G::STEP_BLOCKS;
         const int steps = (total + kStep - 1) / kStep;   // (pieces can come out empty: they are written as such)
         part_lo = kStep * (int)((uint32_t)(steps * lo) / (uint32_t)planned);
         part_hi = kStep * (int)((uint32_t)(steps * hi) / (uint32_t)planned);

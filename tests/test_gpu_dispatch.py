@@ -183,6 +183,45 @@ def test_kept_shards_cut_into_parts_count_every_key(kv_sizes, q_sizes, nh, nkv, 
             assert torch.equal(o32.to(torch.bfloat16), o16) and torch.equal(l32, l16)
 
 
+# Head_dim 128 holds a probability to one bf16 term relative to the largest score of the first block of
+# its piece, so results depend on where a list is cut, and that is between tiles of four blocks. Here the
+# third block of every tile has keys of weight 3/2, the others of weight 1: relative to 1 both are exact
+# in 8 bits, relative to 3/2 a weight of 2/3 is not (2e-3 off). The score is held in two bf16 terms, to
+# 2^-17, the sums in fp32.
+@pytest.mark.parametrize("kv_sizes,q_sizes,keep,packed", [
+    ([15872], [20], False, 0), ([4096], [70], False, 0), ([9600], [300], False, 0),
+    ([5120] * 8, [10] * 8, True, 0), ([3584] * 16, [16] * 16, True, 0), ([20480] * 3, [40, 0, 9], False, 0),
+    ([1280, 1408], [400, 420], False, 3), ([2176], [900], False, 2), ([640] * 4, [200] * 4, False, 6),
+])
+def test_lists_are_cut_between_tiles(kv_sizes, q_sizes, keep, packed):
+    batch, d, nh = max(1, packed), 128, 16
+    x = np.log(1.5)
+    hi = torch.tensor(x, dtype=torch.bfloat16)
+    lo = torch.tensor(x - float(hi), dtype=torch.bfloat16)
+    n = sum(kv_sizes)
+    third = torch.arange(n, device="cuda") // 32 % 4 == 2
+    k = torch.zeros((n, 1, d), dtype=torch.bfloat16, device="cuda")
+    v = torch.zeros_like(k)
+    k[third, :, 0], k[third, :, 1] = hi.cuda(), lo.cuda()
+    v[~third, :, 0], v[third, :, 1] = 1.0, 1.0
+    q = torch.zeros((sum(q_sizes), nh, d), dtype=torch.bfloat16, device="cuda")
+    q[..., :2] = 1.0
+    pos, q_pos = torch.arange(n, dtype=torch.int32, device="cuda"), i32(np.full(len(q), n))
+    # (packed: `batch` such sequences in every shard)
+    cut = lambda y, m: [torch.cat([z] * batch).contiguous()
+                        for z in torch.tensor_split(y, np.cumsum(m)[:-1].tolist())]
+    cu = lambda m: [i32(np.arange(batch + 1) * z) for z in m] if packed else None
+    ring = B.Ring(cut(q, q_sizes), cut(k, kv_sizes), cut(v, kv_sizes), cut(q_pos, q_sizes),
+                  cut(pos, kv_sizes), out_dtype=torch.float32, keep_partials=keep, softmax_scale=1.0,
+                  cu_seqlens_q=cu(q_sizes), cu_seqlens_kv=cu(kv_sizes))
+    out, lse = B.cp_ring_passkv(ring)
+    torch.cuda.synchronize()
+    ref = torch.zeros(d, device="cuda")
+    ref[0], ref[1] = 2 / 3, 1 / 3
+    assert float((torch.cat(out) - ref).abs().max()) < 1e-5
+    assert float((torch.cat(lse) - np.log(n * 1.125)).abs().max()) < 2e-5
+
+
 # A workgroup per row block over several ranks, the late chunks first: row blocks with rows of two
 # chunks, of two ranks, a last one that is short; shards of one length and of others.
 @pytest.mark.parametrize("kv_sizes,q_sizes,nh,nkv,d", [
