@@ -1357,6 +1357,9 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
           ++next_kvh;
         }
       }
+      // (No tile is on its way, but where the compiler cannot see it, behind a walk that ends early, it
+      // waits for them, and for the rows, at the barrier below.)
+      __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
       if (rows_requested)
         request_rows(next_rb, next_kvh, p.rows, tid_e, next_qp, next_ql, next_qf);
     }
