@@ -34,14 +34,14 @@ constexpr int kMaxList = 512;               // blocks looked at per chunk: a thr
 struct Params {
   AttnTable t;
   int64_t rows;              // total_q * group
-  int64_t out_shard_bytes;   // per_shard: distance between the results of two shards
-  int64_t lse_shard_elems;
   int32_t group;
   int32_t n_kv_heads;
   int32_t n_blocks;          // of the table
-  ChunkRule chunks;          // of ordered_row_block
   int32_t per_shard;
-  float scale_log2;
+  ChunkRule chunks;          // of ordered_row_block
+  float scale_log2;          // (up to here one line: what the start asks for)
+  int64_t out_shard_bytes;   // per_shard: distance between the results of two shards
+  int64_t lse_shard_elems;
 };
 
 __device__ __forceinline__ floatx4_t mfma4(float a, float b, floatx4_t c) {
@@ -76,7 +76,7 @@ void attn_fp32_kernel(const Params p) {
   const int touched = touch_arguments<Params>();
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int n = lane & 15, kg = lane >> 4;
-  const int row_block = ordered_row_block(blockIdx.x, gridDim.x, p.t.n_ranks, lane, p.chunks);
+  const int row_block = ordered_row_block(blockIdx.x, gridDim.x, p.t.n_ranks, lane, p.chunks, ROWS);
   const int kvh = blockIdx.y;
   const int z_shard = p.per_shard ? blockIdx.z : 0;
 
@@ -391,7 +391,7 @@ template <int D, int NR, int NWAVE, typename TO>
 int launch_t(const AttnShape& s, Params& p, hipStream_t stream) {
   const int64_t blocks = (p.rows + 16 * NR - 1) / (16 * NR);
   if (blocks > 0x7fffffffLL) return CP_ERR_SHAPE;
-  p.chunks = late_first((int)blocks, p.t.n_ranks, p.rows % (16 * NR) != 0);
+  p.chunks = chunk_rule(p.t.n_ranks, p.t.tok_begin, (uint32_t)p.group);
   hipLaunchKernelGGL((attn_fp32_kernel<D, NR, NWAVE, TO>),
                      dim3((unsigned)blocks, s.n_kv_heads, s.per_shard ? s.n_shards : 1),
                      dim3(NWAVE * 64), 0, stream, p);

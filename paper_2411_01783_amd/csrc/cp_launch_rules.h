@@ -107,29 +107,51 @@ CP_RULE bool encode_in_one_launch(int64_t batch, int64_t lists, int64_t tokens) 
 
 // ---- the chunks of a ring's ranks among the row blocks, for ordered_row_block ----
 
-// First of the B row blocks (over the queries of N ranks back to back) of chunk j: rank j / 2's early
-// chunk (j even) or late chunk (j odd). A block with rows of two chunks is
-//   ends_in: the chunk's that ends in it
-//   late_first: the late chunk's, on either side of it, since its longest walk is a late row's
-// Taken for early, such a block was dispatched last and the call waited for it alone. fp32: 1320 tokens
-// of 4 heads over 4 ranks 38.6 us, 25.4 with it in its place; 3600 157 and 96. bf16: 20000 tokens of 16
-// heads over 4 ranks 1699 and 1406, 33333 of 8 over 4 2542 and 1912, 33333 of 16 over 8 4103 and 3794,
-// 65000 of 8 at head_dim 64 over 8 10264 and 7967; 47777 of 16 over 2 7616 and 7627. The walk behind
-// flags, whose row blocks do not straddle ranks, has ends_in: 33333 of 16 over 2 4008 and 3999, 77777
-// over 16 21602 and 22070. The boundaries are those of equal shards; shards of other sizes only lose
-// some of the order. (B < 2^26: that many row blocks of 16 rows do not fit the memory; N <= 32.)
+// Where the chunks lie, in rows: a rank's early chunk, then its late one. Sharding deals chunks of one length, and what the last ones lack is missing from the late chunks
+// of the first ranks (the whole of it, then the next rank's). Sizes dealt otherwise only lose some of
+// the order.
 struct ChunkRule {
-  uint32_t odd_blocks, up;
+  uint32_t rank, early, missing;
 };
-CP_RULE ChunkRule ends_in(int B) { return {(uint32_t)B, 0}; }
-// `partial`: the last block is not full (or boundaries come out up to a block too far)
-CP_RULE ChunkRule late_first(int B, int N, bool partial) {
-  if (B < 4 * N) return ends_in(B);   // (all of them run at once)
-  return {(uint32_t)B - (partial ? 1 : 0), 2 * (uint32_t)N - 1};
+// `begin`: of every rank, and the end, in tokens of `rows` rows.
+CP_RULE ChunkRule chunk_rule(int N, const int32_t* begin, uint32_t rows) {
+  const int64_t all = (int64_t)begin[N] * rows;
+  int64_t longest = 0;
+  for (int r = 0; r < N; ++r)
+    longest = longest < begin[r + 1] - begin[r] ? begin[r + 1] - begin[r] : longest;
+  int64_t rank = longest * rows, early = longest / 2 * rows;
+  if (rank * N > 0xffff0000ll) {   // (no sharding: 31 bits of rows and 2N tokens of a group are fewer)
+    rank = (all + N - 1) / N;
+    early = rank / 2;
+  }
+  return {(uint32_t)rank, (uint32_t)early, (uint32_t)(rank * N - all)};
 }
-CP_RULE int chunk_begin(int j, int B, int N, ChunkRule rule) {
-  return (int)(((uint32_t)j * (j % 2 ? rule.odd_blocks : (uint32_t)B) + (j % 2 ? 0 : rule.up)) /
-               (2 * (uint32_t)N));
+// The same in row blocks of `rows` rows, `blocks` in all, none of which holds rows of two ranks.
+CP_RULE ChunkRule chunk_rule_in_blocks(int N, ChunkRule c, uint32_t rows, int64_t blocks) {
+  const int64_t rank = ((int64_t)c.rank + rows - 1) / rows, missing = rank * N - blocks;
+  return {(uint32_t)rank, c.early / rows, missing > 0 ? (uint32_t)missing : 0};
+}
+// First of the B row blocks of `rows` rows (over the queries of N ranks back to back) of chunk j: rank
+// j / 2's early chunk (j even) or late chunk (j odd). A block with rows of two chunks is the late one's,
+// on either side of it, since its longest walk is a late row's: taken for early, such a block is
+// dispatched last and the call waits for it alone. So it does for those that lie between the boundaries
+// of equal chunks and the real ones, up to 2N - 1 tokens apart, almost two row blocks of 16 heads over 16
+// ranks. us, with a block the chunk's that ends in it, the late one's between equal chunks, and here:
+//   bf16: 33348 tokens of 8 heads over 16 ranks 2704, 2645 and 2028, 41111 of 16 over 16 6852, 6527 and
+//     6031, 65050 of 16 over 16 15961, 16181 and 14955, 49873 of 8 on 2 over 8 5543, 5368 and 4441, 33001
+//     of 8 at head_dim 64 over 16 3261, 3043 and 2258, 50723 of 8 over 4 5502, 4519 and 4536, 31744 of 16
+//     over 16 3573, 3547 and 3548; none of 28 slower
+//   fp32, between equal chunks and here: 1763 tokens of 4 heads over 4 ranks 45.5 and 35.8, 1761 over 3
+//     41.9 and 35.9, 1320 over 4 25.2 and 25.2, 1345 of 8 on 2 over 4 49.3 and 44.6; none of 27 slower
+//   the walk behind flags, whose row blocks do not straddle ranks, a block the chunk's that ends in it
+//     and here: 44444 of 8 over 8 4491 and 3471, 90001 of 8 on 2 over 8 16364 and 13821, 77777 of 16 over
+//     16 21774 and 20737, 65536 over 16 the same order; none of 16 slower
+CP_RULE int chunk_begin(int j, int B, int N, ChunkRule c, uint32_t rows) {
+  const uint32_t r = (uint32_t)j >> 1;
+  const uint32_t lack = r * c.early < c.missing ? r * c.early : c.missing;
+  const uint32_t x = r * c.rank - lack, first = (x + rows - 1) / rows, late = (x + c.early) / rows;
+  const uint32_t b = j % 2 && late > first ? late : first;
+  return j >= 2 * N || b > (uint32_t)B ? B : (int)b;
 }
 
 // ---- fp32 attention: rows and wavefronts of a workgroup ----

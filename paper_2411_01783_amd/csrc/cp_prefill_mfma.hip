@@ -93,7 +93,7 @@ struct Params {
   int32_t n_sub;          // SPLIT: parts of the KV axis (of every shard's, if per_shard)
   int32_t sub_blocks;     // SPLIT: blocks per part, by their index; 0: equal parts of the visible ones
   int32_t per_shard;      // the shards' results are kept apart
-  ChunkRule chunks;       // WHOLE, SPLIT, RING: of ordered_row_block
+  ChunkRule chunks;       // of ordered_row_block, in rows (RING: in row blocks)
   int32_t xcd_slice;      // WHOLE, SPLIT: workgroups are placed by xcd_slice
   int32_t cut_units;      // PLAN: equal shares (else a workgroup per unit)
   int32_t spin_limit;     // RING: polls per shard before giving up
@@ -332,7 +332,7 @@ void fill_params(const AttnShape& s, const AttnTable& t, Params& p) {
   p.rows_all_heads = s.total_q * s.n_q_heads;
   p.n_row_blocks = (int32_t)(((int64_t)p.rows + BM - 1) / BM);
   p.n_kv_heads = s.n_kv_heads;
-  p.chunks = late_first(p.n_row_blocks, t.n_ranks, p.rows % BM != 0);
+  p.chunks = chunk_rule(t.n_ranks, t.tok_begin, (uint32_t)p.group);
   p.n_blocks = s.n_blocks;
   p.n_sub = p.n_z = 1;
   p.scale_log2 = s.scale * kLog2e;
@@ -548,7 +548,7 @@ int launch_attn_mfma_ring(const AttnShape& s, const AttnTable& t, const int32_t*
   if (blocks == 0) return CP_OK;
   if (blocks * p.n_kv_heads > 0x7fffffffLL) return CP_ERR_SHAPE;
   p.n_row_blocks = (int32_t)blocks;
-  p.chunks = ends_in((int)blocks);   // (late_first: 77777 tokens of 16 heads over 16 ranks 21.6 -> 22.1 ms)
+  p.chunks = chunk_rule_in_blocks(t.n_ranks, p.chunks, BM, blocks);
   return launch_body(out_dtype == CP_BF16 ? prefill_ring_walk_kernel<bf16_t>
                                           : prefill_ring_walk_kernel<float>,
                      Geo<128>::SMEM, dim3((unsigned)(blocks * p.n_kv_heads)), p, stream);

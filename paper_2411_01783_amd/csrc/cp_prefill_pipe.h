@@ -647,7 +647,7 @@ __device__ __forceinline__ Share plan_share(const Params& p, int2* lds_bounds, u
     const int i = blockIdx.x / p.n_kv_heads, kvh = blockIdx.x - i * p.n_kv_heads;
     const int z = p.n_z > 1 ? i / p.n_row_blocks : 0;
     const int rb = ordered_row_block(i - z * p.n_row_blocks, p.n_row_blocks, p.n_ranks, lane,
-                                     ends_in(p.n_row_blocks));
+                                     p.chunks, BM);
     sh.unit = (kvh * p.n_z + z) * p.n_row_blocks + rb;
     return sh;
   }
@@ -857,7 +857,8 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
     }
     const int i = x / p.n_kv_heads;
     kvh = x - i * p.n_kv_heads;
-    row_block = ordered_row_block(i, p.n_row_blocks, p.n_ranks, threadIdx.x & 63, p.chunks);
+    row_block = ordered_row_block(i, p.n_row_blocks, p.n_ranks, threadIdx.x & 63, p.chunks,
+                                  MODE == RING ? 1 : BM);
     z_shard = p.per_shard ? z / p.n_sub : 0;
     z_sub = z - z_shard * p.n_sub;
     if constexpr (MODE == RING) {   // row blocks do not straddle ranks here
@@ -1265,6 +1266,9 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
         // stalls every wavefront behind it.
         auto no_hook = [](auto) {};
         constexpr int PPS = G::PARTS / 2;  // parts per step
+        // (Where the loop begins in a line of 64 bytes tells: from 28 or 60 on 131072 tokens over 16 ranks
+        // behind flags take 57.87 ms, from 16 on 58.24. The other kernels do not tell.)
+        if constexpr (MODE == RING) asm volatile(".p2align 6");
         for (int it = 0; it < n_live; ++it) {
           const bool has_next = it + 1 < n_live;
           const int nb = (it + 1) & 1;

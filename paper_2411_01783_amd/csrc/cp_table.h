@@ -11,16 +11,17 @@ namespace {
 // short. In one rank's shard (chunk r of the sequence, then chunk 2N-1-r) later rows see more
 // keys. Over N ranks back to back the late chunks of all ranks go first, rank 0's (the last of
 // the sequence) at their head, then the early chunks, rank 0's (the first of the sequence) last.
-__device__ __forceinline__ int ordered_row_block(int i, int B, int n_ranks, int lane,
-                                                 ChunkRule rule) {
+// `rows`: of a row block, in the units of the rule.
+__device__ __forceinline__ int ordered_row_block(int i, int B, int n_ranks, int lane, ChunkRule rule,
+                                                 uint32_t rows) {
   if (n_ranks == 1) return B - 1 - i;
   // lane l < N: late chunk of rank l; N <= l < 2N: early chunk of rank 2N-1-l  (N <= 32)
   const bool late = lane < n_ranks;
   const int r = late ? lane : 2 * n_ranks - 1 - lane;
   int lo = 0, hi = 0;
   if (r >= 0) {   // (in 32 bits: 64-bit divisions took 1000 cycles of every start)
-    const int middle = chunk_begin(2 * r + 1, B, n_ranks, rule);
-    const int side = chunk_begin(late ? 2 * r + 2 : 2 * r, B, n_ranks, rule);
+    const int middle = chunk_begin(2 * r + 1, B, n_ranks, rule, rows);
+    const int side = chunk_begin(late ? 2 * r + 2 : 2 * r, B, n_ranks, rule, rows);
     lo = late ? middle : side;
     hi = late ? side : middle;
   }

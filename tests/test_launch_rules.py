@@ -38,8 +38,13 @@ int fp32_form(int head_dim, int64_t rows, int64_t n_kv_heads, int64_t shards, in
                                        total_keys);
   return f.rows * 10 + f.waves;
 }
-int chunk_begin(int j, int B, int N, int rule) {
-  return cp::chunk_begin(j, B, N, rule == 0 ? cp::ends_in(B) : cp::late_first(B, N, rule == 2));
+// begin: of the ranks, in tokens of `group` rows; out: of the 2N + 1 chunks, in blocks of `rows` rows
+// (`apart`: which do not straddle ranks)
+void chunk_begins(int B, int N, const int32_t* begin, uint32_t group, uint32_t rows, int apart,
+                  int32_t* out) {
+  cp::ChunkRule rule = cp::chunk_rule(N, begin, group);
+  if (apart) rule = cp::chunk_rule_in_blocks(N, rule, rows, B);
+  for (int j = 0; j <= 2 * N; ++j) out[j] = cp::chunk_begin(j, B, N, rule, apart ? 1 : rows);
 }
 }
 """
@@ -162,44 +167,88 @@ def test_pieces_of_one_launch_fit_a_wavefront(rules):
                 assert batch <= 64 and -(-batch * lists // 16) <= 64
 
 
-ENDS_IN, LATE, LATE_PARTIAL = range(3)
+def shards(total, N):
+    """Lengths of the early and late chunks of N ranks, as cp_shard_positions deals them."""
+    size = -(-total // (2 * N))
+    length = lambda c: min((c + 1) * size, total) - min(c * size, total)
+    return np.array([[length(r), length(2 * N - 1 - r)] for r in range(N)])
 
 
-def dispatch_order(rules, B, N, rule):
+def chunk_begins(rules, B, sizes, group, rows, apart=False):
+    N = len(sizes)
+    at = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    begin = np.empty(2 * N + 1, np.int32)
+    rules.chunk_begins(B, N, at.ctypes.data_as(ctypes.c_void_p), ctypes.c_uint32(group),
+                       ctypes.c_uint32(rows), int(apart), begin.ctypes.data_as(ctypes.c_void_p))
+    assert begin[0] == 0 and begin[-1] == B and np.all(np.diff(begin) >= 0), (sizes, group, rows)
+    return begin
+
+
+def dispatch_order(rules, B, sizes, group, rows, apart=False):
     """Row blocks as ordered_row_block hands them out: the late chunks of ranks 0, 1, .., then the
     early ones of ranks N - 1, .., 0, each from its end."""
-    begin = [rules.chunk_begin(j, B, N, rule) for j in range(2 * N + 1)]
-    assert begin[0] == 0 and begin[-1] == B and np.all(np.diff(begin) >= 0)
+    N, begin = len(sizes), chunk_begins(rules, B, sizes, group, rows, apart)
     chunks = [2 * r + 1 for r in range(N)] + [2 * r for r in reversed(range(N))]
     return np.concatenate([np.arange(begin[j], begin[j + 1])[::-1] for j in chunks])
 
 
-# Equal chunks of any length, so that row blocks of `rows` rows straddle them or not.
-@pytest.mark.parametrize("rows", [16, 32])
-def test_fp32_row_blocks_with_late_rows_go_first(rules, rows):
+# Row blocks of the fp32 kernel (16 and 32 rows) and of the bf16 kernel, over chunks of any length: equal
+# ones and, where the total is no multiple of 2N, short and empty ones at the end of the sequence.
+@pytest.mark.parametrize("rows", [16, 32, 256])
+@pytest.mark.parametrize("group", [1, 4, 16])
+def test_row_blocks_with_late_rows_go_first(rules, rows, group):
+    rng = np.random.default_rng(rows + group)
     for N in (2, 3, 4, 7, 8, 16, 32):
-        for chunk in list(range(1, 60)) + [128, 165, 225, 256, 450, 1000]:     # rows
-            R = 2 * N * chunk
-            B = -(-R // rows)
-            order = dispatch_order(rules, B, N, LATE_PARTIAL if R % rows else LATE)
+        chunks = list(range(3, 60, 7)) + [128, 165, 225, 256, 450, 1000, 1042, 2079, 3117]
+        totals = [2 * N * c - k for c in chunks for k in {0, 1, N, 2 * N - 1, int(rng.integers(2 * N))}]
+        for total in totals:
+            parts = shards(total, N)
+            B = -(-total * group // rows)
+            order = dispatch_order(rules, B, parts.sum(1), group, rows)
             assert np.array_equal(np.sort(order), np.arange(B))
-            if B < 4 * N:           # (all of them run at once)
-                continue
-            late = np.arange(R) // chunk % 2 == 1
-            has_late = np.array([late[b * rows:(b + 1) * rows].any() for b in range(B)])
-            last_late = np.flatnonzero(has_late[order]).max()
-            # (a partial last block puts the boundaries up to a block too early)
-            assert last_late < has_late.sum() + (2 * N if R % rows else 0), (N, chunk)
+            late = np.repeat(np.tile([False, True], N), parts.ravel() * group)
+            has_late = np.logical_or.reduceat(late, np.arange(B) * rows)
+            # (where a late chunk is empty, a block of two ranks' early rows may be among the late ones)
+            empty = int((parts[:, 1] == 0).sum())
+            assert np.flatnonzero(has_late[order]).max(initial=-1) < has_late.sum() + empty, (N, total)
+
+
+# The walk behind flags, whose row blocks do not straddle ranks. (Short late chunks are taken for whole
+# ones but for what the row blocks are fewer: a boundary can be a block off where they are several.)
+@pytest.mark.parametrize("group", [1, 4, 16])
+def test_row_blocks_of_whole_ranks_go_late_chunk_first(rules, group):
+    rng, rows = np.random.default_rng(group), 256
+    for N in (2, 4, 8, 16, 32):
+        for chunk in [128, 165, 256, 450, 1000, 1042, 2079, 2431, 3117]:
+            for k in {0, 1, N, 2 * N - 1, int(rng.integers(2 * N))}:
+                parts = shards(2 * N * chunk - k, N)
+                per = -(-parts.sum(1) * group // rows)
+                order = dispatch_order(rules, int(per.sum()), parts.sum(1), group, rows, True)
+                assert np.array_equal(np.sort(order), np.arange(per.sum()))
+                # (the first block with a late row of every rank)
+                begin = np.concatenate([[0], np.cumsum(per)])
+                late = np.zeros(per.sum(), bool)
+                for r in range(N):
+                    if parts[r, 1] > 0:
+                        late[begin[r] + parts[r, 0] * group // rows:begin[r + 1]] = True
+                # (a block a rank where a late chunk ends a block early or has no row)
+                short = int((per < per.max()).sum() + (parts[:, 1] == 0).sum())
+                assert np.flatnonzero(late[order]).max() < late.sum() + short, (N, chunk, k)
 
 
 def test_row_blocks_are_all_handed_out(rules):
+    rng = np.random.default_rng(5)
     for N in range(2, 33):
-        for B in list(range(1, 300)) + [1000, 4095, 65537, (1 << 26) - 1]:
-            if B < 300:
-                assert np.array_equal(np.sort(dispatch_order(rules, B, N, ENDS_IN)), np.arange(B))
-            for rule in (ENDS_IN, LATE, LATE_PARTIAL):
-                begin = [rules.chunk_begin(j, B, N, rule) for j in range(2 * N + 1)]
-                assert begin[0] == 0 and begin[-1] == B and np.all(np.diff(begin) >= 0)
+        for total in list(range(1, 200)) + [4095, 65537]:
+            sizes = rng.multinomial(total, rng.dirichlet(np.full(N, .3)))
+            for group, rows in ((1, 16), (3, 32), (16, 256)):
+                B = -(-total * group // rows)
+                assert np.array_equal(np.sort(dispatch_order(rules, B, sizes, group, rows)), np.arange(B))
+    # as many rows as are accepted, dealt evenly and to one rank: boundaries only, within 32 bits
+    for N in (2, 3, 32):
+        for sizes in ([0x7fffffff // N] * N, [0x7fffffff] + [0] * (N - 1), [0] * (N - 1) + [0x7fffffff]):
+            chunk_begins(rules, -(-sum(sizes) // 16), sizes, 1, 16)
+            chunk_begins(rules, sum(-(-n // 16) for n in sizes), sizes, 1, 16, True)
 
 
 # Calls of the fp32 kernel whose time with another form of workgroup (rows, wavefronts) was measured:
