@@ -26,8 +26,11 @@ import sys
 # kernel-name substring -> tag of the summary file (first match wins)
 KERNELS = [("prefill_ring_walk_kernel", "prefill_ring_walk_kernel"),
            ("prefill_mfma_kernel", "prefill_mfma_kernel"),
+           ("decode_flat_merge_one_kernel", "decode_flat_merge_one_kernel"),
            ("decode_flat_merge_kernel", "decode_flat_merge_kernel"),
            ("decode_flat_kernel", "decode_flat_kernel"), ("decode_kernel", "decode_kernel"),
+           ("merge_over_groups_kernel", "merge_over_groups_kernel"),
+           ("merge_table_kernel", "merge_table_kernel"),
            ("plan_merge_kernel", "plan_merge_kernel"), ("merge_kernel", "merge_kernel_ring")]
 COPY_MARK = "MulFunctor"
 
@@ -79,7 +82,7 @@ def mfma_main():
             for c, v in d.items():
                 mean[c] += v / n
         ns = sum(dur[tag].values()) / n
-        wl = workload if tag.startswith("prefill") or tag.endswith("_ring") else "decode_b32"
+        wl = "decode_b32" if tag.startswith("decode") else workload
         out = os.path.join(out_dir, "%s_%s_mfma_counters.txt" % (tag, wl))
         with open(out, "w") as f:
             f.write("command:\n  %s\n\n" % cmd)
@@ -223,7 +226,7 @@ def main():
         w = wr.get(tag, [0.0])
         rb = sum(r) / len(r) * f_rd
         wb = sum(w) / len(w) * f_wr
-        wl = workload if tag.startswith("prefill") or tag.endswith("_ring") else "decode_b32"
+        wl = "decode_b32" if tag.startswith("decode") else workload
         path = os.path.join(out_dir, "%s_%s_hbm_traffic.txt" % (tag, wl))
         with open(path, "w") as f:
             f.write("commands (two runs, one counter each):\n  %s\n\n" % cmd)
