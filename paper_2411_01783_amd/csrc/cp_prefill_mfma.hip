@@ -27,7 +27,7 @@
 //     launch per ring step costs 12 to 17 us at small query shards whatever its work: 256
 //     launches and 256 split merges for 16 ranks, 6.08 ms at 1024 new tokens on 131072 cached
 //     ones, where one launch takes 0.94 ms; 4096 tokens of head_dim 64 over 4 ranks 3.8 ms
-//     on the vector pipe, 59 us here.)
+//     on the vector pipe, 55 to 60 us here.)
 //   - Small and middling calls, whose row blocks would leave compute units idle or with very
 //     different walks, plan in the workgroups themselves (PLAN), if their positions fit LDS: a
 //     workgroup per row block where walks are short, equal shares of all the work elsewhere. Where

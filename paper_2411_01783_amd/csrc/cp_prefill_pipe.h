@@ -449,7 +449,7 @@ __device__ __forceinline__ bool ring_enter(const Params& p, int rank, int step, 
 // prompts' 91: with the next rows asked for behind the epilogue, tables in LDS and the blocks counted
 // and listed in one go 7.9, the call 109.4 -> 102.3 us, 4096 tokens at head_dim 64 59.3 -> 57.9.
 // Six packed prompts of 200 to 3000 tokens over 4 ranks: 241 us with a workgroup per row block and
-// 128-key tiles, 99 us in equal shares of 32-key blocks.
+// 128-key tiles, 97 us in equal shares of 32-key blocks.
 // ---------------------------------------------------------------------------
 
 // Shares: workgroup i of W takes [share_begin(i), share_begin(i + 1)) of the line of all units
@@ -1287,8 +1287,9 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
                                   if (M == 9 && __builtin_expect(has_next, 1)) issue_part(IntC<3>{}, next, nb);
                                 });
           // (the pipeline is at the same parity after two blocks as after four. Nothing of this tile is
-          // in flight then but the V fragments, which the drain waits for. 320 tokens at head_dim 64
-          // 19.1 -> 17.5 us, twelve prompts of 200 to 600 tokens 62.9 -> 59.9.)
+          // in flight then but the V fragments, which the drain waits for. us, without and with: 320
+          // tokens of 8 heads on 2 over 2 ranks at head_dim 64 19.5 and 17.9, 900 of 16 on 2 33.9 and
+          // 31.3, 700 of 16 at head_dim 128 26.6 and 25.2, six packed prompts of 200 to 3000 98.1 and 95.8.)
           if (__builtin_expect(half_tail && !has_next, 0)) break;
           pipe_body<D, 2, BAND>(R, qf, kaddr, vaddr, paddr, qp, ql, scale_log2, mask & 4,
                                 mask & 64, have_ref, no_hook);
