@@ -669,6 +669,30 @@ __device__ __forceinline__ Share plan_share(const Params& p, int2* lds_bounds, u
       }
     }
   }
+  // A row block that can hold a whole chunk, a late one between two early ones, has its longest walk at
+  // neither end: two more queries of it. (Taken for short, such units were one share's, which walked them
+  // whole, and a cut at half tiles made some longer still. 8 heads on 8 KV heads over 8 ranks, us, in whole
+  // tiles, half tiles and so: 1660 tokens 74.1, 82.9 and 40.7, 2843 110.8, 114.7 and 57.7, 900 51.0, 49.3
+  // and 37.7. At head_dim 64 only: it keeps all bits wherever units are cut.)
+  if (D == 64 && p.n_ranks > 1 && p.chunks.early < BM) {
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      if (k * NTHREADS < n_units) {
+        int t[2], a[2] = {0, 0};
+#pragma unroll
+        for (int e = 0; e < 2; ++e) t[e] = tok[k][0] + (tok[k][1] - tok[k][0]) * (e + 1) / 3;
+#pragma unroll 8
+        for (int i = 1; i < p.n_ranks; ++i) {
+          const int begin = p.t.tok_begin[i];
+          a[0] += t[0] >= begin;
+          a[1] += t[1] >= begin;
+        }
+#pragma unroll
+        for (int e = 0; e < 2; ++e)
+          mx[k] = max(mx[k], ((Glb<const int32_t>)L.ranks[a[e]].q_pos)[t[e] - L.tok_begin[a[e]]]);
+      }
+    }
+  }
   plan_bounds(p, lds_bounds, L, tid);
   __syncthreads();
   // Planned tiles: every stride-th block of the range looked at (more of them in a packed batch,
@@ -1266,9 +1290,10 @@ __device__ __forceinline__ void prefill_body(const Params& p) {
         // stalls every wavefront behind it.
         auto no_hook = [](auto) {};
         constexpr int PPS = G::PARTS / 2;  // parts per step
-        // (Where the loop begins in a line of 64 bytes tells: from 28 or 60 on 131072 tokens over 16 ranks
-        // behind flags take 57.87 ms, from 16 on 58.24. The other kernels do not tell.)
-        if constexpr (MODE == RING) asm volatile(".p2align 6");
+        // (Where the loop begins in a line of 64 bytes tells, with one and the same code: 131072 tokens
+        // over 16 ranks behind flags take 57.87 ms from 28 or 60 on and 58.24 from 16 on, rings at
+        // head_dim 64 up to .7 %. The other kernels do not tell.)
+        if constexpr (MODE == RING || D == 64) asm volatile(".p2align 6");
         for (int it = 0; it < n_live; ++it) {
           const bool has_next = it + 1 < n_live;
           const int nb = (it + 1) & 1;

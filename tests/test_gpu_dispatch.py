@@ -267,13 +267,15 @@ def test_tiles_of_two_blocks_count_every_key(tq, tk, nh, d):
 
 
 # Equal shares of several units, whose rows are asked for one unit ahead: row blocks with rows of many
-# ranks (some without any), the last row block short, the step from one KV head to the next.
+# ranks (some without any), the last row block short, the step from one KV head to the next, row blocks
+# longer than a chunk (of 180, 181 and 255 rows).
 @pytest.mark.parametrize("kv_sizes,q_sizes,nh,nkv,d", [
     ([2000, 0, 33, 1], [1, 7, 0, 300], 16, 1, 128),
     ([1500, 700], [700, 33], 12, 3, 128),
     ([40] * 31 + [900], [3, 0, 16, 1, 90, 0, 0, 5] * 4, 16, 2, 128),
     ([1500, 700], [1100, 1], 8, 4, 64),
     ([1100], [2049], 16, 4, 64),
+    ([361] * 8, [361] * 8, 8, 8, 64), ([700, 0, 90, 400], [300, 0, 40, 511], 8, 8, 64),
 ])
 def test_shares_of_units_that_hold_rows_of_many_ranks(kv_sizes, q_sizes, nh, nkv, d):
     n = max(len(kv_sizes), len(q_sizes))
